@@ -5,16 +5,23 @@
 //     M_z <- M_z * (M_p^T M) / (M_p^T M_p M_z + eps)
 //     M_p <- M_p * (M M_z^T) / (M_p M_z M_z^T + eps)
 // Per half update two kernels, all tiles per launch: the k x k Gram matrix of the factor that stays fixed
-// (M_p^T M_p or M_z M_z^T, one lane per entry), then the update itself.
-// M_z update: a workgroup of four wavefronts owns 64 columns of a tile; lane = column, and each wavefront takes a
-// quarter of the tile's rows.  The rows of M_p, which every lane needs, are staged in LDS chunk by chunk and read as
-// broadcasts while the lane streams its column of W (coalesced across the lanes); the four partial numerators of a
-// column are added through LDS in wavefront order; the denominators come from the Gram rows (staged in LDS) and
-// the lane's column of the old M_z.  Splitting tiles this finely is what fills the chip: 64 tiles of 512 columns
-// give 512 workgroups.  The M_p update is the mirror image (lane = row, M_z staged transposed, a wavefront per
-// quarter of the columns).  New factors go to a second buffer (the other half update still needs the old values),
-// the two buffers swap every iteration.  fp32 throughout, every sum in a fixed order.  The ranks are processed KC
-// (8, 16 or 32) at a time, so any k up to 256 (the paper's largest) is served; each pass streams W again.
+// (M_p^T M_p or M_z M_z^T), then the update itself.  Every sum is a contraction, so all of them run on the matrix
+// cores in fp32 (v_mfma_f32_32x32x2, or 16x16x4 up to rank 16): the products are exact fp32 fused multiply-adds, as on
+// the vector ALUs, and the operands come straight from global memory in the instruction's own lane layout, because
+// the order of the reduction index is free and a lane may take neighbouring elements:
+//   * M_z update: a workgroup of four wavefronts owns 64 columns of a tile (a row of them is one 128-byte line in 16
+//     bits) and each wavefront takes a quarter of the rows.  A lane holds 2 (4) neighbouring columns of its row of W and
+//     one value of M_p per step; no LDS in the loop.
+//   * M_p update: a workgroup owns 64 rows, a wavefront a quarter of the columns.  A lane reads 8 neighbouring
+//     columns of its row of W and of its row of M_z per step.
+// The denominators (Gram matrix times the old factor) are split over the wavefronts in the same way, and both partial
+// results are added through LDS in wavefront order.  New factors go to a second buffer (the other half update still
+// needs the old values), the two buffers swap every iteration.  fp32 throughout, every sum in a fixed order.  Up to 128
+// ranks share one pass over W; any k up to 256 (the paper's largest) is served.
+// What bounds it: the fp32 matrix rate, 2 m n k flops per half update (4096 x 9216 at rank 32: 16 us at 154 TFLOP/s), and
+// beside it W from the memory-side cache (75 MB).  Measured there, f16 in 512 x 576 tiles:
+// M_z 52 us, M_p 49 us, Gram matrices 7 and 9 us (one lane per column and vector fused multiply-adds: 215, 183, 31 and
+// 42 us); error against 64 bits after 20 iterations 6.1e-7 (7.5e-7).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -23,11 +30,11 @@
 namespace lrbi {
 
 static constexpr int kNmfThreads = 256;
-static constexpr int kNmfStageFloats = 8192; // 32 KiB of staged factor rows
+static constexpr int kNmfWaves = kNmfThreads / 64;
 static constexpr int kNmfMaxK = 256;
-// A workgroup owns kNmfThreads / PARTS columns (rows) of a tile, one per lane, and PARTS groups of lanes share them, each
-// taking a part of the rows (columns): PARTS = 4 when the tiles alone would not fill the chip, else 1.
-static constexpr int ZB = 16; // rows of W requested together in the M_z update
+static constexpr int kNmfOwn = 64; // columns (rows) of a tile per workgroup
+static constexpr int kGramThreads = 512;
+static constexpr int kGramWaves = kGramThreads / 64;
 
 template <typename T> struct NmfElem;
 template <> struct NmfElem<float> {
@@ -58,65 +65,152 @@ __device__ __forceinline__ void nmf_tile_extent(const Geom &g, int64_t t, int &t
     ct = (int)((g.n - (int64_t)tj * g.c < g.c) ? g.n - (int64_t)tj * g.c : g.c);
 }
 
-// Gram matrix of a tile's fixed factor: G[a][b] = sum_i Mp[i][a] Mp[i][b] (ZSIDE = false, rows of the tile in
-// ascending order) or sum_j Mz[a][j] Mz[b][j] (ZSIDE = true, columns in ascending order).  The factor is staged in LDS
-// chunk by chunk as [row or column][k] (M_z transposed on the way in); a lane owns four neighbouring entries of G (one
-// when k is not a multiple of 4) and reads one broadcast value and one 16-byte piece per staged row.
-template <bool ZSIDE>
-__global__ __launch_bounds__(kNmfThreads) void nmf_gram_kernel(Geom g, const float *__restrict__ F, float *__restrict__ G,
-                                                              int eblocks)
+// fp32 matrix instruction with a square R x R result: lane = (index li of the operand's row / column, reduction index lk)
+template <int R> struct NmfMat;
+template <> struct NmfMat<32> {
+    static constexpr int KS = 2, NR = 16; // reduction steps per instruction, result registers
+    typedef __attribute__((ext_vector_type(16))) float acc_t;
+    __device__ static acc_t mma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0); }
+    __device__ static int row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+};
+template <> struct NmfMat<16> {
+    static constexpr int KS = 4, NR = 4;
+    typedef __attribute__((ext_vector_type(4))) float acc_t;
+    __device__ static acc_t mma(float a, float b, acc_t c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+    __device__ static int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+};
+template <int R> __device__ __forceinline__ typename NmfMat<R>::acc_t nmf_zero()
 {
-    __align__(16) static __shared__ float stage[kNmfStageFloats];
-    const int64_t t = blockIdx.x / eblocks;
-    const int eb = (int)(blockIdx.x - t * eblocks);
-    const int tid = threadIdx.x;
-    const int k = g.k;
-    const bool k4 = (k % 4) == 0;
-    int ti, tj, rt, ct;
-    nmf_tile_extent(g, t, ti, tj, rt, ct);
-    const int count = ZSIDE ? ct : rt;                 // rows (columns) summed over
-    const int per_chunk = kNmfStageFloats / k;
-    const float *f = F + (ZSIDE ? t * (int64_t)k * g.c : t * (int64_t)g.r * k);
-    const int unit = eb * kNmfThreads + tid;           // four entries (k4) or one
-    const int units = k4 ? k * k / 4 : k * k;
-    const bool live = unit < units;
-    const int a = live ? (k4 ? unit / (k / 4) : unit / k) : 0;
-    const int b = live ? (k4 ? (unit - a * (k / 4)) * 4 : unit - a * k) : 0;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int i0 = 0; i0 < count; i0 += per_chunk) {
-        const int n = (count - i0 < per_chunk) ? count - i0 : per_chunk;
-        __syncthreads();
-        if (ZSIDE) { // consecutive lanes read consecutive columns of one row of M_z
-            for (int e = tid; e < n * k; e += kNmfThreads) {
-                const int l = e / n, jj = e - l * n;
-                stage[jj * k + l] = f[(int64_t)l * g.c + i0 + jj];
-            }
-        } else {
-            for (int e = tid; e < n * k; e += kNmfThreads) stage[e] = f[(int64_t)i0 * k + e];
-        }
-        __syncthreads();
-        if (!live) continue;
-        if (k4) {
-            for (int i = 0; i < n; ++i) {
-                const float pa = stage[i * k + a];
-                const float4 pb = *reinterpret_cast<const float4 *>(stage + i * k + b);
-                s.x = fmaf(pa, pb.x, s.x);
-                s.y = fmaf(pa, pb.y, s.y);
-                s.z = fmaf(pa, pb.z, s.z);
-                s.w = fmaf(pa, pb.w, s.w);
-            }
-        } else {
-            for (int i = 0; i < n; ++i) s.x = fmaf(stage[i * k + a], stage[i * k + b], s.x);
-        }
-    }
-    if (!live) return;
-    float *gt = G + t * (int64_t)k * k + (int64_t)a * k + b;
-    if (k4) *reinterpret_cast<float4 *>(gt) = s;
-    else *gt = s.x;
+    typename NmfMat<R>::acc_t z;
+#pragma unroll
+    for (int v = 0; v < NmfMat<R>::NR; ++v) z[v] = 0.f;
+    return z;
 }
 
-// M_z update.  Workgroup = (tile, block of 256 / PARTS columns); lane = column, group of lanes = part of the rows.
-template <typename T, int KC, int PARTS>
+// consecutive workgroups go round the eight XCDs: the workgroups of one tile, which share its factors, get one L2
+__device__ __forceinline__ int64_t nmf_block_id()
+{
+    const unsigned q = gridDim.x / 8, rest = gridDim.x % 8, x = blockIdx.x % 8;
+    return (int64_t)x * q + (x < rest ? x : rest) + blockIdx.x / 8;
+}
+
+// COUNT consecutive elements, VW per load (VW = 1: any alignment); the piece that starts at or past `limit` reads the
+// one at `safe` instead.  The callers replace what such a piece holds by zero, or never store its result.
+template <int COUNT, int VW, typename T>
+__device__ __forceinline__ void nmf_load(T (&out)[COUNT], const T *__restrict__ p, int at, int limit)
+{
+    constexpr int V = VW < COUNT ? VW : COUNT;
+    constexpr int BYTES = V * (int)sizeof(T), CHUNK = BYTES < 16 ? BYTES : 16, PER = CHUNK / (int)sizeof(T);
+#pragma unroll
+    for (int q = 0; q < COUNT; q += V) {
+        const T *src = p + (at + q < limit ? at + q : 0);
+        if constexpr (V == 1) {
+            out[q] = *src;
+        } else {
+#pragma unroll
+            for (int e = 0; e < V; e += PER) {
+                if constexpr (CHUNK == 4) *reinterpret_cast<uint32_t *>(&out[q + e]) = *reinterpret_cast<const uint32_t *>(src + e);
+                else if constexpr (CHUNK == 8) *reinterpret_cast<uint2 *>(&out[q + e]) = *reinterpret_cast<const uint2 *>(src + e);
+                else *reinterpret_cast<uint4 *>(&out[q + e]) = *reinterpret_cast<const uint4 *>(src + e);
+            }
+        }
+    }
+}
+
+// Gram matrix of a tile's fixed factor: G[a][b] = sum_i Mp[i][a] Mp[i][b] (ZSIDE = false) or sum_j Mz[a][j] Mz[b][j]
+// (ZSIDE = true).  Workgroup = (tile, pair of rank blocks a <= b); its eight wavefronts split the sum.
+template <int R, int VW, bool ZSIDE>
+__global__ __launch_bounds__(kGramThreads) void nmf_gram_kernel(Geom g, const float *__restrict__ F, float *__restrict__ G,
+                                                               int kblocks, int pairs)
+{
+    using M = NmfMat<R>;
+    static __shared__ float stage[kGramWaves * M::NR * 64];
+    const int64_t id = nmf_block_id(), t = id / pairs;
+    int pair = (int)(id - t * pairs), ab = 0;
+    while (pair >= kblocks - ab) pair -= kblocks - ab++;
+    const int bb = ab + pair;
+    int ti, tj, rt, ct;
+    nmf_tile_extent(g, t, ti, tj, rt, ct);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane % R, lk = lane / R, k = g.k;
+    const int ra = (ab * R + li < k) ? ab * R + li : k - 1, rb = (bb * R + li < k) ? bb * R + li : k - 1;
+    typename M::acc_t acc = nmf_zero<R>();
+    if (ZSIDE) {
+        const float *f = F + t * (int64_t)k * g.c;
+        const float *fa = f + (int64_t)ra * g.c, *fb = f + (int64_t)rb * g.c;
+        const int steps = (ct + 8 * M::KS - 1) / (8 * M::KS);
+        for (int s = steps * wave / kGramWaves; s < steps * (wave + 1) / kGramWaves; ++s) {
+            const int j = s * 8 * M::KS + 8 * lk;
+            float va[8], vb[8];
+            nmf_load<8, VW>(va, fa, j, ct);
+            nmf_load<8, VW>(vb, fb, j, ct);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool in = j + u < ct;
+                acc = M::mma(in ? va[u] : 0.f, in ? vb[u] : 0.f, acc);
+            }
+        }
+    } else {
+        const float *f = F + t * (int64_t)g.r * k;
+        const int steps = (rt + M::KS - 1) / M::KS;
+        const int send = steps * (wave + 1) / kGramWaves;
+        for (int s0 = steps * wave / kGramWaves; s0 < send; s0 += 8) {
+            float va[8], vb[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int i = (s0 + u) * M::KS + lk, ic = i < rt ? i : rt - 1;
+                va[u] = f[(int64_t)ic * k + ra];
+                vb[u] = f[(int64_t)ic * k + rb];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const bool in = s0 + u < send && (s0 + u) * M::KS + lk < rt;
+                acc = M::mma(in ? va[u] : 0.f, in ? vb[u] : 0.f, acc);
+            }
+        }
+    }
+#pragma unroll
+    for (int v = 0; v < M::NR; ++v) stage[(wave * M::NR + v) * 64 + lane] = acc[v];
+    __syncthreads();
+    for (int v = wave; v < M::NR; v += kGramWaves) {
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kGramWaves; ++w) sum += stage[(w * M::NR + v) * 64 + lane];
+        const int a = ab * R + M::row(v, lane), b = bb * R + li;
+        if (a < k && b < k) {
+            float *gt = G + t * (int64_t)k * k;
+            gt[(int64_t)a * k + b] = sum;
+            if (ab != bb) gt[(int64_t)b * k + a] = sum;
+        }
+    }
+}
+
+// Adds the four wavefronts' partial results of one rank block, in wavefront order; lane and register keep their meaning.
+// A wavefront gets the registers v of [wave * NR / 4, (wave + 1) * NR / 4) of each of the NB result blocks.
+template <int R, int NB, int ITEMS>
+__device__ __forceinline__ void nmf_reduce(float *stage, const typename NmfMat<R>::acc_t (&acc)[NB], float (&out)[ITEMS],
+                                           int wave, int lane)
+{
+    constexpr int NR = NmfMat<R>::NR;
+    __syncthreads(); // what the staging area held has been consumed
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int v = 0; v < NR; ++v) stage[((wave * NB + b) * NR + v) * 64 + lane] = acc[b][v];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < ITEMS; ++e) {
+        const int b = e % NB, v = wave * (NR / kNmfWaves) + e / NB;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < kNmfWaves; ++w) sum += stage[((w * NB + b) * NR + v) * 64 + lane];
+        out[e] = sum;
+    }
+}
+
+// M_z update.  Workgroup = (tile, 64 columns); lane li holds columns NB * li .. + NB - 1, block b of the result the
+// columns NB * li + b.
+template <typename T, int R, int RB, int VW>
 __global__ __launch_bounds__(kNmfThreads) void nmf_update_z_kernel(Geom g, const T *__restrict__ W, int64_t ldw, int method,
                                                                   float w_threshold, float amplify,
                                                                   const float *__restrict__ Mp,
@@ -124,235 +218,216 @@ __global__ __launch_bounds__(kNmfThreads) void nmf_update_z_kernel(Geom g, const
                                                                   float *__restrict__ MzNew, const float *__restrict__ G,
                                                                   float eps, int cblocks)
 {
-    extern __shared__ uint4 lrbi_dyn_smem[];
-    float *stage = (float *)lrbi_dyn_smem;   // [rows of the chunk][k]; then the partial sums [part][rank][lane]
-    float *gramL = stage + kNmfStageFloats;  // the pass's rows of M_p^T M_p: [KC][k]
-    constexpr int kNmfParts = PARTS, kNmfOwn = kNmfThreads / PARTS;
-    static_assert(kNmfParts * KC * kNmfOwn <= kNmfStageFloats && KC * kNmfMaxK <= kNmfStageFloats, "LDS reuse");
-    const int64_t t = blockIdx.x / cblocks;
-    const int cb = (int)(blockIdx.x - t * cblocks);
+    using M = NmfMat<R>;
+    using acc_t = typename M::acc_t;
+    constexpr int NB = kNmfOwn / R, ITEMS = NB * M::NR / kNmfWaves;
+    constexpr int U = RB == 4 ? 4 : 8; // steps whose loads are requested together, ahead of the previous batch's arithmetic
+    static __shared__ float stage[kNmfWaves * NB * M::NR * 64];
+    const int64_t id = nmf_block_id(), t = id / cblocks;
+    const int cb = (int)(id - t * cblocks);
     int ti, tj, rt, ct;
     nmf_tile_extent(g, t, ti, tj, rt, ct);
-    const int tid = threadIdx.x;
-    const int lane = tid & (kNmfOwn - 1), part = tid / kNmfOwn;
-    const int j = cb * kNmfOwn + lane;
-    const bool live = j < ct;
-    const int k = g.k;
-    const bool k4 = (k % 4) == 0;
-    const int rows_per_chunk = kNmfStageFloats / k;
+    if (cb * kNmfOwn >= ct) return; // a cut-off tile (uniform over the workgroup)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane % R, lk = lane / R, k = g.k;
+    const int j = cb * kNmfOwn + NB * li;
     const float *mp = Mp + t * (int64_t)g.r * k;
     const float *mzc = MzCur + t * (int64_t)k * g.c;
     float *mzn = MzNew + t * (int64_t)k * g.c;
     const float *gt = G + t * (int64_t)k * k;
-    const T *wcol = W + (int64_t)ti * g.r * ldw + (int64_t)tj * g.c + (live ? j : 0);
+    const T *wtile = W + (int64_t)ti * g.r * ldw + (int64_t)tj * g.c;
+    const int steps = (rt + M::KS - 1) / M::KS;
+    const int ibeg = steps * wave / kNmfWaves * M::KS;
+    const int iend = steps * (wave + 1) / kNmfWaves * M::KS < rt ? steps * (wave + 1) / kNmfWaves * M::KS : rt;
 
-    for (int l0 = 0; l0 < k; l0 += KC) {
-        const bool full = l0 + KC <= k;             // every rank of this pass exists
-        const int kt = full ? KC : k - l0;          // ranks of this pass
-        float acc[KC];
+    for (int l0 = 0; l0 < k; l0 += RB * R) {
+        int rank[RB]; // ranks beyond k repeat the last one; their sums are never stored
 #pragma unroll
-        for (int l = 0; l < KC; ++l) acc[l] = 0.f;
-        __syncthreads(); // the previous pass has read its Gram rows and partial sums
-        for (int e = tid; e < kt * k; e += kNmfThreads) gramL[e] = gt[(int64_t)l0 * k + e];
-        for (int i0 = 0; i0 < rt; i0 += rows_per_chunk) {
-            const int rows = (rt - i0 < rows_per_chunk) ? rt - i0 : rows_per_chunk;
-            __syncthreads(); // the previous chunk has been consumed
-            for (int e = tid; e < rows * k; e += kNmfThreads) stage[e] = mp[(int64_t)i0 * k + e];
-            __syncthreads();
-            // this wavefront's rows of the chunk
-            const int per = (rows + kNmfParts - 1) / kNmfParts;
-            const int ibeg = part * per, iend = (ibeg + per < rows) ? ibeg + per : rows;
-            if (live) {
-                // sixteen rows at a time: their W loads are requested together; the rows of M_p come out of the staged
-                // chunk as broadcast reads
-                for (int i = ibeg; i < iend; i += ZB) {
-                    T raw[ZB];
-                    float mv[ZB];
+        for (int q = 0; q < RB; ++q) rank[q] = (l0 + q * R + li < k) ? l0 + q * R + li : k - 1;
+        acc_t acc[RB][NB];
 #pragma unroll
-                    for (int u = 0; u < ZB; ++u) {
-                        const int iu = (i + u < iend) ? i + u : iend - 1; // clamped: always a valid row
-                        raw[u] = wcol[(int64_t)(i0 + iu) * ldw];
-                    }
+        for (int q = 0; q < RB; ++q)
 #pragma unroll
-                    for (int u = 0; u < ZB; ++u) {
-                        const float m = nmf_mag<T>(raw[u], method, w_threshold, amplify);
-                        mv[u] = (i + u < iend) ? m : 0.f;
-                    }
+            for (int b = 0; b < NB; ++b) acc[q][b] = nmf_zero<R>();
+
+        T wraw[U][NB];
+        float praw[U][RB];
+        auto load = [&](int i0) __attribute__((always_inline)) {
 #pragma unroll
-                    for (int u = 0; u < ZB; ++u) {
-                        const int iu = (i + u < iend) ? i + u : iend - 1;
-                        const float *row = stage + iu * k + l0;
-                        if (full && k4) { // rows of the staged chunk are 16-byte aligned: four ranks per LDS read
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * M::KS + lk, ic = i < rt ? i : rt - 1;
+                nmf_load<NB, VW>(wraw[u], wtile + (int64_t)ic * ldw, j, ct);
 #pragma unroll
-                            for (int l = 0; l < KC; l += 4) {
-                                const float4 v = *reinterpret_cast<const float4 *>(row + l);
-                                acc[l + 0] = fmaf(v.x, mv[u], acc[l + 0]);
-                                acc[l + 1] = fmaf(v.y, mv[u], acc[l + 1]);
-                                acc[l + 2] = fmaf(v.z, mv[u], acc[l + 2]);
-                                acc[l + 3] = fmaf(v.w, mv[u], acc[l + 3]);
-                            }
-                        } else { // ranks beyond k repeat the last one; their sums are never stored
+                for (int q = 0; q < RB; ++q) praw[u][q] = mp[(int64_t)ic * k + rank[q]];
+            }
+        };
+        if (ibeg < iend) load(ibeg);
+        for (int i0 = ibeg; i0 < iend; i0 += U * M::KS) {
+            float mv[U][NB], pv[U][RB];
 #pragma unroll
-                            for (int l = 0; l < KC; ++l) acc[l] = fmaf(row[l < kt ? l : kt - 1], mv[u], acc[l]);
-                        }
-                    }
+            for (int u = 0; u < U; ++u) {
+                const bool in = i0 + u * M::KS + lk < iend;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const float mag = nmf_mag<T>(wraw[u][b], method, w_threshold, amplify);
+                    mv[u][b] = in ? mag : 0.f;
                 }
+#pragma unroll
+                for (int q = 0; q < RB; ++q) pv[u][q] = in ? praw[u][q] : 0.f;
+            }
+            if (i0 + U * M::KS < iend) load(i0 + U * M::KS);
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[q][b] = M::mma(pv[u][q], mv[u][b], acc[q][b]);
+        }
+
+        float num[RB][ITEMS];
+#pragma unroll
+        for (int q = 0; q < RB; ++q) nmf_reduce<R, NB, ITEMS>(stage, acc[q], num[q], wave, lane);
+
+        // denominators: rows of the Gram matrix times the old M_z
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[q][b] = nmf_zero<R>();
+        const int gsteps = (k + M::KS - 1) / M::KS;
+        for (int s = gsteps * wave / kNmfWaves; s < gsteps * (wave + 1) / kNmfWaves; ++s) {
+            const int l = s * M::KS + lk, lc = l < k ? l : k - 1;
+            float z[NB];
+            nmf_load<NB, VW>(z, mzc + (int64_t)lc * g.c, j, ct);
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                const float a = l < k ? gt[(int64_t)lc * k + rank[q]] : 0.f; // symmetric
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[q][b] = M::mma(a, l < k ? z[b] : 0.f, acc[q][b]);
             }
         }
-        __syncthreads(); // the last chunk has been consumed: the staging area takes the partial sums
 #pragma unroll
-        for (int l = 0; l < KC; ++l) stage[(part * KC + l) * kNmfOwn + lane] = acc[l];
-        __syncthreads();
-        if (live) {
-            // this lane finishes the ranks part, part + 4, ... of its column: numerator in wavefront order, denominator
-            // from the Gram rows and the column of the old M_z
-            float den[KC / kNmfParts];
+        for (int q = 0; q < RB; ++q) {
+            float den[ITEMS];
+            nmf_reduce<R, NB, ITEMS>(stage, acc[q], den, wave, lane);
 #pragma unroll
-            for (int q = 0; q < KC / kNmfParts; ++q) den[q] = 0.f;
-            for (int b = 0; b < k; ++b) {
-                const float z = mzc[(int64_t)b * g.c + j];
-#pragma unroll
-                for (int q = 0; q < KC / kNmfParts; ++q) {
-                    const int l = part + kNmfParts * q;
-                    if (l < kt) den[q] = fmaf(gramL[l * k + b], z, den[q]);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < KC / kNmfParts; ++q) {
-                const int l = part + kNmfParts * q;
-                if (l < kt) {
-                    float num = 0.f;
-#pragma unroll
-                    for (int w = 0; w < kNmfParts; ++w) num += stage[(w * KC + l) * kNmfOwn + lane];
-                    const int64_t at = (int64_t)(l0 + l) * g.c + j;
-                    mzn[at] = mzc[at] * num / (den[q] + eps);
+            for (int e = 0; e < ITEMS; ++e) {
+                const int l = l0 + q * R + M::row(wave * (M::NR / kNmfWaves) + e / NB, lane), jj = j + e % NB;
+                if (l < k && jj < ct) {
+                    const int64_t at = (int64_t)l * g.c + jj;
+                    mzn[at] = mzc[at] * num[q][e] / (den[e] + eps);
                 }
             }
         }
     }
 }
 
-// M_p update.  Workgroup = (tile, block of 256 / PARTS rows); lane = row, group of lanes = part of the columns.
-template <typename T, int KC, int PARTS>
+// M_p update.  Workgroup = (tile, 64 rows); block b of the result holds rows b * R + (its row index), lane li = rank.
+template <typename T, int R, int RB, int VW>
 __global__ __launch_bounds__(kNmfThreads) void nmf_update_p_kernel(Geom g, const T *__restrict__ W, int64_t ldw, int method,
                                                                   float w_threshold, float amplify,
                                                                   const float *__restrict__ MpCur,
                                                                   const float *__restrict__ Mz,
                                                                   float *__restrict__ MpNew, const float *__restrict__ G,
-                                                                  float eps, int rblocks, int w_vec_ok)
+                                                                  float eps, int rblocks)
 {
-    extern __shared__ uint4 lrbi_dyn_smem[];
-    float *stage = (float *)lrbi_dyn_smem;   // [columns of the chunk][k]: M_z transposed; then the partial sums
-    float *gramL = stage + kNmfStageFloats;  // the pass's rows of M_z M_z^T (symmetric): [KC][k]
-    constexpr int kNmfParts = PARTS, kNmfOwn = kNmfThreads / PARTS;
-    const int64_t t = blockIdx.x / rblocks;
-    const int rb = (int)(blockIdx.x - t * rblocks);
+    using M = NmfMat<R>;
+    using acc_t = typename M::acc_t;
+    constexpr int NB = kNmfOwn / R, ITEMS = NB * M::NR / kNmfWaves;
+    static __shared__ float stage[kNmfWaves * NB * M::NR * 64];
+    const int64_t id = nmf_block_id(), t = id / rblocks;
+    const int rblk = (int)(id - t * rblocks);
     int ti, tj, rt, ct;
     nmf_tile_extent(g, t, ti, tj, rt, ct);
-    const int tid = threadIdx.x;
-    const int lane = tid & (kNmfOwn - 1), part = tid / kNmfOwn;
-    const int i = rb * kNmfOwn + lane;
-    const bool live = i < rt;
-    const int k = g.k;
-    const bool k4 = (k % 4) == 0;
-    const int cols_per_chunk = (kNmfStageFloats / k) & ~31; // a multiple of 32: every part is a multiple of 8 columns
+    if (rblk * kNmfOwn >= rt) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int li = lane % R, lk = lane / R, k = g.k;
     const float *mz = Mz + t * (int64_t)k * g.c;
-    const float *mpc = MpCur + (t * (int64_t)g.r + (live ? i : 0)) * k;
-    float *mpn = MpNew + (t * (int64_t)g.r + (live ? i : 0)) * k;
+    const float *mpc = MpCur + t * (int64_t)g.r * k;
+    float *mpn = MpNew + t * (int64_t)g.r * k;
     const float *gt = G + t * (int64_t)k * k;
-    const T *wrow = W + ((int64_t)ti * g.r + (live ? i : 0)) * ldw + (int64_t)tj * g.c;
+    const T *wtile = W + (int64_t)ti * g.r * ldw + (int64_t)tj * g.c;
+    int row[NB]; // rows beyond the tile repeat its last one; their sums are never stored
+#pragma unroll
+    for (int b = 0; b < NB; ++b) row[b] = (rblk * kNmfOwn + b * R + li < rt) ? rblk * kNmfOwn + b * R + li : rt - 1;
+    const int steps = (ct + 8 * M::KS - 1) / (8 * M::KS);
+    const int sbeg = steps * wave / kNmfWaves, send = steps * (wave + 1) / kNmfWaves;
 
-    for (int l0 = 0; l0 < k; l0 += KC) {
-        const bool full = l0 + KC <= k;             // every rank of this pass exists
-        const int kt = full ? KC : k - l0;          // ranks of this pass
-        float acc[KC];
+    for (int l0 = 0; l0 < k; l0 += RB * R) {
+        int rank[RB];
 #pragma unroll
-        for (int l = 0; l < KC; ++l) acc[l] = 0.f;
-        __syncthreads();
-        for (int e = tid; e < kt * k; e += kNmfThreads) gramL[e] = gt[(int64_t)l0 * k + e];
-        for (int j0 = 0; j0 < ct; j0 += cols_per_chunk) {
-            const int cols = (ct - j0 < cols_per_chunk) ? ct - j0 : cols_per_chunk;
-            __syncthreads();
-            // transpose while staging: consecutive lanes read consecutive columns of one row of M_z
-            for (int e = tid; e < cols * k; e += kNmfThreads) {
-                const int l = e / cols, jj = e - l * cols;
-                stage[jj * k + l] = mz[(int64_t)l * g.c + j0 + jj];
-            }
-            __syncthreads();
-            // this wavefront's columns of the chunk, a multiple of 8 so that the 16-byte loads of W stay aligned
-            const int per = ((cols + kNmfParts - 1) / kNmfParts + 7) & ~7;
-            const int jbeg = (part * per < cols) ? part * per : cols, jend = (jbeg + per < cols) ? jbeg + per : cols;
-            if (live) {
-                // eight columns at a time: one 16-byte load of the lane's row of W where the alignment allows it
-                constexpr int VEC = 16 / (int)sizeof(T);
-                const bool vec = w_vec_ok && (((int64_t)tj * g.c + j0) % VEC == 0);
-                for (int jj = jbeg; jj < jend; jj += 8) {
-                    float mv[8];
-                    if (vec && jj + 8 <= jend) {
-                        T tmp[8];
+        for (int q = 0; q < RB; ++q) rank[q] = (l0 + q * R + li < k) ? l0 + q * R + li : k - 1;
+        acc_t acc[RB][NB];
 #pragma unroll
-                        for (int q = 0; q < 8 / VEC; ++q)
-                            *reinterpret_cast<uint4 *>(tmp + q * VEC) = *reinterpret_cast<const uint4 *>(wrow + j0 + jj + q * VEC);
+        for (int q = 0; q < RB; ++q)
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) mv[u] = nmf_mag<T>(tmp[u], method, w_threshold, amplify);
-                    } else {
-                        T raw[8];
+            for (int b = 0; b < NB; ++b) acc[q][b] = nmf_zero<R>();
+
+        T wraw[NB][8];
+        float zraw[RB][8];
+        auto load = [&](int s) __attribute__((always_inline)) {
+            const int j = s * 8 * M::KS + 8 * lk;
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const int ju = (jj + u < jend) ? jj + u : jend - 1;
-                            raw[u] = wrow[j0 + ju];
-                        }
+            for (int b = 0; b < NB; ++b) nmf_load<8, VW>(wraw[b], wtile + (int64_t)row[b] * ldw, j, ct);
 #pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            const float m = nmf_mag<T>(raw[u], method, w_threshold, amplify);
-                            mv[u] = (jj + u < jend) ? m : 0.f;
-                        }
-                    }
+            for (int q = 0; q < RB; ++q) nmf_load<8, VW>(zraw[q], mz + (int64_t)rank[q] * g.c, j, ct);
+        };
+        if (sbeg < send) load(sbeg);
+        for (int s = sbeg; s < send; ++s) {
+            const int j = s * 8 * M::KS + 8 * lk;
+            float mv[NB][8], zv[RB][8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        const int ju = (jj + u < jend) ? jj + u : jend - 1;
-                        const float *col = stage + ju * k + l0;
-                        if (full && k4) { // rows of the staged chunk are 16-byte aligned: four ranks per LDS read
+            for (int u = 0; u < 8; ++u) {
+                const bool in = j + u < ct;
 #pragma unroll
-                            for (int l = 0; l < KC; l += 4) {
-                                const float4 v = *reinterpret_cast<const float4 *>(col + l);
-                                acc[l + 0] = fmaf(v.x, mv[u], acc[l + 0]);
-                                acc[l + 1] = fmaf(v.y, mv[u], acc[l + 1]);
-                                acc[l + 2] = fmaf(v.z, mv[u], acc[l + 2]);
-                                acc[l + 3] = fmaf(v.w, mv[u], acc[l + 3]);
-                            }
-                        } else { // ranks beyond k repeat the last one; their sums are never stored
-#pragma unroll
-                            for (int l = 0; l < KC; ++l) acc[l] = fmaf(col[l < kt ? l : kt - 1], mv[u], acc[l]);
-                        }
-                    }
+                for (int b = 0; b < NB; ++b) {
+                    const float mag = nmf_mag<T>(wraw[b][u], method, w_threshold, amplify);
+                    mv[b][u] = in ? mag : 0.f;
                 }
+#pragma unroll
+                for (int q = 0; q < RB; ++q) zv[q][u] = in ? zraw[q][u] : 0.f;
+            }
+            if (s + 1 < send) load(s + 1);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+#pragma unroll
+                for (int q = 0; q < RB; ++q)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) acc[q][b] = M::mma(mv[b][u], zv[q][u], acc[q][b]);
+        }
+
+        float num[RB][ITEMS];
+#pragma unroll
+        for (int q = 0; q < RB; ++q) nmf_reduce<R, NB, ITEMS>(stage, acc[q], num[q], wave, lane);
+
+        // denominators: the old M_p times columns of the Gram matrix
+#pragma unroll
+        for (int q = 0; q < RB; ++q)
+#pragma unroll
+            for (int b = 0; b < NB; ++b) acc[q][b] = nmf_zero<R>();
+        const int gsteps = (k + M::KS - 1) / M::KS;
+        for (int s = gsteps * wave / kNmfWaves; s < gsteps * (wave + 1) / kNmfWaves; ++s) {
+            const int l = s * M::KS + lk, lc = l < k ? l : k - 1;
+            float p[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b) p[b] = l < k ? mpc[(int64_t)row[b] * k + lc] : 0.f;
+#pragma unroll
+            for (int q = 0; q < RB; ++q) {
+                const float v = l < k ? gt[(int64_t)lc * k + rank[q]] : 0.f;
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[q][b] = M::mma(p[b], v, acc[q][b]);
             }
         }
-        __syncthreads();
 #pragma unroll
-        for (int l = 0; l < KC; ++l) stage[(part * KC + l) * kNmfOwn + lane] = acc[l];
-        __syncthreads();
-        if (live) {
-            float den[KC / kNmfParts];
+        for (int q = 0; q < RB; ++q) {
+            float den[ITEMS];
+            nmf_reduce<R, NB, ITEMS>(stage, acc[q], den, wave, lane);
 #pragma unroll
-            for (int q = 0; q < KC / kNmfParts; ++q) den[q] = 0.f;
-            for (int b = 0; b < k; ++b) {
-                const float pv = mpc[b];
-#pragma unroll
-                for (int q = 0; q < KC / kNmfParts; ++q) {
-                    const int l = part + kNmfParts * q;
-                    if (l < kt) den[q] = fmaf(pv, gramL[l * k + b], den[q]);
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < KC / kNmfParts; ++q) {
-                const int l = part + kNmfParts * q;
-                if (l < kt) {
-                    float num = 0.f;
-#pragma unroll
-                    for (int w = 0; w < kNmfParts; ++w) num += stage[(w * KC + l) * kNmfOwn + lane];
-                    mpn[l0 + l] = mpc[l0 + l] * num / (den[q] + eps);
+            for (int e = 0; e < ITEMS; ++e) {
+                const int i = rblk * kNmfOwn + (e % NB) * R + M::row(wave * (M::NR / kNmfWaves) + e / NB, lane);
+                const int l = l0 + q * R + li;
+                if (i < rt && l < k) {
+                    const int64_t at = (int64_t)i * k + l;
+                    mpn[at] = mpc[at] * num[q][e] / (den[e] + eps);
                 }
             }
         }
@@ -372,30 +447,24 @@ static int nmf_copy(const float *src, float *dst, int64_t count, hipStream_t str
     return LRBI_OK;
 }
 
-template <typename T, int KC, int PARTS>
+template <typename T, int R, int RB, int VW>
 static int nmf_iterate(const Geom &g, const void *dW, int64_t ldw, int method, float w_threshold, float amplify, float *dMp,
                        float *dMz, int iters, float eps, float *wsMp, float *wsMz, float *wsG, hipStream_t stream)
 {
-    constexpr int kNmfOwn = kNmfThreads / PARTS;
     const int64_t tiles = (int64_t)g.tile_rows * g.tile_cols;
     const int cblocks = (g.c + kNmfOwn - 1) / kNmfOwn, rblocks = (g.r + kNmfOwn - 1) / kNmfOwn;
-    const int eunits = (g.k % 4 == 0) ? g.k * g.k / 4 : g.k * g.k; // a lane owns four entries of the Gram matrix, or one
-    const int eblocks = (eunits + kNmfThreads - 1) / kNmfThreads;
-    if (tiles * cblocks > 0x7FFFFFFF || tiles * rblocks > 0x7FFFFFFF || tiles * eblocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
-    const size_t lds = ((size_t)kNmfStageFloats + (size_t)KC * g.k) * 4; // staging area + the pass's Gram rows
-    LRBI_SET_MAX_LDS((nmf_update_z_kernel<T, KC, PARTS>), lds);
-    LRBI_SET_MAX_LDS((nmf_update_p_kernel<T, KC, PARTS>), lds);
+    const int kblocks = (g.k + R - 1) / R, pairs = kblocks * (kblocks + 1) / 2;
+    if (tiles * cblocks > 0x7FFFFFFF || tiles * rblocks > 0x7FFFFFFF || tiles * pairs > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     float *mp_cur = dMp, *mp_new = wsMp, *mz_cur = dMz, *mz_new = wsMz;
-    const int w_vec_ok = (((uintptr_t)dW & 15) == 0) && ((ldw * (int64_t)sizeof(T)) % 16 == 0);
     for (int it = 0; it < iters; ++it) {
-        LRBI_LAUNCH((nmf_gram_kernel<false>), dim3((unsigned)(tiles * eblocks)), dim3(kNmfThreads), 0, stream, g, mp_cur, wsG,
-                    eblocks);
-        LRBI_LAUNCH((nmf_update_z_kernel<T, KC, PARTS>), dim3((unsigned)(tiles * cblocks)), dim3(kNmfThreads), lds, stream, g,
-                           (const T *)dW, ldw, method, w_threshold, amplify, mp_cur, mz_cur, mz_new, wsG, eps, cblocks);
-        LRBI_LAUNCH((nmf_gram_kernel<true>), dim3((unsigned)(tiles * eblocks)), dim3(kNmfThreads), 0, stream, g, mz_new, wsG,
-                    eblocks);
-        LRBI_LAUNCH((nmf_update_p_kernel<T, KC, PARTS>), dim3((unsigned)(tiles * rblocks)), dim3(kNmfThreads), lds, stream, g,
-                           (const T *)dW, ldw, method, w_threshold, amplify, mp_cur, mz_new, mp_new, wsG, eps, rblocks, w_vec_ok);
+        LRBI_LAUNCH((nmf_gram_kernel<R, VW, false>), dim3((unsigned)(tiles * pairs)), dim3(kGramThreads), 0, stream, g, mp_cur,
+                    wsG, kblocks, pairs);
+        LRBI_LAUNCH((nmf_update_z_kernel<T, R, RB, VW>), dim3((unsigned)(tiles * cblocks)), dim3(kNmfThreads), 0, stream, g,
+                    (const T *)dW, ldw, method, w_threshold, amplify, mp_cur, mz_cur, mz_new, wsG, eps, cblocks);
+        LRBI_LAUNCH((nmf_gram_kernel<R, VW, true>), dim3((unsigned)(tiles * pairs)), dim3(kGramThreads), 0, stream, g, mz_new,
+                    wsG, kblocks, pairs);
+        LRBI_LAUNCH((nmf_update_p_kernel<T, R, RB, VW>), dim3((unsigned)(tiles * rblocks)), dim3(kNmfThreads), 0, stream, g,
+                    (const T *)dW, ldw, method, w_threshold, amplify, mp_cur, mz_new, mp_new, wsG, eps, rblocks);
         float *tmp = mp_cur;
         mp_cur = mp_new;
         mp_new = tmp;
@@ -416,14 +485,25 @@ template <typename T>
 static int nmf_dtype(const Geom &g, const void *dW, int64_t ldw, int method, float w_threshold, float amplify, float *dMp,
                      float *dMz, int iters, float eps, float *wsMp, float *wsMz, float *wsG, hipStream_t stream)
 {
-    // ranks held in registers per pass: the smallest of 8 / 16 / 32 that covers k (several passes above 32); tiles are
-    // split four ways more finely when whole-tile column blocks would leave compute units idle
-    const int64_t coarse = (int64_t)g.tile_rows * g.tile_cols * ((((g.c < g.r) ? g.c : g.r) + kNmfThreads - 1) / kNmfThreads);
-    const bool fine = coarse < 2 * (int64_t)compute_units_of(stream);
+    // elements per load: 8, 4 or 1.  A piece lies inside a tile and inside a row as a whole (c and n are multiples of
+    // it) and is aligned to its size or to 16 bytes; the factors are read in 16-byte pieces from 4 elements up.
+    const auto fits = [&](int vw) {
+        const int64_t bytes = (int64_t)vw * (int64_t)sizeof(T) < 16 ? (int64_t)vw * (int64_t)sizeof(T) : 16;
+        return g.c % vw == 0 && g.n % vw == 0 && (ldw * (int64_t)sizeof(T)) % bytes == 0 && ((uintptr_t)dW % bytes) == 0 &&
+               (((uintptr_t)dMz | (uintptr_t)wsMz) & 15) == 0;
+    };
 #define LRBI_NMF_ARGS g, dW, ldw, method, w_threshold, amplify, dMp, dMz, iters, eps, wsMp, wsMz, wsG, stream
-    if (g.k <= 8) return fine ? nmf_iterate<T, 8, 4>(LRBI_NMF_ARGS) : nmf_iterate<T, 8, 1>(LRBI_NMF_ARGS);
-    if (g.k <= 16) return fine ? nmf_iterate<T, 16, 4>(LRBI_NMF_ARGS) : nmf_iterate<T, 16, 1>(LRBI_NMF_ARGS);
-    return fine ? nmf_iterate<T, 32, 4>(LRBI_NMF_ARGS) : nmf_iterate<T, 32, 1>(LRBI_NMF_ARGS);
+#define LRBI_NMF_RANKS(VW)                                                                                  \
+    return g.k <= 16   ? nmf_iterate<T, 16, 1, VW>(LRBI_NMF_ARGS)                                           \
+           : g.k <= 32 ? nmf_iterate<T, 32, 1, VW>(LRBI_NMF_ARGS)                                           \
+           : g.k <= 64 ? nmf_iterate<T, 32, 2, VW>(LRBI_NMF_ARGS)                                           \
+                       : nmf_iterate<T, 32, 4, VW>(LRBI_NMF_ARGS)
+    if constexpr (sizeof(T) == 2) {
+        if (fits(8)) { LRBI_NMF_RANKS(8); }
+    }
+    if (fits(4)) { LRBI_NMF_RANKS(4); }
+    LRBI_NMF_RANKS(1);
+#undef LRBI_NMF_RANKS
 #undef LRBI_NMF_ARGS
 }
 
