@@ -33,6 +33,7 @@ namespace lrbi {
 
 static constexpr int kEvalThreads = 512;
 static constexpr int kEvalWaves = kEvalThreads / 64;
+static constexpr int kSpBatch = 8; // S_p values whose representatives are evaluated in one launch
 
 template <typename T> struct Mag;
 template <> struct Mag<float> {
@@ -148,6 +149,69 @@ __device__ __forceinline__ void search_step_tile(const Geom &g, const SearchStep
     a.st[t] = s;
 }
 
+// I_z of one tile into LDS [k][izw]: a wavefront compares 64 consecutive entries of one row of M_z per step (one
+// coalesced read) and the 64 outcomes, gathered across the lanes, are the two packed words of that step; eight steps'
+// reads are requested together.  out: the tile's packed I_z in global memory, or nullptr.
+__device__ __forceinline__ void tile_iz_bits(const Geom &g, const float *__restrict__ mz, int ct, float tz, uint32_t *iz,
+                                             uint32_t *__restrict__ out)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int steps_per_row = g.izw / 2;
+    const int zsteps = g.k * steps_per_row;
+    constexpr int ZB = 8;
+    for (int st0 = wave; st0 < zsteps; st0 += ZB * kEvalWaves) {
+        float v[ZB];
+        bool ok[ZB];
+#pragma unroll
+        for (int q = 0; q < ZB; ++q) {
+            const int st = st0 + q * kEvalWaves;
+            const int l = st / steps_per_row, sq = st - l * steps_per_row;
+            const int j = 64 * sq + lane;
+            ok[q] = (st < zsteps) && (j < ct); // columns a cut-off tile leaves outside the matrix stay 0
+            v[q] = ok[q] ? mz[(int64_t)l * g.c + j] : 0.f;
+        }
+#pragma unroll
+        for (int q = 0; q < ZB; ++q) {
+            const int st = st0 + q * kEvalWaves;
+            if (st < zsteps) { // uniform over the wavefront
+                const int l = st / steps_per_row, sq = st - l * steps_per_row;
+                const unsigned long long b = __ballot(ok[q] && v[q] >= tz);
+                if (lane < 2) {
+                    const uint32_t bits = (uint32_t)(lane ? (b >> 32) : b);
+                    iz[l * g.izw + 2 * sq + lane] = bits;
+                    if (out) out[l * (int64_t)g.izw + 2 * sq + lane] = bits;
+                }
+            }
+        }
+    }
+}
+
+// I_p of nrows rows of one tile into LDS [nrows][ipw]: one lane per (row, 32-bit word), whose up to 32 entries are
+// read eight at a time.  out: those rows of the packed I_p in global memory, or nullptr.
+__device__ __forceinline__ void tile_ip_bits(const Geom &g, const float *__restrict__ mp, int nrows, float tp, uint32_t *ip,
+                                             uint32_t *__restrict__ out)
+{
+    for (int idx = threadIdx.x; idx < nrows * g.ipw; idx += kEvalThreads) {
+        const int i = idx / g.ipw, wq = idx - i * g.ipw;
+        uint32_t bits = 0u;
+        const int l0 = 32 * wq;
+        const float *mrow = mp + (int64_t)i * g.k;
+        for (int b0 = 0; b0 < 32 && l0 + b0 < g.k; b0 += 8) {
+            float v[8];
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const int l = l0 + b0 + b;
+                v[b] = mrow[l < g.k ? l : g.k - 1]; // clamped: always a valid address
+            }
+#pragma unroll
+            for (int b = 0; b < 8; ++b)
+                if (l0 + b0 + b < g.k && v[b] >= tp) bits |= 1u << (b0 + b);
+        }
+        ip[idx] = bits;
+        if (out) out[idx] = bits;
+    }
+}
+
 // one addend of the cost, in double (a magnitude and its square are exact there)
 template <bool SQ> __device__ __forceinline__ void cost_add(double &acc, float a)
 {
@@ -191,66 +255,21 @@ __global__ __launch_bounds__(kEvalThreads) void threshold_eval_kernel(Geom g, co
     const int row_hi = (band_hi < rt) ? band_hi : rt;
     const int nrows = (row_hi > row_lo) ? row_hi - row_lo : 0;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const float tp = Tp[t], tz = Tz[t];
+    // blockIdx.y = candidate: its own thresholds and results, arrays of one entry per tile (per workgroup) each
+    const int64_t cand_tile = (int64_t)blockIdx.y * g.tile_rows * g.tile_cols + t;
+    const int64_t cand_block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;
+    const float tp = Tp[cand_tile], tz = Tz[cand_tile];
 
     // ---- 1. binary factors of the tile
-    // I_z: a wavefront compares 64 consecutive entries of one row of M_z per step (one coalesced
-    // read) and the 64 outcomes, gathered across the lanes, are the two packed words of that step;
-    // eight steps' reads are requested together
-    const float *mz = Mz + t * (int64_t)g.k * g.c;
-    const int steps_per_row = g.izw / 2;
-    const int zsteps = g.k * steps_per_row;
-    constexpr int ZB = 8;
-    for (int st0 = wave; st0 < zsteps; st0 += ZB * kEvalWaves) {
-        float v[ZB];
-        bool ok[ZB];
-#pragma unroll
-        for (int q = 0; q < ZB; ++q) {
-            const int st = st0 + q * kEvalWaves;
-            const int l = st / steps_per_row, sq = st - l * steps_per_row;
-            const int j = 64 * sq + lane;
-            ok[q] = (st < zsteps) && (j < ct); // columns a cut-off tile leaves outside the matrix stay 0
-            v[q] = ok[q] ? mz[(int64_t)l * g.c + j] : 0.f;
-        }
-#pragma unroll
-        for (int q = 0; q < ZB; ++q) {
-            const int st = st0 + q * kEvalWaves;
-            if (st < zsteps) { // uniform over the wavefront
-                const int l = st / steps_per_row, sq = st - l * steps_per_row;
-                const unsigned long long b = __ballot(ok[q] && v[q] >= tz);
-                if (lane < 2) {
-                    const uint32_t bits = (uint32_t)(lane ? (b >> 32) : b);
-                    iz[l * g.izw + 2 * sq + lane] = bits;
-                    if (IzOut && band == 0) IzOut[(t * g.k + l) * (int64_t)g.izw + 2 * sq + lane] = bits;
-                }
-            }
-        }
-    }
-    // I_p: one lane per (row, 32-bit word); its up to 32 entries are read eight at a time
-    const float *mp = Mp + (t * (int64_t)g.r + row_lo) * g.k;
-    for (int idx = tid; idx < nrows * g.ipw; idx += kEvalThreads) {
-        const int i = idx / g.ipw, wq = idx - i * g.ipw; // row of the band
-        uint32_t bits = 0u;
-        const int l0 = 32 * wq;
-        const float *mrow = mp + (int64_t)i * g.k;
-        for (int b0 = 0; b0 < 32 && l0 + b0 < g.k; b0 += 8) {
-            float v[8];
-#pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                const int l = l0 + b0 + b;
-                v[b] = mrow[l < g.k ? l : g.k - 1]; // clamped: always a valid address
-            }
-#pragma unroll
-            for (int b = 0; b < 8; ++b)
-                if (l0 + b0 + b < g.k && v[b] >= tp) bits |= 1u << (b0 + b);
-        }
-        ip[idx] = bits;
-        if (IpOut) IpOut[(t * g.r + row_lo + i) * (int64_t)g.ipw + wq] = bits;
-    }
+    tile_iz_bits(g, Mz + t * (int64_t)g.k * g.c, ct, tz, iz,
+                 IzOut && band == 0 ? IzOut + t * (int64_t)g.k * g.izw : nullptr);
+    const int64_t prow0 = t * (int64_t)g.r + row_lo;
+    tile_ip_bits(g, Mp + prow0 * g.k, nrows, tp, ip, IpOut ? IpOut + prow0 * g.ipw : nullptr);
     // stored rows of I_p that a cut-off tile leaves outside the matrix are written as zero
     if (IpOut)
         for (int idx = nrows * g.ipw + tid; idx < (band_hi - row_lo) * g.ipw; idx += kEvalThreads)
             IpOut[(t * g.r + row_lo) * (int64_t)g.ipw + idx] = 0u;
+    if (!Kept) return; // only the packed factors are wanted
     __syncthreads();
 
     // ---- 2. the tile as a list of 16-byte pieces (row-major): ones of I_a, and magnitudes kept by
@@ -408,8 +427,8 @@ __global__ __launch_bounds__(kEvalThreads) void threshold_eval_kernel(Geom g, co
             kk += wave_kept[w];
         }
         c *= cost_scale;
-        Cost[blockIdx.x] = c;
-        Kept[blockIdx.x] = kk;
+        Cost[cand_block] = c;
+        Kept[cand_block] = kk;
         if (step.st && bands == 1) search_step_tile(g, step, t, kk, c);
     }
 }
@@ -424,12 +443,13 @@ __global__ __launch_bounds__(256) void threshold_eval_reduce_kernel(const unsign
     if (t >= tiles) return;
     unsigned long long kk = 0ull;
     double c = 0.0;
+    const int64_t ct = (int64_t)blockIdx.y * tiles + t; // blockIdx.y = candidate
     for (int b = 0; b < bands; ++b) {
-        kk += pk[t * bands + b];
-        c += pc[t * bands + b];
+        kk += pk[ct * bands + b];
+        c += pc[ct * bands + b];
     }
-    Kept[t] = kk;
-    Cost[t] = c;
+    Kept[ct] = kk;
+    Cost[ct] = c;
     if (step.st) search_step_tile(g, step, t, kk, c);
 }
 
@@ -458,7 +478,7 @@ EvalPlan plan_threshold_eval(const Geom &g)
 template <typename T>
 static int launch_eval_t(const Geom &g, const void *dW, int64_t ldw, float w_threshold, CostManip manip, const float *dMp,
                          const float *dMz, const float *dTp, const float *dTz, void *dIp, void *dIz, uint64_t *dKept,
-                         double *dCost, void *dWorkspace, hipStream_t stream, const SearchStepArgs &step)
+                         double *dCost, void *dWorkspace, hipStream_t stream, const SearchStepArgs &step, int cands)
 {
     const int64_t tiles = (int64_t)g.tile_rows * g.tile_cols;
     EvalPlan plan = plan_threshold_eval(g);
@@ -469,19 +489,19 @@ static int launch_eval_t(const Geom &g, const void *dW, int64_t ldw, float w_thr
     if (tiles * plan.bands > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     unsigned long long *pk = (unsigned long long *)dKept;
     double *pc = dCost;
-    if (plan.bands > 1) {
+    if (plan.bands > 1 && dKept) {
         pk = (unsigned long long *)dWorkspace;
-        pc = (double *)((char *)dWorkspace + (size_t)tiles * plan.bands * 8);
+        pc = (double *)((char *)dWorkspace + (size_t)tiles * plan.bands * cands * 8);
     }
     const size_t smem = (threshold_eval_lds_bytes(g) + 15) / 16 * 16;
     const int w_vec_ok = (((uintptr_t)dW & 15) == 0) && (ldw % Mag<T>::VEC == 0);
     auto kern = manip.squared ? threshold_eval_kernel<T, true> : threshold_eval_kernel<T, false>;
     LRBI_SET_MAX_LDS(kern, smem);
-    LRBI_LAUNCH(kern, dim3((unsigned)(tiles * plan.bands)), dim3(kEvalThreads), smem, stream, g, (const T *)dW,
+    LRBI_LAUNCH(kern, dim3((unsigned)(tiles * plan.bands), (unsigned)cands), dim3(kEvalThreads), smem, stream, g, (const T *)dW,
                        ldw, w_threshold, manip.scale, dMp, dMz, dTp, dTz, (uint32_t *)dIp, (uint32_t *)dIz, pk, pc, w_vec_ok,
                        plan.bands, plan.rows_per_band, step);
-    if (plan.bands > 1) {
-        LRBI_LAUNCH(threshold_eval_reduce_kernel, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, stream, pk,
+    if (plan.bands > 1 && dKept) {
+        LRBI_LAUNCH(threshold_eval_reduce_kernel, dim3((unsigned)((tiles + 255) / 256), (unsigned)cands), dim3(256), 0, stream, pk,
                            pc, tiles, plan.bands, (unsigned long long *)dKept, dCost, g, step);
     }
     return LRBI_OK;
@@ -490,18 +510,18 @@ static int launch_eval_t(const Geom &g, const void *dW, int64_t ldw, float w_thr
 static int launch_eval_step(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, float w_threshold, CostManip manip,
                             const float *dMp,
                             const float *dMz, const float *dTp, const float *dTz, void *dIp, void *dIz, uint64_t *dKept,
-                            double *dCost, void *dWorkspace, hipStream_t stream, const SearchStepArgs &step)
+                            double *dCost, void *dWorkspace, hipStream_t stream, const SearchStepArgs &step, int cands = 1)
 {
     switch (dt) {
     case LRBI_F32:
         return launch_eval_t<float>(g, dW, ldw, w_threshold, manip, dMp, dMz, dTp, dTz, dIp, dIz, dKept, dCost, dWorkspace, stream,
-                                    step);
+                                    step, cands);
     case LRBI_F16:
         return launch_eval_t<__half>(g, dW, ldw, w_threshold, manip, dMp, dMz, dTp, dTz, dIp, dIz, dKept, dCost, dWorkspace, stream,
-                                     step);
+                                     step, cands);
     case LRBI_BF16:
         return launch_eval_t<__hip_bfloat16>(g, dW, ldw, w_threshold, manip, dMp, dMz, dTp, dTz, dIp, dIz, dKept, dCost, dWorkspace,
-                                             stream, step);
+                                             stream, step, cands);
     default: return LRBI_ERR_DTYPE;
     }
 }
@@ -517,10 +537,12 @@ int launch_threshold_eval(const Geom &g, lrbi_dtype dt, const void *dW, int64_t 
 }
 
 // ---------------------------------------------------------------------------
-// Threshold search of Algorithm 1 (Sec. 2.1), all tiles in lockstep: for every S_p of the
-// caller's list, a bisection on S_z whose probes are evaluated by the kernel above (one launch
-// per probe for all tiles); the per-tile search state lives in the caller's workspace and is
-// advanced inside those launches (search_step_tile), so the host never waits for the device.
+// Threshold search of Algorithm 1 (Sec. 2.1).  The bisection on S_z is steered by the number of ones alone, which
+// needs the factors and not W: one workgroup per (tile, S_p) runs all its probes (search_bisect_kernel), then the
+// kernel above forms the cost of every S_p's representative, all of them in one launch, and search_pick_kernel
+// compares them in list order.  Few tiles that are very large keep the other order (one evaluation launch
+// per probe, split over bands of rows, advancing the tile's state with search_step_tile).  Either way the state lives
+// in the caller's workspace and the host never waits for the device.
 // ---------------------------------------------------------------------------
 
 // Sorts the used entries of one tile's factor (ascending, bitonic network over `padded` = 2^j slots, the
@@ -594,6 +616,139 @@ __global__ __launch_bounds__(256) void search_begin_kernel(Geom g, SearchState *
     Tz[t] = threshold_at(sortedMz + t * stride_z, g.k * ct, sz0);
 }
 
+// A batch of S_p values: the list entries and the first probe of S_z for each (Eq. 7 solved for S_z)
+struct SpBatch {
+    double sp[kSpBatch], sz0[kSpBatch];
+};
+
+// All probes of one (tile, S_p): blockIdx.x = tile, blockIdx.y = S_p.  I_p is packed once; each probe packs I_z from
+// the tile's M_z (in the L2 from the first probe on), counts the ones of I_a from LDS, and lane 0 moves the interval.
+// Bound by the latency of that chain of steps and by vector-ALU issue in the count; W is not touched.  4096 x 9216 f16,
+// 256 x 256 tiles, rank 16, eight S_p, ten probes: 278 us, where 80 sweeps over W took 80 x 25 us; the whole search
+// 2167 -> 598 us.
+__global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, const float *__restrict__ Mp,
+                                                                     const float *__restrict__ Mz,
+                                                                     const float *__restrict__ sortedMp,
+                                                                     const float *__restrict__ sortedMz,
+                                                                     int64_t stride_p, int64_t stride_z, SpBatch batch,
+                                                                     double keep_fraction, int steps,
+                                                                     float *__restrict__ Tp, float *__restrict__ Tz)
+{
+    extern __shared__ uint4 lrbi_dyn_smem[];
+    uint32_t *iz = reinterpret_cast<uint32_t *>(lrbi_dyn_smem); // [k][izw]
+    uint32_t *ip = iz + g.k * g.izw;                            // [r][ipw]
+    static __shared__ unsigned int wave_kept[kEvalWaves];
+    const int64_t t = blockIdx.x;
+    int rt, ct;
+    tile_extent(g, t, rt, ct);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const float tp = threshold_at(sortedMp + t * stride_p, rt * g.k, batch.sp[blockIdx.y]);
+    const float *mz = Mz + t * (int64_t)g.k * g.c;
+    const float *sorted = sortedMz + t * stride_z;
+    const long long target =
+        (long long)floor(__dadd_rn(__dmul_rn(__dmul_rn(keep_fraction, (double)rt), (double)ct), 0.5));
+    tile_ip_bits(g, Mp + t * (int64_t)g.r * g.k, rt, tp, ip, nullptr);
+    // every lane follows the same interval
+    double lo = 0.0, hi = 1.0, sz = batch.sz0[blockIdx.y];
+    long long rep_diff = -1;
+    float rep_tz = 0.f;
+    const int words = (ct + 31) / 32;
+    const int drow = kEvalThreads / words, dword = kEvalThreads - drow * words;
+    const int row0 = tid / words, word0 = tid - row0 * words;
+    for (int step = 0; step < steps; ++step) {
+        const float tz = threshold_at(sorted, g.k * ct, sz);
+        tile_iz_bits(g, mz, ct, tz, iz, nullptr);
+        __syncthreads();
+        unsigned int kept = 0u; // ones of one lane: at most 2^32 / 512 by the limits on r and c
+        for (int i = row0, wc = word0; i < rt;) {
+            uint32_t word = 0u;
+            for (int q = 0; q < g.ipw; ++q) {
+                uint32_t sel = ip[i * g.ipw + q];
+                while (sel) {
+                    const int l = __builtin_ctz(sel) + 32 * q;
+                    sel &= sel - 1u;
+                    word |= iz[l * g.izw + wc];
+                }
+            }
+            kept += (unsigned int)__builtin_popcount(word);
+            i += drow;
+            wc += dword;
+            if (wc >= words) {
+                wc -= words;
+                ++i;
+            }
+        }
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) kept += __shfl_xor(kept, s, 64);
+        if (lane == 0) wave_kept[wave] = kept;
+        __syncthreads(); // also: every lane has read I_z before the next probe writes it
+        long long k = 0;
+#pragma unroll
+        for (int w = 0; w < kEvalWaves; ++w) k += wave_kept[w]; // read again only after the next probe's first barrier
+        const long long diff = (k > target) ? k - target : target - k;
+        if (rep_diff < 0 || diff < rep_diff) {
+            rep_diff = diff;
+            rep_tz = tz;
+        }
+        if (k > target) lo = sz; // too many ones: I_z must get sparser
+        else hi = sz;
+        sz = 0.5 * (lo + hi);
+    }
+    if (tid == 0) {
+        const int64_t at = (int64_t)blockIdx.y * gridDim.x + t;
+        Tp[at] = tp;
+        Tz[at] = rep_tz;
+    }
+}
+
+// Winner of a batch of representatives (arrays of `tiles` entries per S_p) against the winner so far, in list order.
+__global__ __launch_bounds__(256) void search_pick_kernel(Geom g, SearchState *__restrict__ st, int64_t tiles, int count,
+                                                          int first, double keep_fraction, long long tolerance,
+                                                          const float *__restrict__ Tp, const float *__restrict__ Tz,
+                                                          const unsigned long long *__restrict__ Kept,
+                                                          const double *__restrict__ Cost, float *__restrict__ TpBest,
+                                                          float *__restrict__ TzBest,
+                                                          unsigned long long *__restrict__ KeptBest,
+                                                          double *__restrict__ CostBest)
+{
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (t >= tiles) return;
+    int rt, ct;
+    tile_extent(g, t, rt, ct);
+    const long long target =
+        (long long)floor(__dadd_rn(__dmul_rn(__dmul_rn(keep_fraction, (double)rt), (double)ct), 0.5));
+    long long best_diff = first ? -1 : st[t].best_diff;
+    bool best_eligible = first ? false : st[t].best_eligible != 0;
+    int64_t win = -1;
+    double best_cost = first ? 0.0 : CostBest[t];
+    for (int a = 0; a < count; ++a) {
+        const int64_t at = a * tiles + t;
+        const long long k = (long long)Kept[at];
+        const long long diff = (k > target) ? k - target : target - k;
+        const double cost = Cost[at];
+        const bool eligible = diff <= tolerance;
+        bool better;
+        if (best_diff < 0) better = true;
+        else if (eligible != best_eligible) better = eligible;
+        else if (eligible) better = cost < best_cost;
+        else better = diff < best_diff;
+        if (better) {
+            best_diff = diff;
+            best_eligible = eligible;
+            best_cost = cost;
+            win = at;
+        }
+    }
+    st[t].best_diff = best_diff;
+    st[t].best_eligible = best_eligible ? 1 : 0;
+    if (win >= 0) {
+        TpBest[t] = Tp[win];
+        TzBest[t] = Tz[win];
+        KeptBest[t] = Kept[win];
+        CostBest[t] = best_cost;
+    }
+}
+
 constexpr int kSortOnChip = 16384; // floats: 64 KiB of on-chip memory
 
 static int64_t pow2_at_least(int64_t n)
@@ -617,12 +772,23 @@ SearchPlan plan_search(const Geom &g)
     p.off_sorted_mz = up(p.off_sorted_mp + tiles * (uint64_t)p.stride_p * 4);
     p.off_state = up(p.off_sorted_mz + tiles * (uint64_t)p.stride_z * 4);
     p.off_tp = up(p.off_state + tiles * sizeof(SearchState));
-    p.off_tz = up(p.off_tp + tiles * 4);
-    p.off_kept = up(p.off_tz + tiles * 4);
-    p.off_cost = up(p.off_kept + tiles * 8);
-    p.off_eval = up(p.off_cost + tiles * 8);
-    p.bytes = p.off_eval + plan_threshold_eval(g).workspace_bytes;
+    p.off_tz = up(p.off_tp + tiles * kSpBatch * 4);
+    p.off_kept = up(p.off_tz + tiles * kSpBatch * 4);
+    p.off_cost = up(p.off_kept + tiles * kSpBatch * 8);
+    p.off_eval = up(p.off_cost + tiles * kSpBatch * 8);
+    p.bytes = p.off_eval + plan_threshold_eval(g).workspace_bytes * kSpBatch;
     return p;
+}
+
+// Whether one workgroup per (tile, S_p) runs the whole bisection: when that fills the chip, or when a probe is so little
+// work that its launches cost more.  One tile, 10 probes: 512 x 576, rank 32, two S_p 1.28 -> 1.11 ms and four 100 x 100
+// tiles, two S_p 220 -> 64 us (most of the first is the sort); beyond the line one workgroup is the slower form
+// (1000 x 1000, rank 16, one S_p: 653 us against 613; 1900 x 1024: 1364 against 1177).
+static bool search_bisects(const Geom &g, int n_sp)
+{
+    const int64_t tiles = (int64_t)g.tile_rows * g.tile_cols;
+    const int64_t look_ups = (int64_t)g.r * ((g.c + 31) / 32) + (int64_t)g.k * g.c / 4; // per probe, in words
+    return tiles * (n_sp < kSpBatch ? n_sp : kSpBatch) >= 256 || look_ups <= 16384;
 }
 
 int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, float w_threshold, CostManip manip,
@@ -655,14 +821,35 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
     }
     // 2. sweep over S_p, bisection on S_z
     const unsigned sblocks = (unsigned)((tiles + 255) / 256);
-    for (int a = 0; a < n_sp; ++a) {
-        const double sp = sp_values[a];
-        double sz0 = 0.0;
-        if (sp < 1.0) {
-            sz0 = (pow(target_sparsity, 1.0 / (double)g.k) - sp) / (1.0 - sp); // Eq. 7 solved for S_z
-            if (sz0 < 0.0) sz0 = 0.0;
-            if (sz0 > 1.0) sz0 = 1.0;
+    auto first_sz = [&](double sp) { // Eq. 7 solved for S_z
+        if (!(sp < 1.0)) return 0.0;
+        const double sz0 = (pow(target_sparsity, 1.0 / (double)g.k) - sp) / (1.0 - sp);
+        return sz0 < 0.0 ? 0.0 : (sz0 > 1.0 ? 1.0 : sz0);
+    };
+    const bool bisect = search_bisects(g, n_sp);
+    for (int a0 = 0; bisect && a0 < n_sp; a0 += kSpBatch) {
+        const int count = n_sp - a0 < kSpBatch ? n_sp - a0 : kSpBatch;
+        SpBatch batch{};
+        for (int a = 0; a < count; ++a) {
+            batch.sp[a] = sp_values[a0 + a];
+            batch.sz0[a] = first_sz(sp_values[a0 + a]);
         }
+        const size_t smem = (threshold_eval_lds_bytes(g) + 15) / 16 * 16;
+        LRBI_SET_MAX_LDS(search_bisect_kernel, smem);
+        LRBI_LAUNCH(search_bisect_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kEvalThreads), smem, stream, g, dMp,
+                    dMz, sortedMp, sortedMz, p.stride_p, p.stride_z, batch, 1.0 - target_sparsity, steps, Tp, Tz);
+        SearchStepArgs none{};
+        none.st = nullptr;
+        const int rc = launch_eval_step(g, dt, dW, ldw, w_threshold, manip, dMp, dMz, Tp, Tz, nullptr, nullptr, kept, cost,
+                                        eval_ws, stream, none, count);
+        if (rc != LRBI_OK) return rc;
+        LRBI_LAUNCH(search_pick_kernel, dim3(sblocks), dim3(256), 0, stream, g, state, tiles, count, a0 == 0 ? 1 : 0,
+                    1.0 - target_sparsity, (long long)tolerance, Tp, Tz, (const unsigned long long *)kept, cost, dTpBest,
+                    dTzBest, (unsigned long long *)dKeptBest, dCostBest);
+    }
+    for (int a = 0; !bisect && a < n_sp; ++a) {
+        const double sp = sp_values[a];
+        const double sz0 = first_sz(sp);
         LRBI_LAUNCH(search_begin_kernel, dim3(sblocks), dim3(256), 0, stream, g, state, sortedMp, sortedMz,
                            p.stride_p, p.stride_z, tiles, sp, sz0, a == 0 ? 1 : 0, Tp, Tz);
         for (int step = 0; step < steps; ++step) {
@@ -684,10 +871,10 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
             if (rc != LRBI_OK) return rc;
         }
     }
-    // 3. the winning thresholds once more, now writing the packed binary factors
+    // 3. the winning thresholds once more, now writing the packed binary factors (their ones and cost are known)
     if (dIp)
-        return launch_threshold_eval(g, dt, dW, ldw, w_threshold, manip, dMp, dMz, dTpBest, dTzBest, dIp, dIz, dKeptBest,
-                                     dCostBest, eval_ws, stream);
+        return launch_threshold_eval(g, dt, dW, ldw, w_threshold, manip, dMp, dMz, dTpBest, dTzBest, dIp, dIz, nullptr,
+                                     nullptr, eval_ws, stream);
     return LRBI_OK;
 }
 

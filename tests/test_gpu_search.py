@@ -155,3 +155,16 @@ def test_full_size_layer_on_sampled_tiles():
             assert int(kept[tile]) == int(rk[0])
         else:  # only a tie in cost may choose differently
             assert abs(int(kept[tile]) - round((1 - S) * cfg.r * cfg.c)) <= tol
+
+
+@pytest.mark.parametrize("m,n,r,c,k,dtype,sweep", [
+    (200, 168, 64, 56, 33, "f32", [i / 12 for i in range(11)]),   # more S_p values than one batch; cut-off tiles; two words per I_p row
+    (128, 1100, 128, 1100, 5, "bf16", [0.5, 0.8]),                # 35 words per row, the last one partial; row bands
+    (8, 17000, 8, 17000, 2, "f16", [0.4, 0.6, 0.7]),            # more words per row than a workgroup has lanes
+    (1024, 2400, 1024, 2400, 4, "bf16", [0.5, 0.7]),              # one large tile: a launch per probe, split over bands
+])
+def test_search_routes(m, n, r, c, k, dtype, sweep):
+    """The one-workgroup bisection at its edges, and the tile size beyond it.  The thresholds and counts are exact;
+    costs within the rounding of a double-precision sum, as everywhere in this file."""
+    print("search route", m, n, r, c, k, dtype, len(sweep), flush=True)
+    _check(_cfg(m, n, r, c, k, dtype, 70, p=0.15), 0.9, sweep, 4, max(1, r * c // 100))
