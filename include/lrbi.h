@@ -354,8 +354,8 @@ int lrbi_search_workspace_bytes(const lrbi_desc *desc, uint64_t *bytes);
  *   dW: m x n row-major, ldw >= n.  dDY: m x N row-major, lddy >= N.  dDX: n x N row-major,
  *   lddx >= N; overwritten.  All of `dtype`; fp32 accumulation in a fixed order (identical bits
  *   from call to call), rounded to nearest-even on store.  Pointers aligned to the element size;
- *   f16 / bf16 with 16-byte aligned W, ldw % 8 == 0 and n % 8 == 0 run on the matrix cores at
- *   any N, everything else on a plain (and for large m slow) vector-ALU kernel with the same results.
+ *   f16 / bf16 with 16-byte aligned W, ldw % 8 == 0 and n % 8 == 0 run on the 16-bit matrix
+ *   instructions at any N, everything else on the fp32 ones (products exact, sums in fp32).
  *   dWorkspace / workspace_bytes: optional scratch (16-byte aligned) of at least
  *   lrbi_masked_gemm_t_workspace_bytes bytes: partial sums when the reduction over m is split
  *   across workgroups; with NULL or too few bytes it is not split (slower for small n * N).

@@ -17,7 +17,7 @@
 //     dY rows and X rows are both contiguous along the batch, so both operands are staged as
 //     [row][batch] and read with plain 16-byte LDS reads.  The fp32 tile is rounded, parked in
 //     LDS and written as whole 256-byte row pieces, each 16-byte piece masked on its way out.
-// Vector-ALU kernels (fp32, or operands without the alignment): plain, slow, any shape.
+// fp32, and 16-bit rows of W without the alignment, go to the fp32 matrix-core kernels (lrbi_f32.hip).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
 
@@ -698,80 +698,11 @@ __global__ __launch_bounds__(kBwdThreads) void mfma_grad_kernel(Geom g, const ui
 }
 
 // ---------------------------------------------------------------------------
-// Vector-ALU kernels: any dtype, shape and alignment; plain and slow
-// ---------------------------------------------------------------------------
-template <typename T> struct BwdElem;
-template <> struct BwdElem<float> {
-    __device__ static float to_f32(float v) { return v; }
-    __device__ static float from_f32(float v) { return v; }
-};
-template <> struct BwdElem<__half> {
-    __device__ static float to_f32(__half v) { return __half2float(v); }
-    __device__ static __half from_f32(float v) { return __float2half_rn(v); }
-};
-template <> struct BwdElem<__hip_bfloat16> {
-    __device__ static float to_f32(__hip_bfloat16 v) { return __bfloat162float(v); }
-    __device__ static __hip_bfloat16 from_f32(float v) { return __float2bfloat16(v); }
-};
-
-// One wavefront per 64 columns of W and 4 batch columns: lane = column j, loop over the rows of W.
-template <typename T>
-__global__ __launch_bounds__(64) void valu_gemm_t_kernel(Geom g, const T *__restrict__ W, int64_t ldw,
-                                                         const uint32_t *__restrict__ Ip,
-                                                         const uint32_t *__restrict__ Iz, const T *__restrict__ DY,
-                                                         int64_t lddy, int N, T *__restrict__ DX, int64_t lddx)
-{
-    constexpr int NB = 4;
-    const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    const int q0 = blockIdx.y * NB;
-    const int nb = (N - q0 < NB) ? N - q0 : NB;
-    float acc[NB] = {0.f, 0.f, 0.f, 0.f};
-    const bool live = j < g.n;
-    const int64_t jc = live ? j : g.n - 1; // clamped: every lane walks the same rows
-    for (int64_t i = 0; i < g.m; ++i) {
-        const int ti = (int)(i / g.r);
-        const int il = (int)(i - (int64_t)ti * g.r);
-        const uint32_t word = decode_word(g, Ip, Iz, ti, il, (int)(jc >> 5));
-        if (!live || !((word >> (jc & 31)) & 1u)) continue; // pruned: the stored value is never read
-        const float w = BwdElem<T>::to_f32(W[i * ldw + j]);
-#pragma unroll
-        for (int b = 0; b < NB; ++b)
-            if (b < nb) acc[b] = fmaf(w, BwdElem<T>::to_f32(DY[i * lddy + q0 + b]), acc[b]);
-    }
-    if (live)
-        for (int b = 0; b < nb; ++b) DX[j * lddx + q0 + b] = BwdElem<T>::from_f32(acc[b]);
-}
-
-// One wavefront per row of W and 64 columns: lane = column j, loop over the batch.
-template <typename T>
-__global__ __launch_bounds__(64) void valu_grad_kernel(Geom g, const T *__restrict__ DY, int64_t lddy,
-                                                       const T *__restrict__ X, int64_t ldx, int N,
-                                                       const uint32_t *__restrict__ Ip,
-                                                       const uint32_t *__restrict__ Iz, T *__restrict__ DW,
-                                                       int64_t lddw)
-{
-    const int64_t j = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    if (j >= g.n) return;
-    for (int64_t i = blockIdx.y; i < g.m; i += gridDim.y) {
-        const int ti = (int)(i / g.r);
-        const int il = (int)(i - (int64_t)ti * g.r);
-        const uint32_t word = decode_word(g, Ip, Iz, ti, il, (int)(j >> 5));
-        float s = 0.f;
-        if ((word >> (j & 31)) & 1u)
-            for (int q = 0; q < N; ++q)
-                s = fmaf(BwdElem<T>::to_f32(DY[i * lddy + q]), BwdElem<T>::to_f32(X[j * ldx + q]), s);
-        DW[i * lddw + j] = BwdElem<T>::from_f32(s); // pruned: exactly zero
-    }
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 BwdPlan plan_gemm_t(const Geom &g, lrbi_dtype dt, int64_t N, bool aligned)
 {
     BwdPlan p;
-    // (also the narrowest batches: the vector-ALU kernel walks the m rows one by one per lane, with a chain of dependent
-    // factor loads per row: 3.9 ms on a 4096 x 9216 matrix at one column, where the tile kernel takes 26 us)
     p.mfma = (dt != LRBI_F32) && aligned && N >= 1;
     p.bq = (N > 32) ? 128 : 32;
     p.slices = 1;
@@ -837,29 +768,11 @@ static int launch_gemm_t_tile(const Geom &g, const BwdPlan &plan, const void *dW
     return LRBI_OK;
 }
 
-template <typename T>
-static int launch_valu_t(const Geom &g, const void *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz,
-                         const void *dDY, int64_t lddy, int64_t N, void *dDX, int64_t lddx, hipStream_t stream)
-{
-    const int64_t bx = (g.n + 63) / 64, by = (N + 3) / 4;
-    if (bx > 0x7FFFFFFF || by > 65535) return LRBI_ERR_SHAPE;
-    LRBI_LAUNCH(valu_gemm_t_kernel<T>, dim3((unsigned)bx, (unsigned)by), dim3(64), 0, stream, g, (const T *)dW, ldw,
-                       dIp, dIz, (const T *)dDY, lddy, (int)N, (T *)dDX, lddx);
-    return LRBI_OK;
-}
-
 int launch_gemm_t(const Geom &g, const BwdPlan &plan, lrbi_dtype dt, const void *dW, int64_t ldw, const uint32_t *dIp,
                   const uint32_t *dIz, const void *dDY, int64_t lddy, int64_t N, void *dDX, int64_t lddx,
                   void *dWorkspace, hipStream_t stream)
 {
-    if (!plan.mfma) {
-        switch (dt) {
-        case LRBI_F32: return launch_valu_t<float>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
-        case LRBI_F16: return launch_valu_t<__half>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
-        case LRBI_BF16: return launch_valu_t<__hip_bfloat16>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
-        default: return LRBI_ERR_DTYPE;
-        }
-    }
+    if (!plan.mfma) return launch_f32_gemm_t(g, dt, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
     // tile shapes that line up with its blocking: the pipelined kernel (both operands straight into LDS)
     if (plan.bq == 128 && pipe_t_ok(g, dW, ldw, dIz, dDY, lddy, N)) {
         int64_t iper = g.m;
@@ -889,29 +802,11 @@ int launch_gemm_t(const Geom &g, const BwdPlan &plan, lrbi_dtype dt, const void 
 #undef LRBI_T_ARGS
 }
 
-template <typename T>
-static int launch_valu_grad(const Geom &g, const void *dDY, int64_t lddy, const void *dX, int64_t ldx, int64_t N,
-                            const uint32_t *dIp, const uint32_t *dIz, void *dDW, int64_t lddw, hipStream_t stream)
-{
-    const int64_t bx = (g.n + 63) / 64;
-    if (bx > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
-    const unsigned by = (unsigned)(g.m < 65535 ? g.m : 65535);
-    LRBI_LAUNCH(valu_grad_kernel<T>, dim3((unsigned)bx, by), dim3(64), 0, stream, g, (const T *)dDY, lddy,
-                       (const T *)dX, ldx, (int)N, dIp, dIz, (T *)dDW, lddw);
-    return LRBI_OK;
-}
-
-int launch_grad(const Geom &g, lrbi_dtype dt, bool mfma, const void *dDY, int64_t lddy, const void *dX, int64_t ldx,
+int launch_grad(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, const void *dX, int64_t ldx,
                 int64_t N, const uint32_t *dIp, const uint32_t *dIz, void *dDW, int64_t lddw, hipStream_t stream)
 {
-    if (!mfma) {
-        switch (dt) {
-        case LRBI_F32: return launch_valu_grad<float>(g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, stream);
-        case LRBI_F16: return launch_valu_grad<__half>(g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, stream);
-        case LRBI_BF16: return launch_valu_grad<__hip_bfloat16>(g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, stream);
-        default: return LRBI_ERR_DTYPE;
-        }
-    }
+    if (dt == LRBI_F32)
+        return launch_f32_grad(g, (const float *)dDY, lddy, (const float *)dX, ldx, N, dIp, dIz, (float *)dDW, lddw, stream);
     const int64_t iblocks = (g.m + 127) / 128, jblocks = (g.n + BJ - 1) / BJ;
     const int64_t blocks = iblocks * jblocks;
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;

@@ -1,0 +1,385 @@
+// Masked products in fp32 on the matrix cores (v_mfma_f32_32x32x2): the forward product and the weight gradient of
+// fp32 layers, and the transposed product of every type where the 16-bit matrix-core kernels do not apply (fp32, and
+// 16-bit rows that are not whole aligned 16-byte pieces).  The products are exact fp32 fused multiply-adds, the sums
+// fp32 in a fixed order.
+//
+// Operands go from global memory (the caches) to registers in the instruction's lane layout: lane l holds row (column)
+// l & 31 of the left (right) operand at reduction index l >> 5.  One step of the instruction takes 64 cycles, a step's
+// operand loads a few, so tiles through LDS would buy nothing.  A workgroup owns one block of outputs and its
+// wavefronts take chunks of the reduction in turn (the layers are small: the blocks of outputs alone would leave most
+// of the chip idle); their sums are added through LDS in wavefront order.  500 x 800 in 100 x 100 tiles at 64 columns,
+// against the vector-ALU kernels before: product 133 -> 18 us, transposed 498 -> 19 us, gradient 15 -> 12 us (the three calls 667 -> 31 us), most of
+// it the launch and the two chains of factor loads behind a mask word; 4096 x 4096 in 512 x 512 tiles at 64 columns
+// 55, 64 and 57 us (2.1 GFLOP: 14 us at the instruction's rate, the reads of W 13 us), transposed at 8 columns
+// 4019 -> 63 us.  Relative error against 64 bits at 500 x 800, 64 columns: 7.2e-8 -> 6.3e-8, 1.4e-7 -> 7.1e-8 and
+// 1.4e-7 -> 1.1e-7.
+//
+// A zeroed weight still meets its other operand inside the instruction, and 0 * inf is NaN.  The products therefore
+// watch their unmasked operand: a workgroup that has met an infinity or a NaN does its block again one output at a
+// time, stepping over the pruned weights.
+#include <float.h>
+#include <hip/hip_bf16.h>
+#include <hip/hip_fp16.h>
+
+#include "lrbi_internal.hpp"
+
+namespace lrbi {
+
+static constexpr int kF32Waves = 8;
+static constexpr int kF32Threads = 64 * kF32Waves;
+static constexpr int kF32Chunk = 64; // reduction steps of one wavefront between two mask decodes
+
+typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+
+__device__ __forceinline__ f32x16_t mfma_32x32x2(float a, float b, f32x16_t c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+// row of accumulator element v (its column is lane & 31)
+__device__ __forceinline__ int acc_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
+
+__device__ __forceinline__ float as_f32(float v) { return v; }
+__device__ __forceinline__ float as_f32(__half v) { return __half2float(v); }
+__device__ __forceinline__ float as_f32(__hip_bfloat16 v) { return __bfloat162float(v); }
+template <typename T> __device__ __forceinline__ T from_f32(float v);
+template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
+template <> __device__ __forceinline__ __half from_f32<__half>(float v) { return __float2half_rn(v); }
+template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(float v) { return __float2bfloat16(v); }
+
+__device__ __forceinline__ int64_t at_most(int64_t i, int64_t last) { return i < last ? i : last; }
+
+// mask word of row `row`, word column w
+__device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
+{
+    const int ti = (int)(row / g.r);
+    return decode_word(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
+}
+
+// adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it
+template <typename T, int NQ>
+__device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t (&acc)[NQ], int64_t row0, int64_t rows,
+                                             int64_t q0, int64_t N, T *__restrict__ out, int64_t ldo)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) {
+        if (b) __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[wave][acc_row(v, lane) * 32 + (lane & 31)] = acc[b][v];
+        __syncthreads();
+        for (int e = tid; e < 1024; e += kF32Threads) {
+            double s = (double)red[0][e]; // rounded once
+#pragma unroll
+            for (int w = 1; w < kF32Waves; ++w) s += (double)red[w][e];
+            const int64_t i = row0 + (e >> 5), q = q0 + 32 * b + (e & 31);
+            if (i < rows && q < N) out[i * ldo + q] = from_f32<T>((float)s);
+        }
+    }
+}
+
+// dX = (W o I_a)^T dY.  Workgroup = 32 columns of W (rows of dX) x 32 NQ batch columns; a wavefront's chunk is 64
+// rows of W, whose 64 mask words (one per row: the block's columns are one word) its lanes decode together.
+template <typename T, int NQ>
+__global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T *__restrict__ W, int64_t ldw,
+                                                                 const uint32_t *__restrict__ Ip,
+                                                                 const uint32_t *__restrict__ Iz,
+                                                                 const T *__restrict__ DY, int64_t lddy, int64_t N,
+                                                                 T *__restrict__ DX, int64_t lddx, int jblocks)
+{
+    static __shared__ float red[kF32Waves][1024];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
+    const int jb = (int)(blockIdx.x % (unsigned)jblocks);
+    const int64_t j0 = 32 * (int64_t)jb, q0 = 32 * NQ * (int64_t)(blockIdx.x / (unsigned)jblocks);
+    const T *wcol = W + at_most(j0 + li, g.n - 1); // clamped: what lies beyond has no mask bit, or is not stored
+    const T *ycol[NQ];
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) ycol[b] = DY + at_most(q0 + 32 * b + li, N - 1);
+
+    constexpr int U = 8; // steps of the instruction whose operands are requested together
+    f32x16_t acc[NQ] = {};
+    bool bad = false;
+    for (int64_t i0 = (int64_t)kF32Chunk * wave; i0 < g.m; i0 += kF32Chunk * kF32Waves) {
+        T w[2][U], y[2][U][NQ];
+        const auto load = [&](int s0, T (&wv)[U], T (&yv)[U][NQ]) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int64_t i = at_most(i0 + 2 * (s0 + u) + half, g.m - 1);
+                wv[u] = wcol[i * ldw];
+#pragma unroll
+                for (int b = 0; b < NQ; ++b) yv[u][b] = ycol[b][i * lddy];
+            }
+        };
+        load(0, w[0], y[0]);
+        const uint32_t words = (i0 + lane < g.m) ? row_word(g, Ip, Iz, i0 + lane, jb) : 0u;
+#pragma unroll
+        for (int s = 0; s < kF32Chunk / 2 / U; ++s) {
+            if (s + 1 < kF32Chunk / 2 / U) load((s + 1) * U, w[(s + 1) & 1], y[(s + 1) & 1]);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t word = __shfl(words, 2 * (s * U + u) + half, 64);
+                const float a = ((word >> li) & 1u) ? as_f32(w[s & 1][u]) : 0.f;
+#pragma unroll
+                for (int b = 0; b < NQ; ++b) {
+                    const float x = as_f32(y[s & 1][u][b]);
+                    bad |= !(fabsf(x) <= FLT_MAX);
+                    acc[b] = mfma_32x32x2(a, x, acc[b]);
+                }
+            }
+        }
+    }
+    if (__syncthreads_or(bad)) {
+        for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
+            const int64_t j = j0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
+            if (j >= g.n || q >= N) continue;
+            float s = 0.f;
+            for (int64_t i = 0; i < g.m; ++i)
+                if ((row_word(g, Ip, Iz, i, jb) >> (j & 31)) & 1u) s = fmaf(as_f32(W[i * ldw + j]), as_f32(DY[i * lddy + q]), s);
+            DX[j * lddx + q] = from_f32<T>(s);
+        }
+        return;
+    }
+    reduce_store<T, NQ>(red, acc, j0, g.n, q0, N, DX, lddx);
+}
+
+// Y = (W o I_a) X, fp32.  Workgroup = 32 rows of W x 32 NQ batch columns; a wavefront's chunk is 64 columns of W, two
+// mask words per row.  A lane reads four consecutive weights of its row: the instruction's two reduction indices of
+// step e are columns e and 4 + e of a group of eight, so the lane halves hold adjacent 16-byte pieces.
+template <int NQ, bool VEC>
+__global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const float *__restrict__ W, int64_t ldw,
+                                                               const uint32_t *__restrict__ Ip,
+                                                               const uint32_t *__restrict__ Iz,
+                                                               const float *__restrict__ X, int64_t ldx, int64_t N,
+                                                               float *__restrict__ Y, int64_t ldy, int iblocks)
+{
+    static __shared__ float red[kF32Waves][1024];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
+    const int64_t i0 = 32 * (int64_t)(blockIdx.x % (unsigned)iblocks);
+    const int64_t q0 = 32 * NQ * (int64_t)(blockIdx.x / (unsigned)iblocks);
+    const int64_t row = at_most(i0 + li, g.m - 1);
+    const float *wrow = W + row * ldw;
+    const float *xcol[NQ];
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) xcol[b] = X + at_most(q0 + 32 * b + li, N - 1);
+
+    constexpr int G = kF32Chunk / 8; // groups of eight columns per chunk
+    // the sums of 32 columns go into doubles: one fp32 chain over a wavefront's whole share of the row would round more
+    // often than a sum spread over 64 lanes (relative error 1.5e-7 at 300 x 4000, where this gives 6.2e-8)
+    double sum[NQ][16] = {};
+    bool bad = false;
+    for (int64_t j0 = (int64_t)kF32Chunk * wave; j0 < g.n; j0 += kF32Chunk * kF32Waves) {
+        float w[2][4], x[2][4][NQ];
+        const auto load = [&](int gq, float (&wv)[4], float (&xv)[4][NQ]) {
+            const int64_t j = j0 + 8 * gq + 4 * half;
+            if (VEC) {
+                const float4 p = *reinterpret_cast<const float4 *>(wrow + at_most(j, g.n - 4));
+                wv[0] = p.x; wv[1] = p.y; wv[2] = p.z; wv[3] = p.w;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t je = at_most(j + e, g.n - 1);
+                if (!VEC) wv[e] = wrow[je];
+#pragma unroll
+                for (int b = 0; b < NQ; ++b) xv[e][b] = xcol[b][je * ldx];
+            }
+        };
+        load(0, w[0], x[0]);
+        const uint32_t words = row_word(g, Ip, Iz, row, (int)(j0 >> 5) + half); // no bits at or beyond column n
+        f32x16_t acc[NQ];
+        const uint32_t word01[2] = {(uint32_t)__shfl(words, li, 64), (uint32_t)__shfl(words, li + 32, 64)};
+#pragma unroll
+        for (int gq = 0; gq < G; ++gq) {
+            if (gq % 4 == 0) {
+#pragma unroll
+                for (int b = 0; b < NQ; ++b) acc[b] = f32x16_t{};
+            }
+            if (gq + 1 < G) load(gq + 1, w[(gq + 1) & 1], x[(gq + 1) & 1]);
+            const uint32_t bits = word01[gq >> 2] >> (8 * (gq & 3) + 4 * half);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float a = ((bits >> e) & 1u) ? w[gq & 1][e] : 0.f;
+#pragma unroll
+                for (int b = 0; b < NQ; ++b) {
+                    const float v = x[gq & 1][e][b];
+                    bad |= !(fabsf(v) <= FLT_MAX);
+                    acc[b] = mfma_32x32x2(a, v, acc[b]);
+                }
+            }
+            if (gq % 4 == 3) {
+#pragma unroll
+                for (int b = 0; b < NQ; ++b)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) sum[b][v] += (double)acc[b][v];
+            }
+        }
+    }
+    if (__syncthreads_or(bad)) {
+        for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
+            const int64_t i = i0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
+            if (i >= g.m || q >= N) continue;
+            float s = 0.f;
+            for (int64_t j = 0; j < g.n; j += 32)
+                for (uint32_t word = row_word(g, Ip, Iz, i, (int)(j >> 5)); word; word &= word - 1u) {
+                    const int64_t jj = j + __builtin_ctz(word);
+                    s = fmaf(W[i * ldw + jj], X[jj * ldx + q], s);
+                }
+            Y[i * ldy + q] = s;
+        }
+        return;
+    }
+    f32x16_t acc[NQ];
+#pragma unroll
+    for (int b = 0; b < NQ; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = (float)sum[b][v];
+    reduce_store<float, NQ>(red, acc, i0, g.m, q0, N, Y, ldy);
+}
+
+// dW = (dY X^T) o I_a, fp32.  One wavefront per 32 x (32 NJ) block of dW (no reduction is split: the blocks are many
+// and the batch is short).  Both operands are read four batch columns at a time, in the order described above.
+template <int NJ, bool VEC>
+__global__ __launch_bounds__(256) void f32_grad_kernel(Geom g, const float *__restrict__ DY, int64_t lddy,
+                                                       const float *__restrict__ X, int64_t ldx, int64_t N,
+                                                       const uint32_t *__restrict__ Ip, const uint32_t *__restrict__ Iz,
+                                                       float *__restrict__ DW, int64_t lddw, int64_t jblocks, int64_t blocks)
+{
+    const int lane = threadIdx.x & 63, li = lane & 31, half = lane >> 5;
+    const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (blk >= blocks) return; // whole wavefront; no barrier below
+    const int64_t ib = blk / jblocks, i0 = 32 * ib, j0 = 32 * NJ * (blk - ib * jblocks);
+    const float *yrow = DY + at_most(i0 + li, g.m - 1) * lddy;
+    const float *xrow[NJ];
+#pragma unroll
+    for (int b = 0; b < NJ; ++b) xrow[b] = X + at_most(j0 + 32 * b + li, g.n - 1) * ldx;
+    const auto load4 = [&](const float *p, int64_t q, float (&v)[4]) {
+        if (VEC) {
+            if (q < N) {
+                const float4 f = *reinterpret_cast<const float4 *>(p + q);
+                v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = 0.f;
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = (q + e < N) ? p[q + e] : 0.f;
+        }
+    };
+    // groups of eight batch columns go to two sums in turn: half the roundings of one chain, and two independent ones
+    f32x16_t acc[2][NJ] = {};
+    float y[2][4], x[2][NJ][4];
+    const auto load = [&](int64_t q, float (&yv)[4], float (&xv)[NJ][4]) { // past the last batch column: zeros, nothing is read
+        load4(yrow, q + 4 * half, yv);
+#pragma unroll
+        for (int b = 0; b < NJ; ++b) load4(xrow[b], q + 4 * half, xv[b]);
+    };
+    const auto mma = [&](float (&yv)[4], float (&xv)[NJ][4], f32x16_t (&c)[NJ]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int b = 0; b < NJ; ++b) c[b] = mfma_32x32x2(yv[e], xv[b][e], c[b]);
+    };
+    load(0, y[0], x[0]);
+    // the block's mask words: lane l < 32 holds row i0 + l of the first word column, the other half the second's
+    const uint32_t words = row_word(g, Ip, Iz, at_most(i0 + li, g.m - 1), (int)(j0 >> 5) + (NJ == 2 ? half : 0));
+    for (int64_t q = 0; q < N; q += 16) {
+        load(q + 8, y[1], x[1]);
+        mma(y[0], x[0], acc[0]);
+        if (q + 8 >= N) break;
+        load(q + 16, y[0], x[0]);
+        mma(y[1], x[1], acc[1]);
+    }
+#pragma unroll
+    for (int b = 0; b < NJ; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[0][b][v] += acc[1][b][v];
+#pragma unroll
+    for (int b = 0; b < NJ; ++b) {
+        const int64_t j = j0 + 32 * b + li;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int rr = acc_row(v, lane);
+            const uint32_t word = __shfl(words, rr + 32 * b, 64);
+            if (i0 + rr < g.m && j < g.n) DW[(i0 + rr) * lddw + j] = ((word >> li) & 1u) ? acc[0][b][v] : 0.f; // pruned: exactly zero
+        }
+    }
+}
+
+// Two 32-column batch blocks per workgroup halve the reads of W and the mask decodes; one keeps twice the workgroups
+// busy.  The line is where two per workgroup still give every compute unit one.
+static int batch_blocks(int64_t others, int64_t N) { return (N > 32 && others * ((N + 63) / 64) >= 256) ? 2 : 1; }
+
+template <typename T>
+static int launch_t(const Geom &g, const void *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz, const void *dDY,
+                    int64_t lddy, int64_t N, void *dDX, int64_t lddx, hipStream_t stream)
+{
+    const int64_t jblocks = (g.n + 31) / 32;
+    const int nq = batch_blocks(jblocks, N);
+    const int64_t blocks = jblocks * ((N + 32 * nq - 1) / (32 * nq));
+    if (blocks > 0x7FFFFFFF || (N + 3) / 4 > 65535) return LRBI_ERR_SHAPE;
+    if (nq == 2)
+        LRBI_LAUNCH((f32_gemm_t_kernel<T, 2>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
+                    dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
+    else
+        LRBI_LAUNCH((f32_gemm_t_kernel<T, 1>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
+                    dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
+    return LRBI_OK;
+}
+
+int launch_f32_gemm_t(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz,
+                      const void *dDY, int64_t lddy, int64_t N, void *dDX, int64_t lddx, hipStream_t stream)
+{
+    switch (dt) {
+    case LRBI_F32: return launch_t<float>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
+    case LRBI_F16: return launch_t<__half>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
+    case LRBI_BF16: return launch_t<__hip_bfloat16>(g, dW, ldw, dIp, dIz, dDY, lddy, N, dDX, lddx, stream);
+    default: return LRBI_ERR_DTYPE;
+    }
+}
+
+int launch_f32_gemm(const Geom &g, const float *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz, const float *dX,
+                    int64_t ldx, int64_t N, float *dY, int64_t ldy, hipStream_t stream)
+{
+    const int64_t iblocks = (g.m + 31) / 32;
+    const int nq = batch_blocks(iblocks, N);
+    const int64_t blocks = iblocks * ((N + 32 * nq - 1) / (32 * nq));
+    if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
+    const bool vec = ((uintptr_t)dW & 15) == 0 && ldw % 4 == 0 && g.n % 4 == 0;
+#define LRBI_LAUNCH_F32(NQ, V)                                                                                       \
+    LRBI_LAUNCH((f32_gemm_kernel<NQ, V>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, dW, ldw, dIp, dIz, dX, ldx, \
+                N, dY, ldy, (int)iblocks)
+    if (nq == 2) {
+        if (vec) LRBI_LAUNCH_F32(2, true);
+        else LRBI_LAUNCH_F32(2, false);
+    } else {
+        if (vec) LRBI_LAUNCH_F32(1, true);
+        else LRBI_LAUNCH_F32(1, false);
+    }
+#undef LRBI_LAUNCH_F32
+    return LRBI_OK;
+}
+
+int launch_f32_grad(const Geom &g, const float *dDY, int64_t lddy, const float *dX, int64_t ldx, int64_t N,
+                    const uint32_t *dIp, const uint32_t *dIz, float *dDW, int64_t lddw, hipStream_t stream)
+{
+    const int64_t iblocks = (g.m + 31) / 32;
+    // two column blocks per wavefront share its reads of dY; one, while that leaves fewer than two wavefronts per SIMD
+    const int nj = iblocks * ((g.n + 63) / 64) >= 2048 ? 2 : 1;
+    const int64_t jblocks = (g.n + 32 * nj - 1) / (32 * nj), blocks = iblocks * jblocks;
+    if ((blocks + 3) / 4 > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
+    const dim3 grid((unsigned)((blocks + 3) / 4));
+    const bool vec = (((uintptr_t)dDY | (uintptr_t)dX) & 15) == 0 && lddy % 4 == 0 && ldx % 4 == 0 && N % 4 == 0;
+#define LRBI_LAUNCH_F32(NJ, V)                                                                                     \
+    LRBI_LAUNCH((f32_grad_kernel<NJ, V>), grid, dim3(256), 0, stream, g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, jblocks, \
+                blocks)
+    if (nj == 2) {
+        if (vec) LRBI_LAUNCH_F32(2, true);
+        else LRBI_LAUNCH_F32(2, false);
+    } else {
+        if (vec) LRBI_LAUNCH_F32(1, true);
+        else LRBI_LAUNCH_F32(1, false);
+    }
+#undef LRBI_LAUNCH_F32
+    return LRBI_OK;
+}
+
+} // namespace lrbi

@@ -265,6 +265,12 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
             mfma = false;
         }
     }
+    // fp32 batches: the fp32 matrix instructions, whose time hardly depends on N below 64 columns.  Up to four columns
+    // one sweep over W on the vector ALUs is ahead (4096 x 4096: 46 against 50 us at four columns, 90 against 50 at
+    // eight; 300 x 4000: 27 against 43, 54 against 43; 500 x 800: 12 against 14, 19 against 14).
+    if (dtype == LRBI_F32 && N > 4 && (desc->flags & LRBI_FLAG_PATH_MASK) != LRBI_FLAG_PATH_VALU)
+        return launch_f32_gemm(g, (const float *)dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
+                               (const float *)dX, ldx, N, (float *)dY, ldy, s);
     if (!mfma)
         return launch_valu_gemm(g, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
                                 dX, ldx, N, dY, ldy, s);
@@ -580,11 +586,9 @@ extern "C" int lrbi_masked_grad(const lrbi_desc *desc, lrbi_dtype dtype, const v
     if (!aligned_to(dDW, (uintptr_t)es) || !aligned_to(dDY, (uintptr_t)es) || !aligned_to(dX, (uintptr_t)es))
         return LRBI_ERR_ALIGN;
     const Geom g = make_geom(desc);
-    // matrix cores for the 16-bit types at any batch (below 8 columns the slab is mostly zero fill, and the tile kernel
-    // still writes dW seven times faster than the vector-ALU kernel: 4096 x 9216 at one column 23 against 152 us); dW
-    // rows need not be 16-byte aligned (the kernel then writes element by element)
-    const bool mfma = dtype != LRBI_F32;
-    return launch_grad(g, dtype, mfma, dDY, lddy, dX, ldx, N, (const uint32_t *)dIp_packed,
+    // matrix cores for every type at any batch (below 8 columns the slab is mostly zero fill); dW rows need not be 16-byte
+    // aligned (the kernel then writes element by element)
+    return launch_grad(g, dtype, dDY, lddy, dX, ldx, N, (const uint32_t *)dIp_packed,
                        (const uint32_t *)dIz_packed, dDW, lddw, (hipStream_t)stream);
 }
 

@@ -52,6 +52,14 @@ int launch_threshold_eval(const Geom &g, lrbi_dtype dt, const void *dW, int64_t 
                           const float *dMp, const float *dMz, const float *dTp, const float *dTz, void *dIp, void *dIz,
                           uint64_t *dKept, double *dCost, void *dWorkspace, hipStream_t stream);
 
+// fp32 matrix-core kernels (lrbi_f32.hip): any shape and alignment; the transposed product takes every dtype
+int launch_f32_gemm(const Geom &g, const float *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz, const float *dX,
+                    int64_t ldx, int64_t N, float *dY, int64_t ldy, hipStream_t stream);
+int launch_f32_gemm_t(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, const uint32_t *dIp, const uint32_t *dIz,
+                      const void *dDY, int64_t lddy, int64_t N, void *dDX, int64_t lddx, hipStream_t stream);
+int launch_f32_grad(const Geom &g, const float *dDY, int64_t lddy, const float *dX, int64_t ldx, int64_t N,
+                    const uint32_t *dIp, const uint32_t *dIz, float *dDW, int64_t lddw, hipStream_t stream);
+
 // threshold search of Algorithm 1 (lrbi_alg1.hip): workspace layout (byte offsets) and sizes
 struct SearchPlan {
     int np, nz;                 // entries of one tile's M_p, M_z
@@ -67,7 +75,7 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
 
 // backward pass through the masking layer (lrbi_backward.hip)
 struct BwdPlan {
-    bool mfma;     // matrix-core kernel (f16 / bf16, aligned operands, N > 4); otherwise the vector-ALU kernel
+    bool mfma;     // matrix-core kernel of the 16-bit types (f16 / bf16, aligned operands); otherwise the fp32 one
     int bq;        // batch columns per workgroup
     int slices;    // slices over the rows of W (partial planes through the workspace when > 1)
     int64_t iper;  // rows of W per slice
@@ -83,7 +91,7 @@ int pipe_t_slices(const Geom &g, int64_t N, int max_slices, int64_t *iper);
 int launch_pipe_t_gemm(const Geom &g, int slices, int64_t iper, lrbi_dtype dt, const void *dW, int64_t ldw,
                        const uint32_t *dIp, const uint32_t *dIz, const void *dDY, int64_t lddy, int64_t N, void *dDX,
                        int64_t lddx, void *dWorkspace, hipStream_t stream);
-int launch_grad(const Geom &g, lrbi_dtype dt, bool mfma, const void *dDY, int64_t lddy, const void *dX, int64_t ldx,
+int launch_grad(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, const void *dX, int64_t ldx,
                 int64_t N, const uint32_t *dIp, const uint32_t *dIz, void *dDW, int64_t lddw, hipStream_t stream);
 
 struct MfmaPlan {

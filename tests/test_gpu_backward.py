@@ -134,3 +134,41 @@ def test_nonfinite_values_under_pruned_weights_never_reach_dx(N):
     b = lrbi.masked_gemm_t(desc, to_device(Wn, cfg.dtype), dIp, dIz, dY)
     torch.cuda.synchronize()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("cfg,ldpad", [
+    (_small(1, 1, 1, 1, 1, 1.0, 1, "f32"), 0),
+    (_small(65, 33, 20, 33, 3, 0.4, 33, "f32"), 0),             # one row, one column past the blocks; scalar loads
+    (_small(520, 96, 104, 48, 33, 0.05, 64, "f32"), 4),         # a ninth chunk of rows, two I_p words, padded leading dimensions
+    (_small(1030, 4100, 206, 82, 4, 0.2, 132, "f32"), 0),       # two blocks per workgroup, the last one short
+    (_small(130, 77, 65, 11, 4, 0.3, 40, "f16"), 0),            # 16-bit rows that are not whole pieces
+    (_small(70, 8300, 35, 83, 4, 0.3, 70, "bf16"), 0),          # the same, two batch blocks per workgroup
+])
+def test_fp32_matrix_cores(cfg, ldpad):
+    _check(cfg, ldpad=ldpad, what="fp32 instructions")
+
+
+@pytest.mark.parametrize("N", [5, 64])
+def test_fp32_products_with_nonfinite_operands(N):
+    """An infinity or a NaN in the batch reaches the results of kept weights only, in both products."""
+    cfg = _small(200, 168, 50, 56, 4, 0.3, N, "f32")
+    print("nonfinite batch", N, flush=True)
+    data, dY = _inputs(cfg)
+    d = desc_of(cfg)
+    dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], cfg.m, cfg.n, cfg.r, cfg.c, cfg.k)
+    X = data["X"].copy()
+    X[3, 0], X[100, N - 1], dY[7, 0], dY[199, N - 1] = np.inf, np.nan, -np.inf, np.nan
+    W = to_device(data["W"], "f32")
+    Y = lrbi.masked_gemm(d, W, dIp, dIz, to_device(X, "f32"))
+    dX = lrbi.masked_gemm_t(d, W, dIp, dIz, to_device(dY, "f32"))
+    torch.cuda.synchronize()
+    for got, mask, bad in ((Y, M, X), (dX, M.T, dY)):
+        reached = mask.astype(np.float64) @ (~np.isfinite(bad)).astype(np.float64) > 0
+        assert np.array_equal(~np.isfinite(got.cpu().numpy()), reached)
+    ok = [np.where(np.isfinite(a), a, 0).astype(np.float64) for a in (X, dY)]
+    W64 = data["W"].astype(np.float64)
+    for got, ref in ((Y, orc.masked_gemm(W64, M, ok[0])), (dX, orc.masked_gemm_t(W64, M, ok[1]))):
+        h = got.cpu().numpy().astype(np.float64)
+        fin = np.isfinite(h)
+        assert orc.rel_err(np.where(fin, h, 0), np.where(fin, ref, 0)) <= TOL["f32"]

@@ -350,3 +350,26 @@ def test_decode_and_gemm_equals_the_two_calls(idx):
     assert np.array_equal(unpack_device_mask(m1, cfg.n)[:, :cfg.n], M)
     ref, _ = _oracle(cfg, data)
     _assert_close(Y1, ref, cfg.dtype, "fused%d" % idx)
+
+
+@pytest.mark.parametrize("m,n,r,c,k,N,ldpad", [
+    (33, 65, 11, 13, 3, 5, 0),         # scalar loads, one row and one column past the blocks
+    (500, 800, 100, 100, 4, 64, 0),    # a thirteenth chunk of columns
+    (70, 516, 35, 129, 40, 33, 4),     # two I_p words, four columns in the last chunk, padded rows
+    (8200, 72, 200, 72, 4, 70, 0),     # two batch blocks per workgroup, the last one short
+    (8200, 71, 200, 71, 4, 64, 0),
+])
+def test_fp32_batches(m, n, r, c, k, N, ldpad):
+    """fp32 products of five columns and more against the fp64 oracle; fp32 sums of up to 800 terms in chunks."""
+    cfg = workloads.Config("t", m, n, r, c, k, 0.25, N, "f32", 0.05, 5)
+    print("fp32 batch", cfg, ldpad, flush=True)
+    data = workloads.make(cfg)
+    d = desc_of(cfg)
+    dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
+    W = torch.zeros((m, n + ldpad), device=dev())
+    W[:, :n] = to_device(data["W"], "f32")
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], m, n, r, c, k)
+    ref = orc.masked_gemm(data["W"].astype(np.float64), M, data["X"].astype(np.float64))
+    Y = lrbi.masked_gemm(d, W[:, :n], dIp, dIz, to_device(data["X"], "f32"))
+    torch.cuda.synchronize()
+    assert orc.rel_err(Y.double().cpu().numpy(), ref) <= 1e-6
