@@ -155,31 +155,38 @@ __device__ __forceinline__ void search_step_tile(const Geom &g, const SearchStep
 __device__ __forceinline__ void tile_iz_bits(const Geom &g, const float *__restrict__ mz, int ct, float tz, uint32_t *iz,
                                              uint32_t *__restrict__ out)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int steps_per_row = g.izw / 2;
     const int zsteps = g.k * steps_per_row;
     constexpr int ZB = 8;
+    // row l and position sq in it of a wavefront's step, carried along: a division per step cost more than the compares
+    const int dl = kEvalWaves / steps_per_row, dsq = kEvalWaves - dl * steps_per_row;
+    int l = wave / steps_per_row, sq = wave - l * steps_per_row;
     for (int st0 = wave; st0 < zsteps; st0 += ZB * kEvalWaves) {
         float v[ZB];
         bool ok[ZB];
+        int word[ZB];
 #pragma unroll
         for (int q = 0; q < ZB; ++q) {
-            const int st = st0 + q * kEvalWaves;
-            const int l = st / steps_per_row, sq = st - l * steps_per_row;
             const int j = 64 * sq + lane;
-            ok[q] = (st < zsteps) && (j < ct); // columns a cut-off tile leaves outside the matrix stay 0
-            v[q] = ok[q] ? mz[(int64_t)l * g.c + j] : 0.f;
+            ok[q] = (l < g.k) && (j < ct); // columns a cut-off tile leaves outside the matrix stay 0
+            v[q] = mz[(int64_t)(l < g.k ? l : g.k - 1) * g.c + (j < ct ? j : ct - 1)]; // clamped: no test before a load
+            word[q] = (l < g.k) ? l * g.izw + 2 * sq : -1;
+            l += dl;
+            sq += dsq;
+            if (sq >= steps_per_row) {
+                sq -= steps_per_row;
+                ++l;
+            }
         }
 #pragma unroll
         for (int q = 0; q < ZB; ++q) {
-            const int st = st0 + q * kEvalWaves;
-            if (st < zsteps) { // uniform over the wavefront
-                const int l = st / steps_per_row, sq = st - l * steps_per_row;
+            if (word[q] >= 0) { // uniform over the wavefront
                 const unsigned long long b = __ballot(ok[q] && v[q] >= tz);
                 if (lane < 2) {
                     const uint32_t bits = (uint32_t)(lane ? (b >> 32) : b);
-                    iz[l * g.izw + 2 * sq + lane] = bits;
-                    if (out) out[l * (int64_t)g.izw + 2 * sq + lane] = bits;
+                    iz[word[q] + lane] = bits;
+                    if (out) out[word[q] + lane] = bits;
                 }
             }
         }
@@ -545,50 +552,122 @@ int launch_threshold_eval(const Geom &g, lrbi_dtype dt, const void *dW, int64_t 
 // in the caller's workspace and the host never waits for the device.
 // ---------------------------------------------------------------------------
 
-// Sorts the used entries of one tile's factor (ascending, bitonic network over `padded` = 2^j slots, the
-// tail filled with +inf).  which = 0: M_p, the first rt rows of k entries; which = 1: M_z, the first ct
-// entries of each of the k rows (rt x ct = the tile's part inside the matrix).  One workgroup per tile.  Up
-// to 16384 slots the network runs in on-chip memory and the sorted values are written to out + tile *
-// stride; beyond that it runs in place in out + tile * stride (stride >= padded), slower, the workgroup's
-// own barriers ordering its global accesses.
-__global__ __launch_bounds__(512) void tile_sort_kernel(Geom g, int which, const float *__restrict__ in, float *out,
-                                                        int padded, int64_t stride, int on_chip)
+// ---- sort of the used entries of every tile's factor (ascending): which = 0: M_p, the first rt rows of k entries;
+// which = 1: M_z, the first ct entries of each of the k rows (rt x ct = the tile's part inside the matrix).  A bitonic
+// network over chunks of 512 E slots, the unused ones +inf, lane t holding slots t E .. t E + E - 1 in registers:
+// distances below E stay inside a lane, those below 64 E inside a wavefront, and only the few larger ones go through
+// LDS (4096 slots: 6 stages of 78; 576 tiles 87 -> 66 us, bound by the exchanges between lanes).  A factor beyond kSortChunk entries is sorted in chunks of that size by several
+// workgroups; the distances between chunks are passes over the workspace (a search on one 1200 x 600 tile, rank 145:
+// 12.5 -> 1.2 ms).
+static constexpr int kSortThreads = 512;
+static constexpr int kSortChunk = 32 * kSortThreads; // 16384 floats: 64 KiB of LDS
+
+// keeps the smaller (keep_min) or larger of two values that two lanes compare; equal values stay where they are
+__device__ __forceinline__ float sort_keep(float mine, float other, bool keep_min)
+{
+    return (keep_min ? other < mine : other > mine) ? other : mine;
+}
+
+// distances `from` (a power of two below 512 E) down to 1 of one merge
+template <int E> __device__ __forceinline__ void sort_merge(float (&v)[E], float *lds, int from, bool up)
+{
+    const int tid = threadIdx.x;
+    for (int d = from / E; d >= 64; d >>= 1) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) lds[e * kSortThreads + tid] = v[e];
+        __syncthreads();
+        const bool keep_min = ((tid & d) == 0) == up;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = sort_keep(v[e], lds[e * kSortThreads + (tid ^ d)], keep_min);
+        __syncthreads();
+    }
+    for (int d = (from / E < 64) ? from / E : 32; d >= 1; d >>= 1) {
+        const bool keep_min = ((tid & d) == 0) == up;
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = sort_keep(v[e], __shfl_xor(v[e], d, 64), keep_min);
+    }
+#pragma unroll
+    for (int d = E / 2; d >= 1; d >>= 1)
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (!(e & d)) {
+                const float a = v[e], b = v[e | d];
+                const bool swap = up ? a > b : a < b;
+                v[e] = swap ? b : a;
+                v[e | d] = swap ? a : b;
+            }
+}
+
+// blockIdx.x = tile, blockIdx.y = chunk.  merge_size == 0: sorts the chunk, up or down as the merges that follow ask;
+// otherwise: the chunk's part of the merge of that many slots, in place in `out`.
+template <int E>
+__global__ __launch_bounds__(kSortThreads) void tile_sort_kernel(Geom g, int which, const float *__restrict__ in,
+                                                                 float *out, int64_t stride, int merge_size)
 {
     extern __shared__ uint4 lrbi_dyn_smem[];
+    float *lds = reinterpret_cast<float *>(lrbi_dyn_smem);
+    constexpr int CHUNK = E * kSortThreads;
+    const int tid = threadIdx.x, base = (int)blockIdx.y * CHUNK;
     int rt, ct;
     tile_extent(g, blockIdx.x, rt, ct);
-    const int cols = which ? ct : g.k;           // used entries per stored row
-    const int pitch = which ? g.c : g.k;         // entries per stored row
+    const int cols = which ? ct : g.k;   // used entries per stored row
+    const int pitch = which ? g.c : g.k; // entries per stored row
     const int n = which ? g.k * ct : rt * g.k;
     float *dst = out + (int64_t)blockIdx.x * stride;
-    float *v = on_chip ? reinterpret_cast<float *>(lrbi_dyn_smem) : dst;
-    const float *src = in + (int64_t)blockIdx.x * (which ? (int64_t)g.k * g.c : (int64_t)g.r * g.k);
-    for (int i = threadIdx.x; i < padded; i += 512) {
-        float x = __builtin_inff();
-        if (i < n) {
-            const int row = i / cols;
-            x = src[(int64_t)row * pitch + (i - row * cols)];
-        }
-        v[i] = x;
-    }
-    __syncthreads();
-    for (int size = 2; size <= padded; size <<= 1) {
-        for (int stride2 = size >> 1; stride2 > 0; stride2 >>= 1) {
-            for (int i = threadIdx.x; i < padded / 2; i += 512) {
-                const int lo = 2 * i - (i & (stride2 - 1)); // lower index of the pair at this distance
-                const int hi = lo + stride2;
-                const bool up = (lo & size) == 0;
-                const float a = v[lo], b = v[hi];
-                if ((a > b) == up) {
-                    v[lo] = b;
-                    v[hi] = a;
+    float v[E];
+    if (merge_size == 0) {
+        const float *src = in + (int64_t)blockIdx.x * (which ? (int64_t)g.k * g.c : (int64_t)g.r * g.k);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const int i = base + e * kSortThreads + tid; // any order will do: the chunk is about to be sorted
+            float x = __builtin_inff();
+            if (i < n) {
+                int at = i;
+                if (cols != pitch) {
+                    const int row = i / cols;
+                    at = row * pitch + (i - row * cols);
                 }
+                x = src[at];
             }
-            __syncthreads();
+            v[e] = x;
         }
+        const int first = base + tid * E;
+#pragma unroll
+        for (int size = 2; size <= E; size <<= 1) // inside a lane
+#pragma unroll
+            for (int d = size / 2; d >= 1; d >>= 1)
+#pragma unroll
+                for (int e = 0; e < E; ++e)
+                    if (!(e & d)) {
+                        const bool up = ((first + e) & size) == 0;
+                        const float a = v[e], b = v[e | d];
+                        const bool swap = up ? a > b : a < b;
+                        v[e] = swap ? b : a;
+                        v[e | d] = swap ? a : b;
+                    }
+        for (int size = 2 * E; size <= CHUNK; size <<= 1) sort_merge<E>(v, lds, size / 2, (first & size) == 0);
+    } else {
+#pragma unroll
+        for (int e = 0; e < E; ++e) v[e] = dst[base + tid * E + e];
+        sort_merge<E>(v, lds, CHUNK / 2, (base & merge_size) == 0);
     }
-    if (on_chip)
-        for (int i = threadIdx.x; i < n; i += 512) dst[i] = v[i];
+    const int last = gridDim.y > 1 ? base + CHUNK : n; // several chunks: the slots past n take part in the merges
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (base + tid * E + e < last) dst[base + tid * E + e] = v[e];
+}
+
+// one distance of a merge beyond the chunks: blockIdx.x = tile, blockIdx.y: 256 pairs
+__global__ __launch_bounds__(256) void tile_sort_far_kernel(float *out, int64_t stride, int merge_size, int distance)
+{
+    float *v = out + (int64_t)blockIdx.x * stride;
+    const int i = (int)blockIdx.y * 256 + threadIdx.x;
+    const int lo = 2 * i - (i & (distance - 1));
+    const float a = v[lo], b = v[lo + distance];
+    if ((lo & merge_size) == 0 ? a > b : a < b) {
+        v[lo] = b;
+        v[lo + distance] = a;
+    }
 }
 
 __global__ __launch_bounds__(256) void search_begin_kernel(Geom g, SearchState *__restrict__ st,
@@ -624,8 +703,9 @@ struct SpBatch {
 // All probes of one (tile, S_p): blockIdx.x = tile, blockIdx.y = S_p.  I_p is packed once; each probe packs I_z from
 // the tile's M_z (in the L2 from the first probe on), counts the ones of I_a from LDS, and lane 0 moves the interval.
 // Bound by the latency of that chain of steps and by vector-ALU issue in the count; W is not touched.  4096 x 9216 f16,
-// 256 x 256 tiles, rank 16, eight S_p, ten probes: 278 us, where 80 sweeps over W took 80 x 25 us; the whole search
-// 2167 -> 598 us.
+// 256 x 256 tiles, rank 16, eight S_p, ten probes: 244 us (278 with one mask word per look-up), where 80 sweeps over W took
+// 80 x 25 us; the whole search 2167 -> 485 us.
+template <typename V>
 __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, const float *__restrict__ Mp,
                                                                      const float *__restrict__ Mz,
                                                                      const float *__restrict__ sortedMp,
@@ -652,7 +732,10 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
     double lo = 0.0, hi = 1.0, sz = batch.sz0[blockIdx.y];
     long long rep_diff = -1;
     float rep_tz = 0.f;
-    const int words = (ct + 31) / 32;
+    constexpr int VW = sizeof(V) / 4;
+    const int words = (ct + 32 * VW - 1) / (32 * VW); // pieces of VW words per row; the bits past column ct are zero
+    const int pitch = g.izw / VW;
+    const V *izv = reinterpret_cast<const V *>(iz);
     const int drow = kEvalThreads / words, dword = kEvalThreads - drow * words;
     const int row0 = tid / words, word0 = tid - row0 * words;
     for (int step = 0; step < steps; ++step) {
@@ -661,16 +744,17 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
         __syncthreads();
         unsigned int kept = 0u; // ones of one lane: at most 2^32 / 512 by the limits on r and c
         for (int i = row0, wc = word0; i < rt;) {
-            uint32_t word = 0u;
+            V word = {};
             for (int q = 0; q < g.ipw; ++q) {
                 uint32_t sel = ip[i * g.ipw + q];
                 while (sel) {
                     const int l = __builtin_ctz(sel) + 32 * q;
                     sel &= sel - 1u;
-                    word |= iz[l * g.izw + wc];
+                    word |= izv[l * pitch + wc];
                 }
             }
-            kept += (unsigned int)__builtin_popcount(word);
+#pragma unroll
+            for (int e = 0; e < VW; ++e) kept += (unsigned int)__builtin_popcount(word[e]);
             i += drow;
             wc += dword;
             if (wc >= words) {
@@ -702,8 +786,8 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
 }
 
 // Winner of a batch of representatives (arrays of `tiles` entries per S_p) against the winner so far, in list order.
-__global__ __launch_bounds__(256) void search_pick_kernel(Geom g, SearchState *__restrict__ st, int64_t tiles, int count,
-                                                          int first, double keep_fraction, long long tolerance,
+__global__ __launch_bounds__(256) void search_pick_kernel(Geom g, int64_t tiles, int count, int first,
+                                                          double keep_fraction, long long tolerance,
                                                           const float *__restrict__ Tp, const float *__restrict__ Tz,
                                                           const unsigned long long *__restrict__ Kept,
                                                           const double *__restrict__ Cost, float *__restrict__ TpBest,
@@ -717,8 +801,9 @@ __global__ __launch_bounds__(256) void search_pick_kernel(Geom g, SearchState *_
     tile_extent(g, t, rt, ct);
     const long long target =
         (long long)floor(__dadd_rn(__dmul_rn(__dmul_rn(keep_fraction, (double)rt), (double)ct), 0.5));
-    long long best_diff = first ? -1 : st[t].best_diff;
-    bool best_eligible = first ? false : st[t].best_eligible != 0;
+    const long long best_kept = first ? 0 : (long long)KeptBest[t];
+    long long best_diff = first ? -1 : (best_kept > target ? best_kept - target : target - best_kept);
+    bool best_eligible = !first && best_diff <= tolerance;
     int64_t win = -1;
     double best_cost = first ? 0.0 : CostBest[t];
     for (int a = 0; a < count; ++a) {
@@ -739,8 +824,6 @@ __global__ __launch_bounds__(256) void search_pick_kernel(Geom g, SearchState *_
             win = at;
         }
     }
-    st[t].best_diff = best_diff;
-    st[t].best_eligible = best_eligible ? 1 : 0;
     if (win >= 0) {
         TpBest[t] = Tp[win];
         TzBest[t] = Tz[win];
@@ -748,8 +831,6 @@ __global__ __launch_bounds__(256) void search_pick_kernel(Geom g, SearchState *_
         CostBest[t] = best_cost;
     }
 }
-
-constexpr int kSortOnChip = 16384; // floats: 64 KiB of on-chip memory
 
 static int64_t pow2_at_least(int64_t n)
 {
@@ -765,19 +846,50 @@ SearchPlan plan_search(const Geom &g)
     auto up = [](uint64_t v) { return (v + 255) / 256 * 256; };
     p.np = g.r * g.k;
     p.nz = g.k * g.c;
-    // a factor of more than kSortOnChip entries is sorted in place in the workspace, in 2^j slots
-    p.stride_p = p.np <= kSortOnChip ? p.np : pow2_at_least(p.np);
-    p.stride_z = p.nz <= kSortOnChip ? p.nz : pow2_at_least(p.nz);
+    // a factor of more than kSortChunk entries is sorted in place in the workspace, in 2^j slots
+    p.stride_p = p.np <= kSortChunk ? p.np : pow2_at_least(p.np);
+    p.stride_z = p.nz <= kSortChunk ? p.nz : pow2_at_least(p.nz);
     p.off_sorted_mp = 0;
     p.off_sorted_mz = up(p.off_sorted_mp + tiles * (uint64_t)p.stride_p * 4);
-    p.off_state = up(p.off_sorted_mz + tiles * (uint64_t)p.stride_z * 4);
-    p.off_tp = up(p.off_state + tiles * sizeof(SearchState));
+    // one scratch area, either the representatives of a batch of S_p values or the state of the probe-by-probe form
+    p.off_tp = up(p.off_sorted_mz + tiles * (uint64_t)p.stride_z * 4);
     p.off_tz = up(p.off_tp + tiles * kSpBatch * 4);
     p.off_kept = up(p.off_tz + tiles * kSpBatch * 4);
     p.off_cost = up(p.off_kept + tiles * kSpBatch * 8);
     p.off_eval = up(p.off_cost + tiles * kSpBatch * 8);
+    p.off_state = p.off_kept;
+    static_assert(sizeof(SearchState) + 8 + 8 <= 2 * 8 * kSpBatch, "state, kept and cost of a tile inside the two arrays");
     p.bytes = p.off_eval + plan_threshold_eval(g).workspace_bytes * kSpBatch;
     return p;
+}
+
+// Sorts one factor of every tile: n entries of a whole tile, `stride` floats between two tiles' results.
+static int launch_sort(const Geom &g, int which, const float *in, float *out, int n, int64_t stride, hipStream_t stream)
+{
+    const unsigned tiles = (unsigned)(g.tile_rows * (int64_t)g.tile_cols);
+#define LRBI_SORT(E, CHUNKS, MERGE)                                                                                      \
+    do {                                                                                                                 \
+        LRBI_SET_MAX_LDS(tile_sort_kernel<E>, (E) * kSortThreads * 4);                                                   \
+        LRBI_LAUNCH(tile_sort_kernel<E>, dim3(tiles, (unsigned)(CHUNKS)), dim3(kSortThreads), (E) * kSortThreads * 4, stream, g, \
+                    which, in, out, stride, MERGE);                                                                      \
+    } while (0)
+    if (n <= 1 * kSortThreads) LRBI_SORT(1, 1, 0);
+    else if (n <= 2 * kSortThreads) LRBI_SORT(2, 1, 0);
+    else if (n <= 4 * kSortThreads) LRBI_SORT(4, 1, 0);
+    else if (n <= 8 * kSortThreads) LRBI_SORT(8, 1, 0);
+    else if (n <= 16 * kSortThreads) LRBI_SORT(16, 1, 0);
+    else {
+        const int padded = n <= kSortChunk ? kSortChunk : (int)pow2_at_least(n);
+        const int chunks = padded / kSortChunk;
+        LRBI_SORT(32, chunks, 0);
+        for (int size = 2 * kSortChunk; size <= padded; size *= 2) {
+            for (int d = size / 2; d >= kSortChunk; d /= 2)
+                LRBI_LAUNCH(tile_sort_far_kernel, dim3(tiles, (unsigned)(padded / 512)), dim3(256), 0, stream, out, stride, size, d);
+            LRBI_SORT(32, chunks, size);
+        }
+    }
+#undef LRBI_SORT
+    return LRBI_OK;
 }
 
 // Whether one workgroup per (tile, S_p) runs the whole bisection: when that fills the chip, or when a probe is so little
@@ -805,19 +917,16 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
     SearchState *state = (SearchState *)(ws + p.off_state);
     float *Tp = (float *)(ws + p.off_tp);
     float *Tz = (float *)(ws + p.off_tz);
-    uint64_t *kept = (uint64_t *)(ws + p.off_kept);
-    double *cost = (double *)(ws + p.off_cost);
+    const bool bisect = search_bisects(g, n_sp);
+    uint64_t *kept = (uint64_t *)(ws + p.off_kept + (bisect ? 0 : tiles * sizeof(SearchState)));
+    double *cost = bisect ? (double *)(ws + p.off_cost) : (double *)(kept + tiles);
     void *eval_ws = plan_threshold_eval(g).workspace_bytes ? (void *)(ws + p.off_eval) : nullptr;
 
     // 1. sorted factors of every tile (the quantile look-up of "convert with (S_p, S_z)")
     for (int which = 0; which < 2; ++which) {
-        const int n = which ? p.nz : p.np;
-        const int padded = (int)pow2_at_least(n);
-        const int on_chip = n <= kSortOnChip;
-        const size_t smem = on_chip ? (size_t)padded * 4 : 0;
-        LRBI_SET_MAX_LDS(tile_sort_kernel, kSortOnChip * 4);
-        LRBI_LAUNCH(tile_sort_kernel, dim3((unsigned)tiles), dim3(512), smem, stream, g, which, which ? dMz : dMp,
-                           which ? sortedMz : sortedMp, padded, which ? p.stride_z : p.stride_p, on_chip);
+        const int rc = launch_sort(g, which, which ? dMz : dMp, which ? sortedMz : sortedMp, which ? p.nz : p.np,
+                                   which ? p.stride_z : p.stride_p, stream);
+        if (rc != LRBI_OK) return rc;
     }
     // 2. sweep over S_p, bisection on S_z
     const unsigned sblocks = (unsigned)((tiles + 255) / 256);
@@ -826,7 +935,6 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
         const double sz0 = (pow(target_sparsity, 1.0 / (double)g.k) - sp) / (1.0 - sp);
         return sz0 < 0.0 ? 0.0 : (sz0 > 1.0 ? 1.0 : sz0);
     };
-    const bool bisect = search_bisects(g, n_sp);
     for (int a0 = 0; bisect && a0 < n_sp; a0 += kSpBatch) {
         const int count = n_sp - a0 < kSpBatch ? n_sp - a0 : kSpBatch;
         SpBatch batch{};
@@ -835,15 +943,17 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
             batch.sz0[a] = first_sz(sp_values[a0 + a]);
         }
         const size_t smem = (threshold_eval_lds_bytes(g) + 15) / 16 * 16;
-        LRBI_SET_MAX_LDS(search_bisect_kernel, smem);
-        LRBI_LAUNCH(search_bisect_kernel, dim3((unsigned)tiles, (unsigned)count), dim3(kEvalThreads), smem, stream, g, dMp,
+        // 128 columns of a row per look-up where the padded rows of I_z are whole 16-byte pieces, 64 otherwise
+        auto kern = g.izw % 4 == 0 ? search_bisect_kernel<u32x4> : search_bisect_kernel<u32x2>;
+        LRBI_SET_MAX_LDS(kern, smem);
+        LRBI_LAUNCH(kern, dim3((unsigned)tiles, (unsigned)count), dim3(kEvalThreads), smem, stream, g, dMp,
                     dMz, sortedMp, sortedMz, p.stride_p, p.stride_z, batch, 1.0 - target_sparsity, steps, Tp, Tz);
         SearchStepArgs none{};
         none.st = nullptr;
         const int rc = launch_eval_step(g, dt, dW, ldw, w_threshold, manip, dMp, dMz, Tp, Tz, nullptr, nullptr, kept, cost,
                                         eval_ws, stream, none, count);
         if (rc != LRBI_OK) return rc;
-        LRBI_LAUNCH(search_pick_kernel, dim3(sblocks), dim3(256), 0, stream, g, state, tiles, count, a0 == 0 ? 1 : 0,
+        LRBI_LAUNCH(search_pick_kernel, dim3(sblocks), dim3(256), 0, stream, g, tiles, count, a0 == 0 ? 1 : 0,
                     1.0 - target_sparsity, (long long)tolerance, Tp, Tz, (const unsigned long long *)kept, cost, dTpBest,
                     dTzBest, (unsigned long long *)dKeptBest, dCostBest);
     }
