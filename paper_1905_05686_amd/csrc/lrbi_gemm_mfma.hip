@@ -37,7 +37,7 @@ static constexpr int kThreads = 256;
 static constexpr int WS_STRIDE = BK + 8; // halfs; 16-byte pad keeps 16-byte row alignment
 
 template <int BM, int BN> struct Smem {
-    static constexpr int XS_STRIDE = BN + 8;
+    static constexpr int XS_STRIDE = BN + (BN >= 64 ? 32 : 8); // halfs; keeps the transposing reads off shared banks
     static constexpr int ws_halfs = BM * WS_STRIDE;
     static constexpr int xs_halfs = BK * XS_STRIDE;
     static constexpr int ms_words = BM * 2;
@@ -124,6 +124,9 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
     const int wave = tid >> 6;
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
     const int l32 = lane & 31, lg = lane >> 5;
+    // X operand (transposing read): 16-lane group G = lane / 16 serves columns 16 (G % 2) .. + 15 of a 32-column block
+    // and rows 8 (G / 2) .. + 7 of a step; lane d of the group addresses row d / 4 (+ 4), columns 4 (d % 4)
+    const int xtr = (8 * lg + ((lane & 15) >> 2)) * XS_STRIDE + wn * WN + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
 
     uint4 wreg[W_CHUNKS];
     uint4 xreg[X_CHUNKS];
@@ -164,6 +167,25 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
     };
 
     const int64_t mask_cols = (g.n + 127) / 128 * 128; // columns of a mask row up to the end of its last 16-byte piece
+    auto put_word = [&](int slab, int buf, int idx, uint32_t word) {
+        const int k0 = kbeg + slab * BK;
+        const int row = idx >> 1, half = idx & 1;
+        Ms[buf * S::ms_words + idx] = word;
+        // The mask as a by-product (the stand-alone decode's layout: one bit per weight, whole 16-byte pieces
+        // per row, pad bits zero): every (row, word) is formed by exactly one workgroup of the first column
+        // block; the last slab of a row also clears what is left of the row's last 16-byte piece.
+        if (mask_out && ni == 0 && m0 + row < g.m) {
+            const int col0 = k0 + 32 * half;
+            uint32_t *mrow = mask_out + (m0 + row) * mask_pitch32;
+            if (col0 < g.n) {
+                const int64_t left = g.n - col0;
+                mrow[col0 >> 5] = (left < 32) ? (word & ((1u << left) - 1u)) : word;
+            } else if (col0 < mask_cols) {
+                mrow[col0 >> 5] = 0u;
+            }
+            if (slab == nslabs - 1 && kend == g.n && col0 + 64 < mask_cols) mrow[(col0 + 64) >> 5] = 0u;
+        }
+    };
     auto decode_slab = [&](int slab, int buf) {
         const int k0 = kbeg + slab * BK;
         int tj = 0, wt = 0;
@@ -174,26 +196,61 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
 #pragma unroll
         for (int i = 0; i < M_WORDS; ++i) {
             const int idx = tid + kThreads * i;
-            if (idx < BM * 2) {
-                const int row = idx >> 1, half = idx & 1;
-                const uint32_t word = slab_mask_word<ALIGNED>(g, Ip, Iz, m0 + row, k0, half, tj, wt);
-                Ms[buf * S::ms_words + idx] = word;
-                // The mask as a by-product (the stand-alone decode's layout: one bit per weight, whole 16-byte pieces
-                // per row, pad bits zero): every (row, word) is formed by exactly one workgroup of the first column
-                // block; the last slab of a row also clears what is left of the row's last 16-byte piece.
-                if (mask_out && ni == 0 && m0 + row < g.m) {
-                    const int col0 = k0 + 32 * half;
-                    uint32_t *mrow = mask_out + (m0 + row) * mask_pitch32;
-                    if (col0 < g.n) {
-                        const int64_t left = g.n - col0;
-                        mrow[col0 >> 5] = (left < 32) ? (word & ((1u << left) - 1u)) : word;
-                    } else if (col0 < mask_cols) {
-                        mrow[col0 >> 5] = 0u;
-                    }
-                    if (slab == nslabs - 1 && kend == g.n && col0 + 64 < mask_cols) mrow[(col0 + 64) >> 5] = 0u;
-                }
-            }
+            if (idx < BM * 2) put_word(slab, buf, idx, slab_mask_word<ALIGNED>(g, Ip, Iz, m0 + (idx >> 1), k0, idx & 1, tj, wt));
         }
+    };
+
+    // The same word with its two dependent loads spread over the slabs before its own, so that neither is waited for:
+    // the I_p word(s) four slabs ahead, the I_z words of up to four selected ranks three slabs ahead, the OR two
+    // ahead (rows with more set ranks, few at the densities of such factors, load the rest there; eight ranks ahead cost
+    // more in loads than they saved: 6000 x 12000, rank 8, N = 512 350 -> 373 us).  Tile widths
+    // of whole slabs, up to two I_p words.
+    constexpr int RANKS = 4;
+    struct Selected {
+        uint32_t z[RANKS];
+        unsigned long long rest; // ranks beyond those
+        const uint32_t *iz;      // word of the slab in the tile's I_z row 0
+        bool any;
+    };
+    static_assert(M_WORDS == 1 && BM * 2 == kThreads, "one mask word per lane and slab");
+    const bool ahead = ALIGNED && g.ipw <= 2;
+    const bool row_in = m0 + (tid >> 1) < g.m;
+    const int64_t row_c = row_in ? m0 + (tid >> 1) : g.m - 1;
+    const int64_t ti_w = row_c / g.r, il_w = row_c - ti_w * g.r;
+    auto slab_tile = [&](int slab, int &tj, int &wt) { // a slab past the slice: its last one, loaded and not used
+        const int k0 = kbeg + (slab < nslabs ? slab : nslabs - 1) * BK;
+        tj = k0 / g.c;
+        wt = (k0 - tj * g.c) >> 5;
+    };
+    auto load_ip = [&](int slab) -> unsigned long long {
+        int tj, wt;
+        slab_tile(slab, tj, wt);
+        const uint32_t *p = Ip + ((ti_w * g.tile_cols + tj) * g.r + il_w) * g.ipw;
+        const uint32_t lo = p[0], hi = p[g.ipw - 1];
+        return (unsigned long long)lo | (g.ipw > 1 ? (unsigned long long)hi << 32 : 0ull);
+    };
+    auto load_iz = [&](int slab, unsigned long long sel) -> Selected {
+        int tj, wt;
+        slab_tile(slab, tj, wt);
+        Selected w;
+        w.iz = Iz + (ti_w * g.tile_cols + tj) * g.k * (int64_t)g.izw + wt + (tid & 1);
+        w.any = row_in && sel != 0ull;
+        int l = 0;
+#pragma unroll
+        for (int q = 0; q < RANKS; ++q) {
+            if (sel) l = __builtin_ctzll(sel); // none left: the last one again
+            sel &= sel - 1ull;
+            w.z[q] = w.iz[l * g.izw];
+        }
+        w.rest = sel;
+        return w;
+    };
+    auto finish_word = [&](const Selected &w, int slab, int buf) {
+        uint32_t word = 0u;
+#pragma unroll
+        for (int q = 0; q < RANKS; ++q) word |= w.z[q];
+        for (unsigned long long sel = w.rest; sel; sel &= sel - 1ull) word |= w.iz[__builtin_ctzll(sel) * g.izw];
+        put_word(slab, buf, tid, w.any ? word : 0u);
     };
 
     auto stage_slab = [&](int buf) {
@@ -226,13 +283,24 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
     // prologue: slab 0 into buffer 0, slab 1 in flight
+    unsigned long long ip_next = 0ull;
+    Selected iz_next{};
     if (nslabs > 0) {
         load_slab(0);
-        decode_slab(0, 0);
+        if (ahead) {
+            const unsigned long long p0 = load_ip(0), p1 = load_ip(1), p2 = load_ip(2);
+            ip_next = load_ip(3);
+            const Selected w0 = load_iz(0, p0), w1 = load_iz(1, p1);
+            iz_next = load_iz(2, p2);
+            finish_word(w0, 0, 0);
+            if (nslabs > 1) finish_word(w1, 1, 1);
+        } else {
+            decode_slab(0, 0);
+        }
         __syncthreads();
         stage_slab(0);
         if (nslabs > 1) { // the mask words first: their dependent loads are waited for at once, and a wavefront's
-            decode_slab(1, 1); // loads complete in order, so operand loads issued ahead of them would be drained
+            if (!ahead) decode_slab(1, 1); // loads complete in order, so operand loads issued ahead of them would be drained
             load_slab(1);
         }
         __syncthreads();
@@ -251,11 +319,10 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
                 wf[b] = *reinterpret_cast<const uint4 *>(ws + (wm * WM + b * 32 + l32) * WS_STRIDE + kof);
 #pragma unroll
             for (int a = 0; a < FN; ++a) {
-                const uint16_t *col = xs + kof * XS_STRIDE + wn * WN + a * 32 + l32;
-                uint16_t tmp[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) tmp[e] = col[e * XS_STRIDE];
-                xf[a] = *reinterpret_cast<uint4 *>(tmp);
+                const uint16_t *p = xs + kk * 16 * XS_STRIDE + xtr + a * 32;
+                const uint2 lo = lds_read_tr16(p);
+                const uint2 hi = lds_read_tr16(p + 4 * XS_STRIDE);
+                xf[a] = make_uint4(lo.x, lo.y, hi.x, hi.y);
             }
 #pragma unroll
             for (int a = 0; a < FN; ++a)
@@ -264,7 +331,13 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
         }
         if (s + 1 < nslabs) stage_slab(buf ^ 1);
         if (s + 2 < nslabs) {
-            decode_slab(s + 2, buf);
+            if (ahead) {
+                finish_word(iz_next, s + 2, buf);
+                iz_next = load_iz(s + 3, ip_next);
+                ip_next = load_ip(s + 4);
+            } else {
+                decode_slab(s + 2, buf);
+            }
             load_slab(s + 2);
         }
         __syncthreads();
@@ -792,20 +865,33 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
     int split = (int)((flags & LRBI_FLAG_SPLITK_MASK) >> LRBI_FLAG_SPLITK_SHIFT);
     if (split == 0) {
         split = 1;
-        if (tiles < 192) {
+        const bool general = tile < 4;
+        const int64_t min_pairs = general ? 2 : 4;
+        const int64_t cap = npairs / min_pairs > 1 ? npairs / min_pairs : 1;
+        int64_t want = 1;
+        if (general && tiles < 512) {
+            // The general kernel waits for a round of loads per slab (about 2 us whatever else runs), so workgroups in
+            // flight pay off.  Two fit a compute unit: as many slices as 512 hold, since a few workgroups more
+            // cost a second round (4100 x 9224 in 256 x 256 tiles, N = 128: 15 slices 43 us, 19 slices 56, 25 slices 53;
+            // 3000 x 4000 in 300 x 300, N = 200: 8 slices 40, 16 slices 43).  From 129 tiles on that leaves many
+            // idle, and where the rows are long about two rounds of shorter slices even out (4100 x 9224, N = 1024, 264
+            // tiles: unsplit 336 us, 2 slices 315, 4 slices 257, 8 slices 251, 16 slices 289); short rows are
+            // not worth the partial planes (64 x 576, N = 16384: 19.4 us against 18.7 + 4.2 us).
+            if (tiles < 192) want = 512 / tiles;
+            if (tiles > 128) {
+                int64_t rounds2 = (1024 + tiles - 1) / tiles;
+                if (rounds2 > npairs / 8) rounds2 = npairs / 8;
+                if (rounds2 > want) want = rounds2;
+            }
+        } else if (!general && tiles < 192) {
             // The 512-lane panel kernels run one workgroup per compute unit (measured best: one slice per
-            // unit, at least 8 slabs per slice), the 256-lane panel kernels two.  The general kernel pays a
-            // round of dependent factor loads per slab, so short slices and more workgroups in flight pay off
-            // (C4: 12 slices of 4 slabs, 23 us against 32 us with 6 slices).
-            const bool general = tile < 4;
-            const int64_t target = (tile >= 9) ? 256 : (general ? 1024 : 512);
-            int64_t want = (target + tiles - 1) / tiles;
-            const int64_t min_pairs = general ? 2 : 4;
-            const int64_t cap = npairs / min_pairs > 1 ? npairs / min_pairs : 1;
-            if (want > cap) want = cap;
-            if (want > 64) want = 64;
-            split = (int)(want < 1 ? 1 : want);
+            // unit, at least 8 slabs per slice), the 256-lane panel kernels two.
+            const int64_t target = (tile >= 9) ? 256 : 512;
+            want = (target + tiles - 1) / tiles;
         }
+        if (want > cap) want = cap;
+        if (want > 64) want = 64;
+        split = (int)(want < 1 ? 1 : want);
     }
     if (split > npairs) split = (int)npairs;
     int64_t pairs_per = (npairs + split - 1) / split;

@@ -373,3 +373,27 @@ def test_fp32_batches(m, n, r, c, k, N, ldpad):
     Y = lrbi.masked_gemm(d, W[:, :n], dIp, dIz, to_device(data["X"], "f32"))
     torch.cuda.synchronize()
     assert orc.rel_err(Y.double().cpu().numpy(), ref) <= 1e-6
+
+
+@pytest.mark.parametrize("m,n,r,c,k,p,N", [
+    (260, 328, 200, 192, 40, 0.25, 72),    # rows with more than eight set ranks, two I_p words, cut-off tiles
+    (130, 64, 100, 64, 3, 0.3, 40),       # one slab: nothing lies ahead
+    (129, 200, 43, 128, 33, 0.2, 33),     # an odd number of slabs, N not in whole pieces
+    (600, 4104, 150, 64, 16, 0.1, 128),   # slices; every slab in another tile
+    (300, 960, 100, 320, 70, 0.05, 136),  # three I_p words: the words of a slab loaded at once
+])
+def test_general_tile_kernel_masks(m, n, r, c, k, p, N):
+    """The general tile kernel's mask words, loaded ahead of their slab: mask bits exact, product against the oracle."""
+    cfg = workloads.Config("t", m, n, r, c, k, p, N, "f16", 0.05, 11)
+    print("general tile kernel", cfg, flush=True)
+    data = workloads.make(cfg)
+    d = desc_of(cfg)
+    dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], m, n, r, c, k)
+    ref = orc.masked_gemm(workloads.to_float64(data["W"], "f16"), M, workloads.to_float64(data["X"], "f16"))
+    mask, Y = lrbi.decode_and_gemm(d, to_device(data["W"], "f16"), dIp, dIz, to_device(data["X"], "f16"),
+                                   workspace=workspace_for(d, lrbi.F16, N))
+    torch.cuda.synchronize()
+    bits = unpack_device_mask(mask, n)
+    assert np.array_equal(bits[:, :n], M) and not bits[:, n:].any()
+    assert orc.rel_err(to_float64(Y), ref) <= TOL["f16"]
