@@ -329,8 +329,8 @@ int lrbi_threshold_eval_workspace_bytes(const lrbi_desc *desc, uint64_t *bytes);
  * on-chip memory, a larger one in the workspace, more slowly); LRBI_ERR_SHAPE otherwise, and
  * for n_sp < 1, steps < 1, tolerance < 0, S outside (0, 1) or an S_p outside [0, 1].
  * Costs of candidates that differ by less than the rounding of a double-precision sum may
- * rank either way.  Launches on `stream`: two, three or four per eight S_p values (all of a tile's probes run inside
- * one), and one for the packed factors; with few, very large tiles 1 + 2 steps per S_p value instead.  The host does not
+ * rank either way.  Launches on `stream`: one or two for the sorts (more for a factor beyond 16384 entries), three
+ * or four per eight S_p values (all of a tile's probes run inside one), and one for the packed factors; with few, very large tiles 1 + 2 steps per S_p value instead.  The host does not
  * wait for the device.
  */
 int lrbi_search_thresholds(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,

@@ -556,7 +556,8 @@ int launch_threshold_eval(const Geom &g, lrbi_dtype dt, const void *dW, int64_t 
 // which = 1: M_z, the first ct entries of each of the k rows (rt x ct = the tile's part inside the matrix).  A bitonic
 // network over chunks of 512 E slots, the unused ones +inf, lane t holding slots t E .. t E + E - 1 in registers:
 // distances below E stay inside a lane, those below 64 E inside a wavefront, and only the few larger ones go through
-// LDS (4096 slots: 6 stages of 78; 576 tiles 87 -> 66 us, bound by the exchanges between lanes).  A factor beyond kSortChunk entries is sorted in chunks of that size by several
+// LDS (4096 slots: 6 stages of 78; 576 tiles: two sorts
+// 2 x 87 us through LDS, 2 x 66 in registers, 104 in one launch; bound by the exchanges between lanes).  A factor beyond kSortChunk entries is sorted in chunks of that size by several
 // workgroups; the distances between chunks are passes over the workspace (a search on one 1200 x 600 tile, rank 145:
 // 12.5 -> 1.2 ms).
 static constexpr int kSortThreads = 512;
@@ -598,12 +599,23 @@ template <int E> __device__ __forceinline__ void sort_merge(float (&v)[E], float
             }
 }
 
-// blockIdx.x = tile, blockIdx.y = chunk.  merge_size == 0: sorts the chunk, up or down as the merges that follow ask;
+struct SortOperand {
+    const float *in;
+    float *out;
+    int64_t stride; // floats between two tiles' results
+};
+
+// blockIdx.x = tile, blockIdx.y = chunk, blockIdx.z: op0 (factor which0) or op1 (the next).  merge_size == 0: sorts the chunk, up or down as the merges that follow ask;
 // otherwise: the chunk's part of the merge of that many slots, in place in `out`.
 template <int E>
-__global__ __launch_bounds__(kSortThreads) void tile_sort_kernel(Geom g, int which, const float *__restrict__ in,
-                                                                 float *out, int64_t stride, int merge_size)
+__global__ __launch_bounds__(kSortThreads) void tile_sort_kernel(Geom g, int which0, SortOperand op0, SortOperand op1,
+                                                                 int merge_size)
 {
+    const int which = which0 + (int)blockIdx.z;
+    const SortOperand op = blockIdx.z ? op1 : op0;
+    const float *in = op.in;
+    float *out = op.out;
+    const int64_t stride = op.stride;
     extern __shared__ uint4 lrbi_dyn_smem[];
     float *lds = reinterpret_cast<float *>(lrbi_dyn_smem);
     constexpr int CHUNK = E * kSortThreads;
@@ -704,7 +716,7 @@ struct SpBatch {
 // the tile's M_z (in the L2 from the first probe on), counts the ones of I_a from LDS, and lane 0 moves the interval.
 // Bound by the latency of that chain of steps and by vector-ALU issue in the count; W is not touched.  4096 x 9216 f16,
 // 256 x 256 tiles, rank 16, eight S_p, ten probes: 244 us (278 with one mask word per look-up), where 80 sweeps over W took
-// 80 x 25 us; the whole search 2167 -> 485 us.
+// 80 x 25 us; the whole search 2167 -> 458 us.
 template <typename V>
 __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, const float *__restrict__ Mp,
                                                                      const float *__restrict__ Mz,
@@ -718,17 +730,18 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
     uint32_t *iz = reinterpret_cast<uint32_t *>(lrbi_dyn_smem); // [k][izw]
     uint32_t *ip = iz + g.k * g.izw;                            // [r][ipw]
     static __shared__ unsigned int wave_kept[kEvalWaves];
+    static __shared__ float probe_tz;
     const int64_t t = blockIdx.x;
     int rt, ct;
     tile_extent(g, t, rt, ct);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float tp = threshold_at(sortedMp + t * stride_p, rt * g.k, batch.sp[blockIdx.y]);
     const float *mz = Mz + t * (int64_t)g.k * g.c;
     const float *sorted = sortedMz + t * stride_z;
     const long long target =
         (long long)floor(__dadd_rn(__dmul_rn(__dmul_rn(keep_fraction, (double)rt), (double)ct), 0.5));
     tile_ip_bits(g, Mp + t * (int64_t)g.r * g.k, rt, tp, ip, nullptr);
-    // every lane follows the same interval
+    // the first wavefront follows the interval (the others would repeat the same double arithmetic)
     double lo = 0.0, hi = 1.0, sz = batch.sz0[blockIdx.y];
     long long rep_diff = -1;
     float rep_tz = 0.f;
@@ -739,7 +752,12 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
     const int drow = kEvalThreads / words, dword = kEvalThreads - drow * words;
     const int row0 = tid / words, word0 = tid - row0 * words;
     for (int step = 0; step < steps; ++step) {
-        const float tz = threshold_at(sorted, g.k * ct, sz);
+        if (wave == 0) {
+            const float next = threshold_at(sorted, g.k * ct, sz);
+            if (lane == 0) probe_tz = next;
+        }
+        __syncthreads();
+        const float tz = probe_tz; // written again only after this probe's last barrier
         tile_iz_bits(g, mz, ct, tz, iz, nullptr);
         __syncthreads();
         unsigned int kept = 0u; // ones of one lane: at most 2^32 / 512 by the limits on r and c
@@ -766,17 +784,19 @@ __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, con
         for (int s = 32; s >= 1; s >>= 1) kept += __shfl_xor(kept, s, 64);
         if (lane == 0) wave_kept[wave] = kept;
         __syncthreads(); // also: every lane has read I_z before the next probe writes it
-        long long k = 0;
+        if (wave == 0) {
+            long long k = 0;
 #pragma unroll
-        for (int w = 0; w < kEvalWaves; ++w) k += wave_kept[w]; // read again only after the next probe's first barrier
-        const long long diff = (k > target) ? k - target : target - k;
-        if (rep_diff < 0 || diff < rep_diff) {
-            rep_diff = diff;
-            rep_tz = tz;
+            for (int w = 0; w < kEvalWaves; ++w) k += wave_kept[w]; // written again only after the next probe's barriers
+            const long long diff = (k > target) ? k - target : target - k;
+            if (rep_diff < 0 || diff < rep_diff) {
+                rep_diff = diff;
+                rep_tz = tz;
+            }
+            if (k > target) lo = sz; // too many ones: I_z must get sparser
+            else hi = sz;
+            sz = 0.5 * (lo + hi);
         }
-        if (k > target) lo = sz; // too many ones: I_z must get sparser
-        else hi = sz;
-        sz = 0.5 * (lo + hi);
     }
     if (tid == 0) {
         const int64_t at = (int64_t)blockIdx.y * gridDim.x + t;
@@ -863,15 +883,17 @@ SearchPlan plan_search(const Geom &g)
     return p;
 }
 
-// Sorts one factor of every tile: n entries of a whole tile, `stride` floats between two tiles' results.
-static int launch_sort(const Geom &g, int which, const float *in, float *out, int n, int64_t stride, hipStream_t stream)
+// Sorts one factor of every tile (which, n entries of a whole tile); with `both`, M_p as `a` and M_z as `b` in one
+// launch: two to four workgroups per compute unit instead of one or two, in a kernel that waits for exchanges.
+static int launch_sort(const Geom &g, int which, bool both, const SortOperand &a, const SortOperand &b, int n,
+                       hipStream_t stream)
 {
-    const unsigned tiles = (unsigned)(g.tile_rows * (int64_t)g.tile_cols);
+    const unsigned tiles = (unsigned)(g.tile_rows * (int64_t)g.tile_cols), z = both ? 2 : 1;
 #define LRBI_SORT(E, CHUNKS, MERGE)                                                                                      \
     do {                                                                                                                 \
         LRBI_SET_MAX_LDS(tile_sort_kernel<E>, (E) * kSortThreads * 4);                                                   \
-        LRBI_LAUNCH(tile_sort_kernel<E>, dim3(tiles, (unsigned)(CHUNKS)), dim3(kSortThreads), (E) * kSortThreads * 4, stream, g, \
-                    which, in, out, stride, MERGE);                                                                      \
+        LRBI_LAUNCH(tile_sort_kernel<E>, dim3(tiles, (unsigned)(CHUNKS), z), dim3(kSortThreads), (E) * kSortThreads * 4, \
+                    stream, g, which, a, b, MERGE);                                                                      \
     } while (0)
     if (n <= 1 * kSortThreads) LRBI_SORT(1, 1, 0);
     else if (n <= 2 * kSortThreads) LRBI_SORT(2, 1, 0);
@@ -884,7 +906,8 @@ static int launch_sort(const Geom &g, int which, const float *in, float *out, in
         LRBI_SORT(32, chunks, 0);
         for (int size = 2 * kSortChunk; size <= padded; size *= 2) {
             for (int d = size / 2; d >= kSortChunk; d /= 2)
-                LRBI_LAUNCH(tile_sort_far_kernel, dim3(tiles, (unsigned)(padded / 512)), dim3(256), 0, stream, out, stride, size, d);
+                LRBI_LAUNCH(tile_sort_far_kernel, dim3(tiles, (unsigned)(padded / 512)), dim3(256), 0, stream, a.out, a.stride, size,
+                            d);
             LRBI_SORT(32, chunks, size);
         }
     }
@@ -923,9 +946,15 @@ int launch_search(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, flo
     void *eval_ws = plan_threshold_eval(g).workspace_bytes ? (void *)(ws + p.off_eval) : nullptr;
 
     // 1. sorted factors of every tile (the quantile look-up of "convert with (S_p, S_z)")
-    for (int which = 0; which < 2; ++which) {
-        const int rc = launch_sort(g, which, which ? dMz : dMp, which ? sortedMz : sortedMp, which ? p.nz : p.np,
-                                   which ? p.stride_z : p.stride_p, stream);
+    const SortOperand sort_p{dMp, sortedMp, p.stride_p}, sort_z{dMz, sortedMz, p.stride_z};
+    const int most = p.np > p.nz ? p.np : p.nz, least = p.np > p.nz ? p.nz : p.np;
+    if (most <= kSortChunk && 2 * least >= most) { // the larger one's network serves both
+        const int rc = launch_sort(g, 0, true, sort_p, sort_z, most, stream);
+        if (rc != LRBI_OK) return rc;
+    } else {
+        int rc = launch_sort(g, 0, false, sort_p, sort_p, p.np, stream);
+        if (rc != LRBI_OK) return rc;
+        rc = launch_sort(g, 1, false, sort_z, sort_z, p.nz, stream);
         if (rc != LRBI_OK) return rc;
     }
     // 2. sweep over S_p, bisection on S_z
