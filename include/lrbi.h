@@ -253,7 +253,9 @@ int lrbi_masked_conv3x3(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW,
  * of LRBI_STATIC_SCRATCH_BYTES bytes that is part of the library image on every GPU it runs on (held until
  * the process ends).  The call allocates and frees nothing, on the host side or the device side of HIP.
  *   Limit: shapes whose workspace query exceeds LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
- *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB).
+ *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB), except
+ *   those of 192 output tiles and more, which then run unsplit, as lrbi_masked_gemm does without a workspace (the bits
+ *   are those of that call).
  *   The device of `stream` must be the current device (the scratch array is looked up per current device).
  *   All calls on one GPU share that GPU's array: two calls that may overlap in time (different streams, or
  *   graph branches without an edge between them) race on it; calls ordered by one stream do not.

@@ -878,6 +878,7 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
             // tiles: unsplit 336 us, 2 slices 315, 4 slices 257, 8 slices 251, 16 slices 289); short rows are
             // not worth the partial planes (64 x 576, N = 16384: 19.4 us against 18.7 + 4.2 us).
             if (tiles < 192) want = 512 / tiles;
+            p.split_optional = tiles >= 192;
             if (tiles > 128) {
                 int64_t rounds2 = (1024 + tiles - 1) / tiles;
                 if (rounds2 > npairs / 8) rounds2 = npairs / 8;

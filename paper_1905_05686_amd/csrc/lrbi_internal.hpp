@@ -103,6 +103,7 @@ struct MfmaPlan {
     // leave the fp32 planes of the slices in the workspace ([slice][m][ldp], ldp = N rounded up to 4) and skip the
     // reduction into Y: a fused consumer (the LSTM cell kernel) adds and uses them
     bool planes_only = false;
+    bool split_optional = false; // the tiles alone fill the chip: the slices are for evening out, not needed
 };
 MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N);
 // Where the tile kernel leaves the decoded mask as a by-product (rows of 16-byte pieces, one bit per weight), or {nullptr, 0}.

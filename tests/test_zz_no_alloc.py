@@ -66,3 +66,19 @@ def test_sizes_beyond_the_scratch_are_refused_before_any_launch():
     p = ctypes.c_void_p(256)     # never dereferenced: the size check comes before any launch
     assert lib.lrbi_masked_gemm_static(ctypes.byref(d), lrbi.F16, p, 8192, p, p, p, 128, 128, p, 128, None) == -8
     assert "workspace" in lrbi.strerror(-8)
+
+
+def test_many_tiles_beyond_the_scratch_run_unsplit():
+    """264 output tiles whose slices would need more than the scratch array: the bits of a call without a workspace."""
+    cfg = workloads.Config("t", 4100, 2056, 256, 256, 16, 0.08, 1024, "f16", 0.03, 3)
+    print("static scratch, many tiles", cfg, flush=True)
+    _, d, dIp, dIz, W, X = _case(cfg)
+    assert lrbi.masked_gemm_workspace_bytes(d, lrbi.F16, cfg.N) > 32 * 1024 * 1024
+    ref = lrbi.masked_gemm(d, W, dIp, dIz, X)
+    out = torch.full_like(ref, float("nan"))
+    lrbi.masked_gemm_static(d, W, dIp, dIz, X, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    split = lrbi.masked_gemm(d, W, dIp, dIz, X, workspace=workspace_for(d, lrbi.F16, cfg.N))
+    torch.cuda.synchronize()
+    assert orc.rel_err(split.double().cpu().numpy(), ref.double().cpu().numpy()) <= 1e-3  # f16 roundings of fp32 sums
