@@ -452,6 +452,7 @@ __global__ __launch_bounds__(kNmfThreads, (VW == 1 || RB > 1 || sizeof(T) == 4) 
     unsigned char *wlds = lds + wave * WAVE_BYTES, *zlds = wlds + WBYTES;
 
     for (int l0 = 0; l0 < k; l0 += RB * R) {
+        if (l0 > 0) __syncthreads(); // the chunks overlay the staging area, whose last sums a slower wavefront may still be reading
         int rank[RB];
 #pragma unroll
         for (int q = 0; q < RB; ++q) rank[q] = (l0 + q * R + li < k) ? l0 + q * R + li : k - 1;

@@ -129,3 +129,21 @@ EDGES = [
 @pytest.mark.parametrize("idx", range(len(EDGES)))
 def test_nmf_edges_match_the_oracle(idx):
     _check(*EDGES[idx])
+
+
+@pytest.mark.parametrize("m,n,k,dtype", [
+    (192, 96, 65, "f16"),       # three chunks of columns: the first wavefront has none and is at the next pass at once
+    (64, 32, 256, "bf16"),      # one chunk: three wavefronts without one, four passes
+    (300, 1000, 145, "f32"),    # every wavefront has chunks, their numbers differ
+])
+def test_passes_over_the_ranks_do_not_overlap(m, n, k, dtype):
+    """Above 64 ranks the row update goes over its tile several times, in the same on-chip memory: each pass has to wait
+    for the sums of the one before.  The oracle's values, and the same bits from every call."""
+    cfg = _cfg(m, n, m, n, k, dtype, 30)
+    first = _check(cfg, 2)
+    W = to_device(workloads.make(cfg, want_x=False)["W"], dtype)
+    for _ in range(20):
+        Mp, Mz = (torch.from_numpy(a.copy()).to(dev()) for a in _start(cfg))
+        lrbi.nmf(desc_of(cfg), W, Mp, Mz, 2, eps=1e-9)
+        torch.cuda.synchronize()
+        assert torch.equal(Mp, first[0]) and torch.equal(Mz, first[1])
