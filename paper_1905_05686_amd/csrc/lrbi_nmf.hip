@@ -173,6 +173,11 @@ template <int WORDS> __device__ __forceinline__ void nmf_lds_read(uint32_t (&out
 // loop's end into one load right before its use, and nothing is in flight any more.
 __device__ __forceinline__ void nmf_requested() { asm volatile("" ::: "memory"); }
 
+// First of the `steps` steps that belong to wavefront `wave` of `waves` (to the next wavefront's first).  In 64 bits: a tile
+// may have 2^31 rows or columns.
+__host__ __device__ constexpr int nmf_share(int steps, int wave, int waves) { return (int)((int64_t)steps * wave / waves); }
+static_assert(nmf_share(1 << 30, kNmfWaves, kNmfWaves) == 1 << 30 && nmf_share(1 << 30, 7, kGramWaves) == 7 << 27, "shares of 2^30 steps");
+
 // Gram matrix of a tile's fixed factor: G[a][b] = sum_i Mp[i][a] Mp[i][b] (ZSIDE = false) or sum_j Mz[a][j] Mz[b][j]
 // (ZSIDE = true).  Workgroup = (tile, pair of rank blocks a <= b); its eight wavefronts split the sum.
 template <int R, int VW, bool ZSIDE>
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(kGramThreads) void nmf_gram_kernel(Geom g, const fl
         const float *f = F + t * (int64_t)k * g.c;
         const float *fa = f + (int64_t)ra * g.c, *fb = f + (int64_t)rb * g.c;
         const int steps = (ct + 8 * M::KS - 1) / (8 * M::KS);
-        for (int s = steps * wave / kGramWaves; s < steps * (wave + 1) / kGramWaves; ++s) {
+        for (int s = nmf_share(steps, wave, kGramWaves); s < nmf_share(steps, wave + 1, kGramWaves); ++s) {
             const int j = s * 8 * M::KS + 8 * lk;
             NmfPack<float, 8> va, vb;
             nmf_load<VW>(va, fa, j, ct);
@@ -208,8 +213,8 @@ __global__ __launch_bounds__(kGramThreads) void nmf_gram_kernel(Geom g, const fl
     } else {
         const float *f = F + t * (int64_t)g.r * k;
         const int steps = (rt + M::KS - 1) / M::KS;
-        const int send = steps * (wave + 1) / kGramWaves;
-        for (int s0 = steps * wave / kGramWaves; s0 < send; s0 += 8) {
+        const int send = nmf_share(steps, wave + 1, kGramWaves);
+        for (int s0 = nmf_share(steps, wave, kGramWaves); s0 < send; s0 += 8) {
             float va[8], vb[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
@@ -291,8 +296,8 @@ __global__ __launch_bounds__(kNmfThreads, (kNmfWavesPerSimd<T, R, RB, VW>)) void
     const float *gt = G + t * (int64_t)k * k;
     const T *wtile = W + (int64_t)ti * g.r * ldw + (int64_t)tj * g.c;
     const int steps = (rt + M::KS - 1) / M::KS;
-    const int ibeg = steps * wave / kNmfWaves * M::KS;
-    const int iend = steps * (wave + 1) / kNmfWaves * M::KS < rt ? steps * (wave + 1) / kNmfWaves * M::KS : rt;
+    const int ibeg = nmf_share(steps, wave, kNmfWaves) * M::KS;
+    const int iend = wave + 1 < kNmfWaves ? nmf_share(steps, wave + 1, kNmfWaves) * M::KS : rt;
 
     for (int l0 = 0; l0 < k; l0 += RB * R) {
         int rank[RB]; // ranks beyond k repeat the last one; their sums are never stored
@@ -448,7 +453,7 @@ __global__ __launch_bounds__(kNmfThreads, (VW == 1 || RB > 1 || sizeof(T) == 4) 
 #pragma unroll
     for (int b = 0; b < NB; ++b) row[b] = (rblk * kNmfOwn + b * R + li < rt) ? rblk * kNmfOwn + b * R + li : rt - 1;
     const int chunks = (ct + kNmfChunk - 1) / kNmfChunk;
-    const int sbeg = chunks * wave / kNmfWaves, send = chunks * (wave + 1) / kNmfWaves;
+    const int sbeg = nmf_share(chunks, wave, kNmfWaves), send = nmf_share(chunks, wave + 1, kNmfWaves);
     unsigned char *wlds = lds + wave * WAVE_BYTES, *zlds = wlds + WBYTES;
 
     for (int l0 = 0; l0 < k; l0 += RB * R) {
@@ -487,7 +492,7 @@ __global__ __launch_bounds__(kNmfThreads, (VW == 1 || RB > 1 || sizeof(T) == 4) 
 #pragma unroll
             for (int i = 0; i < ZL; ++i) {
                 const int l = z0 + i * ZSTEP;
-                zraw[i] = *reinterpret_cast<const typename ZPiece::type *>(mz + (l < k ? l : k - 1) * g.c + jz);
+                zraw[i] = *reinterpret_cast<const typename ZPiece::type *>(mz + (int64_t)(l < k ? l : k - 1) * g.c + jz);
             }
             nmf_requested();
         };

@@ -147,3 +147,31 @@ def test_passes_over_the_ranks_do_not_overlap(m, n, k, dtype):
         lrbi.nmf(desc_of(cfg), W, Mp, Mz, 2, eps=1e-9)
         torch.cuda.synchronize()
         assert torch.equal(Mp, first[0]) and torch.equal(Mz, first[1])
+
+
+def test_factor_of_more_than_2_31_entries():
+    """One tile whose M_z has more entries than a 32-bit index reaches.  M_z to the usual tolerance (sums of 8 and 256
+    terms); M_p's sums run over 2^23 columns in chains of at most 2^20 fp32 additions, 2^-24 relative each."""
+    k, r, c = 256, 8, 2 ** 23 + 64
+    print("nmf, M_z of", k * c, "entries", flush=True)
+    d = lrbi.Desc(r, c, r, c, k)
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(5)
+    W = (torch.randn((r, c), device=dev(), generator=gen) * 0.05).half()
+    P0 = torch.rand((1, r, k), device=dev(), generator=gen) + 0.1
+    Z0 = torch.rand((1, k, c), device=dev(), generator=gen) + 0.1
+    Mp, Mz = P0.clone(), Z0.clone()
+    lrbi.nmf(d, W, Mp, Mz, 1, eps=1e-9)
+    torch.cuda.synchronize()
+    P = P0[0].double()
+    gram_z = torch.zeros((k, k), dtype=torch.float64, device=dev())
+    num = torch.zeros((r, k), dtype=torch.float64, device=dev())
+    step = 2 ** 18
+    for j in range(0, c, step):
+        A, Z = W[:, j:j + step].double().abs(), Z0[0, :, j:j + step].double()
+        Z = Z * (P.T @ A) / (P.T @ P @ Z + 1e-9)
+        assert float(((Mz[0, :, j:j + step] - Z).abs() / torch.maximum(Z, Z.square().mean().sqrt())).max()) <= 2e-5
+        gram_z += Z @ Z.T
+        num += A @ Z.T
+    ref = P * num / (P @ gram_z + 1e-9)
+    assert float(((Mp[0] - ref).abs() / ref).max()) <= 2 * 2.0 ** 20 * 2.0 ** -24  # numerator and denominator
