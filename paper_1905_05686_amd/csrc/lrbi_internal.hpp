@@ -164,6 +164,16 @@ int launch_lstm_cell(lrbi_dtype dt, const float *dPlanes, int slices, int64_t m,
 #define LRBI_WAVES_PER_SIMD(n)
 #endif
 
+// Grid of a launch of `blocks` workgroups of `threads` lanes that are numbered by wide_block().  A dispatch counts the lanes of
+// a dimension in 32 bits and the runtime cuts off what lies beyond without an error (8396800 workgroups of 512 lanes: the
+// first 8192 ran), so larger launches take a second dimension; the kernel drops the workgroups past the last one.
+inline dim3 wide_grid(int64_t blocks, int threads)
+{
+    const int64_t most = (int64_t)0xFFFFFFFF / threads;
+    const int64_t y = (blocks + most - 1) / most;
+    return dim3((unsigned)((blocks + y - 1) / y), (unsigned)y);
+}
+
 // Kernel launch with its own status: hipLaunchKernel returns the error of this launch, so an error that an
 // earlier HIP call of the caller left behind on this thread is neither reported as ours nor cleared.
 template <typename... P, size_t... I>
@@ -225,6 +235,9 @@ inline int compute_units_of(hipStream_t stream)
 // ---------------------------------------------------------------------------
 // Device helpers for Eq. 3 on packed factors.
 // ---------------------------------------------------------------------------
+
+// number of a workgroup in a launch of wide_grid()
+__device__ __forceinline__ int64_t wide_block() { return (int64_t)blockIdx.y * gridDim.x + blockIdx.x; }
 
 // 32 consecutive bits of a packed I_z row starting at bit offset `off`
 // (off may be negative: the window starts before the row; off > -32).

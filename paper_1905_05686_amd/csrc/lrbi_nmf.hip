@@ -67,6 +67,7 @@ template <typename T, bool PLAIN> __device__ __forceinline__ float nmf_mag(const
     return (m.method == 2) ? squared : ((m.method == 3) ? amplified : a);
 }
 
+__device__ __forceinline__ int64_t nmf_tiles(const Geom &g) { return (int64_t)g.tile_rows * g.tile_cols; }
 __device__ __forceinline__ void nmf_tile_extent(const Geom &g, int64_t t, int &ti, int &tj, int &rt, int &ct)
 {
     ti = (int)(t / g.tile_cols);
@@ -100,6 +101,7 @@ template <int R> __device__ __forceinline__ typename NmfMat<R>::acc_t nmf_zero()
 // consecutive workgroups go round the eight XCDs: the workgroups of one tile, which share its factors, get one L2
 __device__ __forceinline__ int64_t nmf_block_id()
 {
+    if (gridDim.y > 1) return wide_block(); // millions of tiles
     const unsigned q = gridDim.x / 8, rest = gridDim.x % 8, x = blockIdx.x % 8;
     return (int64_t)x * q + (x < rest ? x : rest) + blockIdx.x / 8;
 }
@@ -187,6 +189,7 @@ __global__ __launch_bounds__(kGramThreads) void nmf_gram_kernel(Geom g, const fl
     using M = NmfMat<R>;
     static __shared__ float stage[kGramWaves * M::NR * 64];
     const int64_t id = nmf_block_id(), t = id / pairs;
+    if (t >= nmf_tiles(g)) return;
     int pair = (int)(id - t * pairs), ab = 0;
     while (pair >= kblocks - ab) pair -= kblocks - ab++;
     const int bb = ab + pair;
@@ -283,6 +286,7 @@ __global__ __launch_bounds__(kNmfThreads, (kNmfWavesPerSimd<T, R, RB, VW>)) void
     constexpr int U = 8;
     static __shared__ float stage[kNmfWaves * NB * M::NR * 64];
     const int64_t id = nmf_block_id(), t = id / cblocks;
+    if (t >= nmf_tiles(g)) return;
     const int cb = (int)(id - t * cblocks);
     int ti, tj, rt, ct;
     nmf_tile_extent(g, t, ti, tj, rt, ct);
@@ -438,6 +442,7 @@ __global__ __launch_bounds__(kNmfThreads, (VW == 1 || RB > 1 || sizeof(T) == 4) 
     __align__(16) static __shared__ unsigned char lds[LDS_BYTES];
     float *stage = reinterpret_cast<float *>(lds);
     const int64_t id = nmf_block_id(), t = id / rblocks;
+    if (t >= nmf_tiles(g)) return;
     const int rblk = (int)(id - t * rblocks);
     int ti, tj, rt, ct;
     nmf_tile_extent(g, t, ti, tj, rt, ct);
@@ -605,13 +610,13 @@ static int nmf_iterate(const Geom &g, const void *dW, int64_t ldw, int method, f
     const NmfManip manip{method, w_threshold, amplify};
     float *mp_cur = dMp, *mp_new = wsMp, *mz_cur = dMz, *mz_new = wsMz;
     for (int it = 0; it < iters; ++it) {
-        LRBI_LAUNCH((nmf_gram_kernel<R, VW, false>), dim3((unsigned)(tiles * pairs)), dim3(kGramThreads), 0, stream, g, mp_cur,
+        LRBI_LAUNCH((nmf_gram_kernel<R, VW, false>), wide_grid(tiles * pairs, kGramThreads), dim3(kGramThreads), 0, stream, g, mp_cur,
                     wsG, kblocks, pairs);
-        LRBI_LAUNCH((nmf_update_z_kernel<T, R, RB, VW, PLAIN>), dim3((unsigned)(tiles * cblocks)), dim3(kNmfThreads), 0, stream, g,
+        LRBI_LAUNCH((nmf_update_z_kernel<T, R, RB, VW, PLAIN>), wide_grid(tiles * cblocks, kNmfThreads), dim3(kNmfThreads), 0, stream, g,
                     (const T *)dW, ldw, manip, mp_cur, mz_cur, mz_new, wsG, eps, cblocks);
-        LRBI_LAUNCH((nmf_gram_kernel<R, VW, true>), dim3((unsigned)(tiles * pairs)), dim3(kGramThreads), 0, stream, g, mz_new,
+        LRBI_LAUNCH((nmf_gram_kernel<R, VW, true>), wide_grid(tiles * pairs, kGramThreads), dim3(kGramThreads), 0, stream, g, mz_new,
                     wsG, kblocks, pairs);
-        LRBI_LAUNCH((nmf_update_p_kernel<T, R, RB, VW, PLAIN>), dim3((unsigned)(tiles * rblocks)), dim3(kNmfThreads), 0, stream, g,
+        LRBI_LAUNCH((nmf_update_p_kernel<T, R, RB, VW, PLAIN>), wide_grid(tiles * rblocks, kNmfThreads), dim3(kNmfThreads), 0, stream, g,
                     (const T *)dW, ldw, manip, mp_cur, mz_new, mp_new, wsG, eps, rblocks);
         float *tmp = mp_cur;
         mp_cur = mp_new;

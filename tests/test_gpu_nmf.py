@@ -175,3 +175,33 @@ def test_factor_of_more_than_2_31_entries():
         num += A @ Z.T
     ref = P * num / (P @ gram_z + 1e-9)
     assert float(((Mp[0] - ref).abs() / ref).max()) <= 2 * 2.0 ** 20 * 2.0 ** -24  # numerator and denominator
+
+
+@pytest.mark.parametrize("m,n,r,c", [
+    (4096, 8200, 2, 2),         # more than 2^23 tiles: 512 lanes each in the Gram kernels
+    (4300000, 256, 1, 256),     # four blocks of columns per tile, 256 lanes each, beyond 2^32 lanes
+    (256, 4300000, 256, 1),     # four blocks of rows
+])
+def test_millions_of_tiles(m, n, r, c):
+    """More lanes than one dimension of a launch can count: every tile is still factorised (rank 1, one iteration)."""
+    print("nmf, many tiles", m, n, r, c, flush=True)
+    d = lrbi.Desc(m, n, r, c, 1)
+    tr, tc = m // r, n // c
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(6)
+    W = (torch.rand((m, n), device=dev(), generator=gen) * 0.05).half()
+    P0 = torch.rand((d.tiles, r, 1), device=dev(), generator=gen) + 0.1
+    Z0 = torch.rand((d.tiles, 1, c), device=dev(), generator=gen) + 0.1
+    Mp, Mz = P0.clone(), Z0.clone()
+    lrbi.nmf(d, W, Mp, Mz, 1, eps=1e-9)
+    torch.cuda.synchronize()
+    A4 = W.reshape(tr, r, tc, c).permute(0, 2, 1, 3)  # [tile row, tile column, r, c]
+    slow = 0 if tr >= tc else 1                       # the longer of the two goes in pieces
+    for at in range(0, max(tr, tc), 2 ** 18):
+        A = A4.narrow(slow, at, min(2 ** 18, max(tr, tc) - at)).double()
+        pick = lambda f: f.reshape(tr, tc, *f.shape[1:]).narrow(slow, at, A.shape[slow]).double()
+        P, Z = pick(P0), pick(Z0)
+        Z = Z * (P * A).sum(2, keepdim=True) / ((P * P).sum(2, keepdim=True) * Z + 1e-9)
+        P = P * (A * Z).sum(3, keepdim=True) / (P * (Z * Z).sum(3, keepdim=True) + 1e-9)
+        for got, ref in ((pick(Mz), Z), (pick(Mp), P)):
+            assert bool(((got - ref).abs() <= 2e-5 * ref).all())  # a weight of zero leaves a zero
