@@ -88,8 +88,10 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
 {
     static __shared__ float red[kF32Waves][1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
-    const int jb = (int)(blockIdx.x % (unsigned)jblocks);
-    const int64_t j0 = 32 * (int64_t)jb, q0 = 32 * NQ * (int64_t)(blockIdx.x / (unsigned)jblocks);
+    const unsigned block = (unsigned)wide_block();
+    const int jb = (int)(block % (unsigned)jblocks);
+    const int64_t j0 = 32 * (int64_t)jb, q0 = 32 * NQ * (int64_t)(block / (unsigned)jblocks);
+    if (q0 >= N) return; // past the last workgroup of the grid's second dimension
     const T *wcol = W + at_most(j0 + li, g.n - 1); // clamped: what lies beyond has no mask bit, or is not stored
     const T *ycol[NQ];
 #pragma unroll
@@ -153,8 +155,10 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
 {
     static __shared__ float red[kF32Waves][1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
-    const int64_t i0 = 32 * (int64_t)(blockIdx.x % (unsigned)iblocks);
-    const int64_t q0 = 32 * NQ * (int64_t)(blockIdx.x / (unsigned)iblocks);
+    const unsigned block = (unsigned)wide_block();
+    const int64_t i0 = 32 * (int64_t)(block % (unsigned)iblocks);
+    const int64_t q0 = 32 * NQ * (int64_t)(block / (unsigned)iblocks);
+    if (q0 >= N) return; // past the last workgroup of the grid's second dimension
     const int64_t row = at_most(i0 + li, g.m - 1);
     const float *wrow = W + row * ldw;
     const float *xcol[NQ];
@@ -317,10 +321,10 @@ static int launch_t(const Geom &g, const void *dW, int64_t ldw, const uint32_t *
     const int64_t blocks = jblocks * ((N + 32 * nq - 1) / (32 * nq));
     if (blocks > 0x7FFFFFFF || (N + 3) / 4 > 65535) return LRBI_ERR_SHAPE;
     if (nq == 2)
-        LRBI_LAUNCH((f32_gemm_t_kernel<T, 2>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
+        LRBI_LAUNCH((f32_gemm_t_kernel<T, 2>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
                     dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
     else
-        LRBI_LAUNCH((f32_gemm_t_kernel<T, 1>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
+        LRBI_LAUNCH((f32_gemm_t_kernel<T, 1>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
                     dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
     return LRBI_OK;
 }
@@ -345,7 +349,7 @@ int launch_f32_gemm(const Geom &g, const float *dW, int64_t ldw, const uint32_t 
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     const bool vec = ((uintptr_t)dW & 15) == 0 && ldw % 4 == 0 && g.n % 4 == 0;
 #define LRBI_LAUNCH_F32(NQ, V)                                                                                       \
-    LRBI_LAUNCH((f32_gemm_kernel<NQ, V>), dim3((unsigned)blocks), dim3(kF32Threads), 0, stream, g, dW, ldw, dIp, dIz, dX, ldx, \
+    LRBI_LAUNCH((f32_gemm_kernel<NQ, V>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, dW, ldw, dIp, dIz, dX, ldx, \
                 N, dY, ldy, (int)iblocks)
     if (nq == 2) {
         if (vec) LRBI_LAUNCH_F32(2, true);

@@ -172,3 +172,30 @@ def test_fp32_products_with_nonfinite_operands(N):
         h = got.cpu().numpy().astype(np.float64)
         fin = np.isfinite(h)
         assert orc.rel_err(np.where(fin, h, 0), np.where(fin, ref, 0)) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("transposed", [False, True])
+def test_fp32_products_of_more_lanes_than_a_dimension_counts(transposed):
+    """2^23 + 2 blocks of 32 rows (columns) are more than 2^32 lanes.  One weight per row (column): single products."""
+    size, N = 2 ** 28 + 64, 5
+    print("fp32 product, many blocks, transposed", transposed, flush=True)
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(9)
+    W = torch.randn(size, device=dev(), generator=gen)
+    X = torch.randn((1, N), device=dev(), generator=gen)
+    if transposed:
+        d = lrbi.Desc(1, size, 1, size, 1)
+        dIp = torch.ones((1, 1), dtype=torch.int32, device=dev())
+        dIz = torch.randint(-2 ** 31, 2 ** 31, (1, size // 32), dtype=torch.int32, device=dev(), generator=gen)
+        kept = lambda a, b: ((dIz[0, a // 32:b // 32, None] >> torch.arange(32, device=dev(), dtype=torch.int32)) & 1).reshape(-1)
+        got = lrbi.masked_gemm_t(d, W.reshape(1, size), dIp, dIz, X)
+    else:
+        d = lrbi.Desc(size, 1, size, 1, 1)
+        dIp = torch.randint(0, 2, (size, 1), dtype=torch.int32, device=dev(), generator=gen)
+        dIz = torch.tensor([[1, 0]], dtype=torch.int32, device=dev())
+        kept = lambda a, b: dIp[a:b, 0]
+        got = lrbi.masked_gemm(d, W.reshape(size, 1), dIp, dIz, X)
+    torch.cuda.synchronize()
+    for a in range(0, size, 2 ** 24):
+        b = min(a + 2 ** 24, size)
+        assert torch.equal(got[a:b], torch.where(kept(a, b)[:, None] != 0, W[a:b, None] * X, 0.0)), a
