@@ -180,6 +180,8 @@ template <typename... P, size_t... I>
 inline hipError_t launch_kernel_impl(void (*kern)(P...), dim3 grid, dim3 block, size_t smem, hipStream_t stream,
                                      std::tuple<P...> &vals, std::index_sequence<I...>)
 {
+    // more lanes in a dimension than a dispatch counts: the runtime would run a part of them and report success
+    if ((uint64_t)grid.x * block.x > 0xFFFFFFFFull || (uint64_t)grid.y * block.y > 0xFFFFFFFFull) return hipErrorInvalidConfiguration;
     void *ptrs[sizeof...(P) ? sizeof...(P) : 1] = {(void *)&std::get<I>(vals)...};
     return hipLaunchKernel((const void *)kern, grid, block, ptrs, smem, stream);
 }

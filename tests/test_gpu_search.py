@@ -168,3 +168,15 @@ def test_search_routes(m, n, r, c, k, dtype, sweep):
     costs within the rounding of a double-precision sum, as everywhere in this file."""
     print("search route", m, n, r, c, k, dtype, len(sweep), flush=True)
     _check(_cfg(m, n, r, c, k, dtype, 70, p=0.15), 0.9, sweep, 4, max(1, r * c // 100))
+
+
+def test_more_tiles_than_a_launch_can_count_are_refused():
+    """2^23 tiles of 512 lanes each are one lane more than a launch counts: an error, not results for some of the tiles."""
+    m, n, r, c = 4096, 8192, 2, 2
+    print("search, 2^23 tiles", flush=True)
+    d = lrbi.Desc(m, n, r, c, 1)
+    W = torch.zeros((m, n), dtype=torch.float16, device=dev())
+    Mp, Mz = torch.zeros((d.tiles, r, 1), device=dev()), torch.zeros((d.tiles, 1, c), device=dev())
+    with pytest.raises(lrbi.LrbiError, match="refused the kernel launch"):
+        lrbi.search_thresholds(d, W, 0.1, Mp, Mz, 0.9, [0.5], 1, 1)
+    torch.cuda.synchronize()
