@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
         for (int q = 0; q < RANKS; ++q) {
             if (sel) l = __builtin_ctzll(sel); // none left: the last one again
             sel &= sel - 1ull;
-            w.z[q] = w.iz[l * g.izw];
+            w.z[q] = w.iz[(uint32_t)l * (uint32_t)g.izw]; // l < 64, izw <= 2^26: 32 bits hold it, unsigned
         }
         w.rest = sel;
         return w;
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(kThreads) void mfma_gemm_kernel(
         uint32_t word = 0u;
 #pragma unroll
         for (int q = 0; q < RANKS; ++q) word |= w.z[q];
-        for (unsigned long long sel = w.rest; sel; sel &= sel - 1ull) word |= w.iz[__builtin_ctzll(sel) * g.izw];
+        for (unsigned long long sel = w.rest; sel; sel &= sel - 1ull) word |= w.iz[(uint32_t)__builtin_ctzll(sel) * (uint32_t)g.izw];
         put_word(slab, buf, tid, w.any ? word : 0u);
     };
 

@@ -191,3 +191,27 @@ def test_search_edge_tiles(idx):
     ip_ref, iz_ref = lrbi.pack_factors(desc_of(cfg), Ip, Iz)
     assert np.array_equal(ip.cpu().numpy().view(np.uint32).reshape(-1), np.asarray(ip_ref).view(np.uint32).reshape(-1))
     assert np.array_equal(iz.cpu().numpy().view(np.uint32).reshape(-1), np.asarray(iz_ref).view(np.uint32).reshape(-1))
+
+
+def test_factor_rows_beyond_32_bit_indices():
+    """One tile of more than 2^30 columns at rank 64: the last row of I_z starts more than 2^31 words in.  Whole
+    numbers, so that sums of any order are exact."""
+    n, k, N = 2 ** 30 + 2 ** 25, 64, 5
+    words = n // 32
+    print("I_z of", k * words, "words", flush=True)
+    gen = torch.Generator(device=dev())
+    gen.manual_seed(12)
+    W = torch.zeros((1, n), dtype=torch.float16, device=dev())
+    X = torch.ones((n, N), dtype=torch.float16, device=dev())
+    dIp = torch.tensor([[2, -2 ** 31]], dtype=torch.int32, device=dev())  # ranks 1 and 63
+    dIz = torch.zeros((k, words), dtype=torch.int32, device=dev())
+    dIz[0], dIz[62] = -1, -1                                               # not selected
+    dIz[1, ::3], dIz[63, ::2] = 1, 2
+    # every 2^20-th word has a weight of one under each of its first two columns: below 2^11 kept, a whole number in f16
+    at = torch.arange(0, words, 2 ** 20 + 1, device=dev())
+    W[0, 32 * at], W[0, 32 * at + 1], W[0, 32 * at + 2] = 1.0, 1.0, 1.0
+    d = lrbi.Desc(1, n, 1, n, k)
+    Y = lrbi.masked_gemm(d, W, dIp, dIz, X, workspace=workspace_for(d, lrbi.F16, N))
+    torch.cuda.synchronize()
+    want = int((at % 3 == 0).sum() + (at % 2 == 0).sum())
+    assert Y.tolist() == [[float(want)] * N]
