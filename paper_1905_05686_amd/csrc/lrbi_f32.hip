@@ -133,10 +133,11 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
         for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
             const int64_t j = j0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
             if (j >= g.n || q >= N) continue;
-            float s = 0.f;
+            double s = 0.0; // the finite results of the block are formed again as well: rounded once, as exact as before
             for (int64_t i = 0; i < g.m; ++i)
-                if ((row_word(g, Ip, Iz, i, jb) >> (j & 31)) & 1u) s = fmaf(as_f32(W[i * ldw + j]), as_f32(DY[i * lddy + q]), s);
-            DX[j * lddx + q] = from_f32<T>(s);
+                if ((row_word(g, Ip, Iz, i, jb) >> (j & 31)) & 1u)
+                    s = __fma_rn((double)as_f32(W[i * ldw + j]), (double)as_f32(DY[i * lddy + q]), s);
+            DX[j * lddx + q] = from_f32<T>((float)s);
         }
         return;
     }
@@ -220,13 +221,13 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
         for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
             const int64_t i = i0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
             if (i >= g.m || q >= N) continue;
-            float s = 0.f;
+            double s = 0.0; // as above
             for (int64_t j = 0; j < g.n; j += 32)
                 for (uint32_t word = row_word(g, Ip, Iz, i, (int)(j >> 5)); word; word &= word - 1u) {
                     const int64_t jj = j + __builtin_ctz(word);
-                    s = fmaf(W[i * ldw + jj], X[jj * ldx + q], s);
+                    s = __fma_rn((double)W[i * ldw + jj], (double)X[jj * ldx + q], s);
                 }
-            Y[i * ldy + q] = s;
+            Y[i * ldy + q] = (float)s;
         }
         return;
     }

@@ -199,3 +199,25 @@ def test_fp32_products_of_more_lanes_than_a_dimension_counts(transposed):
     for a in range(0, size, 2 ** 24):
         b = min(a + 2 ** 24, size)
         assert torch.equal(got[a:b], torch.where(kept(a, b)[:, None] != 0, W[a:b, None] * X, 0.0)), a
+
+
+@pytest.mark.parametrize("long_side", ["m", "n"])
+def test_nonfinite_operands_leave_the_finite_results_exact(long_side):
+    """One infinity in the batch has its block done again: the results it does not reach stay as exact as without it.
+    Sums in double, so only the rounding to fp32 is left: 2^-24 of each result."""
+    cfg = _small(9000, 72, 250, 36, 3, 0.3, 20, "f32") if long_side == "m" else _small(72, 9000, 36, 250, 3, 0.3, 20, "f32")
+    print("nonfinite, long side", long_side, flush=True)
+    data, dY = _inputs(cfg)
+    d = desc_of(cfg)
+    dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], cfg.m, cfg.n, cfg.r, cfg.c, cfg.k)
+    W, W64 = to_device(data["W"], "f32"), data["W"].astype(np.float64)
+    X = data["X"].copy()
+    X[5, 3], dY[7, 4] = np.inf, np.inf
+    rest = [q for q in range(20) if q not in (3, 4)]
+    if long_side == "n":
+        got, ref = lrbi.masked_gemm(d, W, dIp, dIz, to_device(X, "f32")), orc.masked_gemm(W64, M, data["X"].astype(np.float64))
+    else:
+        got, ref = lrbi.masked_gemm_t(d, W, dIp, dIz, to_device(dY, "f32")), (W64 * M).T @ np.where(np.isinf(dY), 0, dY).astype(np.float64)
+    torch.cuda.synchronize()
+    assert orc.rel_err(got.cpu().numpy().astype(np.float64)[:, rest], ref[:, rest]) <= 2.0 ** -24 * (1 + 1e-6)
