@@ -15,8 +15,8 @@
 // 1.4e-7 -> 1.1e-7.
 //
 // A zeroed weight still meets its other operand inside the instruction, and 0 * inf is NaN.  The products therefore
-// watch their unmasked operand: a workgroup that has met an infinity or a NaN does its block again one output at a
-// time, stepping over the pruned weights.
+// watch their unmasked operand: batch columns that hold an infinity or a NaN are formed again, stepping over the
+// pruned weights; the others do not meet them.
 #include <float.h>
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -48,6 +48,75 @@ template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(f
 
 __device__ __forceinline__ int64_t at_most(int64_t i, int64_t last) { return i < last ? i : last; }
 
+// The batch columns (bits) of a workgroup's block in which a lane has met a value that is not finite: lane l watches columns
+// (l & 31) + 32 b.  One value for the whole workgroup; columns from N on, which repeat the last one, are left out.
+template <int NQ>
+__device__ __forceinline__ unsigned long long bad_columns(const bool (&bad)[NQ], int64_t cols)
+{
+    static __shared__ uint32_t met[kF32Waves * NQ];
+#pragma unroll
+    for (int b = 0; b < NQ; ++b) {
+        const unsigned long long lanes = __ballot(bad[b]);
+        if ((threadIdx.x & 63) == 0) met[(threadIdx.x >> 6) * NQ + b] = (uint32_t)lanes | (uint32_t)(lanes >> 32);
+    }
+    __syncthreads();
+    unsigned long long all = 0ull;
+#pragma unroll
+    for (int w = 0; w < kF32Waves; ++w)
+#pragma unroll
+        for (int b = 0; b < NQ; ++b) all |= (unsigned long long)met[w * NQ + b] << (32 * b);
+    return cols < 64 ? all & ((1ull << cols) - 1ull) : all;
+}
+
+// How a wavefront forms a row (or column) of results in those columns again: lane = (part of the reduction, column).  The
+// parts' sums are in double and a lane stops at a NaN, which nothing that follows changes.
+struct BadLanes {
+    int parts, part, qlanes;
+    int64_t q;     // column of the block
+    bool last_one; // no column of its own: repeats the last
+    __device__ BadLanes(unsigned long long columns)
+    {
+        const int lane = threadIdx.x & 63, count = __builtin_popcountll(columns);
+        qlanes = 1;
+        while (qlanes < count) qlanes *= 2;
+        parts = 64 / qlanes;
+        part = lane / qlanes;
+        const int ql = lane % qlanes;
+        last_one = ql >= count;
+        for (int skip = last_one ? count - 1 : ql; skip > 0; --skip) columns &= columns - 1ull;
+        q = __builtin_ctzll(columns);
+    }
+    __device__ double total(double s) const
+    {
+        for (int d = qlanes; d < 64; d *= 2) s += __shfl_xor(s, d, 64);
+        return s;
+    }
+    __device__ bool stores() const { return part == 0 && !last_one; }
+};
+
+// s += sum of w[at] x[at], at = base + the set bits, four at a time in flight
+template <typename T>
+__device__ __forceinline__ void add_kept(double &s, unsigned long long bits, int64_t base, const T *w, int64_t wstride, const T *x,
+                                         int64_t xstride)
+{
+    while (bits && s == s) {
+        int64_t at[4];
+        bool live[4];
+        T wv[4], xv[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            live[e] = bits != 0ull;
+            at[e] = live[e] ? base + __builtin_ctzll(bits) : at[0];
+            bits &= bits - 1ull;
+            wv[e] = w[at[e] * wstride];
+            xv[e] = x[at[e] * xstride];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (live[e]) s = __fma_rn((double)as_f32(wv[e]), (double)as_f32(xv[e]), s);
+    }
+}
+
 // mask word of row `row`, word column w
 __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
 {
@@ -55,10 +124,10 @@ __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, 
     return decode_word(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
 }
 
-// adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it
+// adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it, without the batch columns in `skip`
 template <typename T, int NQ>
 __device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t (&acc)[NQ], int64_t row0, int64_t rows,
-                                             int64_t q0, int64_t N, T *__restrict__ out, int64_t ldo)
+                                             int64_t q0, int64_t N, unsigned long long skip, T *__restrict__ out, int64_t ldo)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
@@ -72,7 +141,7 @@ __device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t 
 #pragma unroll
             for (int w = 1; w < kF32Waves; ++w) s += (double)red[w][e];
             const int64_t i = row0 + (e >> 5), q = q0 + 32 * b + (e & 31);
-            if (i < rows && q < N) out[i * ldo + q] = from_f32<T>((float)s);
+            if (i < rows && q < N && !((skip >> (32 * b + (e & 31))) & 1ull)) out[i * ldo + q] = from_f32<T>((float)s);
         }
     }
 }
@@ -99,7 +168,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
 
     constexpr int U = 8; // steps of the instruction whose operands are requested together
     f32x16_t acc[NQ] = {};
-    bool bad = false;
+    bool bad[NQ] = {};
     for (int64_t i0 = (int64_t)kF32Chunk * wave; i0 < g.m; i0 += kF32Chunk * kF32Waves) {
         T w[2][U], y[2][U][NQ];
         const auto load = [&](int s0, T (&wv)[U], T (&yv)[U][NQ]) {
@@ -123,25 +192,38 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
 #pragma unroll
                 for (int b = 0; b < NQ; ++b) {
                     const float x = as_f32(y[s & 1][u][b]);
-                    bad |= !(fabsf(x) <= FLT_MAX);
+                    bad[b] |= !(fabsf(x) <= FLT_MAX);
                     acc[b] = mfma_32x32x2(a, x, acc[b]);
                 }
             }
         }
     }
-    if (__syncthreads_or(bad)) {
-        for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
-            const int64_t j = j0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
-            if (j >= g.n || q >= N) continue;
-            double s = 0.0; // the finite results of the block are formed again as well: rounded once, as exact as before
-            for (int64_t i = 0; i < g.m; ++i)
-                if ((row_word(g, Ip, Iz, i, jb) >> (j & 31)) & 1u)
-                    s = __fma_rn((double)as_f32(W[i * ldw + j]), (double)as_f32(DY[i * lddy + q]), s);
-            DX[j * lddx + q] = from_f32<T>((float)s);
+    const unsigned long long again = bad_columns<NQ>(bad, N - q0);
+    reduce_store<T, NQ>(red, acc, j0, g.n, q0, N, again, DX, lddx);
+    if (!again) return;
+    // a wavefront forms four columns of W; the mask words of 64 rows at a time are decoded once for them
+    const BadLanes lanes(again);
+    unsigned long long mine = 0ull; // the lane's rows of 64
+    for (int i = lanes.part; i < 64; i += lanes.parts) mine |= 1ull << i;
+    constexpr int JW = 32 / kF32Waves;
+    double s[JW] = {};
+    for (int64_t i0 = 0; i0 < g.m; i0 += 64) {
+        const uint32_t words = (i0 + lane < g.m) ? row_word(g, Ip, Iz, i0 + lane, jb) : 0u;
+        bool open = false;
+#pragma unroll
+        for (int u = 0; u < JW; ++u) { // (no bit is set in rows from m on and in columns from n on)
+            const unsigned long long rows = __ballot((words >> (wave * JW + u)) & 1u) & mine;
+            add_kept<T>(s[u], rows, i0, W + at_most(j0 + wave * JW + u, g.n - 1), ldw, DY + q0 + lanes.q, lddy);
+            open |= s[u] == s[u];
         }
-        return;
+        if (!__any(open)) break;
     }
-    reduce_store<T, NQ>(red, acc, j0, g.n, q0, N, DX, lddx);
+#pragma unroll
+    for (int u = 0; u < JW; ++u) {
+        const double sum = lanes.total(s[u]);
+        const int64_t j = j0 + wave * JW + u;
+        if (lanes.stores() && j < g.n) DX[j * lddx + q0 + lanes.q] = from_f32<T>((float)sum);
+    }
 }
 
 // Y = (W o I_a) X, fp32.  Workgroup = 32 rows of W x 32 NQ batch columns; a wavefront's chunk is 64 columns of W, two
@@ -170,7 +252,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
     // the sums of 32 columns go into doubles: one fp32 chain over a wavefront's whole share of the row would round more
     // often than a sum spread over 64 lanes (relative error 1.5e-7 at 300 x 4000, where this gives 6.2e-8)
     double sum[NQ][16] = {};
-    bool bad = false;
+    bool bad[NQ] = {};
     for (int64_t j0 = (int64_t)kF32Chunk * wave; j0 < g.n; j0 += kF32Chunk * kF32Waves) {
         float w[2][4], x[2][4][NQ];
         const auto load = [&](int gq, float (&wv)[4], float (&xv)[4][NQ]) {
@@ -205,7 +287,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
 #pragma unroll
                 for (int b = 0; b < NQ; ++b) {
                     const float v = x[gq & 1][e][b];
-                    bad |= !(fabsf(v) <= FLT_MAX);
+                    bad[b] |= !(fabsf(v) <= FLT_MAX);
                     acc[b] = mfma_32x32x2(a, v, acc[b]);
                 }
             }
@@ -217,26 +299,29 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
             }
         }
     }
-    if (__syncthreads_or(bad)) {
-        for (int e = threadIdx.x; e < 1024 * NQ; e += kF32Threads) {
-            const int64_t i = i0 + e / (32 * NQ), q = q0 + e % (32 * NQ);
-            if (i >= g.m || q >= N) continue;
-            double s = 0.0; // as above
-            for (int64_t j = 0; j < g.n; j += 32)
-                for (uint32_t word = row_word(g, Ip, Iz, i, (int)(j >> 5)); word; word &= word - 1u) {
-                    const int64_t jj = j + __builtin_ctz(word);
-                    s = __fma_rn((double)W[i * ldw + jj], (double)X[jj * ldx + q], s);
-                }
-            Y[i * ldy + q] = (float)s;
-        }
-        return;
-    }
+    const unsigned long long again = bad_columns<NQ>(bad, N - q0);
     f32x16_t acc[NQ];
 #pragma unroll
     for (int b = 0; b < NQ; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[b][v] = (float)sum[b][v];
-    reduce_store<float, NQ>(red, acc, i0, g.m, q0, N, Y, ldy);
+    reduce_store<float, NQ>(red, acc, i0, g.m, q0, N, again, Y, ldy);
+    if (!again) return;
+    // a wavefront forms four rows; 64 mask words of a row are decoded at a time, and a lane takes every parts-th
+    const BadLanes lanes(again);
+    const int words_per_row = (int)((g.n + 31) / 32);
+    for (int64_t i = i0 + wave; i < i0 + 32 && i < g.m; i += kF32Waves) {
+        double s = 0.0;
+        for (int w0 = 0; w0 < words_per_row && __any(s == s); w0 += 64) {
+            const uint32_t words = row_word(g, Ip, Iz, i, w0 + lane); // none past the row
+            for (int step = 0; step < 64; step += lanes.parts) {
+                const int at = step + lanes.part;
+                add_kept<float>(s, __shfl(words, at, 64), 32 * ((int64_t)w0 + at), W + i * ldw, 1, X + q0 + lanes.q, ldx);
+            }
+        }
+        s = lanes.total(s);
+        if (lanes.stores()) Y[i * ldy + q0 + lanes.q] = (float)s;
+    }
 }
 
 // dW = (dY X^T) o I_a, fp32.  One wavefront per 32 x (32 NJ) block of dW (no reduction is split: the blocks are many

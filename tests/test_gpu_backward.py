@@ -148,7 +148,7 @@ def test_fp32_matrix_cores(cfg, ldpad):
     _check(cfg, ldpad=ldpad, what="fp32 instructions")
 
 
-@pytest.mark.parametrize("N", [5, 64])
+@pytest.mark.parametrize("N", [4, 5, 33, 50, 64, 97])  # one, 18 and 32 columns in the last block among them
 def test_fp32_products_with_nonfinite_operands(N):
     """An infinity or a NaN in the batch reaches the results of kept weights only, in both products."""
     cfg = _small(200, 168, 50, 56, 4, 0.3, N, "f32")
@@ -203,8 +203,8 @@ def test_fp32_products_of_more_lanes_than_a_dimension_counts(transposed):
 
 @pytest.mark.parametrize("long_side", ["m", "n"])
 def test_nonfinite_operands_leave_the_finite_results_exact(long_side):
-    """One infinity in the batch has its block done again: the results it does not reach stay as exact as without it.
-    Sums in double, so only the rounding to fp32 is left: 2^-24 of each result."""
+    """An infinity in the batch has its batch column formed again, the results it does not reach in sums in double: only
+    the rounding to fp32 is left of their error, 2^-24 each.  The other columns hold the bits of a call without it."""
     cfg = _small(9000, 72, 250, 36, 3, 0.3, 20, "f32") if long_side == "m" else _small(72, 9000, 36, 250, 3, 0.3, 20, "f32")
     print("nonfinite, long side", long_side, flush=True)
     data, dY = _inputs(cfg)
@@ -212,12 +212,16 @@ def test_nonfinite_operands_leave_the_finite_results_exact(long_side):
     dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
     M = orc.decode_mask(data["Ip01"], data["Iz01"], cfg.m, cfg.n, cfg.r, cfg.c, cfg.k)
     W, W64 = to_device(data["W"], "f32"), data["W"].astype(np.float64)
-    X = data["X"].copy()
-    X[5, 3], dY[7, 4] = np.inf, np.inf
-    rest = [q for q in range(20) if q not in (3, 4)]
-    if long_side == "n":
-        got, ref = lrbi.masked_gemm(d, W, dIp, dIz, to_device(X, "f32")), orc.masked_gemm(W64, M, data["X"].astype(np.float64))
-    else:
-        got, ref = lrbi.masked_gemm_t(d, W, dIp, dIz, to_device(dY, "f32")), (W64 * M).T @ np.where(np.isinf(dY), 0, dY).astype(np.float64)
-    torch.cuda.synchronize()
-    assert orc.rel_err(got.cpu().numpy().astype(np.float64)[:, rest], ref[:, rest]) <= 2.0 ** -24 * (1 + 1e-6)
+    call, batch, mask, product = (lrbi.masked_gemm, data["X"], M, orc.masked_gemm) if long_side == "n" else \
+        (lrbi.masked_gemm_t, dY, M.T, orc.masked_gemm_t)
+    clean = call(d, W, dIp, dIz, to_device(batch, "f32")).cpu().numpy()
+    bad = batch.copy()
+    at = int(mask.sum(axis=0).argmax())
+    bad[at, 3] = np.inf
+    got = call(d, W, dIp, dIz, to_device(bad, "f32")).cpu().numpy()
+    rest = [q for q in range(20) if q != 3]
+    assert np.array_equal(got[:, rest].view(np.int32), clean[:, rest].view(np.int32))
+    reached = mask[:, at] != 0
+    assert np.array_equal(~np.isfinite(got[:, 3]), reached) and reached.any() and not reached.all()
+    ref = product(W64, M, batch.astype(np.float64))[~reached, 3]
+    assert orc.rel_err(got[~reached, 3].astype(np.float64), ref) <= 2.0 ** -24 * (1 + 1e-6)
