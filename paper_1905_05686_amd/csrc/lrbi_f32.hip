@@ -25,8 +25,7 @@
 
 namespace lrbi {
 
-static constexpr int kF32Waves = 8;
-static constexpr int kF32Threads = 64 * kF32Waves;
+static constexpr int kF32Waves = 8; // wavefronts of a product's workgroup, but for a reduction of one chunk
 static constexpr int kF32Chunk = 64; // reduction steps of one wavefront between two mask decodes
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
@@ -48,21 +47,19 @@ template <> __device__ __forceinline__ __hip_bfloat16 from_f32<__hip_bfloat16>(f
 
 __device__ __forceinline__ int64_t at_most(int64_t i, int64_t last) { return i < last ? i : last; }
 
-// The batch columns (bits) of a workgroup's block in which a lane has met a value that is not finite: lane l watches columns
-// (l & 31) + 32 b.  One value for the whole workgroup; columns from N on, which repeat the last one, are left out.
-template <int NQ>
-__device__ __forceinline__ unsigned long long bad_columns(const bool (&bad)[NQ], int64_t cols)
+// The batch columns (bits) of a workgroup's block that hold a value that is not finite; bad[b]: the wavefront's lanes that have met
+// one in their columns (lane & 31) + 32 b.  One value for the whole workgroup; columns from N on, which repeat the last one, are left out.
+template <int NQ, int WAVES>
+__device__ __forceinline__ unsigned long long bad_columns(const unsigned long long (&bad)[NQ], int64_t cols)
 {
-    static __shared__ uint32_t met[kF32Waves * NQ];
+    static __shared__ uint32_t met[WAVES * NQ];
 #pragma unroll
-    for (int b = 0; b < NQ; ++b) {
-        const unsigned long long lanes = __ballot(bad[b]);
-        if ((threadIdx.x & 63) == 0) met[(threadIdx.x >> 6) * NQ + b] = (uint32_t)lanes | (uint32_t)(lanes >> 32);
-    }
+    for (int b = 0; b < NQ; ++b)
+        if ((threadIdx.x & 63) == 0) met[(threadIdx.x >> 6) * NQ + b] = (uint32_t)bad[b] | (uint32_t)(bad[b] >> 32);
     __syncthreads();
     unsigned long long all = 0ull;
 #pragma unroll
-    for (int w = 0; w < kF32Waves; ++w)
+    for (int w = 0; w < WAVES; ++w)
 #pragma unroll
         for (int b = 0; b < NQ; ++b) all |= (unsigned long long)met[w * NQ + b] << (32 * b);
     return cols < 64 ? all & ((1ull << cols) - 1ull) : all;
@@ -125,7 +122,7 @@ __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, 
 }
 
 // adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it, without the batch columns in `skip`
-template <typename T, int NQ>
+template <typename T, int NQ, int WAVES>
 __device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t (&acc)[NQ], int64_t row0, int64_t rows,
                                              int64_t q0, int64_t N, unsigned long long skip, T *__restrict__ out, int64_t ldo)
 {
@@ -136,10 +133,10 @@ __device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t 
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[wave][acc_row(v, lane) * 32 + (lane & 31)] = acc[b][v];
         __syncthreads();
-        for (int e = tid; e < 1024; e += kF32Threads) {
+        for (int e = tid; e < 1024; e += 64 * WAVES) {
             double s = (double)red[0][e]; // rounded once
 #pragma unroll
-            for (int w = 1; w < kF32Waves; ++w) s += (double)red[w][e];
+            for (int w = 1; w < WAVES; ++w) s += (double)red[w][e];
             const int64_t i = row0 + (e >> 5), q = q0 + 32 * b + (e & 31);
             if (i < rows && q < N && !((skip >> (32 * b + (e & 31))) & 1ull)) out[i * ldo + q] = from_f32<T>((float)s);
         }
@@ -148,14 +145,14 @@ __device__ __forceinline__ void reduce_store(float (*red)[1024], const f32x16_t 
 
 // dX = (W o I_a)^T dY.  Workgroup = 32 columns of W (rows of dX) x 32 NQ batch columns; a wavefront's chunk is 64
 // rows of W, whose 64 mask words (one per row: the block's columns are one word) its lanes decode together.
-template <typename T, int NQ>
-__global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T *__restrict__ W, int64_t ldw,
+template <typename T, int NQ, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void f32_gemm_t_kernel(Geom g, const T *__restrict__ W, int64_t ldw,
                                                                  const uint32_t *__restrict__ Ip,
                                                                  const uint32_t *__restrict__ Iz,
                                                                  const T *__restrict__ DY, int64_t lddy, int64_t N,
                                                                  T *__restrict__ DX, int64_t lddx, int jblocks)
 {
-    static __shared__ float red[kF32Waves][1024];
+    static __shared__ float red[WAVES][1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
     const unsigned block = (unsigned)wide_block();
     const int jb = (int)(block % (unsigned)jblocks);
@@ -168,8 +165,8 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
 
     constexpr int U = 8; // steps of the instruction whose operands are requested together
     f32x16_t acc[NQ] = {};
-    bool bad[NQ] = {};
-    for (int64_t i0 = (int64_t)kF32Chunk * wave; i0 < g.m; i0 += kF32Chunk * kF32Waves) {
+    unsigned long long bad[NQ] = {}; // lanes; in scalar registers
+    for (int64_t i0 = (int64_t)kF32Chunk * wave; i0 < g.m; i0 += kF32Chunk * WAVES) {
         T w[2][U], y[2][U][NQ];
         const auto load = [&](int s0, T (&wv)[U], T (&yv)[U][NQ]) {
 #pragma unroll
@@ -192,51 +189,55 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_t_kernel(Geom g, const T
 #pragma unroll
                 for (int b = 0; b < NQ; ++b) {
                     const float x = as_f32(y[s & 1][u][b]);
-                    bad[b] |= !(fabsf(x) <= FLT_MAX);
+                    bad[b] |= __ballot(!(fabsf(x) <= FLT_MAX));
                     acc[b] = mfma_32x32x2(a, x, acc[b]);
                 }
             }
         }
     }
-    const unsigned long long again = bad_columns<NQ>(bad, N - q0);
-    reduce_store<T, NQ>(red, acc, j0, g.n, q0, N, again, DX, lddx);
+    const unsigned long long again = bad_columns<NQ, WAVES>(bad, N - q0);
+    reduce_store<T, NQ, WAVES>(red, acc, j0, g.n, q0, N, again, DX, lddx);
     if (!again) return;
     // a wavefront forms four columns of W; the mask words of 64 rows at a time are decoded once for them
     const BadLanes lanes(again);
     unsigned long long mine = 0ull; // the lane's rows of 64
     for (int i = lanes.part; i < 64; i += lanes.parts) mine |= 1ull << i;
-    constexpr int JW = 32 / kF32Waves;
-    double s[JW] = {};
-    for (int64_t i0 = 0; i0 < g.m; i0 += 64) {
-        const uint32_t words = (i0 + lane < g.m) ? row_word(g, Ip, Iz, i0 + lane, jb) : 0u;
-        bool open = false;
+    constexpr int JW = 4;
+#pragma clang loop unroll(disable)
+    for (int turn = 0; turn < 32 / (JW * WAVES); ++turn) {
+        const int jl = JW * (turn * WAVES + wave);
+        double s[JW] = {};
+        for (int64_t i0 = 0; i0 < g.m; i0 += 64) {
+            const uint32_t words = (i0 + lane < g.m) ? row_word(g, Ip, Iz, i0 + lane, jb) : 0u;
+            bool open = false;
 #pragma unroll
-        for (int u = 0; u < JW; ++u) { // (no bit is set in rows from m on and in columns from n on)
-            const unsigned long long rows = __ballot((words >> (wave * JW + u)) & 1u) & mine;
-            add_kept<T>(s[u], rows, i0, W + at_most(j0 + wave * JW + u, g.n - 1), ldw, DY + q0 + lanes.q, lddy);
-            open |= s[u] == s[u];
+            for (int u = 0; u < JW; ++u) { // (no bit is set in rows from m on and in columns from n on)
+                const unsigned long long rows = __ballot((words >> (jl + u)) & 1u) & mine;
+                add_kept<T>(s[u], rows, i0, W + at_most(j0 + jl + u, g.n - 1), ldw, DY + q0 + lanes.q, lddy);
+                open |= s[u] == s[u];
+            }
+            if (!__any(open)) break;
         }
-        if (!__any(open)) break;
-    }
 #pragma unroll
-    for (int u = 0; u < JW; ++u) {
-        const double sum = lanes.total(s[u]);
-        const int64_t j = j0 + wave * JW + u;
-        if (lanes.stores() && j < g.n) DX[j * lddx + q0 + lanes.q] = from_f32<T>((float)sum);
+        for (int u = 0; u < JW; ++u) {
+            const double sum = lanes.total(s[u]);
+            const int64_t j = j0 + jl + u;
+            if (lanes.stores() && j < g.n) DX[j * lddx + q0 + lanes.q] = from_f32<T>((float)sum);
+        }
     }
 }
 
 // Y = (W o I_a) X, fp32.  Workgroup = 32 rows of W x 32 NQ batch columns; a wavefront's chunk is 64 columns of W, two
 // mask words per row.  A lane reads four consecutive weights of its row: the instruction's two reduction indices of
 // step e are columns e and 4 + e of a group of eight, so the lane halves hold adjacent 16-byte pieces.
-template <int NQ, bool VEC>
-__global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const float *__restrict__ W, int64_t ldw,
+template <int NQ, bool VEC, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void f32_gemm_kernel(Geom g, const float *__restrict__ W, int64_t ldw,
                                                                const uint32_t *__restrict__ Ip,
                                                                const uint32_t *__restrict__ Iz,
                                                                const float *__restrict__ X, int64_t ldx, int64_t N,
                                                                float *__restrict__ Y, int64_t ldy, int iblocks)
 {
-    static __shared__ float red[kF32Waves][1024];
+    static __shared__ float red[WAVES][1024];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 31, half = lane >> 5;
     const unsigned block = (unsigned)wide_block();
     const int64_t i0 = 32 * (int64_t)(block % (unsigned)iblocks);
@@ -252,8 +253,8 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
     // the sums of 32 columns go into doubles: one fp32 chain over a wavefront's whole share of the row would round more
     // often than a sum spread over 64 lanes (relative error 1.5e-7 at 300 x 4000, where this gives 6.2e-8)
     double sum[NQ][16] = {};
-    bool bad[NQ] = {};
-    for (int64_t j0 = (int64_t)kF32Chunk * wave; j0 < g.n; j0 += kF32Chunk * kF32Waves) {
+    unsigned long long bad[NQ] = {}; // lanes; in scalar registers
+    for (int64_t j0 = (int64_t)kF32Chunk * wave; j0 < g.n; j0 += kF32Chunk * WAVES) {
         float w[2][4], x[2][4][NQ];
         const auto load = [&](int gq, float (&wv)[4], float (&xv)[4][NQ]) {
             const int64_t j = j0 + 8 * gq + 4 * half;
@@ -287,7 +288,7 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
 #pragma unroll
                 for (int b = 0; b < NQ; ++b) {
                     const float v = x[gq & 1][e][b];
-                    bad[b] |= !(fabsf(v) <= FLT_MAX);
+                    bad[b] |= __ballot(!(fabsf(v) <= FLT_MAX));
                     acc[b] = mfma_32x32x2(a, v, acc[b]);
                 }
             }
@@ -299,18 +300,18 @@ __global__ __launch_bounds__(kF32Threads) void f32_gemm_kernel(Geom g, const flo
             }
         }
     }
-    const unsigned long long again = bad_columns<NQ>(bad, N - q0);
+    const unsigned long long again = bad_columns<NQ, WAVES>(bad, N - q0);
     f32x16_t acc[NQ];
 #pragma unroll
     for (int b = 0; b < NQ; ++b)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[b][v] = (float)sum[b][v];
-    reduce_store<float, NQ>(red, acc, i0, g.m, q0, N, again, Y, ldy);
+    reduce_store<float, NQ, WAVES>(red, acc, i0, g.m, q0, N, again, Y, ldy);
     if (!again) return;
     // a wavefront forms four rows; 64 mask words of a row are decoded at a time, and a lane takes every parts-th
     const BadLanes lanes(again);
     const int words_per_row = (int)((g.n + 31) / 32);
-    for (int64_t i = i0 + wave; i < i0 + 32 && i < g.m; i += kF32Waves) {
+    for (int64_t i = i0 + wave; i < i0 + 32 && i < g.m; i += WAVES) {
         double s = 0.0;
         for (int w0 = 0; w0 < words_per_row && __any(s == s); w0 += 64) {
             const uint32_t words = row_word(g, Ip, Iz, i, w0 + lane); // none past the row
@@ -406,12 +407,18 @@ static int launch_t(const Geom &g, const void *dW, int64_t ldw, const uint32_t *
     const int nq = batch_blocks(jblocks, N);
     const int64_t blocks = jblocks * ((N + 32 * nq - 1) / (32 * nq));
     if (blocks > 0x7FFFFFFF || (N + 3) / 4 > 65535) return LRBI_ERR_SHAPE;
-    if (nq == 2)
-        LRBI_LAUNCH((f32_gemm_t_kernel<T, 2>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
-                    dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
-    else
-        LRBI_LAUNCH((f32_gemm_t_kernel<T, 1>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, (const T *)dW, ldw, dIp,
-                    dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks);
+#define LRBI_LAUNCH_F32(NQ, WAVES)                                                                                       \
+    LRBI_LAUNCH((f32_gemm_t_kernel<T, NQ, WAVES>), wide_grid(blocks, 64 * WAVES), dim3(64 * WAVES), 0, stream, g, (const T *)dW, \
+                ldw, dIp, dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks)
+    // one chunk of rows: the other wavefronts would only have their zeros added (16 x 65536, N = 1: 24.6 us against 10.0)
+    if (g.m <= kF32Chunk) {
+        if (nq == 2) LRBI_LAUNCH_F32(2, 1);
+        else LRBI_LAUNCH_F32(1, 1);
+    } else {
+        if (nq == 2) LRBI_LAUNCH_F32(2, kF32Waves);
+        else LRBI_LAUNCH_F32(1, kF32Waves);
+    }
+#undef LRBI_LAUNCH_F32
     return LRBI_OK;
 }
 
@@ -435,8 +442,8 @@ int launch_f32_gemm(const Geom &g, const float *dW, int64_t ldw, const uint32_t 
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     const bool vec = ((uintptr_t)dW & 15) == 0 && ldw % 4 == 0 && g.n % 4 == 0;
 #define LRBI_LAUNCH_F32(NQ, V)                                                                                       \
-    LRBI_LAUNCH((f32_gemm_kernel<NQ, V>), wide_grid(blocks, kF32Threads), dim3(kF32Threads), 0, stream, g, dW, ldw, dIp, dIz, dX, ldx, \
-                N, dY, ldy, (int)iblocks)
+    LRBI_LAUNCH((f32_gemm_kernel<NQ, V, kF32Waves>), wide_grid(blocks, 64 * kF32Waves), dim3(64 * kF32Waves), 0, stream, g, dW, ldw, \
+                dIp, dIz, dX, ldx, N, dY, ldy, (int)iblocks)
     if (nq == 2) {
         if (vec) LRBI_LAUNCH_F32(2, true);
         else LRBI_LAUNCH_F32(2, false);

@@ -141,6 +141,8 @@ def test_nonfinite_values_under_pruned_weights_never_reach_dx(N):
     (_small(65, 33, 20, 33, 3, 0.4, 33, "f32"), 0),             # one row, one column past the blocks; scalar loads
     (_small(520, 96, 104, 48, 33, 0.05, 64, "f32"), 4),         # a ninth chunk of rows, two I_p words, padded leading dimensions
     (_small(1030, 4100, 206, 82, 4, 0.2, 132, "f32"), 0),       # two blocks per workgroup, the last one short
+    (_small(64, 9000, 32, 250, 4, 0.3, 40, "f32"), 0),          # one chunk of rows; two blocks per workgroup
+    (_small(64, 301, 64, 301, 4, 0.3, 20, "bf16"), 0),          # one chunk of rows, 16-bit
     (_small(130, 77, 65, 11, 4, 0.3, 40, "f16"), 0),            # 16-bit rows that are not whole pieces
     (_small(70, 8300, 35, 83, 4, 0.3, 70, "bf16"), 0),          # the same, two batch blocks per workgroup
 ])
@@ -148,17 +150,18 @@ def test_fp32_matrix_cores(cfg, ldpad):
     _check(cfg, ldpad=ldpad, what="fp32 instructions")
 
 
+@pytest.mark.parametrize("m", [200, 64])                # 64: a chunk of rows, one wavefront in the transposed product
 @pytest.mark.parametrize("N", [4, 5, 33, 50, 64, 97])  # one, 18 and 32 columns in the last block among them
-def test_fp32_products_with_nonfinite_operands(N):
+def test_fp32_products_with_nonfinite_operands(N, m):
     """An infinity or a NaN in the batch reaches the results of kept weights only, in both products."""
-    cfg = _small(200, 168, 50, 56, 4, 0.3, N, "f32")
+    cfg = _small(m, 168, 50, 56, 4, 0.3, N, "f32")
     print("nonfinite batch", N, flush=True)
     data, dY = _inputs(cfg)
     d = desc_of(cfg)
     dIp, dIz = device_factors(d, data["Ip01"], data["Iz01"])
     M = orc.decode_mask(data["Ip01"], data["Iz01"], cfg.m, cfg.n, cfg.r, cfg.c, cfg.k)
     X = data["X"].copy()
-    X[3, 0], X[100, N - 1], dY[7, 0], dY[199, N - 1] = np.inf, np.nan, -np.inf, np.nan
+    X[3, 0], X[100, N - 1], dY[7, 0], dY[m - 1, N - 1] = np.inf, np.nan, -np.inf, np.nan
     W = to_device(data["W"], "f32")
     Y = lrbi.masked_gemm(d, W, dIp, dIz, to_device(X, "f32"))
     dX = lrbi.masked_gemm_t(d, W, dIp, dIz, to_device(dY, "f32"))
@@ -176,29 +179,29 @@ def test_fp32_products_with_nonfinite_operands(N):
 
 @pytest.mark.parametrize("transposed", [False, True])
 def test_fp32_products_of_more_lanes_than_a_dimension_counts(transposed):
-    """2^23 + 2 blocks of 32 rows (columns) are more than 2^32 lanes.  One weight per row (column): single products."""
-    size, N = 2 ** 28 + 64, 5
+    """131073 blocks of rows (columns) x 65 of batch columns, 512 lanes each, are more than 2^32 lanes.  Rows from all over
+    the result against float64."""
+    size, red, N = 2 ** 22 + 1, 449, 4097
     print("fp32 product, many blocks, transposed", transposed, flush=True)
     gen = torch.Generator(device=dev())
     gen.manual_seed(9)
-    W = torch.randn(size, device=dev(), generator=gen)
-    X = torch.randn((1, N), device=dev(), generator=gen)
-    if transposed:
-        d = lrbi.Desc(1, size, 1, size, 1)
-        dIp = torch.ones((1, 1), dtype=torch.int32, device=dev())
-        dIz = torch.randint(-2 ** 31, 2 ** 31, (1, size // 32), dtype=torch.int32, device=dev(), generator=gen)
-        kept = lambda a, b: ((dIz[0, a // 32:b // 32, None] >> torch.arange(32, device=dev(), dtype=torch.int32)) & 1).reshape(-1)
-        got = lrbi.masked_gemm_t(d, W.reshape(1, size), dIp, dIz, X)
-    else:
-        d = lrbi.Desc(size, 1, size, 1, 1)
-        dIp = torch.randint(0, 2, (size, 1), dtype=torch.int32, device=dev(), generator=gen)
-        dIz = torch.tensor([[1, 0]], dtype=torch.int32, device=dev())
-        kept = lambda a, b: dIp[a:b, 0]
-        got = lrbi.masked_gemm(d, W.reshape(size, 1), dIp, dIz, X)
+    dtype = torch.float16 if transposed else torch.float32
+    X = torch.randn((red, N), device=dev(), generator=gen).to(dtype)
+    W = torch.empty((red, size) if transposed else (size, red), dtype=dtype, device=dev()).normal_(0.0, 0.05, generator=gen)
+    bits = lambda n: torch.randint(0, 2, (n,), dtype=torch.int32, device=dev(), generator=gen)
+    pack = lambda b: (torch.nn.functional.pad(b, (0, -b.numel() % 64)).reshape(-1, 32) << torch.arange(32, device=dev(), dtype=torch.int32)).sum(
+        1, dtype=torch.int32)
+    m, n = W.shape
+    ip, iz = bits(m), bits(n)  # rank 1, one tile
+    got = (lrbi.masked_gemm_t if transposed else lrbi.masked_gemm)(lrbi.Desc(m, n, m, n, 1), W, ip[:, None].contiguous(), pack(iz)[None], X)
     torch.cuda.synchronize()
-    for a in range(0, size, 2 ** 24):
-        b = min(a + 2 ** 24, size)
-        assert torch.equal(got[a:b], torch.where(kept(a, b)[:, None] != 0, W[a:b, None] * X, 0.0)), a
+    rows = torch.cat([torch.randint(0, size, (500,), device=dev(), generator=gen), torch.arange(size - 40, size, device=dev())])
+    Wr = (W.T[rows] if transposed else W[rows]).double()
+    mask = (iz[rows, None] & ip[None]) if transposed else (ip[rows, None] & iz[None])
+    ref = (Wr * mask) @ X.double()
+    tol = 2.0 ** -10 if transposed else 1e-6  # the rounding of f16; fp32 sums of 449 terms in chunks
+    assert float((got[rows].double() - ref).norm() / ref.norm()) <= tol
+    assert torch.equal((got[rows] == 0).all(1), (mask == 0).all(1))
 
 
 @pytest.mark.parametrize("long_side", ["m", "n"])
