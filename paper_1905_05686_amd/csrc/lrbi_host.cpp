@@ -266,9 +266,12 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
         }
     }
     // fp32 batches: the fp32 matrix instructions, whose time hardly depends on N below 64 columns.  Up to four columns
-    // one sweep over W on the vector ALUs is ahead (4096 x 4096: 46 against 50 us at four columns, 90 against 50 at
-    // eight; 300 x 4000: 27 against 43, 54 against 43; 500 x 800: 12 against 14, 19 against 14).
-    if (dtype == LRBI_F32 && N > 4 && (desc->flags & LRBI_FLAG_PATH_MASK) != LRBI_FLAG_PATH_VALU)
+    // one sweep over W on the vector ALUs is level or ahead (4096 x 4096: 45 us against 44, eight columns 89; 300 x 4000: 28
+    // against 40, eight columns 55), and two sweeps are where one or two workgroups of the matrix form would walk long rows
+    // alone (64 x 65536 in 64 x 256 tiles, rank 8: 471 against 598 us at five columns, 519 against 599 at six, 567 against 600
+    // at seven, 597 against 598 at eight).
+    const bool sweep = N <= 4 || (N <= 6 && g.m <= 64 && g.n >= 16384);
+    if (dtype == LRBI_F32 && !sweep && (desc->flags & LRBI_FLAG_PATH_MASK) != LRBI_FLAG_PATH_VALU)
         return launch_f32_gemm(g, (const float *)dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
                                (const float *)dX, ldx, N, (float *)dY, ldy, s);
     if (!mfma)

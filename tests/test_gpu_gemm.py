@@ -397,3 +397,15 @@ def test_general_tile_kernel_masks(m, n, r, c, k, p, N):
     bits = unpack_device_mask(mask, n)
     assert np.array_equal(bits[:, :n], M) and not bits[:, n:].any()
     assert orc.rel_err(to_float64(Y), ref) <= TOL["f16"]
+
+
+@pytest.mark.parametrize("m,n,r,c,k,N", [
+    (64, 576, 64, 64, 8, 5),        # 16 wavefronts, seven of them without a second chunk
+    (65, 1100, 33, 100, 5, 40),     # scalar loads; a last chunk of 12 columns
+    (64, 16384, 64, 256, 8, 6),     # long rows, few of them: vector ALUs up to six columns
+    (64, 16384, 64, 256, 8, 7),
+    (4100, 520, 100, 104, 4, 8),    # 129 workgroups: eight wavefronts again
+])
+def test_fp32_batches_of_few_rows(m, n, r, c, k, N):
+    """fp32 products around the lines between the forms of the kernel, against the fp64 oracle."""
+    test_fp32_batches(m, n, r, c, k, N, 0)
