@@ -88,8 +88,9 @@ __global__ __launch_bounds__(kGemvThreads) void valu_gemm_kernel(Geom g, const T
                     *reinterpret_cast<uint4 *>(xv) = *reinterpret_cast<const uint4 *>(X + j);
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) {
-                        const float w = ((bits >> e) & 1u) ? Elem<T>::to_f32(wv[e]) : 0.f;
-                        acc[0] = fmaf(w, Elem<T>::to_f32(xv[e]), acc[0]);
+                        // the sum is selected: neither value of a pruned weight's product reaches it
+                        const float sum = fmaf(Elem<T>::to_f32(wv[e]), Elem<T>::to_f32(xv[e]), acc[0]);
+                        acc[0] = ((bits >> e) & 1u) ? sum : acc[0];
                     }
                 } else {
 #pragma unroll

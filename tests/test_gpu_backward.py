@@ -151,7 +151,7 @@ def test_fp32_matrix_cores(cfg, ldpad):
 
 
 @pytest.mark.parametrize("m", [200, 64])                # 64: a chunk of rows, one wavefront in the transposed product
-@pytest.mark.parametrize("N", [4, 5, 33, 50, 64, 97])  # one, 18 and 32 columns in the last block among them
+@pytest.mark.parametrize("N", [1, 4, 5, 33, 50, 64, 97])  # one sweep below 5; one, 18 and 32 columns in a last block
 def test_fp32_products_with_nonfinite_operands(N, m):
     """An infinity or a NaN in the batch reaches the results of kept weights only, in both products."""
     cfg = _small(m, 168, 50, 56, 4, 0.3, N, "f32")
