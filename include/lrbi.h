@@ -173,7 +173,10 @@ int lrbi_decode_mask(const lrbi_desc *desc, const void *dIp_packed, const void *
 
 /*
  * Workspace the masked product may use for (desc, dtype, N): partial sums when
- * the reduction over n is split across workgroups.  Host only.  *bytes may be 0.
+ * the reduction over n is split across workgroups.  Host only.  *bytes may be 0.  Up to
+ * 64 planes of m x N fp32 values when the output has few blocks; about 100 MB at most (two to six planes) when
+ * it has 192 to 511 of them on the general kernel, which gain least from it (4100 x 9224, N = 1024: 336 us
+ * without, 251 with).
  */
 int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtype dtype, int64_t N,
                                      uint64_t *bytes);
@@ -252,10 +255,11 @@ int lrbi_masked_conv3x3(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW,
  * lrbi_masked_gemm_workspace_bytes bytes, but the partial sums of a split reduction go to a scratch array
  * of LRBI_STATIC_SCRATCH_BYTES bytes that is part of the library image on every GPU it runs on (held until
  * the process ends).  The call allocates and frees nothing, on the host side or the device side of HIP.
- *   Limit: shapes whose workspace query exceeds LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
- *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB), except
- *   those of 192 output tiles and more, which then run unsplit, as lrbi_masked_gemm does without a workspace (the bits
- *   are those of that call).
+ *   Not split: shapes whose output alone fills the chip (192 blocks of 128 x 128, or of 128 x 64 or 128 x 32 where rows are
+ *   few, on the general kernel).  A workspace lets lrbi_masked_gemm even their last round out; here they run
+ *   unsplit, with the bits of lrbi_masked_gemm without a workspace, and leave the array alone.
+ *   Limit: other shapes whose workspace query exceeds LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
+ *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB).
  *   The device of `stream` must be the current device (the scratch array is looked up per current device).
  *   All calls on one GPU share that GPU's array: two calls that may overlap in time (different streams, or
  *   graph branches without an edge between them) race on it; calls ordered by one stream do not.

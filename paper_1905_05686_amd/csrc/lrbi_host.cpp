@@ -431,11 +431,9 @@ extern "C" int lrbi_masked_gemm_static(const lrbi_desc *desc, lrbi_dtype dtype, 
     uint64_t need = 0;
     const int rc = lrbi_masked_gemm_workspace_bytes(desc, dtype, N, &need);
     if (rc != LRBI_OK) return rc;
-    if (need > (uint64_t)LRBI_STATIC_SCRATCH_BYTES) {
-        // enough tiles to fill the chip unsplit: that form needs no scratch
-        if (!plan_mfma(make_geom(desc), desc->flags, N).split_optional) return LRBI_ERR_WORKSPACE;
-        need = 0;
-    }
+    // tiles enough to fill the chip unsplit: that form leaves the shared array alone, so such calls may overlap in time
+    if (need && plan_mfma(make_geom(desc), desc->flags, N).split_optional) need = 0;
+    if (need > (uint64_t)LRBI_STATIC_SCRATCH_BYTES) return LRBI_ERR_WORKSPACE;
     void *ws = nullptr;
     if (need) {
         ws = scratch_of_current_device();

@@ -82,3 +82,18 @@ def test_many_tiles_beyond_the_scratch_run_unsplit():
     split = lrbi.masked_gemm(d, W, dIp, dIz, X, workspace=workspace_for(d, lrbi.F16, cfg.N))
     torch.cuda.synchronize()
     assert orc.rel_err(split.double().cpu().numpy(), ref.double().cpu().numpy()) <= 1e-3  # f16 roundings of fp32 sums
+
+
+def test_many_tiles_leave_the_scratch_alone():
+    """264 output tiles whose slices would fit the scratch array: unsplit all the same, so that two such calls share nothing."""
+    cfg = workloads.Config("t", 4100, 2056, 256, 256, 16, 0.08, 1000, "f16", 0.03, 3)
+    print("static scratch, many tiles that fit", cfg, flush=True)
+    _, d, dIp, dIz, W, X = _case(cfg)
+    assert 0 < lrbi.masked_gemm_workspace_bytes(d, lrbi.F16, cfg.N) <= 32 * 1024 * 1024
+    ref = lrbi.masked_gemm(d, W, dIp, dIz, X)
+    split = lrbi.masked_gemm(d, W, dIp, dIz, X, workspace=workspace_for(d, lrbi.F16, cfg.N))
+    out = torch.full_like(ref, float("nan"))
+    lrbi.masked_gemm_static(d, W, dIp, dIz, X, out)
+    torch.cuda.synchronize()
+    assert not torch.equal(split, ref)  # the slices add up in another order
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
