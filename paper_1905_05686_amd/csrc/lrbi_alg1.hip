@@ -162,6 +162,31 @@ __device__ __forceinline__ void tile_iz_bits(const Geom &g, const float *__restr
     // row l and position sq in it of a wavefront's step, carried along: a division per step cost more than the compares
     const int dl = kEvalWaves / steps_per_row, dsq = kEvalWaves - dl * steps_per_row;
     int l = wave / steps_per_row, sq = wave - l * steps_per_row;
+    const auto pack = [&](int at, bool in, float v) {
+        const unsigned long long b = __ballot(in && v >= tz);
+        if (lane < 2) {
+            const uint32_t bits = (uint32_t)(lane ? (b >> 32) : b);
+            iz[at + lane] = bits;
+            if (out) out[at + lane] = bits;
+        }
+    };
+    const auto next = [&] {
+        l += dl;
+        sq += dsq;
+        if (sq >= steps_per_row) {
+            sq -= steps_per_row;
+            ++l;
+        }
+    };
+    if (wave + (ZB / 2 - 1) * kEvalWaves >= zsteps) { // a small tile: fewer than half a round, no loads for steps that are none
+#pragma clang loop unroll(disable)
+        for (int st = wave; st < zsteps; st += kEvalWaves) {
+            const int j = 64 * sq + lane;
+            pack(l * g.izw + 2 * sq, j < ct, mz[(int64_t)l * g.c + (j < ct ? j : ct - 1)]);
+            next();
+        }
+        return;
+    }
     for (int st0 = wave; st0 < zsteps; st0 += ZB * kEvalWaves) {
         float v[ZB];
         bool ok[ZB];
@@ -172,24 +197,11 @@ __device__ __forceinline__ void tile_iz_bits(const Geom &g, const float *__restr
             ok[q] = (l < g.k) && (j < ct); // columns a cut-off tile leaves outside the matrix stay 0
             v[q] = mz[(int64_t)(l < g.k ? l : g.k - 1) * g.c + (j < ct ? j : ct - 1)]; // clamped: no test before a load
             word[q] = (l < g.k) ? l * g.izw + 2 * sq : -1;
-            l += dl;
-            sq += dsq;
-            if (sq >= steps_per_row) {
-                sq -= steps_per_row;
-                ++l;
-            }
+            next();
         }
 #pragma unroll
-        for (int q = 0; q < ZB; ++q) {
-            if (word[q] >= 0) { // uniform over the wavefront
-                const unsigned long long b = __ballot(ok[q] && v[q] >= tz);
-                if (lane < 2) {
-                    const uint32_t bits = (uint32_t)(lane ? (b >> 32) : b);
-                    iz[word[q] + lane] = bits;
-                    if (out) out[word[q] + lane] = bits;
-                }
-            }
-        }
+        for (int q = 0; q < ZB; ++q)
+            if (word[q] >= 0) pack(word[q], ok[q], v[q]); // uniform over the wavefront
     }
 }
 
