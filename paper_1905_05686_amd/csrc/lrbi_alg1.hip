@@ -669,7 +669,9 @@ __global__ __launch_bounds__(kSortThreads) void tile_sort_kernel(Geom g, int whi
                         v[e] = swap ? b : a;
                         v[e | d] = swap ? a : b;
                     }
-        for (int size = 2 * E; size <= CHUNK; size <<= 1) sort_merge<E>(v, lds, size / 2, (first & size) == 0);
+        // with one slot per lane the values are the first n slots already: merges up to the power of two that holds them
+        const int top = (E == 1 && n <= CHUNK / 2) ? (n > 1 ? 2 << (31 - __builtin_clz(n - 1)) : 1) : CHUNK;
+        for (int size = 2 * E; size <= top; size <<= 1) sort_merge<E>(v, lds, size / 2, (first & size) == 0);
     } else {
 #pragma unroll
         for (int e = 0; e < E; ++e) v[e] = dst[base + tid * E + e];

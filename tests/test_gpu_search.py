@@ -180,3 +180,17 @@ def test_more_tiles_than_a_launch_can_count_are_refused():
     with pytest.raises(lrbi.LrbiError, match="refused the kernel launch"):
         lrbi.search_thresholds(d, W, 0.1, Mp, Mz, 0.9, [0.5], 1, 1)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("m,n,r,c,k", [
+    (6, 5, 1, 1, 1),            # factors of one entry
+    (24, 30, 8, 10, 3),         # 24 and 30: inside a wavefront
+    (128, 96, 64, 32, 1),       # 64 and 32
+    (130, 130, 65, 65, 1),      # one more: merges between wavefronts begin
+    (64, 128, 32, 64, 8),       # 256 and 512: half of the slots, all of them
+    (99, 250, 33, 88, 8),       # 264 and 704, cut-off tiles
+])
+def test_search_small_tiles(m, n, r, c, k):
+    """Factors of fewer entries than the smallest sort has slots, and tiles of fewer I_z steps than wavefronts."""
+    print("search, small tiles", m, n, r, c, k, flush=True)
+    _check(_cfg(m, n, r, c, k, "f16", 71, p=0.3), 0.8, [0.2, 0.5, 0.7], 5, max(1, r * c // 50))
