@@ -113,15 +113,15 @@ def test_factorisation_then_search_end_to_end():
         assert bits[ti * cfg.r:(ti + 1) * cfg.r, tj * cfg.c:(tj + 1) * cfg.c].sum() == int(kept[t])
 
 
-# Edges of the matrix-core kernels: 16 / 32 / 64 / 128 ranks share a pass, 64 columns (rows) belong to a workgroup, and a
-# lane loads 8, 4 or 1 elements by the divisibility of c and n.
+# Edges of the matrix-core kernels: 16 / 32 / 64 ranks share a pass, 64 columns (rows) belong to a workgroup, and a lane
+# loads 8, 4 or 1 elements by the divisibility of c and n.
 EDGES = [
     (_cfg(64, 64, 64, 64, 16, "f16", 20), 3, 1),          # one block exactly, the largest rank of the 16-wide form
     (_cfg(65, 136, 65, 136, 17, "f16", 21), 3, 1),        # one row and one piece past a block
     (_cfg(96, 200, 48, 72, 33, "bf16", 22), 3, 1),        # ragged columns in whole pieces of 8
     (_cfg(130, 260, 130, 100, 64, "f32", 23), 2, 1),      # pieces of 4
-    (_cfg(200, 250, 150, 200, 65, "f16", 24), 2, 1),      # single elements, first rank of the widest form
-    (_cfg(256, 320, 256, 160, 129, "bf16", 25), 2, 1),    # a second pass of one rank
+    (_cfg(200, 250, 150, 200, 65, "f16", 24), 2, 1),      # single elements, a second pass of one rank
+    (_cfg(256, 320, 256, 160, 129, "bf16", 25), 2, 1),    # a third pass of one rank
     (_cfg(3, 5, 3, 5, 1, "f32", 26), 3, 3),               # wavefronts without a step
 ]
 

@@ -160,7 +160,8 @@ def test_full_size_layer_on_sampled_tiles():
 @pytest.mark.parametrize("m,n,r,c,k,dtype,sweep", [
     (200, 168, 64, 56, 33, "f32", [i / 12 for i in range(11)]),   # more S_p values than one batch; cut-off tiles; two words per I_p row
     (128, 1100, 128, 1100, 5, "bf16", [0.5, 0.8]),                # 35 words per row, the last one partial; row bands
-    (8, 17000, 8, 17000, 2, "f16", [0.4, 0.6, 0.7]),            # more words per row than a workgroup has lanes
+    (8, 17000, 8, 17000, 2, "f16", [0.4, 0.6, 0.7]),            # 133 pieces of four words per row
+    (7, 32832, 7, 32832, 1, "f16", [0.2, 0.5]),                 # 513 pieces of two words: more than a workgroup has lanes
     (1024, 2400, 1024, 2400, 4, "bf16", [0.5, 0.7]),              # one large tile: a launch per probe, split over bands
 ])
 def test_search_routes(m, n, r, c, k, dtype, sweep):
