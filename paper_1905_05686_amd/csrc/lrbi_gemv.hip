@@ -88,9 +88,10 @@ __global__ __launch_bounds__(kGemvThreads) void valu_gemm_kernel(Geom g, const T
                     *reinterpret_cast<uint4 *>(xv) = *reinterpret_cast<const uint4 *>(X + j);
 #pragma unroll
                     for (int e = 0; e < VEC; ++e) {
-                        // the sum is selected: neither value of a pruned weight's product reaches it
-                        const float sum = fmaf(Elem<T>::to_f32(wv[e]), Elem<T>::to_f32(xv[e]), acc[0]);
-                        acc[0] = ((bits >> e) & 1u) ? sum : acc[0];
+                        // both operands are selected: 0 * inf would be a NaN (selecting the sum lengthens its chain: 16 x 65536 fp32
+                        // 78.3 us against 75.5)
+                        const bool on = (bits >> e) & 1u;
+                        acc[0] = fmaf(on ? Elem<T>::to_f32(wv[e]) : 0.f, on ? Elem<T>::to_f32(xv[e]) : 0.f, acc[0]);
                     }
                 } else {
 #pragma unroll
