@@ -871,18 +871,22 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
         int64_t want = 1;
         if (general && tiles < 512) {
             // The general kernel waits for a round of loads per slab (about 2 us whatever else runs), so workgroups in
-            // flight pay off.  Two fit a compute unit: as many slices as 512 hold, since a few workgroups more
-            // cost a second round (4100 x 9224 in 256 x 256 tiles, N = 128: 15 slices 43 us, 19 slices 56, 25 slices 53;
-            // 3000 x 4000 in 300 x 300, N = 200: 8 slices 40, 16 slices 43).  From 129 tiles on that leaves many
-            // idle, and where the rows are long about two rounds of shorter slices even out (4100 x 9224, N = 1024, 264
-            // tiles: unsplit 336 us, 2 slices 315, 4 slices 257, 8 slices 251, 16 slices 289); short rows are
-            // not worth the partial planes (64 x 576, N = 16384: 19.4 us against 18.7 + 4.2 us).
-            if (tiles < 192) want = 512 / tiles;
+            // flight pay off: as many slices as the chip holds at once, since a few workgroups more cost a second round.
+            // Two workgroups fit a compute unit (4100 x 9224 in 256 x 256 tiles, N = 128: 15 slices 43 us, 19 slices 56, 25
+            // slices 53; 3000 x 4000 in 300 x 300, N = 200: 8 slices 40, 16 slices 43), three of the 32-column form, which
+            // takes half the LDS (16000 x 16000 in 500 x 500, N = 6, 125 tiles: 4 slices 274 us, 6 slices 214, 9 slices 261;
+            // 12000 rows 5: 222, 8: 164; 17000 rows 5: 249, 8: 296; two rounds again where one holds fewer than three: 60000
+            // x 4000, 469 tiles: unsplit 240, 3 slices 192).  From 129 tiles on two per unit leave many idle, and
+            // where the rows are long about two rounds of shorter slices even out (4100 x 9224, N = 1024, 264 tiles: unsplit 336
+            // us, 2 slices 315, 4 slices 257, 8 slices 251, 16 slices 289); short rows are not worth the partial planes
+            // (64 x 576, N = 16384: 19.4 us against 18.7 + 4.2 us).
+            const int64_t slots = p.bn == 32 ? 768 : 512;
+            if (tiles < 192) want = slots / tiles;
             p.split_optional = tiles >= 192;
             if (tiles > 128) {
-                int64_t rounds2 = (1024 + tiles - 1) / tiles;
-                if (rounds2 > npairs / 8) rounds2 = npairs / 8;
-                if (rounds2 > want) want = rounds2;
+                int64_t even = p.bn != 32 ? (1024 + tiles - 1) / tiles : (slots / tiles >= 3 ? slots / tiles : 2 * slots / tiles);
+                if (even > npairs / 8) even = npairs / 8;
+                if (even > want) want = even;
             }
         } else if (!general && tiles < 192) {
             // The 512-lane panel kernels run one workgroup per compute unit (measured best: one slice per

@@ -338,3 +338,15 @@ def test_nmf_rejects_bad_arguments_before_any_launch():
     assert f(*args(wsb=8)) == -8
     # a second copy of both factors and a k x k matrix per tile
     assert lrbi.nmf_workspace_bytes(lrbi.Desc(4096, 9216, 256, 256, 16)) == 2 * 576 * 256 * 16 * 4 + 576 * 16 * 16 * 4
+
+
+@pytest.mark.parametrize("m,n,planes", [
+    (16000, 16000, 6),    # 125 output tiles, three per compute unit: 750 workgroups
+    (17000, 16000, 5),
+    (60000, 4000, 3),     # 469 tiles: two rounds
+    (30000, 640, 0),      # 235 tiles of short rows: not split
+])
+def test_slices_of_narrow_batches_fill_the_chip(m, n, planes):
+    """At most 32 batch columns on the general tile kernel: the workspace query tells how many slices the plan has."""
+    d = lrbi.Desc(m, n, 500, 500, 20)
+    assert lrbi.masked_gemm_workspace_bytes(d, lrbi.F16, 6) == planes * m * 8 * 4

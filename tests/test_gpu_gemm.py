@@ -381,6 +381,7 @@ def test_fp32_batches(m, n, r, c, k, N, ldpad):
     (129, 200, 43, 128, 33, 0.2, 33),     # an odd number of slabs, N not in whole pieces
     (600, 4104, 150, 64, 16, 0.1, 128),   # slices; every slab in another tile
     (300, 960, 100, 320, 70, 0.05, 136),  # three I_p words: the words of a slab loaded at once
+    (1100, 2056, 100, 100, 4, 0.3, 6),    # 32-column form: nine tiles, six slices
 ])
 def test_general_tile_kernel_masks(m, n, r, c, k, p, N):
     """The general tile kernel's mask words, loaded ahead of their slab: mask bits exact, product against the oracle."""
