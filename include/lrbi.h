@@ -100,7 +100,7 @@ typedef enum lrbi_status {
     LRBI_ERR_DTYPE = -4,     /* unknown dtype, or dtype not served by forced path */
     LRBI_ERR_PITCH = -5,     /* pitch / leading dimension too small or misaligned */
     LRBI_ERR_ALIGN = -6,     /* a pointer is not aligned as stated               */
-    LRBI_ERR_LAUNCH = -7,    /* the HIP runtime refused a launch                 */
+    LRBI_ERR_LAUNCH = -7,    /* the HIP runtime refused a launch, or would run a part of it */
     LRBI_ERR_WORKSPACE = -8, /* forced split needs a larger workspace            */
     LRBI_ERR_FLAGS = -9      /* unknown bits in desc.flags                       */
 } lrbi_status;
@@ -335,9 +335,10 @@ int lrbi_threshold_eval_workspace_bytes(const lrbi_desc *desc, uint64_t *bytes);
  * on-chip memory, a larger one in the workspace, more slowly); LRBI_ERR_SHAPE otherwise, and
  * for n_sp < 1, steps < 1, tolerance < 0, S outside (0, 1) or an S_p outside [0, 1].
  * Costs of candidates that differ by less than the rounding of a double-precision sum may
- * rank either way.  Launches on `stream`: one or two for the sorts (more for a factor beyond 16384 entries), three
- * or four per eight S_p values (all of a tile's probes run inside one), and one for the packed factors; with few, very large tiles 1 + 2 steps per S_p value instead.  The host does not
- * wait for the device.
+ * rank either way.  Launches on `stream`: one or two for the sorts (more for a factor beyond 16384
+ * entries), three or four per eight S_p values (all of a tile's probes run inside one), and one for the
+ * packed factors; with few, very large tiles 1 + 2 steps per S_p value instead.  The host does not
+ * wait for the device.  A layer of 2^23 tiles and more is LRBI_ERR_LAUNCH (a launch counts 2^32 lanes).
  */
 int lrbi_search_thresholds(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,
                            float w_threshold, int32_t method, float amplify, const float *dMp,
@@ -361,7 +362,8 @@ int lrbi_search_workspace_bytes(const lrbi_desc *desc, uint64_t *bytes);
  *   lddx >= N; overwritten.  All of `dtype`; fp32 accumulation in a fixed order (identical bits
  *   from call to call), rounded to nearest-even on store.  Pointers aligned to the element size;
  *   f16 / bf16 with 16-byte aligned W, ldw % 8 == 0 and n % 8 == 0 run on the 16-bit matrix
- *   instructions at any N, everything else on the fp32 ones (products exact, sums in fp32).
+ *   instructions at any N, everything else on the fp32 ones (products exact, sums in fp32; N up to
+ *   262140, LRBI_ERR_SHAPE beyond).
  *   dWorkspace / workspace_bytes: optional scratch (16-byte aligned) of at least
  *   lrbi_masked_gemm_t_workspace_bytes bytes: partial sums when the reduction over m is split
  *   across workgroups; with NULL or too few bytes it is not split (slower for small n * N).

@@ -568,10 +568,10 @@ int launch_threshold_eval(const Geom &g, lrbi_dtype dt, const void *dW, int64_t 
 // which = 1: M_z, the first ct entries of each of the k rows (rt x ct = the tile's part inside the matrix).  A bitonic
 // network over chunks of 512 E slots, the unused ones +inf, lane t holding slots t E .. t E + E - 1 in registers:
 // distances below E stay inside a lane, those below 64 E inside a wavefront, and only the few larger ones go through
-// LDS (4096 slots: 6 stages of 78; 576 tiles: two sorts
-// 2 x 87 us through LDS, 2 x 66 in registers, 104 in one launch; bound by the exchanges between lanes).  A factor beyond kSortChunk entries is sorted in chunks of that size by several
-// workgroups; the distances between chunks are passes over the workspace (a search on one 1200 x 600 tile, rank 145:
-// 12.5 -> 1.2 ms).
+// LDS (4096 slots: 6 stages of 78; 576 tiles: two sorts 2 x 87 us through LDS, 2 x 66 in registers, 105 in one launch;
+// bound by the exchanges between lanes).  A factor beyond kSortChunk entries is sorted in chunks of that size by several
+// workgroups; the distances between chunks are passes over the workspace (a search on one 1200 x 600 tile, rank 145, one
+// S_p, ten probes: 12.5 -> 1.1 ms).
 static constexpr int kSortThreads = 512;
 static constexpr int kSortChunk = 32 * kSortThreads; // 16384 floats: 64 KiB of LDS
 
@@ -617,8 +617,9 @@ struct SortOperand {
     int64_t stride; // floats between two tiles' results
 };
 
-// blockIdx.x = tile, blockIdx.y = chunk, blockIdx.z: op0 (factor which0) or op1 (the next).  merge_size == 0: sorts the chunk, up or down as the merges that follow ask;
-// otherwise: the chunk's part of the merge of that many slots, in place in `out`.
+// blockIdx.x = tile, blockIdx.y = chunk, blockIdx.z: op0 (factor which0) or op1 (the next).  merge_size == 0: sorts the
+// chunk, up or down as the merges that follow ask; otherwise: the chunk's part of the merge of that many slots, in place
+// in `out`.
 template <int E>
 __global__ __launch_bounds__(kSortThreads) void tile_sort_kernel(Geom g, int which0, SortOperand op0, SortOperand op1,
                                                                  int merge_size)
@@ -729,8 +730,8 @@ struct SpBatch {
 // All probes of one (tile, S_p): blockIdx.x = tile, blockIdx.y = S_p.  I_p is packed once; each probe packs I_z from
 // the tile's M_z (in the L2 from the first probe on), counts the ones of I_a from LDS, and lane 0 moves the interval.
 // Bound by the latency of that chain of steps and by vector-ALU issue in the count; W is not touched.  4096 x 9216 f16,
-// 256 x 256 tiles, rank 16, eight S_p, ten probes: 244 us (278 with one mask word per look-up), where 80 sweeps over W took
-// 80 x 25 us; the whole search 2167 -> 458 us.
+// 256 x 256 tiles, rank 16, eight S_p, ten probes: 242 us (278 with one mask word per look-up), where 80 sweeps over W took
+// 80 x 25 us; the whole search 2167 -> 452 us.
 template <typename V>
 __global__ __launch_bounds__(kEvalThreads) void search_bisect_kernel(Geom g, const float *__restrict__ Mp,
                                                                      const float *__restrict__ Mz,

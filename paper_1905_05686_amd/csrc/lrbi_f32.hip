@@ -7,12 +7,12 @@
 // l & 31 of the left (right) operand at reduction index l >> 5.  One step of the instruction takes 64 cycles, a step's
 // operand loads a few, so tiles through LDS would buy nothing.  A workgroup owns one block of outputs and its
 // wavefronts take chunks of the reduction in turn (the layers are small: the blocks of outputs alone would leave most
-// of the chip idle); their sums are added through LDS in wavefront order.  500 x 800 in 100 x 100 tiles at 64 columns,
-// against the vector-ALU kernels before: product 133 -> 18 us, transposed 498 -> 19 us, gradient 15 -> 12 us (the three calls 667 -> 31 us), most of
-// it the launch and the two chains of factor loads behind a mask word; 4096 x 4096 in 512 x 512 tiles at 64 columns
-// 55, 64 and 57 us (2.1 GFLOP: 14 us at the instruction's rate, the reads of W 13 us), transposed at 8 columns
-// 4019 -> 63 us.  Relative error against 64 bits at 500 x 800, 64 columns: 7.2e-8 -> 6.3e-8, 1.4e-7 -> 7.1e-8 and
-// 1.4e-7 -> 1.1e-7.
+// of the chip idle); their sums are added through LDS in wavefront order.  Kernel times at 500 x 800 in 100 x 100 tiles,
+// 64 columns, against one wavefront per 64 columns (a row) on the vector ALUs: product 131 -> 12.9 us, transposed 522 -> 10.1,
+// gradient 12.9 -> 8.1 (the three calls of a training step 660 -> 31 us), most of it the launch and the two chains of
+// factor loads behind a mask word; 4096 x 4096 in 512 x 512 tiles at 64 columns 55, 62 and 55 us (2.1 GFLOP: 14 us at
+// the instruction's rate, the reads of W 13 us), transposed at 8 columns 4019 -> 63 us.  Relative error against 64 bits
+// at 500 x 800, 64 columns: 7.2e-8 -> 6.3e-8, 1.4e-7 -> 7.1e-8 and 1.4e-7 -> 1.1e-7.
 //
 // A zeroed weight still meets its other operand inside the instruction, and 0 * inf is NaN.  The products therefore
 // watch their unmasked operand: batch columns that hold an infinity or a NaN are formed again, stepping over the
@@ -26,6 +26,7 @@
 namespace lrbi {
 
 static constexpr int kF32Waves = 8; // wavefronts of a product's workgroup, but for a reduction of one chunk
+static constexpr int64_t kMaxColumnsT = 4 * 65535; // the transposed product's limit on N, part of the interface (lrbi.h)
 static constexpr int kF32Chunk = 64; // reduction steps of one wavefront between two mask decodes
 
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
@@ -406,7 +407,7 @@ static int launch_t(const Geom &g, const void *dW, int64_t ldw, const uint32_t *
     const int64_t jblocks = (g.n + 31) / 32;
     const int nq = batch_blocks(jblocks, N);
     const int64_t blocks = jblocks * ((N + 32 * nq - 1) / (32 * nq));
-    if (blocks > 0x7FFFFFFF || (N + 3) / 4 > 65535) return LRBI_ERR_SHAPE;
+    if (blocks > 0x7FFFFFFF || N > kMaxColumnsT) return LRBI_ERR_SHAPE;
 #define LRBI_LAUNCH_F32(NQ, WAVES)                                                                                       \
     LRBI_LAUNCH((f32_gemm_t_kernel<T, NQ, WAVES>), wide_grid(blocks, 64 * WAVES), dim3(64 * WAVES), 0, stream, g, (const T *)dW, \
                 ldw, dIp, dIz, (const T *)dDY, lddy, N, (T *)dDX, lddx, (int)jblocks)

@@ -5,16 +5,17 @@
 // (the reduction dimension) in slabs of BK = 64 columns of W.  Per slab:
 //   1. 16-byte global loads bring the W slab (BM x 64) and the X slab (64 x BN)
 //      into registers, one slab ahead of the arithmetic;
-//   2. every lane rebuilds one or two 32-bit words of the slab's mask from the
-//      packed factors (OR of the I_z words selected by the set bits of the I_p
-//      row) and publishes them in a small LDS array;
+//   2. every lane forms a 32-bit word of the slab's mask from the packed factors
+//      (OR of the I_z words selected by the set bits of the I_p row), on tile
+//      widths of whole slabs out of loads made two to four slabs ahead, and
+//      publishes it in a small LDS array;
 //   3. when the W registers go to LDS, each 16-byte piece is ANDed with the
 //      16-bit-lane expansion of its 8 mask bits: pruned weights become +0 by
 //      select, so nothing stored under a 0 bit (NaN, Inf) reaches the product,
 //      and the masking cost is paid once per slab, not once per MFMA operand;
 //   4. the wavefronts read their operands from LDS and issue 32x32x16 MFMAs.
-//      X sits in LDS in its natural [k][n] order, and the operand needs 8
-//      consecutive k per lane, so it is gathered column-wise.
+//      X sits in LDS in its natural [k][n] order; the transposing read gives a
+//      lane the 8 consecutive k of one column that the instruction wants.
 // LDS is double buffered; there is one workgroup barrier per slab.
 //
 // The MFMA is issued as D = X^T-fragment * W^T-fragment, i.e. the accumulator

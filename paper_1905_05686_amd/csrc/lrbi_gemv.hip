@@ -1,6 +1,6 @@
-// Fused masked product on the vector ALUs: Y = (W o I_a) X for small batches
-// (matrix-vector and a few columns) and for fp32, where the work is bound by
-// streaming W from HBM once and no matrix-core path applies.
+// Fused masked product on the vector ALUs: Y = (W o I_a) X for one to four columns
+// (fp32: and five or six of few, long rows), where the work is bound by streaming
+// W from HBM once, and for 16-bit rows of W that are not whole aligned pieces.
 //
 // One wavefront owns one row of W at a time.  For each segment of 2048 columns
 // the 64 lanes first rebuild the 64 mask words of that segment from the factors

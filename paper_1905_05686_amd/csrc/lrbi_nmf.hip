@@ -20,7 +20,7 @@
 // ranks share one pass over W; any k up to 256 (the paper's largest) is served.
 // What bounds it: the fp32 matrix rate, 2 m n k flops per half update (4096 x 9216 at rank 32: 16 us at 154 TFLOP/s), and
 // beside it W from the memory-side cache (75 MB).  Measured there, f16 in 512 x 576 tiles:
-// M_z 40 us, M_p 42 us, Gram matrices 7 us each (one lane per column and vector fused multiply-adds: 215, 183, 31 and
+// M_z 37 us, M_p 42 us, Gram matrices 7 us each (one lane per column and vector fused multiply-adds: 215, 183, 31 and
 // 42 us); error against 64 bits after 20 iterations 6.2e-7 (7.5e-7).
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
