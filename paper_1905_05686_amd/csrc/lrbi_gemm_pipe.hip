@@ -107,8 +107,10 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     // ---- global -> LDS: per-lane byte offsets of the pieces this lane fetches (they never change)
     // W stage image: row-major 128-byte rows, piece p of row q stored at slot p ^ ((q >> 1) & 7).  A load
     // instruction fills 1 KiB = 8 rows; wavefront w issues the chunks w and w + 8.
-    // X stage image: row-major 256-byte rows, piece p of row q stored at slot p ^ (2 (q & 3)); a load instruction
-    // fills 4 rows; same chunk assignment.
+    // X stage image: row-major 256-byte rows, piece p of row q stored at slot p ^ (4 (q & 3)); a load instruction
+    // fills 4 rows; same chunk assignment.  (Half a wavefront of a transposing read takes 64 bytes of each of four
+    // rows; LDS serves 256 bytes a clock from 64 banks, so the four have to lie 64 bytes apart: measured 256 bytes a
+    // clock and compute unit with this swizzle, 128 with rows 32 bytes apart.)
     uint32_t wvo[2], xvo[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             xvo[i] = (uint32_t)((pix * cg.cin + xp * 8) * 2);
         } else {
             const int xr = chunk * 4 + (lane >> 4);
-            const int xp = (lane & 15) ^ (2 * (xr & 3));
+            const int xp = (lane & 15) ^ (4 * (xr & 3));
             int nn = xp * 8;
             if (n0 + nn + 8 > N) nn = N - 8 - n0; // piece beyond N: fetch a valid piece instead, its columns are dropped
             xvo[i] = (uint32_t)((xr * ldx + nn) * 2);
@@ -138,19 +140,50 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     const uint16_t *wbase = W + m0 * ldw + kbeg;
     const uint16_t *xbase = CONV ? X : X + (int64_t)kbeg * ldx + n0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    // piece i (0, 1: W chunks, 2, 3: X chunks) of a slab into a stage
-    auto issue_piece = [&](int slab, int stage, auto i_c) {
+    // The slabs are asked for in order: (wsl, wp), (xsl, xp) are the next slab of W and of X and where it begins; past the
+    // last slab the last one is fetched again.  (Pointers that advance: two scalar adds per slab.  The same addresses formed
+    // from the slab's number, a division by the channels among them for a convolution, were a third of the loop's scalar
+    // instructions, and the loop is bound by the instructions its wavefronts issue.)
+    const uint16_t *wp = wbase, *xp = xbase;
+    int wsl = 0, xsl = 0;
+    int ci = 0, kw = 0; // CONV: channels ci .. ci + 63 of tap (., kw)
+    if constexpr (CONV) {
+        const int tap = kbeg / cg.cin, kh = tap / 3;
+        ci = kbeg - tap * cg.cin;
+        kw = tap - 3 * kh;
+        xp += (kh * (cg.Wd + 2) + kw) * cg.cin + ci;
+    }
+    const int64_t xstep = (int64_t)BK * ldx;
+    auto next_w = [&]() {
+        if (wsl < last) wp += BK;
+        ++wsl;
+    };
+    auto next_x = [&]() {
+        if (xsl < last) {
+            if constexpr (CONV) {
+                xp += BK; // the next channels, or the first ones of the next tap: the pixel to the right
+                ci += BK;
+                if (ci == cg.cin) {
+                    ci = 0;
+                    if (++kw == 3) { // the first pixel of the tap row below
+                        kw = 0;
+                        xp += (cg.Wd + 2 - 3) * cg.cin;
+                    }
+                }
+            } else
+                xp += xstep;
+        }
+        ++xsl;
+    };
+    // piece i (0, 1: W chunks, 2, 3: X chunks) of the next slab into a stage; the second piece moves on
+    const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
+    auto issue_piece = [&](int stage, auto i_c) {
         constexpr int i = decltype(i_c)::value;
-        const uint32_t sb = lds0 + (uint32_t)stage * STAGE_BYTES + (uint32_t)wave * 1024u;
-        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wbase + slab * BK, wvo[i]);
-        else if constexpr (CONV) {
-            // the slab's 64 reduction indices: channels ci0 .. ci0 + 63 of tap (kh, kw)
-            const int kidx = kbeg + slab * BK;
-            const int tap = kidx / cg.cin, ci0 = kidx - tap * cg.cin;
-            const int kh = tap / 3, kw = tap - 3 * kh;
-            load_to_lds16(sb + STAGE_X + (i - 2) * 8192u, xbase + ((kh * (cg.Wd + 2) + kw) * cg.cin + ci0), xvo[i - 2]);
-        } else
-            load_to_lds16(sb + STAGE_X + (i - 2) * 8192u, xbase + (int64_t)slab * BK * ldx, xvo[i - 2]);
+        const uint32_t sb = lds_w + (uint32_t)stage * STAGE_BYTES;
+        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wp, wvo[i]);
+        else load_to_lds16(sb + STAGE_X + (i - 2) * 8192u, xp, xvo[i - 2]);
+        if constexpr (i == 1) next_w();
+        if constexpr (i == 3) next_x();
     };
 
     // ---- operand reads: byte addresses inside a stage.  This wavefront's steps are kk = 2 kg + j, j = 0, 1.
@@ -164,20 +197,17 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     }
     // X operand (transposing read): 16-lane group G = lane / 16 serves columns 16 (G % 2) .. + 15 of a
     // 32-column block and k group G / 2; lane d of the group addresses row d / 4, columns 4 (d % 4).
-    // Block a sits 64 (a ^ t) bytes further, t = bit 2 of the row's swizzle.
+    // Block a sits at 64 (a ^ (q & 3)), q the row.
     const int d16 = lane & 15, G16 = lane >> 4;
-    uint32_t xfe, xfo; // blocks a = 0, 2 (+128) and a = 1, 3 (+128), step j = 0 (+4096 for j = 1)
+    uint32_t xfa[FN]; // step j = 0 (+4096 for j = 1)
     {
         const int q = 8 * (G16 >> 1) + (d16 >> 2); // row inside the step (+ 4 for the upper half)
-        const int sw = 2 * (q & 3);
-        const int p = (2 * (G16 & 1) + ((d16 & 3) >> 1)) ^ (sw & 2);
-        const int t = (sw >> 2) & 1;
-        const uint32_t base = (uint32_t)(STAGE_X + kg * 8192 + q * 256 + p * 16 + 8 * (d16 & 1));
-        xfe = base + 64u * t;
-        xfo = base + 64u * (1 - t);
+        const uint32_t base = (uint32_t)(STAGE_X + kg * 8192 + q * 256 + (2 * (G16 & 1) + ((d16 & 3) >> 1)) * 16 + 8 * (d16 & 1));
+#pragma unroll
+        for (int a = 0; a < FN; ++a) xfa[a] = base + 64u * (uint32_t)(a ^ (q & 3));
     }
     // mask bytes of this lane's row: 8 bytes per slab, of which this wavefront's steps use bytes 4 kg + 2 j + lg
-    const uint32_t mta = (uint32_t)((wq * 32 + l32) * MT_ROW);
+    const uint32_t mta = (uint32_t)((wq * 32 + l32) * MT_ROW + 4 * kg);
 
     u32x4 wf[2][2], xf[2][FN]; // W operands [slab parity][j]; X operands [j][block]
     auto read_w = [&](int stage, auto par_c, auto j_c) {
@@ -197,7 +227,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             xf[j][a] = *reinterpret_cast<const u32x4 *>(smem + stage * STAGE_BYTES + xca[j] + a * 4096);
             return;
         }
-        const unsigned char *p = smem + stage * STAGE_BYTES + ((a & 1) ? xfo : xfe) + (a >> 1) * 128 + j * 4096;
+        const unsigned char *p = smem + stage * STAGE_BYTES + xfa[a] + j * 4096;
         const u32x2 lo = lds_read_tr16_v((const uint16_t *)p);
         const u32x2 hi = lds_read_tr16_v((const uint16_t *)(p + 1024));
         xf[j][a] = u32x4{lo.x, lo.y, hi.x, hi.y};
@@ -225,11 +255,12 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         wf[par][j].z = select2(wf[par][j].z, (y >> 4) & 0x00010001u);
         wf[par][j].w = select2(wf[par][j].w, (y >> 6) & 0x00010001u);
     };
-    auto fetch_mask = [&](int slab) -> u32x2 {
-        const unsigned char *p = Mt + ((slab / PANEL_SLABS) & 1) * MT_BYTES + (slab % PANEL_SLABS) * 8 + mta;
-        return *reinterpret_cast<const u32x2 *>(p);
+    auto fetch_mask = [&](int slab) -> uint32_t {
+        const uint32_t us = (uint32_t)slab;
+        const unsigned char *p = Mt + ((us / PANEL_SLABS) & 1u) * MT_BYTES + (us % PANEL_SLABS) * 8u + mta;
+        return *reinterpret_cast<const uint32_t *>(p);
     };
-    auto my_bytes = [&](u32x2 mk) -> uint32_t { return (kg ? mk.y : mk.x) >> (8 * lg); };
+    auto my_bytes = [&](uint32_t mk) -> uint32_t { return mk >> (8 * lg); };
 
     // ---- factor slices of one panel: global -> LDS (the same load-to-LDS form), then Eq. 3 for the panel.
     // (ctj, coff): tile column and column offset inside it of the next panel to be loaded; a 128-column unit
@@ -400,12 +431,14 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
 // nothing crosses this line when the compiler orders the instructions
 #define LRBI_SB() __builtin_amdgcn_sched_barrier(0)
 // workgroup barrier without the compiler's own "wait for every outstanding memory operation" in front of it (that
-// wait would drain the slabs in flight); what has to be complete is waited for explicitly
+// wait would drain the slabs in flight); what has to be complete is waited for explicitly.  Operand reads of slab s may be
+// under way across it: what is handed over is the stage of slab s - 1, whose operands have all been multiplied.
 #define LRBI_BARRIER()                                             \
     do {                                                           \
         LRBI_SB();                                                 \
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); /* this wavefront's LDS writes have landed */ \
+        asm volatile("" ::: "memory");                             \
         __builtin_amdgcn_s_barrier();                              \
+        asm volatile("" ::: "memory");                             \
         LRBI_SB();                                                 \
     } while (0)
 
@@ -416,12 +449,11 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     constexpr int kProloguePieces = SPREAD ? (NS - 2) * 4 + 2 : (NS - 1) * 4; // slab copies of this wavefront behind them
     static_for<NS - 1>([&](auto sc) {
         constexpr int st = decltype(sc)::value;
-        const int sl0 = st < last ? st : last;
-        issue_piece(sl0, st, I0{});
-        issue_piece(sl0, st, I1{});
+        issue_piece(st, I0{});
+        issue_piece(st, I1{});
         if constexpr (!(SPREAD && st == NS - 2)) { // SPREAD: the last slab's other half follows in the first iteration
-            issue_piece(sl0, st, I2{});
-            issue_piece(sl0, st, I3{});
+            issue_piece(st, I2{});
+            issue_piece(st, I3{});
         }
     });
     wait_loads<kProloguePieces>();
@@ -459,21 +491,19 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             const int s = s0 + st;
             if (s < nslabs) {
                 uint32_t y;
-                u32x2 mk;
-                const int sl = s + NS - 1 < last ? s + NS - 1 : last;
-                const int sp = s + NS - 2 < last ? s + NS - 2 : last;
+                uint32_t mk;
                 // first step
                 mma(Par{}, I0{}, I0{}); read_x(st, I1{}, I0{}); y = mask_lo(Par{}, I1{}, mcur);
                 mma(Par{}, I0{}, I1{}); read_x(st, I1{}, I1{}); mask_hi(Par{}, I1{}, y);
-                if constexpr (SPREAD) issue_piece(sp, stp, I2{});
+                if constexpr (SPREAD) issue_piece(stp, I2{});
                 mma(Par{}, I0{}, I2{}); read_x(st, I1{}, I2{});
                 mk = fetch_mask(s + 1 < last ? s + 1 : last); // mask bytes of the next slab
                 mma(Par{}, I0{}, I3{}); read_x(st, I1{}, I3{});
-                if constexpr (SPREAD) issue_piece(sp, stp, I3{});
+                if constexpr (SPREAD) issue_piece(stp, I3{});
                 // factor slices of the next panel, requested at the panel's first slab: they have landed, for
                 // every wavefront, behind the next iteration's wait and barrier
-                const int ps = s % PANEL_SLABS;
-                const int np = s / PANEL_SLABS + 1;
+                const int ps = (uint32_t)s % PANEL_SLABS;
+                const int np = (uint32_t)s / PANEL_SLABS + 1;
                 if (ps == 0 && np < npanels) load_factors();
                 // slab s + 1 has landed (four younger loads may still be in flight with four stages; EMIT: and the mask
                 // store of the panel that the previous iteration turned into mask bytes)
@@ -482,16 +512,19 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_x(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});
-                issue_piece(sl, stn, I0{});
+                issue_piece(stn, I0{});
                 mma(Par{}, I1{}, I1{}); read_x(st1, I0{}, I1{}); mcur = my_bytes(mk);
-                issue_piece(sl, stn, I1{});
+                issue_piece(stn, I1{});
                 mma(Par{}, I1{}, I2{}); read_x(st1, I0{}, I2{}); y = mask_lo(Nxt{}, I0{}, mcur);
-                if constexpr (!SPREAD) issue_piece(sl, stn, I2{});
+                if constexpr (!SPREAD) issue_piece(stn, I2{});
                 mma(Par{}, I1{}, I3{}); read_x(st1, I0{}, I3{}); mask_hi(Nxt{}, I0{}, y);
-                if constexpr (!SPREAD) issue_piece(sl, stn, I3{});
+                if constexpr (!SPREAD) issue_piece(stn, I3{});
                 // mask of the next panel, turned into mask bytes at the panel's slab 2; the first read of the new
                 // mask bytes is at slab 7
-                if (ps == 2 && np < npanels) decode_panel(np);
+                if (ps == 2 && np < npanels) {
+                    decode_panel(np);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the mask bytes have landed before the next barrier
+                }
             }
         });
     }

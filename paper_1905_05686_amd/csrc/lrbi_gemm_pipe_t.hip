@@ -93,14 +93,16 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     const int wq = wave & 3;  // which 32 columns of W (rows of dX)
     const int l32 = lane & 31, lg = lane >> 5;
 
-    // ---- global -> LDS: both slabs are 64 rows of 256 bytes; piece p of row q is stored at slot p ^ (2 (q & 3)); a
-    // load instruction fills 4 rows; wavefront w issues the chunks w and w + 8
+    // ---- global -> LDS: both slabs are 64 rows of 256 bytes; piece p of row q is stored at slot p ^ (4 (q & 3)); a
+    // load instruction fills 4 rows; wavefront w issues the chunks w and w + 8.  (Half a wavefront of a transposing read
+    // takes 64 bytes of each of four rows: 64 bytes apart they meet all 64 banks once; 32 bytes apart they took twice
+    // the clocks.)
     uint32_t wvo[2], yvo[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int chunk = wave + 8 * i;
         const int xr = chunk * 4 + (lane >> 4);
-        const int xp = (lane & 15) ^ (2 * (xr & 3));
+        const int xp = (lane & 15) ^ (4 * (xr & 3));
         wvo[i] = (uint32_t)((xr * ldw + xp * 8) * 2);
         int nn = xp * 8;
         if (q0 + nn + 8 > N) nn = N - 8 - q0; // piece beyond N: fetch a valid piece instead, its columns are dropped
@@ -109,30 +111,43 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     const uint16_t *wbase = W + ibeg * ldw + j0;
     const uint16_t *ybase = DY + ibeg * lddy + q0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
-    auto issue_piece = [&](int slab, int stage, auto i_c) {
+    // (wsl, wp), (ysl, yp): the next slab of W and of dY to be asked for and where it begins; past the last slab the last
+    // one is fetched again (pointers that advance, as in the forward kernel)
+    const uint16_t *wp = wbase, *yp = ybase;
+    int wsl = 0, ysl = 0;
+    const int64_t wstep = (int64_t)BK * ldw, ystep = (int64_t)BK * lddy;
+    // piece i (0, 1: W chunks, 2, 3: dY chunks) of the next slab into a stage; the second piece moves on
+    const uint32_t lds_w = lds0 + (uint32_t)wave * 1024u;
+    auto issue_piece = [&](int stage, auto i_c) {
         constexpr int i = decltype(i_c)::value;
-        const uint32_t sb = lds0 + (uint32_t)stage * PT_STAGE_BYTES + (uint32_t)wave * 1024u;
-        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wbase + (int64_t)slab * BK * ldw, wvo[i]);
-        else load_to_lds16(sb + PT_STAGE_Y + (i - 2) * 8192u, ybase + (int64_t)slab * BK * lddy, yvo[i - 2]);
+        const uint32_t sb = lds_w + (uint32_t)stage * PT_STAGE_BYTES;
+        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wp, wvo[i]);
+        else load_to_lds16(sb + PT_STAGE_Y + (i - 2) * 8192u, yp, yvo[i - 2]);
+        if constexpr (i == 1) {
+            if (wsl < last) wp += wstep;
+            ++wsl;
+        }
+        if constexpr (i == 3) {
+            if (ysl < last) yp += ystep;
+            ++ysl;
+        }
     };
 
     // ---- operand reads (transposing read): 16-lane group G = lane / 16 serves columns 16 (G % 2) .. + 15 of a
     // 32-column block and reduction group G / 2; lane d of the group addresses row d / 4, columns 4 (d % 4).
-    // Block a sits 64 (a ^ t) bytes further, t = bit 2 of the row's swizzle.  This wavefront's steps are 2 kg + j.
+    // Block a sits at 64 (a ^ (q & 3)), q the row.  This wavefront's steps are 2 kg + j.
     const int d16 = lane & 15, G16 = lane >> 4;
-    uint32_t xfe, xfo; // blocks a = 0, 2 (+128) and a = 1, 3 (+128) of a slab image, step j = 0 (+4096 for j = 1)
+    uint32_t xfa[FN]; // the blocks of a slab image, step j = 0 (+4096 for j = 1)
+    uint32_t wta;     // the W block of this wavefront
     {
         const int q = 8 * (G16 >> 1) + (d16 >> 2);
-        const int sw = 2 * (q & 3);
-        const int p = (2 * (G16 & 1) + ((d16 & 3) >> 1)) ^ (sw & 2);
-        const int t = (sw >> 2) & 1;
-        const uint32_t base = (uint32_t)(kg * 8192 + q * 256 + p * 16 + 8 * (d16 & 1));
-        xfe = base + 64u * t;
-        xfo = base + 64u * (1 - t);
+        const uint32_t base = (uint32_t)(kg * 8192 + q * 256 + (2 * (G16 & 1) + ((d16 & 3) >> 1)) * 16 + 8 * (d16 & 1));
+#pragma unroll
+        for (int a = 0; a < FN; ++a) xfa[a] = base + 64u * (uint32_t)(a ^ (q & 3));
+        wta = base + 64u * (uint32_t)(wq ^ (q & 3));
     }
-    const uint32_t wta = ((wq & 1) ? xfo : xfe) + (uint32_t)((wq >> 1) * 128); // the W block of this wavefront
     // mask bytes of this lane's column of W: 8 bytes per slab, of which this wavefront's steps use bytes 4 kg + 2 j + lg
-    const uint32_t mta = (uint32_t)((wq * 32 + l32) * PT_MT_ROW);
+    const uint32_t mta = (uint32_t)((wq * 32 + l32) * PT_MT_ROW + 4 * kg);
 
     u32x4 wf[2][2], yf[2][FN]; // W operands [slab parity][j]; dY operands [j][block]
     auto read_w = [&](int stage, auto par_c, auto j_c) {
@@ -144,7 +159,7 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     };
     auto read_y = [&](int stage, auto j_c, auto a_c) {
         constexpr int j = decltype(j_c)::value, a = decltype(a_c)::value;
-        const unsigned char *p = smem + stage * PT_STAGE_BYTES + PT_STAGE_Y + ((a & 1) ? xfo : xfe) + (a >> 1) * 128 + j * 4096;
+        const unsigned char *p = smem + stage * PT_STAGE_BYTES + PT_STAGE_Y + xfa[a] + j * 4096;
         const u32x2 lo = lds_read_tr16_v((const uint16_t *)p);
         const u32x2 hi = lds_read_tr16_v((const uint16_t *)(p + 1024));
         yf[j][a] = u32x4{lo.x, lo.y, hi.x, hi.y};
@@ -172,11 +187,12 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
         wf[par][j].z = select2(wf[par][j].z, (y >> 4) & 0x00010001u);
         wf[par][j].w = select2(wf[par][j].w, (y >> 6) & 0x00010001u);
     };
-    auto fetch_mask = [&](int slab) -> u32x2 {
-        const unsigned char *p = Mt + ((slab / PANEL_SLABS) & 1) * PT_MT_BYTES + (slab % PANEL_SLABS) * 8 + mta;
-        return *reinterpret_cast<const u32x2 *>(p);
+    auto fetch_mask = [&](int slab) -> uint32_t {
+        const uint32_t us = (uint32_t)slab;
+        const unsigned char *p = Mt + ((us / PANEL_SLABS) & 1u) * PT_MT_BYTES + (us % PANEL_SLABS) * 8u + mta;
+        return *reinterpret_cast<const uint32_t *>(p);
     };
-    auto my_bytes = [&](u32x2 mk) -> uint32_t { return (kg ? mk.y : mk.x) >> (8 * lg); };
+    auto my_bytes = [&](uint32_t mk) -> uint32_t { return mk >> (8 * lg); };
 
     // ---- factor slices of one panel (512 rows of W = four units of 128 rows): global -> LDS, word by word, in the
     // order the gathers below want them: I_z as [unit][word of the 128 columns][rank] (a lane then reads four ranks of
@@ -400,11 +416,13 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
 #define LRBI_SB() __builtin_amdgcn_sched_barrier(0)
+// (operand reads of slab s may be under way across it: the stage handed over is that of slab s - 1)
 #define LRBI_BARRIER()                                             \
     do {                                                           \
         LRBI_SB();                                                 \
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");         \
+        asm volatile("" ::: "memory");                             \
         __builtin_amdgcn_s_barrier();                              \
+        asm volatile("" ::: "memory");                             \
         LRBI_SB();                                                 \
     } while (0)
 
@@ -414,12 +432,11 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     constexpr int kProloguePieces = (NS - 2) * 4 + 2;
     static_for<NS - 1>([&](auto sc) {
         constexpr int st = decltype(sc)::value;
-        const int sl0 = st < last ? st : last;
-        issue_piece(sl0, st, I0{});
-        issue_piece(sl0, st, I1{});
+        issue_piece(st, I0{});
+        issue_piece(st, I1{});
         if constexpr (st != NS - 2) {
-            issue_piece(sl0, st, I2{});
-            issue_piece(sl0, st, I3{});
+            issue_piece(st, I2{});
+            issue_piece(st, I3{});
         }
     });
     wait_loads<kProloguePieces>();
@@ -460,27 +477,25 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
             const int s = s0 + st;
             if (s < nslabs) {
                 uint32_t y;
-                u32x2 mk;
-                const int sl = s + NS - 1 < last ? s + NS - 1 : last;
-                const int sp = s + NS - 2 < last ? s + NS - 2 : last;
+                uint32_t mk;
                 // first step
                 mma(Par{}, I0{}, I0{}); read_y(st, I1{}, I0{}); y = mask_lo(Par{}, I1{}, mcur);
                 mma(Par{}, I0{}, I1{}); read_y(st, I1{}, I1{}); mask_hi(Par{}, I1{}, y);
-                issue_piece(sp, stp, I2{});
+                issue_piece(stp, I2{});
                 mma(Par{}, I0{}, I2{}); read_y(st, I1{}, I2{});
                 mk = fetch_mask(s + 1 < last ? s + 1 : last);
                 mma(Par{}, I0{}, I3{}); read_y(st, I1{}, I3{});
-                issue_piece(sp, stp, I3{});
-                const int ps = s % PANEL_SLABS;
-                const int np = s / PANEL_SLABS + 1;
+                issue_piece(stp, I3{});
+                const int ps = (uint32_t)s % PANEL_SLABS;
+                const int np = (uint32_t)s / PANEL_SLABS + 1;
                 if (ps == 0 && np < npanels) load_factors();
                 wait_loads<(NS - 3) * 4>();
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_y(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});
-                issue_piece(sl, stn, I0{});
+                issue_piece(stn, I0{});
                 mma(Par{}, I1{}, I1{}); read_y(st1, I0{}, I1{}); mcur = my_bytes(mk);
-                issue_piece(sl, stn, I1{});
+                issue_piece(stn, I1{});
                 mma(Par{}, I1{}, I2{}); read_y(st1, I0{}, I2{}); y = mask_lo(Nxt{}, I0{}, mcur);
                 mma(Par{}, I1{}, I3{}); read_y(st1, I0{}, I3{}); mask_hi(Nxt{}, I0{}, y);
                 // mask of the next panel: its factor slices, asked for at slab 0, were waited for by every wavefront in
@@ -494,6 +509,8 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
                         if constexpr (HALF) panel_step3b();
                         else panel_step4(np);
                     } else if (HALF && ps == 4) panel_step4(np); // (written behind slab 4's barrier, first read at slab 7)
+                    // what a step read and wrote of the factors and the mask is done before the next barrier
+                    if (ps >= 1 && ps <= 4) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 }
             }
         });
