@@ -83,9 +83,9 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         const int64_t per = gridDim.x / 8;
         bid = (bid % 8) * per + bid / 8;
     }
-    const int ni = (int)(bid % nblocks);
-    const int mi = (int)((bid / nblocks) % mblocks);
     const int slice = (int)(bid / ((int64_t)nblocks * mblocks));
+    int mi, ni;
+    grouped_tile<4>(bid - (int64_t)slice * nblocks * mblocks, mblocks, nblocks, &mi, &ni);
     const int64_t m0 = (int64_t)mi * PIPE_BM;
     const int n0 = ni * PIPE_BN;
     const int kbeg = (int)(slice * kper);

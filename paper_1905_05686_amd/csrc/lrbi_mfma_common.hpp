@@ -117,4 +117,18 @@ static constexpr int PANEL_UNITS = PW / 128; // 128-column units; each lies insi
 static constexpr int FAST_MAX_K = 64;
 
 
+// Tile (mi, ni) of the b-th workgroup of a grid of mblocks x nblocks tiles: groups of GM tile rows, the rows of a group
+// fastest.  The 32 workgroups that an XCD's compute units hold at a time (b .. b + 31) then cover GM x 32 / GM tiles and
+// ask that XCD's L2 for GM + 32 / GM operand blocks a slab, where a whole row of 32 tiles asks for 33.
+template <int GM> __device__ __forceinline__ void grouped_tile(int64_t b, int mblocks, int nblocks, int *mi, int *ni)
+{
+    const int64_t per_group = (int64_t)GM * nblocks;
+    const int64_t group = b / per_group;
+    const int first = (int)group * GM;
+    const int rows = mblocks - first < GM ? mblocks - first : GM;
+    const int in = (int)(b - group * per_group);
+    *ni = in / rows;
+    *mi = first + in - *ni * rows;
+}
+
 } // namespace lrbi
