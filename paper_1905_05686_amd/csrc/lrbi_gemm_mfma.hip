@@ -820,9 +820,10 @@ struct TileDef {
 static const TileDef kTiles[] = {{0, 0, false},    {128, 128, false}, {128, 64, false}, {128, 32, false},
                                  {128, 128, true}, {128, 128, true},  {128, 64, true},  {128, 32, true},
                                  {128, 128, true}, {128, 128, true},  {128, 64, true},  {128, 32, true},
-                                 {128, 128, true}, {128, 128, true},  {128, 128, true}};
-static constexpr int kNumTiles = 14;
+                                 {128, 128, true}, {128, 128, true},  {128, 128, true}, {256, 256, true}};
+static constexpr int kNumTiles = 15;
 static constexpr int kFirstPipeTile = 12; // 12 .. 14: the software-pipelined kernel (lrbi_gemm_pipe.hip), variants 0 .. 2
+static constexpr int kPipe256Tile = 15;   // the same in 256 x 256 tiles (lrbi_gemm_pipe256.hip); never split over n
 
 static bool panel_ok(const Geom &g, int bm)
 {
@@ -836,6 +837,7 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
     if (tile >= 1 && tile <= kNumTiles && kTiles[tile].panel && !panel_ok(g, kTiles[tile].bm) &&
         !(tile >= kFirstPipeTile && pipe_shape_ok(g)))
         tile = 0;
+    int split = (int)((flags & LRBI_FLAG_SPLITK_MASK) >> LRBI_FLAG_SPLITK_SHIFT);
     if (tile < 1 || tile > kNumTiles) {
         tile = (N > 64) ? 1 : (N > 32 ? 2 : 3);
         // 14 (the pipelined kernel, also at 33 to 64 columns: HBM-cold 4096 x 9216 at N = 64 25.0 against 26.9 us on
@@ -845,7 +847,9 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
         // column block idle, but W is streamed at the same rate: 4096 x 9216 in 512 x 576 tiles, N = 64, 25 us against
         // 40 us on the generic kernel); falls back to the generic kernel when X is not 16-byte readable
         else if (N > 32 && pipe_shape_ok(g)) tile = 14;
-        else if (tile == 1) {
+        if (tile == 14) {
+            if (pipe256_wins(g, N)) tile = kPipe256Tile;
+        } else if (tile == 1) {
             // few rows, many columns (a small convolution layer as a product): narrower column blocks that fill the
             // chip by themselves instead of a split with its round trip of partial planes (64 x 576, N = 16384:
             // 19.4 us against 18.7 + 4.2 us)
@@ -856,6 +860,10 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
             }
         }
     }
+    if (tile == kPipe256Tile) {
+        if (split > 1) tile = 14;
+        else split = 1;
+    }
     p.tile = tile;
     p.bm = kTiles[tile].bm;
     p.bn = kTiles[tile].bn;
@@ -863,7 +871,6 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
     const int64_t nblocks = (N + p.bn - 1) / p.bn;
     const int64_t tiles = mblocks * nblocks;
     const int64_t npairs = (g.n + 2 * BK - 1) / (2 * BK); // slices are cut at multiples of 128 columns
-    int split = (int)((flags & LRBI_FLAG_SPLITK_MASK) >> LRBI_FLAG_SPLITK_SHIFT);
     if (split == 0) {
         split = 1;
         const bool general = tile < 4;
@@ -1056,7 +1063,10 @@ int launch_mfma_gemm(const Geom &g, const MfmaPlan &plan_in, lrbi_dtype dt, cons
     MfmaPlan plan = plan_in;
     if (plan.tile >= kFirstPipeTile) {
         if (pipe_ok(g, dIz, dX, ldw, ldx, N)) {
-            const int pf = plan.tile - kFirstPipeTile;
+            // (the mask as a by-product and the planes of a fused consumer come from the 128 x 128 form)
+            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr)
+                return launch_pipe256_gemm(g, dt, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, stream);
+            const int pf = plan.tile == kPipe256Tile ? 2 : plan.tile - kFirstPipeTile;
             const int rc = launch_pipe_gemm(g, plan, dt, pf, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, stream, mo);
             if (rc != LRBI_OK) return rc;
             if (plan.splitk > 1 && !plan.planes_only) {

@@ -504,10 +504,12 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 // every wavefront, behind the next iteration's wait and barrier
                 const int ps = (uint32_t)s % PANEL_SLABS;
                 const int np = (uint32_t)s / PANEL_SLABS + 1;
-                if (ps == 0 && np < npanels) load_factors();
                 // slab s + 1 has landed (four younger loads may still be in flight with four stages; EMIT: and the mask
                 // store of the panel that the previous iteration turned into mask bytes)
-                if (EMIT && ps == 3 && np < npanels) wait_loads<(NS - 3) * 4 + 1>();
+                if (ps == 0 && np < npanels) {
+                    load_factors();
+                    wait_loads<(NS - 3) * 4 + (HALF ? 6 : 2)>(); // (and the factor loads: two or three, HALF six)
+                } else if (EMIT && ps == 3 && np < npanels) wait_loads<(NS - 3) * 4 + 1>();
                 else wait_loads<(NS - 3) * 4>();
                 LRBI_BARRIER();
                 // second step

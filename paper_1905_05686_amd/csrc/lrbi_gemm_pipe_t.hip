@@ -488,8 +488,11 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
                 issue_piece(stp, I3{});
                 const int ps = (uint32_t)s % PANEL_SLABS;
                 const int np = (uint32_t)s / PANEL_SLABS + 1;
-                if (ps == 0 && np < npanels) load_factors();
-                wait_loads<(NS - 3) * 4>();
+                if (ps == 0 && np < npanels) {
+                    load_factors();
+                    wait_loads<(NS - 3) * 4 + (HALF ? 6 : 4)>(); // (the factor loads are younger too)
+                } else
+                    wait_loads<(NS - 3) * 4>();
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_y(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});

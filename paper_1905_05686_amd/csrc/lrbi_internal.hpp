@@ -148,6 +148,12 @@ int launch_pipe_gemm(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, int pf,
                      const uint32_t *dIp, const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY,
                      int64_t ldy, void *dWorkspace, hipStream_t stream, MaskOut mo = {nullptr, 0});
 
+// the same in 256 x 256 tiles (lrbi_gemm_pipe256.hip): shapes of pipe_ok(), unsplit, no mask as a by-product
+bool pipe256_wins(const Geom &g, int64_t N);
+int launch_pipe256_gemm(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, const uint32_t *dIp,
+                        const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY, int64_t ldy,
+                        hipStream_t stream);
+
 // non-negative factorisation of the magnitude matrix (lrbi_nmf.hip)
 uint64_t nmf_workspace_bytes(const Geom &g);
 int launch_nmf(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, int method, float w_threshold, float amplify,

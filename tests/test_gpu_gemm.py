@@ -410,3 +410,27 @@ def test_general_tile_kernel_masks(m, n, r, c, k, p, N):
 def test_fp32_batches_of_few_rows(m, n, r, c, k, N):
     """fp32 products around the lines between the forms of the kernel, against the fp64 oracle."""
     test_fp32_batches(m, n, r, c, k, N, 0)
+
+
+# 256 x 256 tiles: one slab panel and several, tile rows that change inside a workgroup's rows, an odd number of 128-row
+# blocks, half units of two tiles, one and two I_p words, column blocks cut off at N, tile groups that are not full
+@pytest.mark.parametrize("m,n,r,c,k,N,dtype", [
+    (128, 64, 128, 64, 5, 8, "bf16"),
+    (256, 128, 256, 128, 32, 256, "f16"),
+    (384, 576, 128, 192, 33, 264, "f16"),
+    (512, 1024, 256, 512, 64, 248, "bf16"),
+    (640, 1152, 128, 576, 32, 520, "bf16"),
+    (1408, 320, 128, 64, 16, 1032, "f16"),
+])
+def test_tiles_of_256(m, n, r, c, k, N, dtype):
+    print("256 x 256 tiles", m, n, r, c, k, N, dtype, flush=True)
+    cfg = workloads.Config("t256", m, n, r, c, k, 0.12, N, dtype, 0.05)
+    data = workloads.make(cfg)
+    ref, _ = _oracle(cfg, data)
+    for ldpad in (0, 8):
+        Y = _run(cfg, data, flags=lrbi.flag_tile(15), ldpad=ldpad)
+        _assert_close(Y, ref, dtype, "256 x 256")
+    # the sums are formed per accumulator in the order of the columns in either form, but in other groups: close, not equal
+    Y2 = _run(cfg, data, flags=lrbi.flag_tile(14))
+    _assert_close(Y2, ref, dtype, "128 x 128")
+    assert torch.equal(Y, _run(cfg, data, flags=lrbi.flag_tile(15), ldpad=8))
