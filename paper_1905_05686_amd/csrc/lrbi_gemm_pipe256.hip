@@ -33,7 +33,7 @@ static constexpr int P256_HU = P256_PW / 64;   // half units of a panel
 static constexpr int P256_MT_ROW = 36;         // bytes per row of a mask panel: 32 + 4 (rows of a read on distinct banks)
 static constexpr int P256_MT = P256_B * P256_MT_ROW;
 static constexpr int P256_FZ_ROW = P256_HU * 8; // bytes of a rank's I_z words under a panel
-static constexpr int P256_FZ_SET = (FAST_MAX_K + 1) * P256_FZ_ROW; // (row FAST_MAX_K stays zero)
+static constexpr int P256_FZ_SET = (FAST_MAX_K + 1) * P256_FZ_ROW; // (row 32 stays zero)
 static constexpr int P256_FACTOR_LOADS = 6;    // load instructions of a wavefront per panel
 
 struct SmemP256 {
@@ -45,7 +45,8 @@ struct SmemP256 {
 static_assert(SmemP256::bytes <= 160 * 1024, "LDS of a compute unit");
 static_assert(SmemP256::fz_off % 16 == 0 && SmemP256::fip_off % 16 == 0, "16-byte pieces");
 
-template <typename Tag>
+// KW: I_p words per row (ranks up to 32, up to 64).  HALF: tile widths that are an odd multiple of 64.
+template <typename Tag, int KW, bool HALF>
 __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm_pipe256_kernel(
     Geom g, const uint16_t *__restrict__ W, int64_t ldw, const uint32_t *__restrict__ Ip,
     const uint32_t *__restrict__ Iz, const uint16_t *__restrict__ X, int64_t ldx, int N, uint16_t *__restrict__ Y,
@@ -70,7 +71,6 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
     const int n0 = ni * P256_B;
     const int nslabs = (int)(g.n / P256_BK);
     const int last = nslabs - 1;
-    const int npanels = (nslabs + P256_PSLABS - 1) / P256_PSLABS;
     // the upper 128 rows of the last tile row of an odd number of 128-row blocks repeat the lower ones and are not stored
     const int64_t mh = (m0 + 128 < g.m) ? m0 + 128 : m0;
     const int ti0 = (int)(m0 / g.r), ti1 = (int)(mh / g.r);
@@ -167,45 +167,50 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
         constexpr int j = decltype(j_c)::value, a = decltype(a_c)::value, b = decltype(b_c)::value;
         acc[a][b] = mfma_32x32x16(Tag{}, xf[j][a], wf[j][b], acc[a][b]);
     };
-    auto mask_w = [&](auto j_c, auto b_c, uint32_t m) { // m: the row's mask word, shifted by 8 (lane / 32)
+    // mask of a W operand in two halves (between two matrix instructions each); m: the row's mask word, shifted by 8 (lane / 32)
+    auto mask_lo = [&](auto j_c, auto b_c, uint32_t m) -> uint32_t {
         constexpr int j = decltype(j_c)::value, b = decltype(b_c)::value;
-        wf[j][b] = apply_mask8(wf[j][b], (m >> (16 * j)) & 0xFFu);
+        const uint32_t y = ((m >> (16 * j)) & 0xFFu) * 0x8001u;
+        wf[j][b].x = select2(wf[j][b].x, y & 0x00010001u);
+        wf[j][b].y = select2(wf[j][b].y, (y >> 2) & 0x00010001u);
+        return y;
     };
-    auto fetch_mask = [&](int slab, int b) -> uint32_t {
-        const uint32_t us = (uint32_t)slab;
-        return *reinterpret_cast<const uint32_t *>(Mt + ((us / P256_PSLABS) & 1u) * P256_MT + (us % P256_PSLABS) * 4u + mta + b * (32 * P256_MT_ROW));
+    auto mask_hi = [&](auto j_c, auto b_c, uint32_t y) {
+        constexpr int j = decltype(j_c)::value, b = decltype(b_c)::value;
+        wf[j][b].z = select2(wf[j][b].z, (y >> 4) & 0x00010001u);
+        wf[j][b].w = select2(wf[j][b].w, (y >> 6) & 0x00010001u);
+    };
+    // mask word of this lane's row of block b under slab `ps` of the panel whose bytes start at `panel`
+    auto fetch_mask = [&](uint32_t panel, int ps, int b) -> uint32_t {
+        return *reinterpret_cast<const uint32_t *>(Mt + panel + mta + ps * 4 + b * (32 * P256_MT_ROW));
     };
 
     // ---- factor slices of one panel: global -> LDS, word by word, per 64-column half unit (two words of an I_z row).
-    // (ctj, coff): tile column and offset of the next panel's first half unit.  Ranks at or beyond k fetch rank 0 (no I_p
-    // bit selects them); half units past the last column fetch the first one (their mask bytes are never read).
-    int ctj = 0, coff = 0, ccol = 0;
+    // A lane fetches for one of the panel's half units; (ftj, foff, fcol): that half unit's tile column, offset in it and
+    // first column, carried from panel to panel.  Ranks at or beyond k fetch rank 0 (no I_p bit selects them); half units
+    // past the last column fetch the tile row's first tile (their mask bytes are never read).
     const uint32_t izs = (uint32_t)(g.k * g.izw * 4), ips = (uint32_t)(g.r * g.ipw * 4); // bytes of a tile's factors
     const uint32_t z0 = (uint32_t)ti0 * (uint32_t)g.tile_cols * izs, z1 = (uint32_t)ti1 * (uint32_t)g.tile_cols * izs;
     const uint32_t p0 = (uint32_t)ti0 * (uint32_t)g.tile_cols * ips + (uint32_t)(il0 * g.ipw * 4);
     const uint32_t p1 = (uint32_t)ti1 * (uint32_t)g.tile_cols * ips + (uint32_t)(il1 * g.ipw * 4);
+    int fcol = 64 * ((lane >> 1) & 3);
+    int ftj = fcol / g.c, foff = fcol - ftj * g.c;
+    const int n_cols = (int)g.n;
     auto load_factors = [&]() {
-        uint32_t zo[P256_HU], po[P256_HU]; // byte offsets of each half unit's slices inside the tile row (uniform)
-#pragma unroll
-        for (int h = 0; h < P256_HU; ++h) {
-            const bool ok = ccol < g.n;
-            zo[h] = ok ? (uint32_t)ctj * izs + (uint32_t)(coff >> 5) * 4u : 0u;
-            po[h] = ok ? (uint32_t)ctj * ips : 0u;
-            ccol += 64;
-            coff += 64;
-            if (coff >= g.c) {
-                coff = 0;
-                ++ctj;
-            }
+        const bool ok = fcol < n_cols;
+        const uint32_t zsel = ok ? (uint32_t)ftj * izs + (uint32_t)(foff >> 5) * 4u : 0u;
+        const uint32_t psel = ok ? (uint32_t)ftj * ips : 0u;
+        fcol += P256_PW;
+        foff += P256_PW;
+        while (foff >= g.c) {
+            foff -= g.c;
+            ++ftj;
         }
-        const int hu = (lane >> 1) & 3;
-        const uint32_t zsel = (hu & 2) ? ((hu & 1) ? zo[3] : zo[2]) : ((hu & 1) ? zo[1] : zo[0]);
-        const uint32_t psel = (hu & 2) ? ((hu & 1) ? po[3] : po[2]) : ((hu & 1) ? po[1] : po[0]);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int q = wave * 2 + i, half = q >> 3, qq = q & 7; // ranks 8 qq .. + 7, lane = (rank, half unit, word)
             const int rank = qq * 8 + (lane >> 3);
-            load_to_lds4(lds0 + (uint32_t)(S::fz_off + half * P256_FZ_SET + qq * 256), Iz,
+            load_to_lds4(lds0 + (uint32_t)(S::fz_off + half * P256_FZ_SET + qq * 256 + (qq >= 4 ? P256_FZ_ROW : 0)), Iz,
                          (half ? z1 : z0) + zsel + (uint32_t)((((rank < g.k) ? rank : 0) * g.izw + (lane & 1)) * 4));
         }
         const int iw = (lane & 1) < g.ipw ? (lane & 1) : 0;
@@ -216,37 +221,70 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
             load_to_lds4(lds0 + (uint32_t)(S::fip_off + q * 256), Ip, (half ? p1 : p0) + psel + (uint32_t)((row * g.ipw + iw) * 4));
         }
     };
-    // Eq. 3 for the panel: a lane forms the four mask words of one row under two half units, each from the I_p word(s)
-    // and the I_z words of its own tile; the first two ranks of both halves without a test, the rest in a loop.
-    auto decode_panel = [&](int panel) {
-        const int row = tid >> 1, u = tid & 1;
-        const uint32_t *fp = Fip + (row * P256_HU + 2 * u) * 2;
-        const unsigned char *fz = Fz + (row >> 7) * P256_FZ_SET + u * 16;
-        uint32_t *out = reinterpret_cast<uint32_t *>(Mt + (panel & 1) * P256_MT + row * P256_MT_ROW + u * 16);
-        const u32x4 w4 = *reinterpret_cast<const u32x4 *>(fp);
-        unsigned long long s0 = w4.x, s1 = w4.z;
-        if (g.ipw > 1) {
-            s0 |= (unsigned long long)w4.y << 32;
-            s1 |= (unsigned long long)w4.w << 32;
+    // Eq. 3 for the panel: a lane forms the four mask words of one row under one 128-column unit (HALF: under its two half
+    // units, each from the factors of its own tile).  The set ranks are taken two at a time, over three slabs of the loop, so
+    // that the reads have come back when they are added; rows with more ranks than that (few: the factors are sparse) loop
+    // over the rest.  Ranks are found per 32-bit word of I_p; a word without one left reads the zero row, 32 (which is what
+    // counting its trailing zeros gives), rank l >= 32 sits in row l + 1.
+    constexpr int NH = HALF ? 2 : 1, PER = KW == 1 ? 2 : 1;
+    using zvec = std::conditional_t<HALF, u32x2, u32x4>;
+    const int drow = tid >> 1, du = tid & 1;
+    const unsigned char *dfz = Fz + (drow >> 7) * P256_FZ_SET + du * 16;
+    uint32_t sel[NH][KW];
+    zvec dz[NH][KW * PER], dh[NH];
+    auto decode_words = [&]() {
+        const uint32_t *fp = Fip + (drow * P256_HU + 2 * du) * 2;
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+#pragma unroll
+            for (int w = 0; w < KW; ++w) sel[h][w] = fp[2 * h + w];
+            dh[h] = zvec(0u);
         }
-        u32x2 h0 = {0u, 0u}, h1 = {0u, 0u};
-        auto next = [&]() { // one rank of either half; the zero row when there is none left
-            const int l0 = s0 ? __builtin_ctzll(s0) : FAST_MAX_K, l1 = s1 ? __builtin_ctzll(s1) : FAST_MAX_K;
-            s0 &= s0 - 1ull;
-            s1 &= s1 - 1ull;
-            h0 |= *reinterpret_cast<const u32x2 *>(fz + l0 * P256_FZ_ROW);
-            h1 |= *reinterpret_cast<const u32x2 *>(fz + l1 * P256_FZ_ROW + 8);
+    };
+    auto decode_ask = [&]() {
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int w = 0; w < KW; ++w)
+#pragma unroll
+                for (int e = 0; e < PER; ++e) {
+                    const uint32_t v = sel[h][w];
+                    const uint32_t l = v ? (uint32_t)__builtin_ctz(v) : 32u;
+                    sel[h][w] = v & (v - 1u);
+                    // (the second word's ranks are 33 rows on; its zero row is the first word's)
+                    const uint32_t row = w == 0 ? l : (v ? l + 33u : 32u);
+                    dz[h][w * PER + e] = *reinterpret_cast<const zvec *>(dfz + row * P256_FZ_ROW + h * 8);
+                }
+    };
+    auto decode_add = [&]() {
+#pragma unroll
+        for (int h = 0; h < NH; ++h) dh[h] |= dz[h][0] | dz[h][1];
+    };
+    auto decode_store = [&](uint32_t panel) {
+        auto left = [&]() {
+            uint32_t any = 0u;
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int w = 0; w < KW; ++w) any |= sel[h][w];
+            return any;
         };
-        next();
-        next();
-        while (s0 | s1) {
-            next();
-            next();
+        while (left()) {
+            decode_ask();
+            decode_add();
         }
-        out[0] = h0.x;
-        out[1] = h0.y;
-        out[2] = h1.x;
-        out[3] = h1.y;
+        uint32_t *out = reinterpret_cast<uint32_t *>(Mt + panel + drow * P256_MT_ROW + du * 16);
+        if constexpr (HALF) {
+            out[0] = dh[0].x;
+            out[1] = dh[0].y;
+            out[2] = dh[1].x;
+            out[3] = dh[1].y;
+        } else {
+            out[0] = dh[0].x;
+            out[1] = dh[0].y;
+            out[2] = dh[0].z;
+            out[3] = dh[0].w;
+        }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // landed before the next barrier
     };
 
@@ -267,7 +305,7 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
     } while (0)
 
     // ---- prologue: factor slices of panel 0, slabs 0 .. NS - 2 (the last one's X half follows in the first iteration)
-    if (tid < 2 * P256_HU * 2) *reinterpret_cast<uint32_t *>(Fz + (tid / (P256_HU * 2)) * P256_FZ_SET + FAST_MAX_K * P256_FZ_ROW + (tid % (P256_HU * 2)) * 4) = 0u;
+    if (tid < 2 * P256_HU * 2) *reinterpret_cast<uint32_t *>(Fz + (tid / (P256_HU * 2)) * P256_FZ_SET + 32 * P256_FZ_ROW + (tid % (P256_HU * 2)) * 4) = 0u;
     load_factors();
     constexpr int kProloguePieces = (NS - 2) * 4 + 2;
     static_for<NS - 1>([&](auto sc) {
@@ -281,74 +319,95 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
     });
     wait_loads<kProloguePieces>();
     __syncthreads();
-    decode_panel(0);
+    decode_words();
+    decode_store(0);
     wait_loads<kProloguePieces - 4>(); // slab 0
     __syncthreads();
     uint32_t mcur[2], mnext[2];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) mcur[b] = fetch_mask(0, b) >> (8 * lg);
+    for (int b = 0; b < 2; ++b) mcur[b] = fetch_mask(0, 0, b) >> (8 * lg);
     static_for<2>([&](auto b) { read_w(I0{}, I0{}, b); });
     static_for<4>([&](auto a) { read_x(I0{}, I0{}, a); });
-    static_for<2>([&](auto b) { mask_w(I0{}, b, mcur[decltype(b)::value]); });
+    static_for<2>([&](auto b) { mask_hi(I0{}, b, mask_lo(I0{}, b, mcur[decltype(b)::value])); });
 
-    // ---- main loop, unrolled by NS so that the stage of a slab is a compile-time constant.  Iteration s multiplies slab
-    // s out of stage s % NS in two steps.  Between them every wavefront waits until its own pieces of slab s + 1 have
-    // landed; the barrier makes the whole slab visible and tells that nobody reads slab s - 1 any more.
-    for (int s0 = 0; s0 < nslabs; s0 += NS) {
-        static_for<NS>([&](auto sc) {
-            constexpr int st = decltype(sc)::value;
+    // ---- main loop, unrolled by a panel (two rounds of the ring), so that the stage of a slab and its place in the panel are
+    // compile-time constants.  Iteration s multiplies slab s out of stage s % NS in two steps.  Between them every wavefront
+    // waits until its own pieces of slab s + 1 have landed; the barrier makes the whole slab visible and tells that nobody
+    // reads slab s - 1 any more.  What stands between two LRBI_SB() is issued there: the other instructions of a step, spread
+    // over its eight matrix instructions.
+    // (Behind the last panel one more is formed, from stand-ins, and not used: without tests the waits for operand reads stay
+    // exact.)
+    uint32_t mt_cur = 0, mt_next = P256_MT; // mask bytes of this panel and of the next one
+    for (int s0 = 0; s0 < nslabs; s0 += P256_PSLABS) {
+        static_for<P256_PSLABS>([&](auto sc) {
+            constexpr int ps = decltype(sc)::value;
+            constexpr int st = ps % NS;
             using St = std::integral_constant<int, st>;
             using St1 = std::integral_constant<int, (st + 1) % NS>;
             constexpr int stn = (st + NS - 1) % NS; // stage of slab s + NS - 1
             constexpr int stp = (st + NS - 2) % NS; // stage of slab s + NS - 2
-            const int s = s0 + st;
-            if (s < nslabs) {
+            if (s0 + ps < nslabs) {
+                uint32_t y;
                 // first step; the second step's operands
-                read_w(St{}, I1{}, I0{}); read_w(St{}, I1{}, I1{});
-                mma(I0{}, I0{}, I0{}); read_x(St{}, I1{}, I0{});
-                mma(I0{}, I0{}, I1{}); read_x(St{}, I1{}, I1{});
-                issue_piece(stp, I2{});
-                mma(I0{}, I1{}, I0{}); read_x(St{}, I1{}, I2{});
-                mma(I0{}, I1{}, I1{}); read_x(St{}, I1{}, I3{});
-                issue_piece(stp, I3{});
-                mnext[0] = fetch_mask(s + 1 < last ? s + 1 : last, 0);
-                mnext[1] = fetch_mask(s + 1 < last ? s + 1 : last, 1);
-                mma(I0{}, I2{}, I0{});
-                mask_w(I1{}, I0{}, mcur[0]);
-                mma(I0{}, I2{}, I1{});
-                mask_w(I1{}, I1{}, mcur[1]);
-                mma(I0{}, I3{}, I0{});
-                mma(I0{}, I3{}, I1{});
+                if constexpr (ps >= 3 && ps <= 5) decode_ask();
+                read_w(St{}, I1{}, I0{}); read_w(St{}, I1{}, I1{}); read_x(St{}, I1{}, I0{});
+                LRBI_SB();
+                mma(I0{}, I0{}, I0{}); read_x(St{}, I1{}, I1{});
+                LRBI_SB();
+                mma(I0{}, I0{}, I1{}); read_x(St{}, I1{}, I2{}); issue_piece(stp, I2{});
+                LRBI_SB();
+                mma(I0{}, I1{}, I0{}); read_x(St{}, I1{}, I3{}); issue_piece(stp, I3{});
+                LRBI_SB();
+                mma(I0{}, I1{}, I1{});
+                mnext[0] = fetch_mask(ps == P256_PSLABS - 1 ? mt_next : mt_cur, (ps + 1) % P256_PSLABS, 0);
+                mnext[1] = fetch_mask(ps == P256_PSLABS - 1 ? mt_next : mt_cur, (ps + 1) % P256_PSLABS, 1);
+                LRBI_SB();
+                mma(I0{}, I2{}, I0{}); y = mask_lo(I1{}, I0{}, mcur[0]);
+                LRBI_SB();
+                mma(I0{}, I2{}, I1{}); mask_hi(I1{}, I0{}, y);
+                LRBI_SB();
+                mma(I0{}, I3{}, I0{}); y = mask_lo(I1{}, I1{}, mcur[1]);
+                LRBI_SB();
+                mma(I0{}, I3{}, I1{}); mask_hi(I1{}, I1{}, y);
+                if constexpr (ps >= 3 && ps <= 5) decode_add();
+                LRBI_SB();
                 // factor slices of the next panel, asked for at the panel's first slab: landed, for every wavefront,
                 // behind the next iteration's wait and barrier
-                const int ps = (uint32_t)s % P256_PSLABS;
-                const int np = (uint32_t)s / P256_PSLABS + 1;
-                if (ps == 0 && np < npanels) {
+                if constexpr (ps == 0) {
                     load_factors();
                     wait_loads<(NS - 3) * 4 + P256_FACTOR_LOADS>(); // slab s + 1: everything older than these
                 } else
                     wait_loads<(NS - 3) * 4>();
                 LRBI_BARRIER();
                 // second step; the next slab's first operands
-                read_w(St1{}, I0{}, I0{}); read_w(St1{}, I0{}, I1{});
-                mma(I1{}, I0{}, I0{}); read_x(St1{}, I0{}, I0{});
-                mma(I1{}, I0{}, I1{}); read_x(St1{}, I0{}, I1{});
-                issue_piece(stn, I0{});
-                mma(I1{}, I1{}, I0{}); read_x(St1{}, I0{}, I2{});
-                mma(I1{}, I1{}, I1{}); read_x(St1{}, I0{}, I3{});
-                issue_piece(stn, I1{});
+                read_w(St1{}, I0{}, I0{}); read_w(St1{}, I0{}, I1{}); read_x(St1{}, I0{}, I0{});
+                LRBI_SB();
+                mma(I1{}, I0{}, I0{}); read_x(St1{}, I0{}, I1{});
+                LRBI_SB();
+                mma(I1{}, I0{}, I1{}); read_x(St1{}, I0{}, I2{}); issue_piece(stn, I0{});
+                LRBI_SB();
+                mma(I1{}, I1{}, I0{}); read_x(St1{}, I0{}, I3{}); issue_piece(stn, I1{});
+                LRBI_SB();
+                mma(I1{}, I1{}, I1{});
                 mcur[0] = mnext[0] >> (8 * lg);
                 mcur[1] = mnext[1] >> (8 * lg);
-                mma(I1{}, I2{}, I0{});
-                mask_w(I0{}, I0{}, mcur[0]);
-                mma(I1{}, I2{}, I1{});
-                mask_w(I0{}, I1{}, mcur[1]);
-                mma(I1{}, I3{}, I0{});
-                mma(I1{}, I3{}, I1{});
-                // mask of the next panel, formed at the panel's slab 2; first read at slab 7
-                if (ps == 2 && np < npanels) decode_panel(np);
+                LRBI_SB();
+                mma(I1{}, I2{}, I0{}); y = mask_lo(I0{}, I0{}, mcur[0]);
+                LRBI_SB();
+                mma(I1{}, I2{}, I1{}); mask_hi(I0{}, I0{}, y);
+                LRBI_SB();
+                mma(I1{}, I3{}, I0{}); y = mask_lo(I0{}, I1{}, mcur[1]);
+                LRBI_SB();
+                mma(I1{}, I3{}, I1{}); mask_hi(I0{}, I1{}, y);
+                LRBI_SB();
+                // mask of the next panel: written in front of slab 6's barrier, first read at slab 7
+                if constexpr (ps == 2) decode_words();
+                if constexpr (ps == 5) decode_store(mt_next);
             }
         });
+        const uint32_t t = mt_cur;
+        mt_cur = mt_next;
+        mt_next = t;
     }
 #undef LRBI_SB
 #undef LRBI_BARRIER
@@ -411,7 +470,12 @@ int launch_pipe256_gemm(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ld
     const int64_t blocks = mblocks * nblocks;
     if (blocks > 0x7FFFFFFF / P256_THREADS) return LRBI_ERR_SHAPE;
     const int y_vec_ok = (((uintptr_t)dY & 7) == 0) && (ldy % 4 == 0);
-    auto kern = dt == LRBI_F16 ? mfma_gemm_pipe256_kernel<F16Tag> : mfma_gemm_pipe256_kernel<BF16Tag>;
+    const bool half = (g.c % 128) != 0;
+    auto kern = dt == LRBI_F16
+                    ? (g.ipw == 1 ? (half ? mfma_gemm_pipe256_kernel<F16Tag, 1, true> : mfma_gemm_pipe256_kernel<F16Tag, 1, false>)
+                                  : (half ? mfma_gemm_pipe256_kernel<F16Tag, 2, true> : mfma_gemm_pipe256_kernel<F16Tag, 2, false>))
+                    : (g.ipw == 1 ? (half ? mfma_gemm_pipe256_kernel<BF16Tag, 1, true> : mfma_gemm_pipe256_kernel<BF16Tag, 1, false>)
+                                  : (half ? mfma_gemm_pipe256_kernel<BF16Tag, 2, true> : mfma_gemm_pipe256_kernel<BF16Tag, 2, false>));
     LRBI_SET_MAX_LDS(kern, SmemP256::bytes);
     LRBI_LAUNCH(kern, dim3((unsigned)blocks), dim3(P256_THREADS), SmemP256::bytes, stream, g, (const uint16_t *)dW, ldw, dIp,
                 dIz, (const uint16_t *)dX, ldx, (int)N, (uint16_t *)dY, ldy, (int)mblocks, (int)nblocks,
