@@ -807,6 +807,8 @@ int launch_grad(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, con
 {
     if (dt == LRBI_F32)
         return launch_f32_grad(g, (const float *)dDY, lddy, (const float *)dX, ldx, N, dIp, dIz, (float *)dDW, lddw, stream);
+    if (grad256_wins(g, N) && grad256_ok(g, dDY, lddy, dX, ldx, N))
+        return launch_grad256(g, dt, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, stream);
     const int64_t iblocks = (g.m + 127) / 128, jblocks = (g.n + BJ - 1) / BJ;
     const int64_t blocks = iblocks * jblocks;
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;

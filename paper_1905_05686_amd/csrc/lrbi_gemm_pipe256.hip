@@ -452,7 +452,11 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
     }
 }
 
-// Shapes that this kernel is chosen for, of those that pipe_shape_ok() admits: enough 256 x 256 tiles.
+// Shapes that this kernel is chosen for, of those that pipe_shape_ok() admits: a round of 256 x 256 tiles takes 2.2 to 2.5
+// times a round of 128 x 128 ones (bf16, rank 32, 512 x 512 tiles, us, 256 against 128: 4096 x 4096, N = 4096, 256 tiles:
+// 114 / 183; N = 3072, 192 tiles: 95 / 136; 6144 x 4096, N = 1536, 144 tiles: 89 / 121; 5120 x 4096, N = 4096, 320 tiles, two
+// rounds against five: 190 / 216; 4096 x 512, N = 4096: 26 / 43; 16384 x 16384, N = 1024: 440 / 642).  Below half a round of
+// them the smaller tiles have two rounds at most.
 bool pipe256_wins(const Geom &g, int64_t N)
 {
     if (!pipe_shape_ok(g)) return false;

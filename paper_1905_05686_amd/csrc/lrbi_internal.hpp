@@ -94,6 +94,12 @@ int launch_pipe_t_gemm(const Geom &g, int slices, int64_t iper, lrbi_dtype dt, c
 int launch_grad(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, const void *dX, int64_t ldx,
                 int64_t N, const uint32_t *dIp, const uint32_t *dIz, void *dDW, int64_t lddw, hipStream_t stream);
 
+// the weight gradient in 256 x 256 tiles (lrbi_grad256.hip): what it takes, and where it is the better choice
+bool grad256_ok(const Geom &g, const void *dDY, int64_t lddy, const void *dX, int64_t ldx, int64_t N);
+bool grad256_wins(const Geom &g, int64_t N);
+int launch_grad256(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, const void *dX, int64_t ldx, int64_t N,
+                   const uint32_t *dIp, const uint32_t *dIz, void *dDW, int64_t lddw, hipStream_t stream);
+
 struct MfmaPlan {
     int tile;     // tile variant id (1-based, see lrbi_gemm_mfma.hip)
     int bm, bn;   // workgroup tile

@@ -228,3 +228,27 @@ def test_nonfinite_operands_leave_the_finite_results_exact(long_side):
     assert np.array_equal(~np.isfinite(got[:, 3]), reached) and reached.any() and not reached.all()
     ref = product(W64, M, batch.astype(np.float64))[~reached, 3]
     assert orc.rel_err(got[~reached, 3].astype(np.float64), ref) <= 2.0 ** -24 * (1 + 1e-6)
+
+
+# gradients in 256 x 256 tiles (rounds of 256 tiles nearly full from 128 batch columns, one round of 144 and more from 512): an
+# odd number of 128-row blocks, a last column block cut off inside a half unit, two I_p words, half units of two tiles
+@pytest.mark.parametrize("m,n,r,c,k,N,dtype", [
+    (3968, 4032, 128, 64, 5, 128, "bf16"),
+    (4096, 4032, 256, 576, 40, 160, "f16"),
+    (2944, 3008, 128, 64, 64, 512, "bf16"),
+])
+def test_gradient_in_tiles_of_256(m, n, r, c, k, N, dtype):
+    cfg = workloads.Config("g256", m, n, r, c, k, 0.15, N, dtype, 0.05)
+    print("gradient, 256 x 256 tiles", cfg, flush=True)
+    data, dYs = _inputs(cfg)
+    desc = desc_of(cfg)
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], m, n, r, c, k)
+    ref = orc.masked_grad(workloads.to_float64(dYs, dtype), workloads.to_float64(data["X"], dtype), M)
+    for ldpad in (0, 8):
+        X, dY = _padded(to_device(data["X"], dtype), ldpad), _padded(to_device(dYs, dtype), ldpad)
+        dW = lrbi.masked_grad(desc, dY, X, dIp, dIz)
+        dWh = to_float64(dW)
+        assert orc.rel_err(dWh, ref) <= TOL[dtype]
+        assert not dWh[M == 0].any(), "pruned weights must get exactly zero"
+        assert torch.equal(dW.view(torch.int16), lrbi.masked_grad(desc, dY, X, dIp, dIz).view(torch.int16))
