@@ -505,6 +505,7 @@ struct LstmFuse {
     int64_t ldh2;
     int fp_words; // I_p words per tile column in LDS: 16 rows x ipw
     int fp_instr; // copy instructions for all of them
+    int units;    // hidden units of a workgroup (resident_lstm_kernel)
 };
 
 __device__ __forceinline__ float lstm_sigm(float z) { return 1.f / (1.f + expf(-z)); }
@@ -721,6 +722,240 @@ __global__ __launch_bounds__(ST_THREADS) void stream_lstm_kernel(Geom g, StreamA
     }
 }
 
+// The same step with everything asked for at once: all of X in LDS, W in registers.  The ring kernel above keeps two slabs of W
+// (16 KB) in flight per workgroup and walks them one memory round trip after another (6000 x 3000, 20 columns: 15.2 us, of
+// which the 36 MB of W need 7); here a wavefront asks for its share of the workgroup's rows, P pieces of 16 rows x 64 bytes
+// per block of 16 operand rows, in the layout in which the matrix instruction takes them, half of them ahead of the mask
+// rebuild, X and the rest behind it (a wavefront cannot issue while the memory pipeline is full, and it has to get to the
+// mask; two layers, 35 steps: half 1019 us, a quarter 1030, three quarters 1050, X ahead of the mask as well 1034).
+// One workgroup per compute unit: four hidden units (NB = 1 block of operand rows, row 4 gate + unit) or up to eight (NB = 2
+// blocks, row 8 gate + unit), so that a layer of up to 2048 units is one round.  Wavefront w takes the 32-column steps w, w +
+// 8, ..., as above: the sums are formed in the same order.
+// Two layers, 35 steps in a graph, us, here against the ring kernel: 1500 units, 300 x 300 tiles, rank 8, 20 columns 1019 /
+// 1084; 1024 units 613 / 722; 256 units, 100 x 100 tiles 391 / 458; 300 units, 1200 x 600 untiled, rank 145: 475 / 700.
+template <typename Tag, int NB, int P>
+__global__ __launch_bounds__(ST_THREADS) void resident_lstm_kernel(Geom g, StreamArgs a, LstmFuse f)
+{
+    constexpr int ROWS = 16 * NB, UB = NB == 1 ? 2 : 3, SLOTS = 1 << UB; // unit slots of a gate
+    extern __shared__ uint4 lrbi_dyn_smem[];
+    unsigned char *smem = (unsigned char *)lrbi_dyn_smem;
+    unsigned char *Xs = smem;                                   // x_stage bytes: [n][N], the last piece repeated to whole steps
+    uint32_t *Ms = (uint32_t *)(smem + a.x_stage);              // [ROWS][ms_pitch]: the rows' whole mask
+    uint32_t *Fz = Ms + ROWS * a.ms_pitch;                      // [4 gates][fz_pad]: [tile_cols][k][izw] each
+    uint32_t *Fp = Fz + 4 * a.fz_pad;                           // [tile_cols][ROWS][ipw]
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t j0 = (int64_t)blockIdx.x * f.units;
+    const int n = (int)g.n;
+    const int N = a.N;
+    const int nsteps = (n + 31) / 32;
+
+    // the cell state this lane will update (units x N <= 256 of them), asked for before anything else
+    const int my_unit = tid / N, my_b = tid - my_unit * N;
+    const bool have_cell = tid < f.units * N;
+    float c_prev = 0.f;
+    if (have_cell) c_prev = f.C[(j0 + my_unit) * f.ldc + my_b];
+
+    // Operand row rr = (gate << UB) + unit is row gate * H + j0 + unit of W (unit slots past the workgroup's units repeat the
+    // last one; their results are dropped).  The units of a gate lie in one tile row: gate_ti(), from row gate_il() of it on.
+    auto tile_row_of = [&](int gate) { return (int)((uint32_t)(gate * f.H + j0) / (uint32_t)g.r); };
+    const int ti0 = tile_row_of(0), ti1 = tile_row_of(1), ti2 = tile_row_of(2), ti3 = tile_row_of(3);
+    auto gate_ti = [=](int gate) {
+        const int lo = (gate & 1) ? ti1 : ti0, hi = (gate & 1) ? ti3 : ti2;
+        return (gate & 2) ? hi : lo;
+    };
+    auto gate_il = [&](int gate) { return (int)(uint32_t)(gate * f.H + j0) - gate_ti(gate) * g.r; };
+    auto slot_unit = [&](int rr) {
+        const int unit = rr & (SLOTS - 1);
+        return unit < f.units ? unit : f.units - 1;
+    };
+
+    // ---- factor copies: per gate the packed I_z of its tile row, then the I_p words, entry (tile column, operand row, word)
+    {
+        const int per_instr = a.fz_vec ? 256 : 64; // words per copy instruction
+        const int instr_per_gate = (a.fz_words + per_instr - 1) / per_instr;
+        for (int q = wave; q < 4 * instr_per_gate; q += ST_WAVES) {
+            const int gate = q & 3, chunk = q >> 2;
+            const uint32_t *zsrc = a.Iz + (int64_t)gate_ti(gate) * g.tile_cols * g.k * (int64_t)g.izw;
+            uint32_t *dst = Fz + gate * a.fz_pad + chunk * per_instr;
+            if (a.fz_vec) {
+                const int pieces = a.fz_words >> 2;
+                int p = chunk * 64 + lane;
+                if (p >= pieces) p = pieces - 1;
+                load_to_lds16(lds_address(dst), zsrc, 16u * (uint32_t)p);
+            } else {
+                int w = chunk * 64 + lane;
+                if (w >= a.fz_words) w = a.fz_words - 1;
+                load_to_lds4(lds_address(dst), zsrc, 4u * (uint32_t)w);
+            }
+        }
+        const int entries = g.tile_cols * f.fp_words;
+        for (int i = wave; i < f.fp_instr; i += ST_WAVES) {
+            int e = i * 64 + lane;
+            if (e >= entries) e = entries - 1;
+            const uint32_t q = g.ipw == 1 ? (uint32_t)e : (uint32_t)e / (uint32_t)g.ipw;
+            const uint32_t iw = (uint32_t)e - q * (uint32_t)g.ipw;
+            const int rr = (int)(q & (ROWS - 1)), tj = (int)(q / ROWS), gate = rr >> UB;
+            const uint32_t tile = (uint32_t)gate_ti(gate) * (uint32_t)g.tile_cols + (uint32_t)tj;
+            const uint32_t il = (uint32_t)(gate_il(gate) + slot_unit(rr));
+            load_to_lds4(lds_address(Fp + i * 64), a.Ip, ((tile * (uint32_t)g.r + il) * (uint32_t)g.ipw + iw) * 4u); // below 2^32: host
+        }
+    }
+
+    // ---- W: piece p of this wavefront = 32-column step wave + 8 p; lane (row16, kg) holds 8 columns of operand row row16
+    const int row16 = lane & 15, kg = lane >> 4;
+    const char *wrow[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) wrow[b] = (const char *)(a.W + (((16 * b + row16) >> UB) * f.H + j0 + slot_unit(row16)) * a.ldw);
+    u32x4 w[P][NB];
+    auto load_piece = [&](int p, int b) {
+        int col = (wave + ST_WAVES * p) * 32 + 8 * kg;
+        if (col > n - 8) col = n - 8; // (meets zero mask bits)
+        return *reinterpret_cast<const u32x4 *>(wrow[b] + (size_t)col * 2);
+    };
+    constexpr int H = P / 2;
+    static_for<H>([&](auto p) {
+        static_for<NB>([&](auto b) { w[decltype(p)::value][decltype(b)::value] = load_piece(p, b); });
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = tid; i < ROWS * a.ms_pitch; i += ST_THREADS) Ms[i] = 0u;
+#define LRBI_BARRIER()                                      \
+    do {                                                    \
+        __builtin_amdgcn_sched_barrier(0);                  \
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  \
+        __builtin_amdgcn_s_barrier();                       \
+        asm volatile("" ::: "memory");                      \
+        __builtin_amdgcn_sched_barrier(0);                  \
+    } while (0)
+    wait_loads<H * NB>(); // the factors
+    LRBI_BARRIER();
+
+    // ---- Eq. 3 from the factors in LDS.  Wavefront w takes the units w / 4, w / 4 + 2, ... of gate w % 4, all of them at a time,
+    // its lanes the (tile, word) pairs of their rows: the reads of up to four rows are in flight together.  (One row after
+    // another took 3 us of the step.)
+    {
+        constexpr int RU = 2 * NB;
+        const int gate = wave & 3;
+        const uint32_t items = (uint32_t)g.tile_cols * (uint32_t)g.izw;
+        const uint32_t *fz = Fz + gate * a.fz_pad;
+        for (uint32_t j = lane; j < items; j += 64) {
+            const uint32_t tj = (g.izw == 1) ? j : __umulhi(j, a.izw_magic);
+            const uint32_t wz = j - tj * (uint32_t)g.izw;
+            const int in_tile = (int)wz * 32;
+            const int col0 = (int)tj * g.c + in_tile;
+            if (in_tile >= g.c || col0 >= n) continue;
+            const uint32_t *zcol = fz + (size_t)tj * g.k * g.izw + wz;
+            const uint32_t *fp = Fp + tj * f.fp_words + ((gate << UB) + (wave >> 2)) * g.ipw;
+            uint32_t v[RU];
+#pragma unroll
+            for (int u = 0; u < RU; ++u) v[u] = 0u;
+            for (int iw = 0; iw < g.ipw; ++iw) {
+                uint32_t sel[RU], any = 0u;
+#pragma unroll
+                for (int u = 0; u < RU; ++u) any |= sel[u] = fp[2 * u * g.ipw + iw];
+                while (any) { // two ranks of each row; a row without one left reads the word of rank 0 and drops it
+                    any = 0u;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+#pragma unroll
+                        for (int u = 0; u < RU; ++u) {
+                            const uint32_t l = sel[u] ? (uint32_t)__builtin_ctz(sel[u]) : 0u;
+                            const uint32_t z = zcol[(32u * iw + l) * (uint32_t)g.izw];
+                            v[u] |= sel[u] ? z : 0u;
+                            sel[u] &= sel[u] - 1u;
+                        }
+#pragma unroll
+                    for (int u = 0; u < RU; ++u) any |= sel[u];
+                }
+            }
+            const int lim = (g.c - in_tile < n - col0) ? g.c - in_tile : n - col0;
+            const uint32_t keep = lim < 32 ? (1u << lim) - 1u : 0xFFFFFFFFu;
+            const int sh = col0 & 31;
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                const uint32_t m = v[u] & keep;
+                if (m == 0u) continue;
+                uint32_t *dst = Ms + ((gate << UB) + (wave >> 2) + 2 * u) * a.ms_pitch + (col0 >> 5);
+                __hip_atomic_fetch_or(dst, m << sh, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                if (sh && (m >> (32 - sh)))
+                    __hip_atomic_fetch_or(dst + 1, m >> (32 - sh), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (int i = wave; i < a.x_instr; i += ST_WAVES) {
+        uint32_t piece = 64u * i + lane;
+        if (piece >= a.x_pieces) piece = a.x_pieces - 1u; // stays inside X; meets zeroed weights only
+        load_to_lds16(lds_address(Xs) + 1024u * i, a.X, piece * 16u);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    static_for<P - H>([&](auto p) {
+        static_for<NB>([&](auto b) { w[H + decltype(p)::value][decltype(b)::value] = load_piece(H + p, b); });
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    wait_loads<(P - H) * NB>(); // X
+    LRBI_BARRIER();
+
+    // ---- arithmetic: 16 x 16 x 32 products, as in the ring kernel
+    f32x4 acc[NB][2];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b][0] = acc[b][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int nblocks = (N > 16) ? 2 : 1;
+    static_for<P>([&](auto pc) {
+        constexpr int p = decltype(pc)::value;
+        const int step = wave + ST_WAVES * p;
+        if (step < nsteps) {
+            const int kk = step * 32 + 8 * kg;
+            u32x4 am[NB];
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+                am[b] = apply_mask8(w[p][b], ((const unsigned char *)(Ms + (16 * b + row16) * a.ms_pitch))[step * 4 + kg]);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                if (cb >= nblocks) break;
+                const unsigned char *q = Xs + ((size_t)(kk + (row16 >> 2)) * N + cb * 16 + 4 * (row16 & 3)) * 2;
+                const u32x2 lo = lds_read_tr16_v((const uint16_t *)q);
+                const u32x2 hi = lds_read_tr16_v((const uint16_t *)(q + (size_t)4 * N * 2));
+                const u32x4 xf = {lo.x, lo.y, hi.x, hi.y};
+#pragma unroll
+                for (int b = 0; b < NB; ++b) acc[b][cb] = mfma_16x16x32(Tag{}, am[b], xf, acc[b][cb]);
+            }
+        }
+    });
+    LRBI_BARRIER(); // everyone has read X
+
+    // wavefronts' partial accumulators -> LDS; lane holds operand rows 4 kg + v of a block, column row16
+    float *red = (float *)smem; // [8][2][ROWS][16]
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red[((wave * 2 + cb) * ROWS + 16 * b + 4 * kg + v) * 16 + row16] = acc[b][cb][v];
+    LRBI_BARRIER();
+#undef LRBI_BARRIER
+    if (have_cell) {
+        const int cb = my_b >> 4, cc = my_b & 15;
+        float z[4];
+#pragma unroll
+        for (int gate = 0; gate < 4; ++gate) {
+            float v = 0.f;
+#pragma unroll
+            for (int wv = 0; wv < ST_WAVES; ++wv) v += red[((wv * 2 + cb) * ROWS + (gate << UB) + my_unit) * 16 + cc];
+            z[gate] = v;
+        }
+        const int64_t j = j0 + my_unit;
+        const float c = lstm_sigm(z[1]) * c_prev + lstm_sigm(z[0]) * tanhf(z[2]);
+        const float h = lstm_sigm(z[3]) * tanhf(c);
+        f.C[j * f.ldc + my_b] = c;
+        const uint16_t hs = cvt_store(Tag{}, h);
+        f.H1[j * f.ldh1 + my_b] = hs;
+        if (f.H2) f.H2[j * f.ldh2 + my_b] = hs;
+    }
+}
+
 // The kernel serves: f16 / bf16, N = 1 or a multiple of 4 up to 32, X contiguous ([n][N] with ldx = N) and 16-byte
 // aligned, W rows 16-byte aligned, n a multiple of 8, a tile row's packed I_z small enough for LDS, and enough rows to
 // give every compute unit a workgroup or so.
@@ -886,6 +1121,56 @@ static int launch_stream_lstm_t(const Geom &g, const StreamPlan &p, const LstmFu
     return LRBI_OK;
 }
 
+template <typename Tag, int NB>
+static int launch_resident_lstm_t(const Geom &g, const StreamPlan &p, const LstmFuse &f, int pieces, hipStream_t stream)
+{
+    auto kern = pieces <= 2 ? resident_lstm_kernel<Tag, NB, 2> : pieces <= 4 ? resident_lstm_kernel<Tag, NB, 4>
+              : pieces <= 6 ? resident_lstm_kernel<Tag, NB, 6> : pieces <= 8 ? resident_lstm_kernel<Tag, NB, 8>
+              : pieces <= 10 ? resident_lstm_kernel<Tag, NB, 10> : resident_lstm_kernel<Tag, NB, 12>;
+    LRBI_SET_MAX_LDS(kern, p.lds);
+    LRBI_LAUNCH(kern, dim3(p.grid), dim3(ST_THREADS), p.lds, stream, g, p.a, f);
+    return LRBI_OK;
+}
+
+// Plan of the step with everything resident: rows of up to 3072 columns, X and the factors in one compute unit's LDS, and a
+// number of hidden units per workgroup that divides H and the tile height (a gate's rows then lie in one tile row) and makes
+// at most one workgroup per compute unit.  Fills the fields of p.a and f that depend on it.
+static bool plan_resident_lstm(const Geom &g, int64_t H, int64_t B, int cus, StreamPlan &p, LstmFuse &f, int *pieces)
+{
+    const int64_t nsteps = (g.n + 31) / 32;
+    *pieces = (int)((nsteps + ST_WAVES - 1) / ST_WAVES);
+    if (*pieces > 12) return false;
+    int units = 0;
+    for (int u : {4, 5, 6, 7, 8})
+        if (H % u == 0 && g.r % u == 0 && H / u <= cus) {
+            units = u;
+            break;
+        }
+    if (units == 0) return false;
+    const int rows = units == 4 ? 16 : 32;
+    // (X of 128 KB per workgroup, 1024 units, 32 columns, 128 x 128 tiles of rank 32: 850 us a two-layer sequence of 35 steps
+    // against 836 in the ring kernel; 120 KB, 1536 units, 20 columns: 1052 against 1074)
+    const int64_t x_bytes = nsteps * 32 * B * 2;
+    if (x_bytes > 124 * 1024) return false;
+    const int x_instr = (int)((x_bytes + 1023) / 1024);
+    int64_t x_stage = (int64_t)x_instr * 1024 + 2 * ST_X_PAD;
+    const int64_t red = (int64_t)ST_WAVES * 2 * rows * 16 * 4;
+    if (x_stage < red) x_stage = red;
+    const int ms_pitch = (int)nsteps + 1 + ((nsteps + 1) % 2 == 0 ? 1 : 0); // odd
+    const int fp_words = rows * g.ipw, fp_instr = (g.tile_cols * fp_words + 63) / 64;
+    const size_t lds = (size_t)x_stage + ((size_t)rows * ms_pitch + (size_t)4 * p.a.fz_pad + (size_t)fp_instr * 64) * 4;
+    if (lds > 160 * 1024) return false;
+    p.a.x_instr = x_instr;
+    p.a.x_stage = (int)x_stage;
+    p.a.ms_pitch = ms_pitch;
+    f.fp_words = fp_words;
+    f.fp_instr = fp_instr;
+    f.units = units;
+    p.lds = lds;
+    p.grid = (unsigned)(H / units);
+    return true;
+}
+
 int launch_stream_lstm(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw, const uint32_t *dIp,
                        const uint32_t *dIz, const void *dXH, int64_t B, float *dC, int64_t ldc, void *dH1, int64_t ldh1,
                        void *dH2, int64_t ldh2, int cus, hipStream_t stream)
@@ -909,17 +1194,6 @@ int launch_stream_lstm(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw
     f.ldh2 = ldh2;
     f.fp_words = 16 * g.ipw;
     f.fp_instr = (g.tile_cols * f.fp_words + 63) / 64;
-    const size_t fixed = ((size_t)16 * a.ms_pitch + (size_t)4 * a.fz_pad + (size_t)f.fp_instr * 64) * 4;
-    int ns = 0;
-    for (int cand : {6, 4, 3}) {
-        if ((size_t)cand * (ST_WSTAGE + a.x_stage) + fixed <= 80 * 1024) {
-            ns = cand;
-            break;
-        }
-    }
-    if (ns == 0) return LRBI_ERR_SHAPE;
-    p.lds = (size_t)ns * (ST_WSTAGE + a.x_stage) + fixed;
-    p.grid = (unsigned)(H / 4);
     a.W = (const uint16_t *)dW;
     a.ldw = ldw;
     a.Ip = dIp;
@@ -934,6 +1208,31 @@ int launch_stream_lstm(const Geom &g, lrbi_dtype dt, const void *dW, int64_t ldw
     a.mask_out = nullptr;
     a.mask_pitch32 = 0;
     a.mask_words = 0;
+    {
+        StreamPlan rp = p;
+        LstmFuse rf = f;
+        int pieces = 0;
+        if (plan_resident_lstm(g, H, B, cus, rp, rf, &pieces)) {
+            if (dt == LRBI_F16)
+                return rf.units == 4 ? launch_resident_lstm_t<F16Tag, 1>(g, rp, rf, pieces, stream)
+                                     : launch_resident_lstm_t<F16Tag, 2>(g, rp, rf, pieces, stream);
+            if (dt == LRBI_BF16)
+                return rf.units == 4 ? launch_resident_lstm_t<BF16Tag, 1>(g, rp, rf, pieces, stream)
+                                     : launch_resident_lstm_t<BF16Tag, 2>(g, rp, rf, pieces, stream);
+            return LRBI_ERR_DTYPE;
+        }
+    }
+    const size_t fixed = ((size_t)16 * a.ms_pitch + (size_t)4 * a.fz_pad + (size_t)f.fp_instr * 64) * 4;
+    int ns = 0;
+    for (int cand : {6, 4, 3}) {
+        if ((size_t)cand * (ST_WSTAGE + a.x_stage) + fixed <= 80 * 1024) {
+            ns = cand;
+            break;
+        }
+    }
+    if (ns == 0) return LRBI_ERR_SHAPE;
+    p.lds = (size_t)ns * (ST_WSTAGE + a.x_stage) + fixed;
+    p.grid = (unsigned)(H / 4);
 #define LRBI_LSTM_NS(TAG)                                                     \
     switch (ns) {                                                             \
     case 6: return launch_stream_lstm_t<TAG, 6>(g, p, f, stream);             \

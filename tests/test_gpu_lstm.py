@@ -234,3 +234,19 @@ def test_lstm_sequence_on_the_rank_145_layer():
         ec = orc.rel_err(to_float64(c[l]), ref["c"][l])
         print("rank-145 layer %d: h err %.3e, c err %.3e" % (l, eh, ec), flush=True)
         assert eh <= 1e-2 and ec <= 1e-2
+
+
+# the step with X in LDS and W in registers: five to eight hidden units per workgroup, rows from one piece per wavefront to
+# twelve, X up to what is held and just beyond (the ring kernel), two I_p words, tiles cut through mask words
+@pytest.mark.parametrize("H,n,r,c,k,B,dtype", [
+    (1060, 72, 100, 40, 5, 4, "f16"),
+    (1500, 264, 300, 88, 8, 20, "bf16"),
+    (1764, 1000, 84, 96, 33, 32, "f16"),
+    (2048, 520, 128, 130, 6, 12, "bf16"),
+    (64, 3072, 64, 512, 16, 20, "f16"),
+    (64, 3080, 64, 512, 16, 20, "f16"),
+    (64, 1984, 64, 64, 40, 32, "bf16"),
+    (64, 1992, 64, 83, 8, 32, "f16"),
+])
+def test_lstm_step_with_everything_resident(H, n, r, c, k, B, dtype):
+    test_fused_lstm_step_small_shapes(H, n, r, c, k, B, dtype, 0)
