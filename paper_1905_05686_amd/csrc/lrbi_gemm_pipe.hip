@@ -34,7 +34,7 @@ static constexpr int STAGE_BYTES = 32768; // W: 128 rows x 128 bytes, then X: 64
 static constexpr int STAGE_X = 16384;
 static constexpr int MT_ROW = 72;                    // bytes per row of a mask panel: 64 + 8 (conflict-free 8-byte reads)
 static constexpr int MT_BYTES = PIPE_BM * MT_ROW;    // one mask panel
-static constexpr int FZ_ROWS = FAST_MAX_K + 1;       // I_z rows under a panel; row 64 stays zero
+static constexpr int FZ_ROWS = FAST_MAX_K + 2;       // I_z rows under a panel: 0 .. 31, a zero row, 32 .. 63, a zero row
 static constexpr int FZ_ROW_BYTES = PANEL_WORDS * 4; // 64
 
 template <int NS, bool HALF = false> struct SmemDma {
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     extern __shared__ uint4 lrbi_dyn_smem[];
     unsigned char *smem = (unsigned char *)lrbi_dyn_smem;
     unsigned char *Mt = smem + S::mt_off;                // [2][128][MT_ROW]  mask bytes of two panels
-    uint32_t *Fz = (uint32_t *)(smem + S::fz_off);       // [65][16]          I_z rows under the panel being decoded
+    uint32_t *Fz = (uint32_t *)(smem + S::fz_off);       // [66][16]          I_z rows under the panel being decoded
     uint32_t *Fip = (uint32_t *)(smem + S::fip_off);     // [128][4][2]       I_p words per row and 128-column unit
                                                          // (HALF: [128][8][2], per 64-column half unit)
 
@@ -92,7 +92,6 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     const int kend = (int)((kbeg + kper < g.n) ? kbeg + kper : g.n);
     const int nslabs = (kend - kbeg) / BK; // whole slabs only: n % 128 == 0, kper % 128 == 0
     const int last = nslabs - 1;
-    const int npanels = (nslabs + PANEL_SLABS - 1) / PANEL_SLABS;
     const int ti = (int)(m0 / g.r); // the workgroup's rows lie inside one tile row (r % 128 == 0)
     const int il0 = (int)(m0 - (int64_t)ti * g.r);
     const int64_t trow = (int64_t)ti * g.tile_cols;
@@ -263,49 +262,49 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     auto my_bytes = [&](uint32_t mk) -> uint32_t { return mk >> (8 * lg); };
 
     // ---- factor slices of one panel: global -> LDS (the same load-to-LDS form), then Eq. 3 for the panel.
-    // (ctj, coff): tile column and column offset inside it of the next panel to be loaded; a 128-column unit
-    // lies inside one tile (c % 128 == 0), so stepping by 128 lands exactly on tile borders.
+    // A lane fetches for one of the panel's 128-column units (HALF: 64-column half units), each inside one tile: fz_u of I_z,
+    // fp_u of I_p; (.tj, .off, .col): that unit's tile column, offset in it and first column, carried from panel to panel.
     // I_z: wavefronts 0 .. 3 fetch ranks 16 w .. + 15, lane = (rank, unit): the unit's four words of that
     // rank's row.  Ranks at or beyond k fetch rank 0 instead: no I_p bit selects them (pad bits are zero).
-    // Units beyond the reduction range fetch the range's first unit instead: their mask bytes are never read.
+    // Units beyond the reduction range fetch the tile row's first tile instead: their mask bytes are never read.
     // I_p: one word per lane, 256 bytes per instruction, two instructions per wavefront, image [row][unit][2];
     // with one word per row the second word's slot receives the first word again and is ignored below.
-    int ctj = kbeg / g.c, coff = kbeg - (kbeg / g.c) * g.c, ccol = kbeg;
-    const uint32_t zb_first = (uint32_t)((((trow + ctj) * g.k) * (int64_t)g.izw + (coff >> 5)) * 4);
-    const uint32_t pb_first = (uint32_t)((((trow + ctj) * g.r + il0) * (int64_t)g.ipw) * 4);
+    // (Per lane, not for all units with the lane's picked: a third of the instructions.)
+    struct Unit {
+        int col, tj, off;
+    };
+    auto unit_at = [&](int col) {
+        const int tj = col / g.c;
+        return Unit{col, tj, col - tj * g.c};
+    };
+    auto next_panel = [&](Unit &u) {
+        u.col += PW;
+        u.off += PW;
+        while (u.off >= g.c) {
+            u.off -= g.c;
+            ++u.tj;
+        }
+    };
+    Unit fz_u = unit_at(kbeg + (HALF ? 64 * ((lane >> 1) & 7) : 128 * (lane & 3)));
+    Unit fp_u = unit_at(kbeg + (HALF ? 64 * ((lane >> 1) & 7) : 128 * ((lane >> 1) & 3)));
+    const uint32_t izs = (uint32_t)(g.k * g.izw * 4), ips = (uint32_t)(g.r * g.ipw * 4); // bytes of a tile's factors
+    const uint32_t z_row = (uint32_t)trow * izs, p_row = (uint32_t)trow * ips + (uint32_t)(il0 * g.ipw * 4);
     const int fz_l = wq * 16 + (lane >> 2);
     const uint32_t fz_lane = (uint32_t)(((fz_l < g.k) ? fz_l : 0) * g.izw * 4);
-    const int fz_u = lane & 3;
     auto load_factors = [&]() {
+        const uint32_t zsel = z_row + (fz_u.col < kend ? (uint32_t)fz_u.tj * izs + (uint32_t)(fz_u.off >> 5) * 4u : 0u);
+        const uint32_t psel = p_row + (fp_u.col < kend ? (uint32_t)fp_u.tj * ips : 0u);
+        next_panel(fz_u);
+        next_panel(fp_u);
         if constexpr (HALF) {
             // per half unit (64 columns, two words of an I_z row): one word per lane.  I_z: instruction q of 16
             // (two per wavefront) fills ranks 4 q .. + 3, lane = (rank, half unit, word); I_p: image
             // [row][half unit][2], four instructions per wavefront.
-            constexpr int HU = 2 * PANEL_UNITS;
-            uint32_t zb[HU], pb[HU];
-#pragma unroll
-            for (int h = 0; h < HU; ++h) {
-                const bool ok = ccol < kend;
-                zb[h] = ok ? (uint32_t)((((trow + ctj) * g.k) * (int64_t)g.izw + (coff >> 5)) * 4) : zb_first;
-                pb[h] = ok ? (uint32_t)((((trow + ctj) * g.r + il0) * (int64_t)g.ipw) * 4) : pb_first;
-                ccol += 64;
-                coff += 64;
-                if (coff >= g.c) {
-                    coff = 0;
-                    ++ctj;
-                }
-            }
-            const int hu = (lane >> 1) & 7;
-            const uint32_t zlo = (hu & 2) ? ((hu & 1) ? zb[3] : zb[2]) : ((hu & 1) ? zb[1] : zb[0]);
-            const uint32_t zhi = (hu & 2) ? ((hu & 1) ? zb[7] : zb[6]) : ((hu & 1) ? zb[5] : zb[4]);
-            const uint32_t plo = (hu & 2) ? ((hu & 1) ? pb[3] : pb[2]) : ((hu & 1) ? pb[1] : pb[0]);
-            const uint32_t phi = (hu & 2) ? ((hu & 1) ? pb[7] : pb[6]) : ((hu & 1) ? pb[5] : pb[4]);
-            const uint32_t zsel = (hu & 4) ? zhi : zlo, psel = (hu & 4) ? phi : plo;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const int q = wave * 2 + i;
                 const int rank = q * 4 + (lane >> 4);
-                load_to_lds4(lds0 + (uint32_t)S::fz_off + (uint32_t)q * 256u, Iz,
+                load_to_lds4(lds0 + (uint32_t)S::fz_off + (uint32_t)(q * 256 + (q >= 8 ? FZ_ROW_BYTES : 0)), Iz,
                              zsel + (uint32_t)((((rank < g.k) ? rank : 0) * g.izw + (lane & 1)) * 4));
             }
             const int iw = (lane & 1) < g.ipw ? (lane & 1) : 0;
@@ -317,111 +316,92 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             }
             return;
         }
-        uint32_t zb[PANEL_UNITS], pb[PANEL_UNITS]; // byte offsets of each unit's tile slices (uniform)
-#pragma unroll
-        for (int u = 0; u < PANEL_UNITS; ++u) {
-            const bool ok = ccol < kend;
-            zb[u] = ok ? (uint32_t)((((trow + ctj) * g.k) * (int64_t)g.izw + (coff >> 5)) * 4) : zb_first;
-            pb[u] = ok ? (uint32_t)((((trow + ctj) * g.r + il0) * (int64_t)g.ipw) * 4) : pb_first;
-            ccol += 128;
-            coff += 128;
-            if (coff >= g.c) {
-                coff = 0;
-                ++ctj;
-            }
-        }
-        if (kg == 0) {
-            const uint32_t zsel = fz_u == 0 ? zb[0] : (fz_u == 1 ? zb[1] : (fz_u == 2 ? zb[2] : zb[3]));
-            load_to_lds16(lds0 + (uint32_t)S::fz_off + (uint32_t)wq * 1024u, Iz, zsel + fz_lane);
-        }
+        if (kg == 0) load_to_lds16(lds0 + (uint32_t)S::fz_off + (uint32_t)(wq * 1024 + (wq >= 2 ? FZ_ROW_BYTES : 0)), Iz, zsel + fz_lane);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int idx = (wave * 2 + i) * 64 + lane;
-            const int row = idx >> 3, u = (idx >> 1) & 3, iw = (idx & 1) < g.ipw ? (idx & 1) : 0;
-            const uint32_t psel = u == 0 ? pb[0] : (u == 1 ? pb[1] : (u == 2 ? pb[2] : pb[3]));
-            load_to_lds4(lds0 + (uint32_t)S::fip_off + (uint32_t)(wave * 2 + i) * 256u, Ip,
-                         psel + (uint32_t)((row * g.ipw + iw) * 4));
+            const int row = idx >> 3, iw = (idx & 1) < g.ipw ? (idx & 1) : 0;
+            load_to_lds4(lds0 + (uint32_t)S::fip_off + (uint32_t)(wave * 2 + i) * 256u, Ip, psel + (uint32_t)((row * g.ipw + iw) * 4));
         }
     };
-    // Eq. 3 for the panel.  A lane forms the 4 mask words of one row under one 128-column unit: it takes the row's
-    // I_p word(s), picks the first two set ranks without looking at memory (rank 64 = the zero row when there are
-    // fewer), and ORs their I_z pieces, both reads in flight together; rows with more set ranks (few: the factors
-    // are sparse) loop over the rest.
-    auto decode_panel = [&](int panel) {
-        const int row = tid >> 2, u = tid & 3;
-        unsigned char *out = Mt + (panel & 1) * MT_BYTES + row * MT_ROW + u * 16;
-        const uint32_t *fp = Fip + (row * PANEL_UNITS + u) * (HALF ? 4 : 2);
-        const uint32_t *fz = Fz + 4 * u;
-        uint4 a;
-        if constexpr (HALF) {
-            // the unit's two halves, each from the I_p word(s) and the two I_z words of its own tile
-            uint2 hv[2];
+    // Eq. 3 for the panel.  A lane forms the 4 mask words of one row under one 128-column unit (HALF: under its two half
+    // units, each from the factors of its own tile).  The set ranks are taken two at a time, over three slabs of the loop, so
+    // that the reads have come back when they are added (all at once took a tenth of a product's time); rows with more
+    // ranks than that (few: the factors are sparse) loop over the rest.  Ranks are found in one 32-bit word of I_p at a time,
+    // the first one and, where there is one, the second; a word without one left reads the zero row behind the word's
+    // rows, which is where counting its trailing zeros (32) leads.
+    constexpr int NH = HALF ? 2 : 1;
+    using zvec = std::conditional_t<HALF, u32x2, u32x4>;
+    const int drow = tid >> 2, du = tid & 3;
+    const unsigned char *dfz = (const unsigned char *)Fz + du * 16;
+    uint32_t sel[NH], sel2[NH]; // the word in work and the one that waits
+    uint32_t dbase = 0, dbase2 = 33 * FZ_ROW_BYTES;
+    zvec dz[NH][2], dh[NH];
+    auto decode_words = [&]() {
+        const uint32_t *fp = Fip + (drow * PANEL_UNITS + du) * (HALF ? 4 : 2);
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                unsigned long long sel = (unsigned long long)fp[2 * h];
-                if (g.ipw > 1) sel |= (unsigned long long)fp[2 * h + 1] << 32;
-                const uint32_t *fh = fz + 2 * h;
-                const int l0 = sel ? __builtin_ctzll(sel) : FAST_MAX_K;
-                sel &= sel - 1ull;
-                const int l1 = sel ? __builtin_ctzll(sel) : FAST_MAX_K;
-                sel &= sel - 1ull;
-                const uint2 z0 = *reinterpret_cast<const uint2 *>(fh + l0 * PANEL_WORDS);
-                const uint2 z1 = *reinterpret_cast<const uint2 *>(fh + l1 * PANEL_WORDS);
-                uint2 o = make_uint2(z0.x | z1.x, z0.y | z1.y);
-                while (sel) {
-                    const int le = __builtin_ctzll(sel);
-                    sel &= sel - 1ull;
-                    const uint2 ze = *reinterpret_cast<const uint2 *>(fh + le * PANEL_WORDS);
-                    o.x |= ze.x;
-                    o.y |= ze.y;
-                }
-                hv[h] = o;
+        for (int h = 0; h < NH; ++h) {
+            sel[h] = fp[2 * h];
+            sel2[h] = g.ipw > 1 ? fp[2 * h + 1] : 0u;
+            dh[h] = zvec(0u);
+        }
+        dbase = 0;
+        dbase2 = 33 * FZ_ROW_BYTES;
+    };
+    auto decode_other = [&](bool turn) { // the waiting word, if `turn`
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+            const uint32_t t = sel[h];
+            sel[h] = turn ? sel2[h] : t;
+            sel2[h] = turn ? t : sel2[h];
+        }
+        const uint32_t t = dbase;
+        dbase = turn ? dbase2 : t;
+        dbase2 = turn ? t : dbase2;
+    };
+    auto decode_ask = [&]() {
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const uint32_t l = sel[h] ? (uint32_t)__builtin_ctz(sel[h]) : 32u;
+                sel[h] &= sel[h] - 1u;
+                dz[h][e] = *reinterpret_cast<const zvec *>(dfz + dbase + l * FZ_ROW_BYTES + h * 8);
             }
-            a = make_uint4(hv[0].x, hv[0].y, hv[1].x, hv[1].y);
-        } else if (g.ipw == 1) { // ranks up to 32: one word
-            uint32_t sel = fp[0];
-            const int l0 = sel ? __builtin_ctz(sel) : FAST_MAX_K;
-            sel &= sel - 1u;
-            const int l1 = sel ? __builtin_ctz(sel) : FAST_MAX_K;
-            sel &= sel - 1u;
-            const uint4 z0 = *reinterpret_cast<const uint4 *>(fz + l0 * PANEL_WORDS);
-            const uint4 z1 = *reinterpret_cast<const uint4 *>(fz + l1 * PANEL_WORDS);
-            a = make_uint4(z0.x | z1.x, z0.y | z1.y, z0.z | z1.z, z0.w | z1.w);
-            while (sel) {
-                const int le = __builtin_ctz(sel);
-                sel &= sel - 1u;
-                const uint4 ze = *reinterpret_cast<const uint4 *>(fz + le * PANEL_WORDS);
-                a.x |= ze.x;
-                a.y |= ze.y;
-                a.z |= ze.z;
-                a.w |= ze.w;
-            }
-        } else {
-            unsigned long long sel = (unsigned long long)fp[0] | ((unsigned long long)fp[1] << 32);
-            const int l0 = sel ? __builtin_ctzll(sel) : FAST_MAX_K;
-            sel &= sel - 1ull;
-            const int l1 = sel ? __builtin_ctzll(sel) : FAST_MAX_K;
-            sel &= sel - 1ull;
-            const uint4 z0 = *reinterpret_cast<const uint4 *>(fz + l0 * PANEL_WORDS);
-            const uint4 z1 = *reinterpret_cast<const uint4 *>(fz + l1 * PANEL_WORDS);
-            a = make_uint4(z0.x | z1.x, z0.y | z1.y, z0.z | z1.z, z0.w | z1.w);
-            while (sel) {
-                const int le = __builtin_ctzll(sel);
-                sel &= sel - 1ull;
-                const uint4 ze = *reinterpret_cast<const uint4 *>(fz + le * PANEL_WORDS);
-                a.x |= ze.x;
-                a.y |= ze.y;
-                a.z |= ze.z;
-                a.w |= ze.w;
+    };
+    auto decode_add = [&]() {
+#pragma unroll
+        for (int h = 0; h < NH; ++h) dh[h] |= dz[h][0] | dz[h][1];
+    };
+    auto decode_store = [&](int panel) {
+        auto left = [&]() {
+            uint32_t any = sel[0];
+            if constexpr (HALF) any |= sel[1];
+            return any;
+        };
+        while (left()) {
+            decode_ask();
+            decode_add();
+        }
+        if (g.ipw > 1) {
+            decode_other(true);
+            while (left()) {
+                decode_ask();
+                decode_add();
             }
         }
+        uint4 a;
+        if constexpr (HALF) a = make_uint4(dh[0].x, dh[0].y, dh[1].x, dh[1].y);
+        else a = make_uint4(dh[0].x, dh[0].y, dh[0].z, dh[0].w);
+        unsigned char *out = Mt + (panel & 1) * MT_BYTES + drow * MT_ROW + du * 16;
         *reinterpret_cast<uint2 *>(out) = make_uint2(a.x, a.y);
         *reinterpret_cast<uint2 *>(out + 8) = make_uint2(a.z, a.w);
         if constexpr (EMIT) {
             // units past the end of this workgroup's reduction range were formed from stand-in factors: not stored
-            const int unit = kbeg / 128 + panel * PANEL_UNITS + u;
-            if (ni == 0 && unit * 128 < kend) mask_out[(m0 + row) * mask_pitch16 + unit] = a;
+            const int unit = kbeg / 128 + panel * PANEL_UNITS + du;
+            if (ni == 0 && unit * 128 < kend) mask_out[(m0 + drow) * mask_pitch16 + unit] = a;
         }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the mask bytes have landed before the next barrier
     };
 
     using I0 = std::integral_constant<int, 0>;
@@ -444,7 +424,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
 
     // ---- prologue: the factor slices of panel 0 first, then slabs 0 .. NS - 2; the panel is decoded as soon as the
     // factor slices are in (the slabs issued behind them stay in flight), and slab 0 is waited for after that
-    if (tid < PANEL_WORDS) Fz[FAST_MAX_K * PANEL_WORDS + tid] = 0u;
+    if (tid < 2 * PANEL_WORDS) Fz[(tid < PANEL_WORDS ? 32 : 64) * PANEL_WORDS + tid] = 0u; // rows 32 and 65
     load_factors();
     constexpr int kProloguePieces = SPREAD ? (NS - 2) * 4 + 2 : (NS - 1) * 4; // slab copies of this wavefront behind them
     static_for<NS - 1>([&](auto sc) {
@@ -458,9 +438,10 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     });
     wait_loads<kProloguePieces>();
     __syncthreads();
-    decode_panel(0);
-    // slab 0 (EMIT: the panel's mask store is one more, younger, entry of the same in-order count)
-    wait_loads<kProloguePieces - 4 + (EMIT ? 1 : 0)>();
+    decode_words();
+    decode_store(0);
+    // slab 0 (EMIT: a mask store, where there is one, is younger: the wait is one piece longer than it has to be)
+    wait_loads<kProloguePieces - 4>();
     __syncthreads();
     // entry state of the loop: X operands of this wavefront's first step, its W operand masked, the second read
     uint32_t mcur = my_bytes(fetch_mask(0));
@@ -475,42 +456,46 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         mask_hi(I0{}, I0{}, y);
     }
 
-    // ---- main loop, unrolled by NS so that the stage of a slab is a compile-time constant.
+    // ---- main loop, unrolled by a panel (two rounds of the ring), so that the stage of a slab and its place in the panel are
+    // compile-time constants.
     // Iteration s multiplies slab s out of stage s % NS: each wavefront its two 16-column steps.  After the
     // first step every wavefront waits until its own pieces of slab s + 1 have landed; the barrier makes the
     // whole slab visible and tells that nobody reads slab s - 1 any more; the second step then runs next to the
     // loads of slab s + NS - 1 into the stage slab s - 1 occupied and to the reads of slab s + 1's operands.
-    for (int s0 = 0; s0 < nslabs; s0 += NS) {
-        static_for<NS>([&](auto sc) {
-            constexpr int st = decltype(sc)::value;       // stage of slab s
+    // The next panel's mask is formed in any case, behind the last one from stand-ins (and not used): tests there would
+    // cost more than it does.
+    static_assert(PANEL_SLABS == 2 * NS, "two rounds of the ring");
+    for (int s0 = 0; s0 < nslabs; s0 += PANEL_SLABS) {
+        static_for<PANEL_SLABS>([&](auto sc) {
+            constexpr int ps = decltype(sc)::value;
+            constexpr int st = ps % NS;                   // stage of slab s
             constexpr int st1 = (st + 1) % NS;            // stage of slab s + 1
             constexpr int stn = (st + NS - 1) % NS;       // stage of slab s - 1 = stage of slab s + NS - 1
             constexpr int stp = (st + NS - 2) % NS;       // stage of slab s - 2 = stage of slab s + NS - 2
             using Par = std::integral_constant<int, st & 1>;        // register set of slab s's W operands
             using Nxt = std::integral_constant<int, (st & 1) ^ 1>;  // ... of slab s + 1's
-            const int s = s0 + st;
+            const int s = s0 + ps;
             if (s < nslabs) {
                 uint32_t y;
                 uint32_t mk;
                 // first step
+                if constexpr (ps == 4) decode_other(g.ipw > 1);
+                if constexpr (ps >= 3 && ps <= 5) decode_ask();
                 mma(Par{}, I0{}, I0{}); read_x(st, I1{}, I0{}); y = mask_lo(Par{}, I1{}, mcur);
                 mma(Par{}, I0{}, I1{}); read_x(st, I1{}, I1{}); mask_hi(Par{}, I1{}, y);
                 if constexpr (SPREAD) issue_piece(stp, I2{});
                 mma(Par{}, I0{}, I2{}); read_x(st, I1{}, I2{});
-                mk = fetch_mask(s + 1 < last ? s + 1 : last); // mask bytes of the next slab
+                mk = fetch_mask(s + 1); // mask bytes of the next slab (past the last one: not used)
                 mma(Par{}, I0{}, I3{}); read_x(st, I1{}, I3{});
                 if constexpr (SPREAD) issue_piece(stp, I3{});
+                if constexpr (ps >= 3 && ps <= 5) decode_add();
                 // factor slices of the next panel, requested at the panel's first slab: they have landed, for
                 // every wavefront, behind the next iteration's wait and barrier
-                const int ps = (uint32_t)s % PANEL_SLABS;
-                const int np = (uint32_t)s / PANEL_SLABS + 1;
-                // slab s + 1 has landed (four younger loads may still be in flight with four stages; EMIT: and the mask
-                // store of the panel that the previous iteration turned into mask bytes)
-                if (ps == 0 && np < npanels) {
+                if constexpr (ps == 0) {
                     load_factors();
-                    wait_loads<(NS - 3) * 4 + (HALF ? 6 : 2)>(); // (and the factor loads: two or three, HALF six)
-                } else if (EMIT && ps == 3 && np < npanels) wait_loads<(NS - 3) * 4 + 1>();
-                else wait_loads<(NS - 3) * 4>();
+                    wait_loads<(NS - 3) * 4 + (HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six)
+                } else
+                    wait_loads<(NS - 3) * 4>(); // slab s + 1 has landed (four younger loads may still be in flight)
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_x(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});
@@ -521,12 +506,9 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 if constexpr (!SPREAD) issue_piece(stn, I2{});
                 mma(Par{}, I1{}, I3{}); read_x(st1, I0{}, I3{}); mask_hi(Nxt{}, I0{}, y);
                 if constexpr (!SPREAD) issue_piece(stn, I3{});
-                // mask of the next panel, turned into mask bytes at the panel's slab 2; the first read of the new
-                // mask bytes is at slab 7
-                if (ps == 2 && np < npanels) {
-                    decode_panel(np);
-                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the mask bytes have landed before the next barrier
-                }
+                // mask of the next panel: its words at slab 2, written in front of slab 6's barrier, first read at slab 7
+                if constexpr (ps == 2) decode_words();
+                if constexpr (ps == 5) decode_store(s / PANEL_SLABS + 1);
             }
         });
     }
