@@ -830,7 +830,20 @@ static bool panel_ok(const Geom &g, int bm)
     return (g.c % 128 == 0) && (g.r % bm == 0) && (g.k <= FAST_MAX_K) && !g.ragged;
 }
 
-MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
+// Matrices that end inside a tile (or inside a 128-column unit) on tile shapes that the pipelined kernel lines up with: it
+// against the general kernel, bf16, us: 4100 x 9224 in 256 x 256 tiles, N = 128 27 / 42, N = 1024 163 / 236; 5000 x 5000 in 512
+// x 576, N = 200 30 / 80; 1280 x 1216 in 256 x 64, N = 1000 21 / 34; 640 x 320, N = 4000 12 / 14.5.  The general kernel, of which two
+// workgroups share a compute unit and which splits long sums, keeps several rounds of short ones (16000 x 400, N = 1000 50 /
+// 44; 8000 x 200, N = 2000 41 / 33; 16000 x 800, N = 1000 62 / 68) and narrow batches that the pipelined one's longer slices leave on few units (2048 x 1728, N = 64
+// 16.1 / 15.6).
+static bool cut_off_on_pipe(const Geom &g, int64_t N)
+{
+    const int64_t tiles = ((g.m + 127) / 128) * ((N + 127) / 128);
+    if (N <= 64 && tiles * (g.n / 512) < 64) return false;
+    return tiles <= 256 || g.n >= 4096;
+}
+
+MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces)
 {
     MfmaPlan p;
     int tile = (int)((flags & LRBI_FLAG_TILE_MASK) >> LRBI_FLAG_TILE_SHIFT);
@@ -846,7 +859,7 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
         // tile widths of 64 (2 j + 1): no panel kernel, so the pipelined kernel also takes 33 to 64 columns (half of its
         // column block idle, but W is streamed at the same rate: 4096 x 9216 in 512 x 576 tiles, N = 64, 25 us against
         // 40 us on the generic kernel); falls back to the generic kernel when X is not 16-byte readable
-        else if (N > 32 && pipe_shape_ok(g)) tile = 14;
+        else if (N > 32 && pipe_shape_ok(g) && ((!g.ragged && g.n % 128 == 0) || (x_pieces && cut_off_on_pipe(g, N)))) tile = 14;
         if (tile == 14) {
             if (pipe256_wins(g, N)) tile = kPipe256Tile;
         } else if (tile == 1) {
@@ -861,7 +874,7 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
         }
     }
     if (tile == kPipe256Tile) {
-        if (split > 1) tile = 14;
+        if (split > 1 || g.ragged) tile = 14;
         else split = 1;
     }
     p.tile = tile;
@@ -901,6 +914,8 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N)
             // unit, at least 8 slabs per slice), the 256-lane panel kernels two.
             const int64_t target = (tile >= 9) ? 256 : 512;
             want = (target + tiles - 1) / tiles;
+            // (a few workgroups more than that cost a second round: 4100 x 9224, N = 128, 33 tiles: 8 slices 38 us, 7 slices 27)
+            if (want * tiles > target) want = target / tiles;
         }
         if (want > cap) want = cap;
         if (want > 64) want = 64;
@@ -1064,7 +1079,7 @@ int launch_mfma_gemm(const Geom &g, const MfmaPlan &plan_in, lrbi_dtype dt, cons
     if (plan.tile >= kFirstPipeTile) {
         if (pipe_ok(g, dIz, dX, ldw, ldx, N)) {
             // (the mask as a by-product and the planes of a fused consumer come from the 128 x 128 form)
-            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr)
+            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr && !g.ragged)
                 return launch_pipe256_gemm(g, dt, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, stream);
             const int pf = plan.tile == kPipe256Tile ? 2 : plan.tile - kFirstPipeTile;
             const int rc = launch_pipe_gemm(g, plan, dt, pf, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, stream, mo);

@@ -58,7 +58,10 @@ static_assert(SmemDma<4, true>::bytes <= 160 * 1024, "LDS of a compute unit");
 // HALF: tile widths that are an odd multiple of 64 (the paper's 576-column tiles, Table 2): a 128-column unit may
 // then lie across two tile columns, so the factor slices are gathered, and Eq. 3 is evaluated, per 64-column half
 // unit, each with the I_p word and the I_z words of its own tile.  Everything behind the mask bytes is the same.
-template <typename Tag, int NS, bool SPREAD, bool SPLIT, bool CONV, bool EMIT = false, bool HALF = false>
+// RAG: matrices that end inside a tile, or whose rows end inside a 128-column unit.  Rows past the last one are fetched as the last one and not stored; in the last slab,
+// pieces of W past the last column and rows of X past the last one are fetched as the last ones and meet zero mask bits (the
+// mask words are cut at the last column).
+template <typename Tag, int NS, bool SPREAD, bool SPLIT, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false>
 __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     Geom g, const uint16_t *__restrict__ W, int64_t ldw, const uint32_t *__restrict__ Ip,
     const uint32_t *__restrict__ Iz, const uint16_t *__restrict__ X, int64_t ldx, int N,
@@ -68,7 +71,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     static_assert(NS == 4, "LDS stages (an even number: the W operand registers alternate with the slab's parity)");
     static_assert(!SPREAD || NS == 4, "loads spread over the iteration land one iteration later: four stages");
     constexpr int FN = PIPE_BN / 32; // 32-column blocks of the wave tile
-    static_assert(!(HALF && CONV), "half units: the plain product only");
+    static_assert(!(HALF && CONV) && !(RAG && CONV), "half units, cut-off tiles: the plain product only");
     using S = SmemDma<NS, HALF>;
 
     extern __shared__ uint4 lrbi_dyn_smem[];
@@ -90,7 +93,8 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     const int n0 = ni * PIPE_BN;
     const int kbeg = (int)(slice * kper);
     const int kend = (int)((kbeg + kper < g.n) ? kbeg + kper : g.n);
-    const int nslabs = (kend - kbeg) / BK; // whole slabs only: n % 128 == 0, kper % 128 == 0
+    // whole slabs only: n % 128 == 0 (RAG: n % 8 == 0, the last slab may be short), kper % 128 == 0
+    const int nslabs = RAG ? (kend - kbeg + BK - 1) / BK : (kend - kbeg) / BK;
     const int last = nslabs - 1;
     const int ti = (int)(m0 / g.r); // the workgroup's rows lie inside one tile row (r % 128 == 0)
     const int il0 = (int)(m0 - (int64_t)ti * g.r);
@@ -110,13 +114,17 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     // fills 4 rows; same chunk assignment.  (Half a wavefront of a transposing read takes 64 bytes of each of four
     // rows; LDS serves 256 bytes a clock from 64 banks, so the four have to lie 64 bytes apart: measured 256 bytes a
     // clock and compute unit with this swizzle, 128 with rows 32 bytes apart.)
-    uint32_t wvo[2], xvo[2];
+    uint32_t wvo[2], xvo[2], wvl[2], xvl[2]; // (.vl, RAG: in the last slab)
+    const int m_last = RAG && g.m - m0 < PIPE_BM ? (int)(g.m - m0) - 1 : PIPE_BM - 1;
+    const int k_left = kend - kbeg - last * BK; // columns of the last slab
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int chunk = wave + 8 * i;
         const int wr = chunk * 8 + (lane >> 3);
         const int wp = (lane & 7) ^ ((wr >> 1) & 7);
-        wvo[i] = (uint32_t)((wr * ldw + wp * 8) * 2);
+        const int wrow = RAG && wr > m_last ? m_last : wr;
+        wvo[i] = (uint32_t)((wrow * ldw + wp * 8) * 2);
+        if constexpr (RAG) wvl[i] = (uint32_t)((wrow * ldw + (wp * 8 < k_left ? wp * 8 : k_left - 8)) * 2);
         if constexpr (CONV) {
             // same image as W: 8 columns of X (128 bytes of channels each) per instruction
             const int xr = chunk * 8 + (lane >> 3);
@@ -134,6 +142,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             int nn = xp * 8;
             if (n0 + nn + 8 > N) nn = N - 8 - n0; // piece beyond N: fetch a valid piece instead, its columns are dropped
             xvo[i] = (uint32_t)((xr * ldx + nn) * 2);
+            if constexpr (RAG) xvl[i] = (uint32_t)(((xr < k_left ? xr : k_left - 1) * ldx + nn) * 2);
         }
     }
     const uint16_t *wbase = W + m0 * ldw + kbeg;
@@ -179,8 +188,8 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     auto issue_piece = [&](int stage, auto i_c) {
         constexpr int i = decltype(i_c)::value;
         const uint32_t sb = lds_w + (uint32_t)stage * STAGE_BYTES;
-        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wp, wvo[i]);
-        else load_to_lds16(sb + STAGE_X + (i - 2) * 8192u, xp, xvo[i - 2]);
+        if constexpr (i < 2) load_to_lds16(sb + i * 8192u, wp, RAG && wsl >= last ? wvl[i] : wvo[i]);
+        else load_to_lds16(sb + STAGE_X + (i - 2) * 8192u, xp, RAG && xsl >= last ? xvl[i - 2] : xvo[i - 2]);
         if constexpr (i == 1) next_w();
         if constexpr (i == 3) next_x();
     };
@@ -393,13 +402,20 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         uint4 a;
         if constexpr (HALF) a = make_uint4(dh[0].x, dh[0].y, dh[1].x, dh[1].y);
         else a = make_uint4(dh[0].x, dh[0].y, dh[0].z, dh[0].w);
+        if constexpr (RAG) { // whatever the factors hold beyond the last column stays out
+            const int left = kend - (kbeg + panel * PW + du * 128);
+            a.x &= bit_range(0, left < 0 ? 0 : (left < 32 ? left : 32));
+            a.y &= bit_range(0, left < 32 ? 0 : (left < 64 ? left - 32 : 32));
+            a.z &= bit_range(0, left < 64 ? 0 : (left < 96 ? left - 64 : 32));
+            a.w &= bit_range(0, left < 96 ? 0 : (left < 128 ? left - 96 : 32));
+        }
         unsigned char *out = Mt + (panel & 1) * MT_BYTES + drow * MT_ROW + du * 16;
         *reinterpret_cast<uint2 *>(out) = make_uint2(a.x, a.y);
         *reinterpret_cast<uint2 *>(out + 8) = make_uint2(a.z, a.w);
         if constexpr (EMIT) {
             // units past the end of this workgroup's reduction range were formed from stand-in factors: not stored
             const int unit = kbeg / 128 + panel * PANEL_UNITS + du;
-            if (ni == 0 && unit * 128 < kend) mask_out[(m0 + drow) * mask_pitch16 + unit] = a;
+            if (ni == 0 && unit * 128 < kend && drow <= m_last) mask_out[(m0 + drow) * mask_pitch16 + unit] = a;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); // the mask bytes have landed before the next barrier
     };
@@ -556,7 +572,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             // 4096 x 9216 matrix at 128 columns, most of it the end of this kernel)
             typedef float nt_f4 __attribute__((ext_vector_type(4)));
             nt_f4 ov = {o.x, o.y, o.z, o.w};
-            if (col < ldp) __builtin_nontemporal_store(ov, reinterpret_cast<nt_f4 *>(P + ((int64_t)slice * g.m + row0 + rr) * ldp + col));
+            if (col < ldp && (!RAG || row0 + rr < g.m)) __builtin_nontemporal_store(ov, reinterpret_cast<nt_f4 *>(P + ((int64_t)slice * g.m + row0 + rr) * ldp + col));
         }
     } else {
         constexpr int RS = 128 * 2 + 8;
@@ -578,6 +594,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             const uint2 lo = *reinterpret_cast<const uint2 *>(strip + rr * RS + l16 * 16);
             const uint2 hi = *reinterpret_cast<const uint2 *>(strip + rr * RS + l16 * 16 + 8);
             uint16_t *yp = Y + (row0 + rr) * ldy + col;
+            if (RAG && row0 + rr >= g.m) continue;
             if (y16 && col + 7 < N) {
                 *reinterpret_cast<uint4 *>(yp) = make_uint4(lo.x, lo.y, hi.x, hi.y);
             } else {
@@ -591,11 +608,11 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
 }
 
 // tile shapes the pipelined kernel's blocking lines up with: tile rows in blocks of 128, tile widths a multiple of
-// 128, or of 64 (gathered per half unit) when the row length is still a multiple of 128
+// 128, or of 64 (gathered per half unit); the matrix may end inside a tile, its rows are whole 16-byte pieces
 bool pipe_shape_ok(const Geom &g)
 {
-    if ((g.r % PIPE_BM) != 0 || g.k > FAST_MAX_K || g.ragged) return false;
-    return (g.c % 128) == 0 || ((g.c % 64) == 0 && (g.n % 128) == 0);
+    if ((g.r % PIPE_BM) != 0 || g.k > FAST_MAX_K) return false;
+    return (g.c % 64) == 0 && g.n % 8 == 0;
 }
 
 // true when the pipelined kernel serves this call: aligned tile shapes, X readable in 16-byte pieces, offsets
@@ -612,12 +629,12 @@ bool pipe_ok(const Geom &g, const void *dIz, const void *dX, int64_t ldw, int64_
     return true;
 }
 
-template <typename Tag, int NS, bool SPREAD, bool CONV, bool EMIT = false, bool HALF = false>
+template <typename Tag, int NS, bool SPREAD, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false>
 static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, int64_t ldw, const uint32_t *dIp,
                          const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY, int64_t ldy,
                          void *dWorkspace, const ConvGeom &cg, hipStream_t stream, MaskOut mo = {nullptr, 0})
 {
-    const int64_t mblocks = g.m / PIPE_BM;
+    const int64_t mblocks = (g.m + PIPE_BM - 1) / PIPE_BM;
     const int64_t nblocks = (N + PIPE_BN - 1) / PIPE_BN;
     const int64_t blocks = mblocks * nblocks * plan.splitk;
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
@@ -626,8 +643,8 @@ static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, in
     const int xcd_remap = (blocks % 8 == 0) ? 1 : 0;
     const int64_t ldp = (N + 3) / 4 * 4;
     const size_t smem = SmemDma<NS, HALF>::bytes;
-    auto kern = split ? mfma_gemm_pipe_kernel<Tag, NS, SPREAD, true, CONV, EMIT, HALF>
-                      : mfma_gemm_pipe_kernel<Tag, NS, SPREAD, false, CONV, EMIT, HALF>;
+    auto kern = split ? mfma_gemm_pipe_kernel<Tag, NS, SPREAD, true, CONV, EMIT, HALF, RAG>
+                      : mfma_gemm_pipe_kernel<Tag, NS, SPREAD, false, CONV, EMIT, HALF, RAG>;
     LRBI_SET_MAX_LDS(kern, smem);
     LRBI_LAUNCH(kern, dim3((unsigned)blocks), dim3(PIPE_THREADS), smem, stream, g, (const uint16_t *)dW, ldw, dIp, dIz,
                 (const uint16_t *)dX, ldx, (int)N, (uint16_t *)dY, ldy, (float *)dWorkspace, ldp, (int)mblocks,
@@ -643,6 +660,21 @@ int launch_pipe_gemm(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, int var
                      int64_t ldy, void *dWorkspace, hipStream_t stream, MaskOut mo)
 {
     const ConvGeom none = {0, 0, 0};
+    if (g.ragged || g.n % 128 != 0) { // cut-off tiles or panels: one variant per dtype and kind of unit, with or without the mask
+#define LRBI_PIPE_RAG(TAG, EM, HF)                                                                                           \
+    launch_pipe_t<TAG, 4, true, false, EM, HF, true>(g, plan, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, none, stream, mo)
+        const bool half = g.c % 128 != 0;
+        if (dt == LRBI_F16) {
+            if (mo.ptr) return half ? LRBI_PIPE_RAG(F16Tag, true, true) : LRBI_PIPE_RAG(F16Tag, true, false);
+            return half ? LRBI_PIPE_RAG(F16Tag, false, true) : LRBI_PIPE_RAG(F16Tag, false, false);
+        }
+        if (dt == LRBI_BF16) {
+            if (mo.ptr) return half ? LRBI_PIPE_RAG(BF16Tag, true, true) : LRBI_PIPE_RAG(BF16Tag, true, false);
+            return half ? LRBI_PIPE_RAG(BF16Tag, false, true) : LRBI_PIPE_RAG(BF16Tag, false, false);
+        }
+#undef LRBI_PIPE_RAG
+        return LRBI_ERR_DTYPE;
+    }
     if (g.c % 128 != 0) { // half units: one variant per dtype (loads spread over the iteration), with or without the mask
 #define LRBI_PIPE_ARGS g, plan, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, none, stream, mo
         if (dt == LRBI_F16)

@@ -459,7 +459,7 @@ __global__ __launch_bounds__(P256_THREADS) LRBI_WAVES_PER_SIMD(2) void mfma_gemm
 // them the smaller tiles have two rounds at most.
 bool pipe256_wins(const Geom &g, int64_t N)
 {
-    if (!pipe_shape_ok(g)) return false;
+    if (!pipe_shape_ok(g) || g.ragged) return false;
     constexpr int64_t cus = 256;
     const int64_t t256 = ((g.m + 255) / 256) * ((N + 255) / 256), t128 = (g.m / 128) * ((N + 127) / 128);
     const int64_t r256 = (t256 + cus - 1) / cus, r128 = (t128 + cus - 1) / cus;

@@ -223,6 +223,8 @@ extern "C" int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtyp
     if (use_mfma(desc, dtype, N)) {
         const Geom g = make_geom(desc);
         *bytes = plan_mfma(g, desc->flags, N).workspace_bytes;
+        const uint64_t pieces = plan_mfma(g, desc->flags, N, true).workspace_bytes; // whichever kernel X's address leads to
+        if (pieces > *bytes) *bytes = pieces;
     }
     return LRBI_OK;
 }
@@ -277,13 +279,14 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
     if (!mfma)
         return launch_valu_gemm(g, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
                                 dX, ldx, N, dY, ldy, s);
-    MfmaPlan plan = plan_mfma(g, desc->flags, N);
+    const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
+    MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
     if (plan.splitk > 1) {
         const bool ws_ok = dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= plan.workspace_bytes;
         if (!ws_ok) {
             if (desc->flags & LRBI_FLAG_SPLITK_MASK) return LRBI_ERR_WORKSPACE;
             // no scratch: fall back to one slice over the whole n range
-            plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N);
+            plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N, pieces);
         }
     }
     return launch_mfma_gemm(g, plan, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
@@ -324,12 +327,13 @@ extern "C" int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, con
     // their own use and store it on the way (the workgroups of the first block of batch columns do).
     if (use_mfma(desc, dtype, N) && aligned_to(dW, 16) && ldw % 8 == 0 && desc->n % 8 == 0) {
         const Geom g = make_geom(desc);
-        MfmaPlan plan = plan_mfma(g, desc->flags, N);
+        const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
+        MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
         if (plan.splitk > 1) {
             const bool ws_ok = dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= plan.workspace_bytes;
             if (!ws_ok) {
                 if (desc->flags & LRBI_FLAG_SPLITK_MASK) return LRBI_ERR_WORKSPACE;
-                plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N);
+                plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N, pieces);
             }
         }
         if (mfma_gemm_emits_mask(g, plan, dW, ldw, dIz_packed, dX, ldx, N))

@@ -111,7 +111,9 @@ struct MfmaPlan {
     bool planes_only = false;
     bool split_optional = false; // the tiles alone fill the chip: the slices are for evening out, not needed
 };
-MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N);
+// x_pieces: the pipelined kernel can read X (pipe_ok()); asked for shapes that it only takes in its cut-off form, whose
+// alternative, the general kernel, is planned differently
+MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces = false);
 // Where the tile kernel leaves the decoded mask as a by-product (rows of 16-byte pieces, one bit per weight), or {nullptr, 0}.
 struct MaskOut {
     void *ptr;

@@ -434,3 +434,38 @@ def test_tiles_of_256(m, n, r, c, k, N, dtype):
     Y2 = _run(cfg, data, flags=lrbi.flag_tile(14))
     _assert_close(Y2, ref, dtype, "128 x 128")
     assert torch.equal(Y, _run(cfg, data, flags=lrbi.flag_tile(15), ldpad=8))
+
+
+# the pipelined kernel on matrices that end inside a tile: last rows, last slab and last panel cut at every kind of place, one
+# tile larger than the matrix, half units, split and not, the mask stored as well, junk in what cut-off tiles do not use
+@pytest.mark.parametrize("m,n,r,c,k,N,dtype", [
+    (260, 520, 128, 128, 8, 96, "f16"),
+    (127, 8, 128, 64, 5, 40, "bf16"),
+    (129, 72, 256, 64, 33, 136, "f16"),
+    (300, 1096, 128, 192, 40, 64, "bf16"),
+    (513, 2312, 256, 576, 16, 128, "f16"),
+    (255, 632, 256, 1024, 9, 72, "bf16"),
+    (384, 576, 128, 192, 12, 264, "f16"),
+    (4100, 520, 512, 256, 16, 1032, "bf16"),
+])
+def test_pipelined_kernel_on_cut_off_tiles(m, n, r, c, k, N, dtype):
+    print("pipelined kernel, cut-off tiles", m, n, r, c, k, N, dtype, flush=True)
+    cfg = workloads.Config("rag", m, n, r, c, k, 0.12, N, dtype, 0.05)
+    data = workloads.make(cfg)
+    ref, M = _oracle(cfg, data)
+    for ldpad in (0, 8):
+        for use_workspace in (True, False):
+            _assert_close(_run(cfg, data, use_workspace=use_workspace, ldpad=ldpad), ref, dtype, "cut off")
+    # factors packed as for whole tiles: bits outside the matrix are there and must be ignored
+    desc = desc_of(cfg)
+    ip, iz = lrbi.pack_factors(lrbi.Desc(-(-m // r) * r, -(-n // c) * c, r, c, k), data["Ip01"], data["Iz01"])
+    dIp, dIz = torch.from_numpy(ip.view(np.int32)).to(dev()), torch.from_numpy(iz.view(np.int64)).to(dev())
+    mask = torch.full((m, 16 * ((n + 127) // 128) + 16), 0x5A, dtype=torch.uint8, device=dev())
+    out, Y = lrbi.decode_and_gemm(desc, to_device(data["W"], dtype), dIp, dIz, to_device(data["X"], dtype), mask=mask,
+                                  workspace=workspace_for(desc, DT_CODE[dtype], N))
+    torch.cuda.synchronize()
+    _assert_close(Y, ref, dtype, "cut off, mask stored")
+    bits = unpack_device_mask(out, n)
+    used = 128 * ((n + 127) // 128)
+    assert np.array_equal(bits[:, :n], M) and not bits[:, n:used].any()
+    assert (out.cpu().numpy()[:, used // 8:] == 0x5A).all()
