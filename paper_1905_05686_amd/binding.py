@@ -176,17 +176,44 @@ def unpack_mask(desc: Desc, mask_bytes: np.ndarray) -> np.ndarray:
     return out
 
 
-def _stream_ptr(stream):
+# What a call asks of torch besides its tensors, looked up at the first call (the package imports without torch).  A call on a
+# small layer is shorter than its marshalling was (500 x 800 f32, one column: kernel 5.0 us, call 10.3, of which the current
+# stream's Python object, three imports and a dozen c_void_p objects): plain integers go to the library, the current
+# stream's handle comes without an object around it.
+_codes = None
+_current_stream = None
+
+
+def _look_up_torch():
+    global _codes, _current_stream
     import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+    if raw and device:
+        _current_stream = lambda: raw(device())  # noqa: E731
+    else:
+        _current_stream = lambda: torch.cuda.current_stream().cuda_stream  # noqa: E731
+    _codes = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
+
+
+def _stream_ptr(stream):
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_stream is None:
+        _look_up_torch()
+    return _current_stream()
 
 
 def _dev_ptr(t, what):
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % what)
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+def _scratch(workspace):
+    """Address and size of an optional workspace."""
+    if workspace is None:
+        return None, 0
+    return _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size()
 
 
 def default_pitch(n: int) -> int:
@@ -209,8 +236,9 @@ def decode_mask(desc: Desc, dIp, dIz, out=None, pitch_bytes=None, stream=None):
 
 
 def _dtype_code(t):
-    import torch
-    return {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}[t.dtype]
+    if _codes is None:
+        _look_up_torch()
+    return _codes[t.dtype]
 
 
 def masked_gemm_workspace_bytes(desc: Desc, dtype_code: int, N: int) -> int:
@@ -220,57 +248,62 @@ def masked_gemm_workspace_bytes(desc: Desc, dtype_code: int, N: int) -> int:
     return out.value
 
 
+def _product_operands(desc, W, X):
+    """The checks of a product's operands; N and the two leading dimensions."""
+    n, xs = desc.n, X.shape
+    if W.dim() != 2 or len(xs) != 2 or W.shape != (desc.m, n) or xs[0] != n:
+        raise ValueError("shape mismatch")
+    N = xs[1]
+    (ldw, w1), (ldx, x1) = W.stride(), X.stride()
+    if w1 != 1 or (N > 1 and x1 != 1) or W.dtype != X.dtype:
+        raise ValueError("W and X must be row-major tensors of the same dtype")
+    return N, ldw, ldx
+
+
+def _row_major_out(out, rows, cols, like):
+    """The output tensor [rows, cols] (made here when there is none) and its leading dimension."""
+    if out is None:
+        import torch
+        out = torch.empty((rows, cols), dtype=like.dtype, device=like.device)
+    if out.shape != (rows, cols) or out.dtype != like.dtype:
+        raise ValueError("bad out tensor")
+    ld, inner = out.stride()
+    if cols > 1 and inner != 1:
+        raise ValueError("bad out tensor")
+    return out, ld
+
+
 def masked_gemm(desc: Desc, W, dIp, dIz, X, out=None, workspace=None, stream=None):
     """lrbi_masked_gemm: Y = (W o decode(Ip, Iz)) X.  W [m, n], X [n, N] (or [n]),
     row-major device tensors of one dtype; rows may be padded (stride(0) >= width)."""
-    import torch
     squeeze = X.dim() == 1
     if squeeze:
         X = X.unsqueeze(1)
-    if W.dim() != 2 or X.dim() != 2 or W.shape != (desc.m, desc.n) or X.shape[0] != desc.n:
-        raise ValueError("shape mismatch")
-    if W.stride(1) != 1 or (X.shape[1] > 1 and X.stride(1) != 1) or W.dtype != X.dtype:
-        raise ValueError("W and X must be row-major tensors of the same dtype")
-    N = X.shape[1]
-    if out is None:
-        out = torch.empty((desc.m, N), dtype=W.dtype, device=W.device)
-    if out.shape != (desc.m, N) or out.dtype != W.dtype or (N > 1 and out.stride(1) != 1):
-        raise ValueError("bad out tensor")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size()
+    N, ldw, ldx = _product_operands(desc, W, X)
+    out, ldy = _row_major_out(out, desc.m, N, W)
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().lrbi_masked_gemm(
-        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), W.stride(0), _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
-        _dev_ptr(X, "X"), X.stride(0), N, _dev_ptr(out, "Y"), out.stride(0), ws_ptr, ws_bytes, _stream_ptr(stream)),
-        "lrbi_masked_gemm")
+        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), ldw, _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
+        _dev_ptr(X, "X"), ldx, N, _dev_ptr(out, "Y"), ldy, ws_ptr, ws_bytes, _stream_ptr(stream)), "lrbi_masked_gemm")
     return out[:, 0] if squeeze else out
 
 
 def decode_and_gemm(desc: Desc, W, dIp, dIz, X, out=None, mask=None, pitch_bytes=None, workspace=None, stream=None):
     """lrbi_decode_and_gemm: the packed mask [m, pitch] (uint8) and Y = (W o mask) X from one call; arguments as
     for decode_mask and masked_gemm.  Returns (mask, Y)."""
-    import torch
-    if W.dim() != 2 or X.dim() != 2 or W.shape != (desc.m, desc.n) or X.shape[0] != desc.n:
-        raise ValueError("shape mismatch")
-    if W.stride(1) != 1 or (X.shape[1] > 1 and X.stride(1) != 1) or W.dtype != X.dtype:
-        raise ValueError("W and X must be row-major tensors of the same dtype")
-    N = X.shape[1]
-    if out is None:
-        out = torch.empty((desc.m, N), dtype=W.dtype, device=W.device)
-    if out.shape != (desc.m, N) or out.dtype != W.dtype or (N > 1 and out.stride(1) != 1):
-        raise ValueError("bad out tensor")
+    N, ldw, ldx = _product_operands(desc, W, X)
+    out, ldy = _row_major_out(out, desc.m, N, W)
     if pitch_bytes is None:
         pitch_bytes = mask.shape[1] if mask is not None else default_pitch(desc.n)
+    import torch
     if mask is None:
         mask = torch.empty((desc.m, pitch_bytes), dtype=torch.uint8, device=W.device)
     if mask.dtype != torch.uint8 or not mask.is_contiguous() or mask.shape != (desc.m, pitch_bytes):
         raise ValueError("mask must be a contiguous uint8 [m, pitch_bytes] tensor")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size()
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().lrbi_decode_and_gemm(
-        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), W.stride(0), _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
-        _dev_ptr(X, "X"), X.stride(0), N, _dev_ptr(out, "Y"), out.stride(0), _dev_ptr(mask, "mask"), int(pitch_bytes),
+        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), ldw, _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
+        _dev_ptr(X, "X"), ldx, N, _dev_ptr(out, "Y"), ldy, _dev_ptr(mask, "mask"), int(pitch_bytes),
         ws_ptr, ws_bytes, _stream_ptr(stream)), "lrbi_decode_and_gemm")
     return mask, out
 
@@ -298,9 +331,7 @@ def masked_conv3x3(desc: Desc, W, dIp, dIz, act_padded, out=None, workspace=None
         out = torch.empty((desc.m, N), dtype=W.dtype, device=W.device)
     if out.shape != (desc.m, N) or out.dtype != W.dtype or out.stride(1) != 1:
         raise ValueError("bad out tensor")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size()
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().lrbi_masked_conv3x3(
         ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), W.stride(0), _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
         _dev_ptr(act_padded, "act"), batch, H, Wd, cin, _dev_ptr(out, "Y"), out.stride(0), ws_ptr, ws_bytes,
@@ -423,42 +454,38 @@ def masked_gemm_t_workspace_bytes(desc: Desc, dtype_code: int, N: int) -> int:
 def masked_gemm_t(desc: Desc, W, dIp, dIz, dY, out=None, workspace=None, stream=None):
     """lrbi_masked_gemm_t: dX = (W o decode(Ip, Iz))^T dY.  W [m, n], dY [m, N] row-major device tensors of one
     dtype (rows may be padded); returns dX [n, N]."""
-    import torch
-    if W.dim() != 2 or dY.dim() != 2 or W.shape != (desc.m, desc.n) or dY.shape[0] != desc.m:
+    m, n, ys = desc.m, desc.n, dY.shape
+    if W.dim() != 2 or len(ys) != 2 or W.shape != (m, n) or ys[0] != m:
         raise ValueError("shape mismatch")
-    if W.stride(1) != 1 or (dY.shape[1] > 1 and dY.stride(1) != 1) or W.dtype != dY.dtype:
+    N = ys[1]
+    (ldw, w1), (lddy, y1) = W.stride(), dY.stride()
+    if w1 != 1 or (N > 1 and y1 != 1) or W.dtype != dY.dtype:
         raise ValueError("W and dY must be row-major tensors of the same dtype")
-    N = dY.shape[1]
-    if out is None:
-        out = torch.empty((desc.n, N), dtype=W.dtype, device=W.device)
-    if out.shape != (desc.n, N) or out.dtype != W.dtype or (N > 1 and out.stride(1) != 1):
-        raise ValueError("bad out tensor")
-    ws_ptr, ws_bytes = ctypes.c_void_p(0), 0
-    if workspace is not None:
-        ws_ptr, ws_bytes = _dev_ptr(workspace, "workspace"), workspace.numel() * workspace.element_size()
+    out, lddx = _row_major_out(out, n, N, W)
+    ws_ptr, ws_bytes = _scratch(workspace)
     _check(load_library().lrbi_masked_gemm_t(
-        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), W.stride(0), _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
-        _dev_ptr(dY, "dY"), dY.stride(0), N, _dev_ptr(out, "dX"), out.stride(0), ws_ptr, ws_bytes,
-        _stream_ptr(stream)), "lrbi_masked_gemm_t")
+        ctypes.byref(desc), _dtype_code(W), _dev_ptr(W, "W"), ldw, _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"),
+        _dev_ptr(dY, "dY"), lddy, N, _dev_ptr(out, "dX"), lddx, ws_ptr, ws_bytes, _stream_ptr(stream)),
+        "lrbi_masked_gemm_t")
     return out
 
 
 def masked_grad(desc: Desc, dY, X, dIp, dIz, out=None, stream=None):
     """lrbi_masked_grad: dW = (dY X^T) o decode(Ip, Iz).  dY [m, N], X [n, N] row-major device tensors of one
     dtype (rows may be padded); returns dW [m, n] with exact zeros at pruned weights."""
-    import torch
-    if dY.dim() != 2 or X.dim() != 2 or dY.shape[0] != desc.m or X.shape[0] != desc.n or dY.shape[1] != X.shape[1]:
+    m, n, ys, xs = desc.m, desc.n, dY.shape, X.shape
+    if len(ys) != 2 or len(xs) != 2 or ys[0] != m or xs[0] != n or ys[1] != xs[1]:
         raise ValueError("shape mismatch")
-    N = dY.shape[1]
-    if (N > 1 and (dY.stride(1) != 1 or X.stride(1) != 1)) or dY.dtype != X.dtype:
+    N = ys[1]
+    (lddy, y1), (ldx, x1) = dY.stride(), X.stride()
+    if (N > 1 and (y1 != 1 or x1 != 1)) or dY.dtype != X.dtype:
         raise ValueError("dY and X must be row-major tensors of the same dtype")
-    if out is None:
-        out = torch.empty((desc.m, desc.n), dtype=dY.dtype, device=dY.device)
-    if out.shape != (desc.m, desc.n) or out.dtype != dY.dtype or out.stride(1) != 1:
+    out, lddw = _row_major_out(out, m, n, dY)
+    if out.stride(1) != 1:
         raise ValueError("bad out tensor")
     _check(load_library().lrbi_masked_grad(
-        ctypes.byref(desc), _dtype_code(dY), _dev_ptr(dY, "dY"), dY.stride(0), _dev_ptr(X, "X"), X.stride(0), N,
-        _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"), _dev_ptr(out, "dW"), out.stride(0), _stream_ptr(stream)),
+        ctypes.byref(desc), _dtype_code(dY), _dev_ptr(dY, "dY"), lddy, _dev_ptr(X, "X"), ldx, N,
+        _dev_ptr(dIp, "Ip"), _dev_ptr(dIz, "Iz"), _dev_ptr(out, "dW"), lddw, _stream_ptr(stream)),
         "lrbi_masked_grad")
     return out
 
