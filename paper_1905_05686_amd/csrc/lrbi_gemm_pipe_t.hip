@@ -80,7 +80,6 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
     const int64_t iend = (ibeg + iper < g.m) ? ibeg + iper : g.m;
     const int nslabs = (int)((iend - ibeg) / BK); // whole slabs only: m % 128 == 0, iper % 128 == 0
     const int last = nslabs - 1;
-    const int npanels = (nslabs + PANEL_SLABS - 1) / PANEL_SLABS;
     const int tj = j0 / g.c;                       // the workgroup's columns lie inside one tile column (c % 128 == 0)
     const int coff = j0 - tj * g.c;
     const int tjb = (j0 + 64) / g.c;               // HALF: tile column and offset of the upper 64 columns
@@ -465,16 +464,20 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
         mask_hi(I0{}, I0{}, y);
     }
 
-    // ---- main loop, unrolled by NS: the schedule of the forward kernel (loads spread over the iteration)
-    for (int s0 = 0; s0 < nslabs; s0 += NS) {
-        static_for<NS>([&](auto sc) {
-            constexpr int st = decltype(sc)::value;
+    // ---- main loop, unrolled by a panel: the schedule of the forward kernel (loads spread over the iteration).  The next
+    // panel's mask is only formed where there is one: a panel takes longer to form here, and slices are short.
+    static_assert(PANEL_SLABS == 2 * NS, "two rounds of the ring");
+    for (int s0 = 0; s0 < nslabs; s0 += PANEL_SLABS) {
+        const bool more = s0 + PANEL_SLABS < nslabs;
+        static_for<PANEL_SLABS>([&](auto sc) {
+            constexpr int ps = decltype(sc)::value;
+            constexpr int st = ps % NS;
             constexpr int st1 = (st + 1) % NS;
             constexpr int stn = (st + NS - 1) % NS;
             constexpr int stp = (st + NS - 2) % NS;
             using Par = std::integral_constant<int, st & 1>;
             using Nxt = std::integral_constant<int, (st & 1) ^ 1>;
-            const int s = s0 + st;
+            const int s = s0 + ps;
             if (s < nslabs) {
                 uint32_t y;
                 uint32_t mk;
@@ -483,12 +486,10 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
                 mma(Par{}, I0{}, I1{}); read_y(st, I1{}, I1{}); mask_hi(Par{}, I1{}, y);
                 issue_piece(stp, I2{});
                 mma(Par{}, I0{}, I2{}); read_y(st, I1{}, I2{});
-                mk = fetch_mask(s + 1 < last ? s + 1 : last);
+                mk = fetch_mask(s + 1);
                 mma(Par{}, I0{}, I3{}); read_y(st, I1{}, I3{});
                 issue_piece(stp, I3{});
-                const int ps = (uint32_t)s % PANEL_SLABS;
-                const int np = (uint32_t)s / PANEL_SLABS + 1;
-                if (ps == 0 && np < npanels) {
+                if (ps == 0 && more) {
                     load_factors();
                     wait_loads<(NS - 3) * 4 + (HALF ? 6 : 4)>(); // (the factor loads are younger too)
                 } else
@@ -503,17 +504,19 @@ __global__ __launch_bounds__(PT_THREADS) void mfma_gemm_pipe_t_kernel(
                 mma(Par{}, I1{}, I3{}); read_y(st1, I0{}, I3{}); mask_hi(Nxt{}, I0{}, y);
                 // mask of the next panel: its factor slices, asked for at slab 0, were waited for by every wavefront in
                 // front of slab 1's barrier; the three steps follow the barriers of slabs 1, 2 and 3; first read at slab 7
-                if (np < npanels) {
-                    if (ps == 1) panel_step1();
-                    else if (ps == 2) {
+                if (ps >= 1 && ps <= 4 && more) {
+                    if constexpr (ps == 1) panel_step1();
+                    if constexpr (ps == 2) {
                         panel_step2();
                         panel_step3();
-                    } else if (ps == 3) {
+                    }
+                    if constexpr (ps == 3) {
                         if constexpr (HALF) panel_step3b();
-                        else panel_step4(np);
-                    } else if (HALF && ps == 4) panel_step4(np); // (written behind slab 4's barrier, first read at slab 7)
+                        else panel_step4(s / PANEL_SLABS + 1);
+                    }
+                    if constexpr (HALF && ps == 4) panel_step4(s / PANEL_SLABS + 1); // (written behind slab 4's barrier, first read at slab 7)
                     // what a step read and wrote of the factors and the mask is done before the next barrier
-                    if (ps >= 1 && ps <= 4) asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 }
             }
         });
