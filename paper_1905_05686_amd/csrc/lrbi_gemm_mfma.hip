@@ -931,6 +931,34 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces)
     return p;
 }
 
+// Two launches instead of one, so the product has to be worth it (bf16, us, decode and pipelined kernel against the general
+// one: 3000 x 3000 in 300 x 300 tiles, N = 512 31 / 90; 1000 x 1000 in 100 x 100, N = 1000 22 / 42; 4096 x 4096 in 64 x 64, N = 2048
+// 88 / 138; 2304 x 2048 in 576 x 512, rank 145, N = 128 21 / 25; 600 x 1200, N = 512 19.5 / 20.7; 12000 x 12000, N = 40 103 / 142;
+// but 3000 x 3000, N = 64 23.0 / 22.7; 1000 x 1000, N = 256 20.6 / 19.2; 300 x 5000, N = 96 22.6 / 19.7; 8000 x 200, N = 2000 42 / 40).
+bool plan_given(const Geom &g, uint32_t flags, int64_t N, MfmaPlan *out)
+{
+    if ((flags & (LRBI_FLAG_TILE_MASK | LRBI_FLAG_SPLITK_MASK)) != 0) return false; // a kernel or a split asked for by flag
+    if (N <= 32 || N % 8 != 0 || g.n % 8 != 0) return false;
+    if (plan_mfma(g, flags, N, true).tile >= 4) return false; // served without
+    MfmaPlan p;
+    p.tile = 14;
+    p.bm = p.bn = 128;
+    p.mask_given = true;
+    const int64_t tiles = ((g.m + 127) / 128) * ((N + 127) / 128), npairs = (g.n + 2 * BK - 1) / (2 * BK);
+    int64_t want = tiles < 192 ? 256 / tiles : 1; // one workgroup per compute unit, at least eight slabs each
+    if (g.n < 384 || tiles * npairs < 192 || (N < 96 && g.m * g.n < ((int64_t)1 << 25))) return false;
+    if (want > npairs / 4) want = npairs / 4;
+    if (want > 64) want = 64;
+    if (want < 1) want = 1;
+    const int64_t pairs_per = (npairs + want - 1) / want;
+    p.splitk = (int)((npairs + pairs_per - 1) / pairs_per);
+    p.kper = pairs_per * 2 * BK;
+    const int64_t ldp = (N + 3) / 4 * 4;
+    p.workspace_bytes = p.splitk > 1 ? (uint64_t)p.splitk * (uint64_t)g.m * (uint64_t)ldp * 4u : 0u;
+    *out = p;
+    return true;
+}
+
 // adds the split-K partial planes in slice order and rounds to the storage dtype
 template <typename Tag>
 static int launch_reduce(const Geom &g, const MfmaPlan &plan, int64_t N, void *dY, int64_t ldy, void *dWorkspace,
@@ -1077,9 +1105,9 @@ int launch_mfma_gemm(const Geom &g, const MfmaPlan &plan_in, lrbi_dtype dt, cons
     if (((uintptr_t)dW & 15) != 0 || ldw % 8 != 0 || g.n % 8 != 0) return LRBI_ERR_ALIGN;
     MfmaPlan plan = plan_in;
     if (plan.tile >= kFirstPipeTile) {
-        if (pipe_ok(g, dIz, dX, ldw, ldx, N)) {
+        if (plan.mask_given || pipe_ok(g, dIz, dX, ldw, ldx, N)) {
             // (the mask as a by-product and the planes of a fused consumer come from the 128 x 128 form)
-            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr && !g.ragged)
+            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr && !g.ragged && !plan.mask_given)
                 return launch_pipe256_gemm(g, dt, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, stream);
             const int pf = plan.tile == kPipe256Tile ? 2 : plan.tile - kFirstPipeTile;
             const int rc = launch_pipe_gemm(g, plan, dt, pf, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, stream, mo);

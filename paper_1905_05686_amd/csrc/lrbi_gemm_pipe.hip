@@ -61,7 +61,10 @@ static_assert(SmemDma<4, true>::bytes <= 160 * 1024, "LDS of a compute unit");
 // RAG: matrices that end inside a tile, or whose rows end inside a 128-column unit.  Rows past the last one are fetched as the last one and not stored; in the last slab,
 // pieces of W past the last column and rows of X past the last one are fetched as the last ones and meet zero mask bits (the
 // mask words are cut at the last column).
-template <typename Tag, int NS, bool SPREAD, bool SPLIT, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false>
+// PRE: tile shapes that line up with nothing, and any rank.  The mask has been decoded to global memory before (mask_out, rows
+// of mask_pitch16 pieces): a panel of it is copied into LDS as it lies there, 64 bytes a row, piece p of row q at slot p ^
+// ((q >> 2) & 3), and nothing is formed here.
+template <typename Tag, int NS, bool SPREAD, bool SPLIT, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false, bool PRE = false>
 __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     Geom g, const uint16_t *__restrict__ W, int64_t ldw, const uint32_t *__restrict__ Ip,
     const uint32_t *__restrict__ Iz, const uint16_t *__restrict__ X, int64_t ldx, int N,
@@ -71,6 +74,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     static_assert(NS == 4, "LDS stages (an even number: the W operand registers alternate with the slab's parity)");
     static_assert(!SPREAD || NS == 4, "loads spread over the iteration land one iteration later: four stages");
     constexpr int FN = PIPE_BN / 32; // 32-column blocks of the wave tile
+    static_assert(!PRE || (RAG && !EMIT && !HALF), "a decoded mask: the cut-off form, nothing stored");
     static_assert(!(HALF && CONV) && !(RAG && CONV), "half units, cut-off tiles: the plain product only");
     using S = SmemDma<NS, HALF>;
 
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         for (int a = 0; a < FN; ++a) xfa[a] = base + 64u * (uint32_t)(a ^ (q & 3));
     }
     // mask bytes of this lane's row: 8 bytes per slab, of which this wavefront's steps use bytes 4 kg + 2 j + lg
-    const uint32_t mta = (uint32_t)((wq * 32 + l32) * MT_ROW + 4 * kg);
+    const uint32_t mta = (uint32_t)((wq * 32 + l32) * (PRE ? 64 : MT_ROW) + 4 * kg);
 
     u32x4 wf[2][2], xf[2][FN]; // W operands [slab parity][j]; X operands [j][block]
     auto read_w = [&](int stage, auto par_c, auto j_c) {
@@ -265,6 +269,10 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     };
     auto fetch_mask = [&](int slab) -> uint32_t {
         const uint32_t us = (uint32_t)slab;
+        if constexpr (PRE) {
+            const uint32_t slot = ((us % PANEL_SLABS) >> 1) ^ (uint32_t)((l32 >> 2) & 3);
+            return *reinterpret_cast<const uint32_t *>(Mt + ((us / PANEL_SLABS) & 1u) * 8192u + mta + slot * 16u + (us & 1u) * 8u);
+        }
         const unsigned char *p = Mt + ((us / PANEL_SLABS) & 1u) * MT_BYTES + (us % PANEL_SLABS) * 8u + mta;
         return *reinterpret_cast<const uint32_t *>(p);
     };
@@ -300,7 +308,18 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     const uint32_t z_row = (uint32_t)trow * izs, p_row = (uint32_t)trow * ips + (uint32_t)(il0 * g.ipw * 4);
     const int fz_l = wq * 16 + (lane >> 2);
     const uint32_t fz_lane = (uint32_t)(((fz_l < g.k) ? fz_l : 0) * g.izw * 4);
+    int pre_piece = kbeg / 128 + ((lane & 3) ^ ((lane >> 4) & 3)), pre_buf = 0; // PRE: this lane's piece of the next panel
+    const int pre_row = wave * 16 + (lane >> 2);
+    const uint32_t pre_off = (uint32_t)((pre_row < m_last ? pre_row : m_last) * mask_pitch16 * 16);
+    const int pre_last = (int)((g.n + 127) / 128) - 1;
     auto load_factors = [&]() {
+        if constexpr (PRE) {
+            load_to_lds16(lds0 + (uint32_t)S::mt_off + (uint32_t)(pre_buf * 8192 + wave * 1024), mask_out + m0 * mask_pitch16,
+                          pre_off + (uint32_t)((pre_piece < pre_last ? pre_piece : pre_last) * 16));
+            pre_piece += PANEL_UNITS;
+            pre_buf ^= 1;
+            return;
+        }
         const uint32_t zsel = z_row + (fz_u.col < kend ? (uint32_t)fz_u.tj * izs + (uint32_t)(fz_u.off >> 5) * 4u : 0u);
         const uint32_t psel = p_row + (fp_u.col < kend ? (uint32_t)fp_u.tj * ips : 0u);
         next_panel(fz_u);
@@ -452,10 +471,12 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             issue_piece(st, I3{});
         }
     });
-    wait_loads<kProloguePieces>();
-    __syncthreads();
-    decode_words();
-    decode_store(0);
+    if constexpr (!PRE) {
+        wait_loads<kProloguePieces>();
+        __syncthreads();
+        decode_words();
+        decode_store(0);
+    }
     // slab 0 (EMIT: a mask store, where there is one, is younger: the wait is one piece longer than it has to be)
     wait_loads<kProloguePieces - 4>();
     __syncthreads();
@@ -495,8 +516,8 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 uint32_t y;
                 uint32_t mk;
                 // first step
-                if constexpr (ps == 4) decode_other(g.ipw > 1);
-                if constexpr (ps >= 3 && ps <= 5) decode_ask();
+                if constexpr (ps == 4 && !PRE) decode_other(g.ipw > 1);
+                if constexpr (ps >= 3 && ps <= 5 && !PRE) decode_ask();
                 mma(Par{}, I0{}, I0{}); read_x(st, I1{}, I0{}); y = mask_lo(Par{}, I1{}, mcur);
                 mma(Par{}, I0{}, I1{}); read_x(st, I1{}, I1{}); mask_hi(Par{}, I1{}, y);
                 if constexpr (SPREAD) issue_piece(stp, I2{});
@@ -504,12 +525,12 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 mk = fetch_mask(s + 1); // mask bytes of the next slab (past the last one: not used)
                 mma(Par{}, I0{}, I3{}); read_x(st, I1{}, I3{});
                 if constexpr (SPREAD) issue_piece(stp, I3{});
-                if constexpr (ps >= 3 && ps <= 5) decode_add();
+                if constexpr (ps >= 3 && ps <= 5 && !PRE) decode_add();
                 // factor slices of the next panel, requested at the panel's first slab: they have landed, for
                 // every wavefront, behind the next iteration's wait and barrier
                 if constexpr (ps == 0) {
                     load_factors();
-                    wait_loads<(NS - 3) * 4 + (HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six)
+                    wait_loads<(NS - 3) * 4 + (PRE ? 1 : HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six, PRE one)
                 } else
                     wait_loads<(NS - 3) * 4>(); // slab s + 1 has landed (four younger loads may still be in flight)
                 LRBI_BARRIER();
@@ -523,8 +544,8 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 mma(Par{}, I1{}, I3{}); read_x(st1, I0{}, I3{}); mask_hi(Nxt{}, I0{}, y);
                 if constexpr (!SPREAD) issue_piece(stn, I3{});
                 // mask of the next panel: its words at slab 2, written in front of slab 6's barrier, first read at slab 7
-                if constexpr (ps == 2) decode_words();
-                if constexpr (ps == 5) decode_store(s / PANEL_SLABS + 1);
+                if constexpr (ps == 2 && !PRE) decode_words();
+                if constexpr (ps == 5 && !PRE) decode_store(s / PANEL_SLABS + 1);
             }
         });
     }
@@ -629,7 +650,14 @@ bool pipe_ok(const Geom &g, const void *dIz, const void *dX, int64_t ldw, int64_
     return true;
 }
 
-template <typename Tag, int NS, bool SPREAD, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false>
+// the same for the form that reads a decoded mask: any tile shape and rank
+bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N)
+{
+    if ((((uintptr_t)dX & 15) != 0) || (ldx % 8 != 0) || (N % 8 != 0) || N < 8 || g.n % 8 != 0) return false;
+    return ldw <= (1 << 22) && ldx <= (1 << 22);
+}
+
+template <typename Tag, int NS, bool SPREAD, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false, bool PRE = false>
 static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, int64_t ldw, const uint32_t *dIp,
                          const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY, int64_t ldy,
                          void *dWorkspace, const ConvGeom &cg, hipStream_t stream, MaskOut mo = {nullptr, 0})
@@ -643,8 +671,8 @@ static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, in
     const int xcd_remap = (blocks % 8 == 0) ? 1 : 0;
     const int64_t ldp = (N + 3) / 4 * 4;
     const size_t smem = SmemDma<NS, HALF>::bytes;
-    auto kern = split ? mfma_gemm_pipe_kernel<Tag, NS, SPREAD, true, CONV, EMIT, HALF, RAG>
-                      : mfma_gemm_pipe_kernel<Tag, NS, SPREAD, false, CONV, EMIT, HALF, RAG>;
+    auto kern = split ? mfma_gemm_pipe_kernel<Tag, NS, SPREAD, true, CONV, EMIT, HALF, RAG, PRE>
+                      : mfma_gemm_pipe_kernel<Tag, NS, SPREAD, false, CONV, EMIT, HALF, RAG, PRE>;
     LRBI_SET_MAX_LDS(kern, smem);
     LRBI_LAUNCH(kern, dim3((unsigned)blocks), dim3(PIPE_THREADS), smem, stream, g, (const uint16_t *)dW, ldw, dIp, dIz,
                 (const uint16_t *)dX, ldx, (int)N, (uint16_t *)dY, ldy, (float *)dWorkspace, ldp, (int)mblocks,
@@ -660,6 +688,15 @@ int launch_pipe_gemm(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, int var
                      int64_t ldy, void *dWorkspace, hipStream_t stream, MaskOut mo)
 {
     const ConvGeom none = {0, 0, 0};
+    if (plan.mask_given) { // the mask is in mo already
+        if (dt == LRBI_F16)
+            return launch_pipe_t<F16Tag, 4, true, false, false, false, true, true>(g, plan, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy,
+                                                                                    dWorkspace, none, stream, mo);
+        if (dt == LRBI_BF16)
+            return launch_pipe_t<BF16Tag, 4, true, false, false, false, true, true>(g, plan, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy,
+                                                                                     dWorkspace, none, stream, mo);
+        return LRBI_ERR_DTYPE;
+    }
     if (g.ragged || g.n % 128 != 0) { // cut-off tiles or panels: one variant per dtype and kind of unit, with or without the mask
 #define LRBI_PIPE_RAG(TAG, EM, HF)                                                                                           \
     launch_pipe_t<TAG, 4, true, false, EM, HF, true>(g, plan, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, none, stream, mo)

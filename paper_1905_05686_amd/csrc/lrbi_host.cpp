@@ -210,6 +210,13 @@ static bool use_mfma(const lrbi_desc *desc, lrbi_dtype dt, int64_t N)
     return N > 4 || (N >= 2 && (int64_t)desc->m * desc->n >= ((int64_t)1 << 23)); // (level at 2048 x 2048, the sweep ahead at 1024 x 1024)
 }
 
+// scratch for the partial planes of a product, whichever kernel X's address leads to
+static uint64_t planes_bytes(const Geom &g, uint32_t flags, int64_t N)
+{
+    const uint64_t a = plan_mfma(g, flags, N).workspace_bytes, b = plan_mfma(g, flags, N, true).workspace_bytes;
+    return a > b ? a : b;
+}
+
 extern "C" int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtype dtype, int64_t N,
                                                 uint64_t *bytes)
 {
@@ -222,9 +229,12 @@ extern "C" int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtyp
     *bytes = 0;
     if (use_mfma(desc, dtype, N)) {
         const Geom g = make_geom(desc);
-        *bytes = plan_mfma(g, desc->flags, N).workspace_bytes;
-        const uint64_t pieces = plan_mfma(g, desc->flags, N, true).workspace_bytes; // whichever kernel X's address leads to
-        if (pieces > *bytes) *bytes = pieces;
+        *bytes = planes_bytes(g, desc->flags, N);
+        MfmaPlan given; // a decoded mask behind the planes
+        if (dtype != LRBI_F32 && plan_given(g, desc->flags, N, &given)) {
+            const uint64_t both = given.workspace_bytes + (uint64_t)g.m * (uint64_t)mask_pitch_of(g);
+            if (both > *bytes) *bytes = both;
+        }
     }
     return LRBI_OK;
 }
@@ -279,6 +289,20 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
     if (!mfma)
         return launch_valu_gemm(g, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
                                 dX, ldx, N, dY, ldy, s);
+    {
+        MfmaPlan given;
+        if (dWorkspace && aligned_to(dWorkspace, 16) && plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N)) {
+            const int64_t pitch = mask_pitch_of(g);
+            const uint64_t planes = given.workspace_bytes; // whole fp32 rows of four: a multiple of 16
+            if (workspace_bytes >= planes + (uint64_t)g.m * (uint64_t)pitch) {
+                void *mask = (char *)dWorkspace + planes;
+                const int rcd = launch_decode(g, desc->flags, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, mask, pitch, s);
+                if (rcd != LRBI_OK) return rcd;
+                return launch_mfma_gemm(g, given, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, dX,
+                                        ldx, N, dY, ldy, dWorkspace, s, MaskOut{mask, pitch / 16});
+            }
+        }
+    }
     const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
     MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
     if (plan.splitk > 1) {
@@ -327,6 +351,15 @@ extern "C" int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, con
     // their own use and store it on the way (the workgroups of the first block of batch columns do).
     if (use_mfma(desc, dtype, N) && aligned_to(dW, 16) && ldw % 8 == 0 && desc->n % 8 == 0) {
         const Geom g = make_geom(desc);
+        MfmaPlan given;
+        if (plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N) &&
+            (given.splitk == 1 || (dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= given.workspace_bytes))) {
+            // the mask that the caller wants, then the product on it
+            const int rcd = lrbi_decode_mask(desc, dIp_packed, dIz_packed, dMask, mask_pitch_bytes, stream);
+            if (rcd != LRBI_OK) return rcd;
+            return launch_mfma_gemm(g, given, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, dX, ldx,
+                                    N, dY, ldy, dWorkspace, (hipStream_t)stream, MaskOut{dMask, mask_pitch_bytes / 16});
+        }
         const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
         MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
         if (plan.splitk > 1) {
@@ -435,6 +468,9 @@ extern "C" int lrbi_masked_gemm_static(const lrbi_desc *desc, lrbi_dtype dtype, 
     uint64_t need = 0;
     const int rc = lrbi_masked_gemm_workspace_bytes(desc, dtype, N, &need);
     if (rc != LRBI_OK) return rc;
+    // What the planes of a split take decides (a decoded mask is only put behind them where there is room): shapes that need
+    // none leave the array alone, and none is refused for its mask.
+    if (need) need = planes_bytes(make_geom(desc), desc->flags, N);
     // tiles enough to fill the chip unsplit: that form leaves the shared array alone, so such calls may overlap in time
     if (need && plan_mfma(make_geom(desc), desc->flags, N).split_optional) need = 0;
     if (need > (uint64_t)LRBI_STATIC_SCRATCH_BYTES) return LRBI_ERR_WORKSPACE;

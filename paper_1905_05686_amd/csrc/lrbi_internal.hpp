@@ -109,11 +109,16 @@ struct MfmaPlan {
     // leave the fp32 planes of the slices in the workspace ([slice][m][ldp], ldp = N rounded up to 4) and skip the
     // reduction into Y: a fused consumer (the LSTM cell kernel) adds and uses them
     bool planes_only = false;
+    bool mask_given = false; // the pipelined kernel on a mask decoded before (plan_given())
     bool split_optional = false; // the tiles alone fill the chip: the slices are for evening out, not needed
 };
 // x_pieces: the pipelined kernel can read X (pipe_ok()); asked for shapes that it only takes in its cut-off form, whose
 // alternative, the general kernel, is planned differently
 MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces = false);
+// Tile shapes and ranks that the pipelined kernel cannot form the mask for: the mask decoded first, then the pipelined kernel
+// on it.  True where that is the better choice; *p: its plan (workspace_bytes: the planes alone).
+bool plan_given(const Geom &g, uint32_t flags, int64_t N, MfmaPlan *p);
+inline int64_t mask_pitch_of(const Geom &g) { return (g.n + 127) / 128 * 16; }
 // Where the tile kernel leaves the decoded mask as a by-product (rows of 16-byte pieces, one bit per weight), or {nullptr, 0}.
 struct MaskOut {
     void *ptr;
@@ -152,6 +157,7 @@ int launch_mfma_conv(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, const C
 // software-pipelined tile kernel (lrbi_gemm_pipe.hip)
 bool pipe_shape_ok(const Geom &g);
 bool pipe_ok(const Geom &g, const void *dIz, const void *dX, int64_t ldw, int64_t ldx, int64_t N);
+bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N);
 int launch_pipe_gemm(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, int pf, const void *dW, int64_t ldw,
                      const uint32_t *dIp, const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY,
                      int64_t ldy, void *dWorkspace, hipStream_t stream, MaskOut mo = {nullptr, 0});

@@ -469,3 +469,32 @@ def test_pipelined_kernel_on_cut_off_tiles(m, n, r, c, k, N, dtype):
     used = 128 * ((n + 127) // 128)
     assert np.array_equal(bits[:, :n], M) and not bits[:, n:used].any()
     assert (out.cpu().numpy()[:, used // 8:] == 0x5A).all()
+
+
+# tile shapes that line up with nothing and ranks above 64, more than 32 columns: the mask decoded first, behind the planes of
+# the workspace or in the caller's own buffer, then the pipelined kernel on it; without a workspace the general kernel
+@pytest.mark.parametrize("m,n,r,c,k,N,dtype", [
+    (1200, 3000, 300, 300, 8, 512, "bf16"),
+    (1153, 2048, 576, 512, 145, 136, "f16"),
+    (1000, 1992, 100, 100, 33, 264, "bf16"),
+    (4100, 1096, 192, 83, 5, 520, "f16"),
+])
+def test_pipelined_kernel_on_a_decoded_mask(m, n, r, c, k, N, dtype):
+    print("pipelined kernel, decoded mask", m, n, r, c, k, N, dtype, flush=True)
+    cfg = workloads.Config("given", m, n, r, c, k, 0.12 if k < 64 else 0.03, N, dtype, 0.05)
+    data = workloads.make(cfg)
+    ref, M = _oracle(cfg, data)
+    for ldpad in (0, 8):
+        for use_workspace in (True, False):
+            _assert_close(_run(cfg, data, use_workspace=use_workspace, ldpad=ldpad), ref, dtype, "decoded mask")
+    desc = desc_of(cfg)
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    W, X = to_device(data["W"], dtype), to_device(data["X"], dtype)
+    ws = workspace_for(desc, DT_CODE[dtype], N)
+    mask, Y = lrbi.decode_and_gemm(desc, W, dIp, dIz, X, workspace=ws)
+    torch.cuda.synchronize()
+    _assert_close(Y, ref, dtype, "mask wanted")
+    assert np.array_equal(unpack_device_mask(mask, n)[:, :n], M)
+    # a pruned weight never reaches the sum, whatever it holds
+    Wn = torch.where(torch.from_numpy(M.astype(bool)).to(dev()), W, torch.full_like(W, float("nan")))
+    assert torch.equal(lrbi.masked_gemm(desc, Wn, dIp, dIz, X, workspace=ws), lrbi.masked_gemm(desc, W, dIp, dIz, X, workspace=ws))
