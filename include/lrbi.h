@@ -173,17 +173,19 @@ int lrbi_decode_mask(const lrbi_desc *desc, const void *dIp_packed, const void *
 
 /*
  * Workspace the masked product may use for (desc, dtype, N): partial sums when
- * the reduction over n is split across workgroups.  Host only.  *bytes may be 0.  Up to
+ * the reduction over n is split across workgroups, and the decoded mask (m rows of
+ * 16 * ceil(n / 128) bytes) on tile shapes and ranks that the tuned kernels cannot rebuild it for.
+ * Host only.  *bytes may be 0.  Up to
  * 64 planes of m x N fp32 values when the output has few blocks; about 100 MB at most (two to six planes) when
- * it has 192 to 511 of them on the general kernel, which gain least from it (4100 x 9224, N = 1024: 336 us
- * without, 251 with).
+ * it has 192 to 511 of them on the general kernel, which gain least from it.
  */
 int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtype dtype, int64_t N,
                                      uint64_t *bytes);
 
 /*
  * Fused masked layer product Y = (W o I_a) X: the mask of Eq. 3 is rebuilt from
- * the factors inside the kernel (it never goes through HBM), applied to W as a
+ * the factors inside the kernel (it never goes through HBM; on tile shapes and ranks that no tuned
+ * kernel lines up with, and with a workspace that has room, it is decoded there first), applied to W as a
  * masking layer (Sec. 2, Sec. 2.2: a pruned weight contributes nothing, whatever
  * value is stored under it, NaN and Inf included), and multiplied with X.
  *   dW: m x n row-major, leading dimension ldw >= n (elements).
@@ -252,13 +254,14 @@ int lrbi_masked_conv3x3(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW,
  * lrbi_masked_gemm for callers that cannot allocate device memory and have no workspace to hand over: code
  * under HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments, results
  * (identical bits) and launches as lrbi_masked_gemm called with a workspace of
- * lrbi_masked_gemm_workspace_bytes bytes, but the partial sums of a split reduction go to a scratch array
- * of LRBI_STATIC_SCRATCH_BYTES bytes that is part of the library image on every GPU it runs on (held until
+ * LRBI_STATIC_SCRATCH_BYTES bytes, but the partial sums of a split reduction (and the decoded mask, where it is
+ * decoded first and fits behind them) go to a scratch array of that many bytes that is part of the library image on every GPU it runs on (held until
  * the process ends).  The call allocates and frees nothing, on the host side or the device side of HIP.
  *   Not split: shapes whose output alone fills the chip (192 blocks of 128 x 128, or of 128 x 64 or 128 x 32 where rows are
  *   few, on the general kernel).  A workspace lets lrbi_masked_gemm even their last round out; here they run
- *   unsplit, with the bits of lrbi_masked_gemm without a workspace, and leave the array alone.
- *   Limit: other shapes whose workspace query exceeds LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
+ *   unsplit, with the bits of lrbi_masked_gemm without a workspace, and leave the array alone; so do shapes
+ *   that have no partial sums.
+ *   Limit: other shapes whose partial sums exceed LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
  *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB).
  *   The device of `stream` must be the current device (the scratch array is looked up per current device).
  *   All calls on one GPU share that GPU's array: two calls that may overlap in time (different streams, or

@@ -9,7 +9,7 @@
 // into a ring of four LDS stages, read with plain 16-byte LDS reads.  One barrier per slab, counted waits.
 // The mask touches only the output: its bits under the tile are formed once (Eq. 3), in the first iteration, from factor
 // slices in LDS (tiles line up with 64 columns and 128 rows), and select on the way out.
-// 4096 x 4096 bf16, 512 x 512 tiles: batch 1024 51 -> 38 us, 512 33 -> 27, 256 24 -> 21.
+// 4096 x 4096 bf16, 512 x 512 tiles: batch 1024 51 -> 39 us, 512 33 -> 27, 256 24 -> 21.
 #include "lrbi_internal.hpp"
 #include "lrbi_lds_dma.hpp"
 #include "lrbi_mfma_common.hpp"
@@ -303,7 +303,7 @@ bool grad256_ok(const Geom &g, const void *dDY, int64_t lddy, const void *dX, in
     return tiles * g.k * g.izw * 4 < (int64_t)1 << 31 && tiles * g.r * g.ipw * 4 < (int64_t)1 << 31;
 }
 // One workgroup per compute unit does its round alone, so the rounds have to be nearly full, or a single one on a long
-// batch (bf16, us, 256 against 128: 4096 x 4096, 256 tiles: batch 128 17.6 / 19.1, 1024 38 / 51; 2304 x 4096, 144 tiles, batch
+// batch (bf16, us, 256 against 128: 4096 x 4096, 256 tiles: batch 128 17.6 / 19.1, 1024 39 / 51; 2304 x 4096, 144 tiles, batch
 // 1024: 31.7 / 34.6; but 4096 x 9216, 576 tiles in three rounds: batch 512 67 / 60, 128 43 / 33; 2048 x 4096, 128 tiles, batch
 // 1024: 31.2 / 29.0).
 bool grad256_wins(const Geom &g, int64_t N)
