@@ -121,6 +121,11 @@ __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, 
     const int ti = (int)(row / g.r);
     return decode_word(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
 }
+__device__ __forceinline__ uint32_t row_word_ahead(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
+{
+    const int ti = (int)(row / g.r);
+    return decode_word_ahead(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
+}
 
 // adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it, without the batch columns in `skip`
 template <typename T, int NQ, int WAVES>
@@ -179,7 +184,7 @@ __global__ __launch_bounds__(64 * WAVES) void f32_gemm_t_kernel(Geom g, const T 
             }
         };
         load(0, w[0], y[0]);
-        const uint32_t words = (i0 + lane < g.m) ? row_word(g, Ip, Iz, i0 + lane, jb) : 0u;
+        const uint32_t words = (i0 + lane < g.m) ? row_word_ahead(g, Ip, Iz, i0 + lane, jb) : 0u;
 #pragma unroll
         for (int s = 0; s < kF32Chunk / 2 / U; ++s) {
             if (s + 1 < kF32Chunk / 2 / U) load((s + 1) * U, w[(s + 1) & 1], y[(s + 1) & 1]);
@@ -372,7 +377,7 @@ __global__ __launch_bounds__(256) void f32_grad_kernel(Geom g, const float *__re
     };
     load(0, y[0], x[0]);
     // the block's mask words: lane l < 32 holds row i0 + l of the first word column, the other half the second's
-    const uint32_t words = row_word(g, Ip, Iz, at_most(i0 + li, g.m - 1), (int)(j0 >> 5) + (NJ == 2 ? half : 0));
+    const uint32_t words = row_word_ahead(g, Ip, Iz, at_most(i0 + li, g.m - 1), (int)(j0 >> 5) + (NJ == 2 ? half : 0));
     for (int64_t q = 0; q < N; q += 16) {
         load(q + 8, y[1], x[1]);
         mma(y[0], x[0], acc[0]);

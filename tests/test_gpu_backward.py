@@ -252,3 +252,15 @@ def test_gradient_in_tiles_of_256(m, n, r, c, k, N, dtype):
         assert orc.rel_err(dWh, ref) <= TOL[dtype]
         assert not dWh[M == 0].any(), "pruned weights must get exactly zero"
         assert torch.equal(dW.view(torch.int16), lrbi.masked_grad(desc, dY, X, dIp, dIz).view(torch.int16))
+
+
+# mask words formed with four ranks at a time: windows that start before a tile's I_z row and end behind it, tiles narrower than a
+# word, two and more I_p words, every rank set and none
+@pytest.mark.parametrize("m,n,r,c,k,p,N,dtype", [
+    (70, 90, 32, 9, 5, 1.0, 8, "f32"),
+    (130, 200, 65, 33, 40, 0.5, 40, "f32"),
+    (100, 264, 64, 100, 70, 0.1, 40, "bf16"),
+    (96, 136, 50, 31, 3, 0.0, 16, "f16"),
+])
+def test_mask_words_four_ranks_at_a_time(m, n, r, c, k, p, N, dtype):
+    _check(workloads.Config("ahead", m, n, r, c, k, p, N, dtype, 0.05, 3), what="mask words")
