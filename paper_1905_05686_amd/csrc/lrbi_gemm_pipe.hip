@@ -650,11 +650,12 @@ bool pipe_ok(const Geom &g, const void *dIz, const void *dX, int64_t ldw, int64_
     return true;
 }
 
-// the same for the form that reads a decoded mask: any tile shape and rank
-bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N)
+// the same for the form that reads a decoded mask: any tile shape and rank.  A lane's byte offset into the mask rows of its
+// tile has 32 bits as well: the last byte of 128 rows lies below 2^32.
+bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N, int64_t mask_pitch_bytes)
 {
     if ((((uintptr_t)dX & 15) != 0) || (ldx % 8 != 0) || (N % 8 != 0) || N < 8 || g.n % 8 != 0) return false;
-    return ldw <= (1 << 22) && ldx <= (1 << 22);
+    return ldw <= (1 << 22) && ldx <= (1 << 22) && mask_pitch_bytes <= ((int64_t)1 << 32) / PIPE_BM;
 }
 
 template <typename Tag, int NS, bool SPREAD, bool CONV, bool EMIT = false, bool HALF = false, bool RAG = false, bool PRE = false>

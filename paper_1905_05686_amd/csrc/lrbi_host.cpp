@@ -291,7 +291,8 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
                                 dX, ldx, N, dY, ldy, s);
     {
         MfmaPlan given;
-        if (dWorkspace && aligned_to(dWorkspace, 16) && plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N)) {
+        if (dWorkspace && aligned_to(dWorkspace, 16) && plan_given(g, desc->flags, N, &given) &&
+            pipe_given_ok(g, dX, ldw, ldx, N, mask_pitch_of(g))) {
             const int64_t pitch = mask_pitch_of(g);
             const uint64_t planes = given.workspace_bytes; // whole fp32 rows of four: a multiple of 16
             if (workspace_bytes >= planes + (uint64_t)g.m * (uint64_t)pitch) {
@@ -352,7 +353,7 @@ extern "C" int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, con
     if (use_mfma(desc, dtype, N) && aligned_to(dW, 16) && ldw % 8 == 0 && desc->n % 8 == 0) {
         const Geom g = make_geom(desc);
         MfmaPlan given;
-        if (plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N) &&
+        if (plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N, mask_pitch_bytes) &&
             (given.splitk == 1 || (dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= given.workspace_bytes))) {
             // the mask that the caller wants, then the product on it
             const int rcd = lrbi_decode_mask(desc, dIp_packed, dIz_packed, dMask, mask_pitch_bytes, stream);

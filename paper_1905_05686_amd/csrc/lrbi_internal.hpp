@@ -157,7 +157,7 @@ int launch_mfma_conv(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, const C
 // software-pipelined tile kernel (lrbi_gemm_pipe.hip)
 bool pipe_shape_ok(const Geom &g);
 bool pipe_ok(const Geom &g, const void *dIz, const void *dX, int64_t ldw, int64_t ldx, int64_t N);
-bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N);
+bool pipe_given_ok(const Geom &g, const void *dX, int64_t ldw, int64_t ldx, int64_t N, int64_t mask_pitch_bytes);
 int launch_pipe_gemm(const Geom &g, const MfmaPlan &plan, lrbi_dtype dt, int pf, const void *dW, int64_t ldw,
                      const uint32_t *dIp, const uint32_t *dIz, const void *dX, int64_t ldx, int64_t N, void *dY,
                      int64_t ldy, void *dWorkspace, hipStream_t stream, MaskOut mo = {nullptr, 0});

@@ -498,3 +498,21 @@ def test_pipelined_kernel_on_a_decoded_mask(m, n, r, c, k, N, dtype):
     # a pruned weight never reaches the sum, whatever it holds
     Wn = torch.where(torch.from_numpy(M.astype(bool)).to(dev()), W, torch.full_like(W, float("nan")))
     assert torch.equal(lrbi.masked_gemm(desc, Wn, dIp, dIz, X, workspace=ws), lrbi.masked_gemm(desc, W, dIp, dIz, X, workspace=ws))
+
+
+def test_decoded_mask_with_rows_far_apart():
+    """Rows of the caller's mask more than 2^32 / 127 bytes apart: a lane's 32-bit offset does not reach the tile's last rows."""
+    m, n, r, c, k, N = 128, 3000, 300, 300, 8, 4096
+    pitch = 33818656  # 127 rows further lies 2016 bytes past 2^32
+    print("mask rows %d bytes apart" % pitch, flush=True)
+    cfg = workloads.Config("far", m, n, r, c, k, 0.12, N, "f16", 0.05)
+    data = workloads.make(cfg)
+    ref, M = _oracle(cfg, data)
+    desc = desc_of(cfg)
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    mask = torch.empty((m, pitch), dtype=torch.uint8, device=dev())
+    ws = workspace_for(desc, lrbi.F16, N)
+    out, Y = lrbi.decode_and_gemm(desc, to_device(data["W"], "f16"), dIp, dIz, to_device(data["X"], "f16"), mask=mask, workspace=ws)
+    torch.cuda.synchronize()
+    assert np.array_equal(unpack_device_mask(out[:, :16 * ((n + 127) // 128)], n)[:, :n], M)
+    _assert_close(Y, ref, "f16", "far rows")
