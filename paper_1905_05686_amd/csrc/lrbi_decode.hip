@@ -694,6 +694,7 @@ static bool plan_nibble(const Geom &g, NibblePlan &p, int64_t pitch_bytes, const
     p.bands_per_tile_row = (g.r + p.rows_per_band - 1) / p.rows_per_band;
     p.items = (int64_t)p.spans * g.tile_rows * p.bands_per_tile_row;
     if (p.items < (int64_t)cus || p.items > 0x7FFFFFFF) return false;
+    if (p.rows_per_band > ((int64_t)1 << 32) / pitch_bytes) return false; // a band's rows lie within 32-bit byte offsets
     p.iz16 = (((uintptr_t)dIz & 15) == 0) ? 1 : 0;
     p.pitch16 = pitch_bytes / 16;
     p.t_pieces = p.span_tiles * (per_tile_pieces + kNibTileSkew);

@@ -170,3 +170,20 @@ def test_runs_on_a_side_stream():
     s.synchronize()
     ref = orc.decode_mask(d["Ip01"], d["Iz01"], cfg.m, cfg.n, cfg.r, cfg.c, cfg.k)
     assert np.array_equal(unpack_device_mask(out, cfg.n)[:, :cfg.n], ref)
+
+
+def test_rows_of_a_band_beyond_32_bit_offsets():
+    """512 mask rows of 8 MiB and 16 bytes: the last row of a band lies past 2^32."""
+    d = lrbi.Desc(512, 1 << 20, 512, 512, 32)
+    pitch = (1 << 23) + 16
+    print("decode, mask rows %d bytes apart" % pitch, flush=True)
+    gen = torch.Generator(device=dev()).manual_seed(4)
+
+    def words(shape):  # about one bit in eight set
+        draw = lambda: torch.randint(-2 ** 31, 2 ** 31, shape, dtype=torch.int32, device=dev(), generator=gen)  # noqa: E731
+        return draw() & draw() & draw()
+    ip, iz = words((d.tiles * d.r, 1)), words((d.tiles * d.k, 16))
+    ref = lrbi.decode_mask(d.with_flags(lrbi.FLAG_DECODE_GENERIC), ip, iz)
+    out = lrbi.decode_mask(d, ip, iz, pitch_bytes=pitch)
+    torch.cuda.synchronize()
+    assert torch.equal(out[:, :ref.shape[1]], ref)
