@@ -212,12 +212,14 @@ int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, in
  * AND the fused masked product Y = (W o I_a) X (arguments of lrbi_masked_gemm, workspace as sized by
  * lrbi_masked_gemm_workspace_bytes).  For f16 / bf16 layers this is one product launch (plus the split reduction
  * when the plan splits) on the kernels that rebuild the mask in a form they can store on the way, so that the
- * stand-alone decode kernel and its launch drop out: the pipelined tile kernel (c % 128 == 0, or c % 64 == 0 with
- * n % 128 == 0; r % 128 == 0, k <= 64, no cut-off tiles, N > 32, X and W readable in 16-byte pieces), the generic
+ * stand-alone decode kernel and its launch drop out: the pipelined tile kernel in 128 x 128 tiles (c % 64 == 0, r % 128 == 0,
+ * k <= 64, N > 32, X and W readable in 16-byte pieces), the generic
  * tile kernel (any tile shape and rank, cut-off tiles, N > 4, W readable in 16-byte pieces), and the row-streaming
- * kernels for narrow batches (N = 1 or a multiple of 4 up to 32, any tile shape).  Every other case (fp32, the
+ * kernels for narrow batches (N = 1 or a multiple of 4 up to 32, any tile shape).  Where lrbi_masked_gemm decodes the mask
+ * first, it is decoded into dMask (rows up to 32 MiB apart) and the product reads it there.  Every other case (fp32, results
+ * large enough for 256 x 256 tiles, the
  * staged panel kernels, unaligned W) runs lrbi_decode_mask and then lrbi_masked_gemm on `stream`.  Results are
- * bit-identical to those two calls.
+ * bit-identical to those two calls with the same workspace.
  * Errors: those of the two entry points.
  */
 int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,

@@ -1094,7 +1094,9 @@ bool mfma_gemm_emits_mask(const Geom &g, const MfmaPlan &plan, const void *dW, i
 {
     if (((uintptr_t)dW & 15) != 0 || ldw % 8 != 0 || g.n % 8 != 0) return false;
     if (plan.tile >= 1 && plan.tile <= 3) return true; // the generic kernel: any shape
-    return plan.tile >= kFirstPipeTile && pipe_ok(g, dIz, dX, ldw, ldx, N);
+    // (the 256 x 256 form does not store it; the 128 x 128 form in its place gave other bits than lrbi_masked_gemm and took
+    // longer than a decode and the 256 x 256 form: 16384 x 16384, N = 4096 2352 us against 1641, 4096 x 512 41 against 28)
+    return plan.tile >= kFirstPipeTile && plan.tile != kPipe256Tile && pipe_ok(g, dIz, dX, ldw, ldx, N);
 }
 
 int launch_mfma_gemm(const Geom &g, const MfmaPlan &plan_in, lrbi_dtype dt, const void *dW, int64_t ldw,
@@ -1106,8 +1108,8 @@ int launch_mfma_gemm(const Geom &g, const MfmaPlan &plan_in, lrbi_dtype dt, cons
     MfmaPlan plan = plan_in;
     if (plan.tile >= kFirstPipeTile) {
         if (plan.mask_given || pipe_ok(g, dIz, dX, ldw, ldx, N)) {
-            // (the mask as a by-product and the planes of a fused consumer come from the 128 x 128 form)
-            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr && !g.ragged && !plan.mask_given)
+            // (the planes of a fused consumer come from the 128 x 128 form)
+            if (plan.tile == kPipe256Tile && plan.splitk == 1 && !plan.planes_only && !mo.ptr && !g.ragged)
                 return launch_pipe256_gemm(g, dt, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, stream);
             const int pf = plan.tile == kPipe256Tile ? 2 : plan.tile - kFirstPipeTile;
             const int rc = launch_pipe_gemm(g, plan, dt, pf, dW, ldw, dIp, dIz, dX, ldx, N, dY, ldy, dWorkspace, stream, mo);

@@ -239,6 +239,26 @@ extern "C" int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtyp
     return LRBI_OK;
 }
 
+// The matrix-core plan of a product, for lrbi_masked_gemm and lrbi_decode_and_gemm alike (the same arguments give the same
+// bits from either).  mask_given: the mask goes behind the planes in the workspace first.
+static int choose_product(const lrbi_desc *desc, const Geom &g, int64_t ldw, const void *dIz_packed, const void *dX, int64_t ldx,
+                          int64_t N, const void *dWorkspace, uint64_t workspace_bytes, MfmaPlan *plan)
+{
+    const bool ws_usable = dWorkspace && aligned_to(dWorkspace, 16);
+    const int64_t pitch = mask_pitch_of(g);
+    if (ws_usable && plan_given(g, desc->flags, N, plan) && pipe_given_ok(g, dX, ldw, ldx, N, pitch) &&
+        workspace_bytes >= plan->workspace_bytes + (uint64_t)g.m * (uint64_t)pitch)
+        return LRBI_OK;
+    const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
+    *plan = plan_mfma(g, desc->flags, N, pieces);
+    if (plan->splitk > 1 && !(ws_usable && workspace_bytes >= plan->workspace_bytes)) {
+        if (desc->flags & LRBI_FLAG_SPLITK_MASK) return LRBI_ERR_WORKSPACE;
+        // no scratch: one slice over the whole n range
+        *plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N, pieces);
+    }
+    return LRBI_OK;
+}
+
 extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,
                                 const void *dIp_packed, const void *dIz_packed, const void *dX, int64_t ldx,
                                 int64_t N, void *dY, int64_t ldy, void *dWorkspace, uint64_t workspace_bytes,
@@ -289,33 +309,18 @@ extern "C" int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const v
     if (!mfma)
         return launch_valu_gemm(g, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
                                 dX, ldx, N, dY, ldy, s);
-    {
-        MfmaPlan given;
-        if (dWorkspace && aligned_to(dWorkspace, 16) && plan_given(g, desc->flags, N, &given) &&
-            pipe_given_ok(g, dX, ldw, ldx, N, mask_pitch_of(g))) {
-            const int64_t pitch = mask_pitch_of(g);
-            const uint64_t planes = given.workspace_bytes; // whole fp32 rows of four: a multiple of 16
-            if (workspace_bytes >= planes + (uint64_t)g.m * (uint64_t)pitch) {
-                void *mask = (char *)dWorkspace + planes;
-                const int rcd = launch_decode(g, desc->flags, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, mask, pitch, s);
-                if (rcd != LRBI_OK) return rcd;
-                return launch_mfma_gemm(g, given, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, dX,
-                                        ldx, N, dY, ldy, dWorkspace, s, MaskOut{mask, pitch / 16});
-            }
-        }
-    }
-    const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
-    MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
-    if (plan.splitk > 1) {
-        const bool ws_ok = dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= plan.workspace_bytes;
-        if (!ws_ok) {
-            if (desc->flags & LRBI_FLAG_SPLITK_MASK) return LRBI_ERR_WORKSPACE;
-            // no scratch: fall back to one slice over the whole n range
-            plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N, pieces);
-        }
+    MfmaPlan plan;
+    const int rcp = choose_product(desc, g, ldw, dIz_packed, dX, ldx, N, dWorkspace, workspace_bytes, &plan);
+    if (rcp != LRBI_OK) return rcp;
+    MaskOut mask = {nullptr, 0};
+    if (plan.mask_given) {
+        const int64_t pitch = mask_pitch_of(g);
+        mask = MaskOut{(char *)dWorkspace + plan.workspace_bytes, pitch / 16}; // whole fp32 rows of four: a multiple of 16
+        const int rcd = launch_decode(g, desc->flags, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, mask.ptr, pitch, s);
+        if (rcd != LRBI_OK) return rcd;
     }
     return launch_mfma_gemm(g, plan, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed,
-                            dX, ldx, N, dY, ldy, dWorkspace, s);
+                            dX, ldx, N, dY, ldy, dWorkspace, s, mask);
 }
 
 extern "C" int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,
@@ -352,25 +357,17 @@ extern "C" int lrbi_decode_and_gemm(const lrbi_desc *desc, lrbi_dtype dtype, con
     // their own use and store it on the way (the workgroups of the first block of batch columns do).
     if (use_mfma(desc, dtype, N) && aligned_to(dW, 16) && ldw % 8 == 0 && desc->n % 8 == 0) {
         const Geom g = make_geom(desc);
-        MfmaPlan given;
-        if (plan_given(g, desc->flags, N, &given) && pipe_given_ok(g, dX, ldw, ldx, N, mask_pitch_bytes) &&
-            (given.splitk == 1 || (dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= given.workspace_bytes))) {
-            // the mask that the caller wants, then the product on it
-            const int rcd = lrbi_decode_mask(desc, dIp_packed, dIz_packed, dMask, mask_pitch_bytes, stream);
+        MfmaPlan plan;
+        const int rcp = choose_product(desc, g, ldw, dIz_packed, dX, ldx, N, dWorkspace, workspace_bytes, &plan);
+        if (rcp != LRBI_OK) return rcp;
+        bool stores = false; // the product leaves the mask, or reads the caller's
+        if (plan.mask_given) {
+            stores = pipe_given_ok(g, dX, ldw, ldx, N, mask_pitch_bytes);
+            const int rcd = stores ? lrbi_decode_mask(desc, dIp_packed, dIz_packed, dMask, mask_pitch_bytes, stream) : LRBI_OK;
             if (rcd != LRBI_OK) return rcd;
-            return launch_mfma_gemm(g, given, dtype, dW, ldw, (const uint32_t *)dIp_packed, (const uint32_t *)dIz_packed, dX, ldx,
-                                    N, dY, ldy, dWorkspace, (hipStream_t)stream, MaskOut{dMask, mask_pitch_bytes / 16});
-        }
-        const bool pieces = pipe_ok(g, dIz_packed, dX, ldw, ldx, N);
-        MfmaPlan plan = plan_mfma(g, desc->flags, N, pieces);
-        if (plan.splitk > 1) {
-            const bool ws_ok = dWorkspace && aligned_to(dWorkspace, 16) && workspace_bytes >= plan.workspace_bytes;
-            if (!ws_ok) {
-                if (desc->flags & LRBI_FLAG_SPLITK_MASK) return LRBI_ERR_WORKSPACE;
-                plan = plan_mfma(g, (desc->flags & ~LRBI_FLAG_SPLITK_MASK) | (1u << LRBI_FLAG_SPLITK_SHIFT), N, pieces);
-            }
-        }
-        if (mfma_gemm_emits_mask(g, plan, dW, ldw, dIz_packed, dX, ldx, N))
+        } else
+            stores = mfma_gemm_emits_mask(g, plan, dW, ldw, dIz_packed, dX, ldx, N);
+        if (stores)
             return launch_mfma_gemm(g, plan, dtype, dW, ldw, (const uint32_t *)dIp_packed,
                                     (const uint32_t *)dIz_packed, dX, ldx, N, dY, ldy, dWorkspace, (hipStream_t)stream,
                                     MaskOut{dMask, mask_pitch_bytes / 16});

@@ -516,3 +516,31 @@ def test_decoded_mask_with_rows_far_apart():
     torch.cuda.synchronize()
     assert np.array_equal(unpack_device_mask(out[:, :16 * ((n + 127) // 128)], n)[:, :n], M)
     _assert_close(Y, ref, "f16", "far rows")
+
+
+# the 256 x 256 form (which does not store the mask), tiles that line up with nothing (the mask decoded first, if the workspace
+# has room for it), cut-off tiles, the general kernel
+@pytest.mark.parametrize("m,n,r,c,k,N", [
+    (4096, 128, 128, 64, 8, 4096),
+    (1200, 3000, 300, 300, 8, 512),
+    (1290, 1096, 128, 192, 40, 264),
+    (300, 960, 100, 64, 33, 100),
+])
+def test_mask_and_product_in_one_call_have_the_bits_of_two(m, n, r, c, k, N):
+    cfg = workloads.Config("both", m, n, r, c, k, 0.12, N, "bf16", 0.05)
+    print("mask and product in one call", cfg, flush=True)
+    data = workloads.make(cfg)
+    desc = desc_of(cfg)
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    W, X = to_device(data["W"], "bf16"), to_device(data["X"], "bf16")
+    ref_mask = lrbi.decode_mask(desc, dIp, dIz)
+    asked = lrbi.masked_gemm_workspace_bytes(desc, lrbi.BF16, N)
+    for nbytes in (asked, asked - ref_mask.numel(), 0):  # (without room for a mask)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=dev()) if nbytes > 0 else None
+        ref = lrbi.masked_gemm(desc, W, dIp, dIz, X, workspace=ws)
+        for pad in (0, 16):
+            mask = torch.empty((m, ref_mask.shape[1] + pad), dtype=torch.uint8, device=dev())
+            mask, Y = lrbi.decode_and_gemm(desc, W, dIp, dIz, X, mask=mask, workspace=ws)
+            torch.cuda.synchronize()
+            assert torch.equal(mask[:, :ref_mask.shape[1]], ref_mask)
+            assert torch.equal(Y.view(torch.int16), ref.view(torch.int16)), (nbytes, pad)
