@@ -190,6 +190,9 @@ int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtype dtype, in
  * value is stored under it, NaN and Inf included), and multiplied with X.
  *   dW: m x n row-major, leading dimension ldw >= n (elements).
  *   dX: n x N row-major, ldx >= N.   dY: m x N row-major, ldy >= N; overwritten.
+ *   f16 / bf16: X should be finite.  In the columns of Y that have an infinity or a NaN above them in X, rows that prune its
+ *   weight get a NaN (the zeroed weight is multiplied with it); rows that keep it get what IEEE arithmetic gives.  fp32
+ *   products step over it.
  *   W, X, Y share `dtype`.  Products are accumulated in fp32 (order unspecified
  *   but fixed: two calls with the same arguments give identical bits) and
  *   rounded to nearest-even on store.
@@ -198,9 +201,10 @@ int lrbi_masked_gemm_workspace_bytes(const lrbi_desc *desc, lrbi_dtype dtype, in
  *   vector paths, anything else a slower scalar path with the same results.
  *   dWorkspace / workspace_bytes: optional scratch (16-byte aligned).  With NULL
  *   or fewer bytes than lrbi_masked_gemm_workspace_bytes reports, the library
- *   uses an unsplit kernel (slower for small m * N), unless desc.flags forces a
+ *   uses a kernel that rebuilds the mask itself, and an unsplit one where the partial
+ *   sums have no room (slower for small m * N), unless desc.flags forces a
  *   split, which then fails with LRBI_ERR_WORKSPACE.
- * One or two kernel launches on `stream`.
+ * One to three kernel launches on `stream`.
  */
 int lrbi_masked_gemm(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW, int64_t ldw,
                      const void *dIp_packed, const void *dIz_packed, const void *dX, int64_t ldx,

@@ -58,9 +58,10 @@ static_assert(SmemDma<4, true>::bytes <= 160 * 1024, "LDS of a compute unit");
 // HALF: tile widths that are an odd multiple of 64 (the paper's 576-column tiles, Table 2): a 128-column unit may
 // then lie across two tile columns, so the factor slices are gathered, and Eq. 3 is evaluated, per 64-column half
 // unit, each with the I_p word and the I_z words of its own tile.  Everything behind the mask bytes is the same.
-// RAG: matrices that end inside a tile, or whose rows end inside a 128-column unit.  Rows past the last one are fetched as the last one and not stored; in the last slab,
-// pieces of W past the last column and rows of X past the last one are fetched as the last ones and meet zero mask bits (the
-// mask words are cut at the last column).
+// RAG: matrices that end inside a tile, or whose rows end inside a 128-column unit.  Rows past the last one are fetched as the
+// last one and not stored; in the last slab, pieces of W past the last column are fetched as the last ones and meet zero mask
+// bits (the mask words are cut at the last column), rows of X past the last one too, and are then cleared in LDS: an infinity
+// in the last row would come back as a NaN from the zeroed weights.
 // PRE: tile shapes that line up with nothing, and any rank.  The mask has been decoded to global memory before (mask_out, rows
 // of mask_pitch16 pieces): a panel of it is copied into LDS as it lies there, 64 bytes a row, piece p of row q at slot p ^
 // ((q >> 2) & 3), and nothing is formed here.
@@ -197,6 +198,18 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         if constexpr (i == 1) next_w();
         if constexpr (i == 3) next_x();
     };
+    // RAG: this wavefront's pieces of X rows past the last column become zero in a stage (they have landed: waited for by count;
+    // in front of the barrier that hands the slab over)
+    auto clear_tail = [&](int stage) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int chunk = wave + 8 * i;
+            if (chunk * 4 + (lane >> 4) >= k_left)
+                *reinterpret_cast<uint4 *>(smem + stage * STAGE_BYTES + STAGE_X + chunk * 1024 + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    const int tail_slab = RAG && k_left < BK ? last : -1;
 
     // ---- operand reads: byte addresses inside a stage.  This wavefront's steps are kk = 2 kg + j, j = 0, 1.
     // W operand of step kk: row q = 32 wq + (lane % 32), piece 2 kk + (lane / 32)
@@ -479,6 +492,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     }
     // slab 0 (EMIT: a mask store, where there is one, is younger: the wait is one piece longer than it has to be)
     wait_loads<kProloguePieces - 4>();
+    if (RAG && tail_slab == 0) clear_tail(0);
     __syncthreads();
     // entry state of the loop: X operands of this wavefront's first step, its W operand masked, the second read
     uint32_t mcur = my_bytes(fetch_mask(0));
@@ -533,6 +547,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                     wait_loads<(NS - 3) * 4 + (PRE ? 1 : HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six, PRE one)
                 } else
                     wait_loads<(NS - 3) * 4>(); // slab s + 1 has landed (four younger loads may still be in flight)
+                if (RAG && s + 1 == tail_slab) clear_tail(st1);
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_x(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});

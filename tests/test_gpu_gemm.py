@@ -544,3 +544,33 @@ def test_mask_and_product_in_one_call_have_the_bits_of_two(m, n, r, c, k, N):
             torch.cuda.synchronize()
             assert torch.equal(mask[:, :ref_mask.shape[1]], ref_mask)
             assert torch.equal(Y.view(torch.int16), ref.view(torch.int16)), (nbytes, pad)
+
+
+# infinities in the last row of X where the last slab of 64 columns is cut off: a kept weight carries them to Y as infinities, as on
+# the general kernel (a pruned one meets them as zero: NaN); nothing but the last row itself may be multiplied with them
+@pytest.mark.parametrize("m,n,r,c,k,N,tile", [
+    (127, 8, 128, 64, 5, 40, 14), (260, 520, 128, 128, 8, 96, 14), (300, 1096, 128, 192, 40, 64, 14), (255, 632, 256, 1024, 9, 72, 14),
+    (513, 2312, 256, 576, 16, 128, 0), (1200, 3000, 300, 300, 8, 512, 0), (640, 1992, 100, 100, 33, 1032, 0),
+])
+def test_infinities_in_the_last_row_of_x(m, n, r, c, k, N, tile):
+    cfg = workloads.Config("inf", m, n, r, c, k, 0.3, N, "f16", 0.05)
+    print("infinities in the last row of X", cfg, "tile", tile, flush=True)
+    data = workloads.make(cfg)
+    M = orc.decode_mask(data["Ip01"], data["Iz01"], m, n, r, c, k)
+    X = data["X"].copy()
+    X[n - 1, ::3] = np.inf
+    X[n - 1, 1::3] = -np.inf
+    with np.errstate(invalid="ignore"):
+        ref = (workloads.to_float64(data["W"], "f16") * M) @ workloads.to_float64(X, "f16")
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    desc = desc_of(cfg, lrbi.flag_tile(tile))
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    W, dX = to_device(data["W"], "f16"), to_device(X, "f16")
+    ws = workspace_for(desc, lrbi.F16, N)
+    for Y in (lrbi.masked_gemm(desc, W, dIp, dIz, dX, workspace=ws), lrbi.decode_and_gemm(desc, W, dIp, dIz, dX, workspace=ws)[1]):
+        torch.cuda.synchronize()
+        Y = to_float64(Y)
+        assert np.array_equal(np.isnan(Y), np.isnan(ref))
+        assert np.array_equal(np.where(np.isinf(Y), Y, 0), np.where(np.isinf(ref), ref, 0))
+        ok = np.isfinite(ref)
+        assert orc.rel_err(np.where(ok, Y, 0), np.where(ok, ref, 0)) <= TOL["f16"]
