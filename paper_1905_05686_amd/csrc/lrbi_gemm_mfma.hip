@@ -914,8 +914,19 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces)
             // unit, at least 8 slabs per slice), the 256-lane panel kernels two.
             const int64_t target = (tile >= 9) ? 256 : 512;
             want = (target + tiles - 1) / tiles;
-            // (a few workgroups more than that cost a second round: 4100 x 9224, N = 128, 33 tiles: 8 slices 38 us, 7 slices 27)
-            if (want * tiles > target) want = target / tiles;
+            if (want * tiles > target) {
+                // A few workgroups more than the units.  Where one fills a unit (the pipelined kernel, its stand-ins 9 and 10)
+                // they cost a second round: 4100 x 9224, N = 128, 33 tiles: 8 slices 38 us, 7 slices 27.  Two fit a unit of the
+                // 32-column form and of the general kernel, the pipelined one's stand-in on tile widths of 64 (2 j + 1) when X
+                // cannot be read in pieces: one slice fewer leaves units idle there (us, more against fewer slices: 32 columns,
+                // 16640 x 4096, N = 5, 130 tiles 50 / 74, 12800 x 4096, 100 tiles 37 / 42; general, 128 x 64 tiles, 16640 x 4096,
+                // N = 36 161 / 258, 128 x 192 tiles, 5504 x 4608, N = 389 195 / 350), unless nine columns and more keep at least
+                // four fifths of them busy (4224 x 9216, N = 18, 33 tiles 42 / 38, N = 5 33.2 / 33.2; 8832 x 2304, N = 30 27 / 25;
+                // 12800 x 4096, N = 13 45 / 47, 11008 x 8192, 86 tiles, N = 13 78 / 85).
+                const int64_t fewer = target / tiles;
+                const bool alone = tile >= kFirstPipeTile ? (x_pieces || panel_ok(g, 128)) : (tile == 9 || tile == 10);
+                if (alone || (tile == 11 && N > 8 && fewer * tiles * 5 >= target * 4)) want = fewer;
+            }
         }
         if (want > cap) want = cap;
         if (want > 64) want = 64;

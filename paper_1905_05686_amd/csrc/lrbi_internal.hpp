@@ -112,8 +112,7 @@ struct MfmaPlan {
     bool mask_given = false; // the pipelined kernel on a mask decoded before (plan_given())
     bool split_optional = false; // the tiles alone fill the chip: the slices are for evening out, not needed
 };
-// x_pieces: the pipelined kernel can read X (pipe_ok()); asked for shapes that it only takes in its cut-off form, whose
-// alternative, the general kernel, is planned differently
+// x_pieces: the pipelined kernel can read X (pipe_ok()); the kernels that run where it cannot are planned differently
 MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces = false);
 // Tile shapes and ranks that the pipelined kernel cannot form the mask for: the mask decoded first, then the pipelined kernel
 // on it.  True where that is the better choice; *p: its plan (workspace_bytes: the planes alone).

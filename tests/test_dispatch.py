@@ -44,3 +44,32 @@ def test_decoded_mask_offsets_fit_32_bits(pitch, ok):
     assert given_ok(geom(1200, 3000, 300, 300, 8), 3000, 512, 512, pitch) is ok
     if ok:
         assert 127 * pitch + 16 * ((3000 + 127) // 128) <= 1 << 32
+
+
+class Plan(ctypes.Structure):
+    """Mirror of the library's internal MfmaPlan."""
+    _fields_ = [("tile", ctypes.c_int), ("bm", ctypes.c_int), ("bn", ctypes.c_int), ("splitk", ctypes.c_int), ("kper", i64),
+                ("workspace_bytes", ctypes.c_uint64), ("planes_only", ctypes.c_bool), ("mask_given", ctypes.c_bool),
+                ("split_optional", ctypes.c_bool)]
+
+
+def plan(g, N, pieces, flags=0):
+    return internal("_ZN4lrbi9plan_mfmaERKNS_4GeomEjlb", Plan, vp, ctypes.c_uint32, i64, ctypes.c_bool)(ctypes.addressof(g), flags, N, pieces)
+
+
+PIPE, PIPE256 = 14, 15
+
+
+@pytest.mark.parametrize("m,n,c,N,pieces,tile,slices", [
+    # the 32-column panel kernel, two workgroups per compute unit
+    (16640, 4096, 512, 5, False, 11, 2), (16640, 4096, 512, 30, False, 11, 2), (12800, 4096, 512, 7, False, 11, 3),
+    (11008, 8192, 512, 13, False, 11, 3), (4224, 9216, 512, 5, False, 11, 8), (4224, 9216, 512, 18, False, 11, 7),
+    # tile widths of 64 (2 j + 1), X not in 16-byte pieces: the general kernel runs, two workgroups per compute unit
+    (16640, 4096, 64, 36, False, PIPE, 2), (5504, 4608, 192, 389, False, PIPE, 2), (4224, 9216, 192, 389, False, PIPE, 2),
+    # the pipelined kernel, one workgroup per compute unit, and the panel kernel that stands in for it
+    (5504, 4608, 192, 392, True, PIPE, 1), (5504, 4608, 512, 389, False, PIPE, 1), (4224, 9216, 512, 128, True, PIPE, 7),
+])
+def test_slices_of_panel_plans(m, n, c, N, pieces, tile, slices):
+    p = plan(geom(m, n, 128, c, 16), N, pieces)
+    assert (p.tile, p.splitk) == (tile, slices)
+    assert p.workspace_bytes == (slices * m * (-(-N // 4) * 4) * 4 if slices > 1 else 0)
