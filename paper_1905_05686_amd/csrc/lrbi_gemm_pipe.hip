@@ -60,8 +60,9 @@ static_assert(SmemDma<4, true>::bytes <= 160 * 1024, "LDS of a compute unit");
 // unit, each with the I_p word and the I_z words of its own tile.  Everything behind the mask bytes is the same.
 // RAG: matrices that end inside a tile, or whose rows end inside a 128-column unit.  Rows past the last one are fetched as the
 // last one and not stored; in the last slab, pieces of W past the last column are fetched as the last ones and meet zero mask
-// bits (the mask words are cut at the last column), rows of X past the last one too, and are then cleared in LDS: an infinity
-// in the last row would come back as a NaN from the zeroed weights.
+// bits (the mask words are cut at the last column), rows of X past the last one too: a short last slab is multiplied behind the
+// loop, where the operands of such rows are cleared (an infinity in the last row would come back as a NaN from the zeroed weights;
+// a test for that slab inside the loop cost up to 7 % of it).
 // PRE: tile shapes that line up with nothing, and any rank.  The mask has been decoded to global memory before (mask_out, rows
 // of mask_pitch16 pieces): a panel of it is copied into LDS as it lies there, 64 bytes a row, piece p of row q at slot p ^
 // ((q >> 2) & 3), and nothing is formed here.
@@ -198,18 +199,6 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
         if constexpr (i == 1) next_w();
         if constexpr (i == 3) next_x();
     };
-    // RAG: this wavefront's pieces of X rows past the last column become zero in a stage (they have landed: waited for by count;
-    // in front of the barrier that hands the slab over)
-    auto clear_tail = [&](int stage) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int chunk = wave + 8 * i;
-            if (chunk * 4 + (lane >> 4) >= k_left)
-                *reinterpret_cast<uint4 *>(smem + stage * STAGE_BYTES + STAGE_X + chunk * 1024 + lane * 16) = make_uint4(0u, 0u, 0u, 0u);
-        }
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    };
-    const int tail_slab = RAG && k_left < BK ? last : -1;
 
     // ---- operand reads: byte addresses inside a stage.  This wavefront's steps are kk = 2 kg + j, j = 0, 1.
     // W operand of step kk: row q = 32 wq + (lane % 32), piece 2 kk + (lane / 32)
@@ -492,7 +481,6 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     }
     // slab 0 (EMIT: a mask store, where there is one, is younger: the wait is one piece longer than it has to be)
     wait_loads<kProloguePieces - 4>();
-    if (RAG && tail_slab == 0) clear_tail(0);
     __syncthreads();
     // entry state of the loop: X operands of this wavefront's first step, its W operand masked, the second read
     uint32_t mcur = my_bytes(fetch_mask(0));
@@ -516,7 +504,9 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     // The next panel's mask is formed in any case, behind the last one from stand-ins (and not used): tests there would
     // cost more than it does.
     static_assert(PANEL_SLABS == 2 * NS, "two rounds of the ring");
-    for (int s0 = 0; s0 < nslabs; s0 += PANEL_SLABS) {
+    const bool tail = RAG && k_left < BK; // the last slab is short: multiplied behind the loop
+    const int nloop = tail ? nslabs - 1 : nslabs;
+    for (int s0 = 0; s0 < nloop; s0 += PANEL_SLABS) {
         static_for<PANEL_SLABS>([&](auto sc) {
             constexpr int ps = decltype(sc)::value;
             constexpr int st = ps % NS;                   // stage of slab s
@@ -526,7 +516,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
             using Par = std::integral_constant<int, st & 1>;        // register set of slab s's W operands
             using Nxt = std::integral_constant<int, (st & 1) ^ 1>;  // ... of slab s + 1's
             const int s = s0 + ps;
-            if (s < nslabs) {
+            if (s < nloop) {
                 uint32_t y;
                 uint32_t mk;
                 // first step
@@ -547,7 +537,6 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                     wait_loads<(NS - 3) * 4 + (PRE ? 1 : HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six, PRE one)
                 } else
                     wait_loads<(NS - 3) * 4>(); // slab s + 1 has landed (four younger loads may still be in flight)
-                if (RAG && s + 1 == tail_slab) clear_tail(st1);
                 LRBI_BARRIER();
                 // second step
                 mma(Par{}, I1{}, I0{}); read_x(st1, I0{}, I0{}); read_w(st1, Nxt{}, I0{}); read_w(st1, Nxt{}, I1{});
@@ -566,6 +555,26 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     }
 #undef LRBI_SB
 #undef LRBI_BARRIER
+    if constexpr (RAG) {
+        if (tail) { // its first operands are in registers, as in front of any other slab
+            static_for<NS>([&](auto sc) {
+                constexpr int st = decltype(sc)::value;
+                using Par = std::integral_constant<int, st & 1>;
+                if (last % NS != st) return;
+                static_for<FN>([&](auto a) { read_x(st, I1{}, a); });
+                mask_hi(Par{}, I1{}, mask_lo(Par{}, I1{}, mcur));
+                static_for<2>([&](auto j_c) {
+                    constexpr int j = decltype(j_c)::value;
+                    const bool in = 16 * (2 * kg + j) + 8 * lg < k_left; // the eight rows of X that this lane holds
+                    static_for<FN>([&](auto a_c) {
+                        constexpr int a = decltype(a_c)::value;
+                        if (!in) xf[j][a] = u32x4{0u, 0u, 0u, 0u};
+                        mma(Par{}, j_c, a_c);
+                    });
+                });
+            });
+        }
+    }
     wait_loads<0>(); // nothing may still be landing in LDS
     __syncthreads();
 
