@@ -833,9 +833,9 @@ static bool panel_ok(const Geom &g, int bm)
 // Matrices that end inside a tile (or inside a 128-column unit) on tile shapes that the pipelined kernel lines up with: it
 // against the general kernel, bf16, us: 4100 x 9224 in 256 x 256 tiles, N = 128 27 / 42, N = 1024 163 / 236; 5000 x 5000 in 512
 // x 576, N = 200 30 / 80; 1280 x 1216 in 256 x 64, N = 1000 21 / 34; 640 x 320, N = 4000 12 / 14.5.  The general kernel, of which two
-// workgroups share a compute unit and which splits long sums, keeps several rounds of short ones (16000 x 400, N = 1000 50 /
-// 44; 8000 x 200, N = 2000 41 / 33; 16000 x 800, N = 1000 62 / 68) and narrow batches that the pipelined one's longer slices leave on few units (2048 x 1728, N = 64
-// 16.1 / 15.6).
+// workgroups share a compute unit and which splits long sums, keeps several rounds of short ones (16000 x 400, N = 1000 45 /
+// 43; 8000 x 200, N = 2000 41 / 33; not all of them: 16000 x 800, N = 1000 58 / 66, where a decode first takes 61, see
+// given_wins()) and narrow batches that the pipelined one's longer slices leave on few units (2048 x 1728, N = 64 16.1 / 15.6).
 static bool cut_off_on_pipe(const Geom &g, int64_t N)
 {
     const int64_t tiles = ((g.m + 127) / 128) * ((N + 127) / 128);
@@ -942,22 +942,52 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces)
     return p;
 }
 
-// Two launches instead of one, so the product has to be worth it (bf16, us, decode and pipelined kernel against the general
-// one: 3000 x 3000 in 300 x 300 tiles, N = 512 31 / 90; 1000 x 1000 in 100 x 100, N = 1000 22 / 42; 4096 x 4096 in 64 x 64, N = 2048
-// 88 / 138; 2304 x 2048 in 576 x 512, rank 145, N = 128 21 / 25; 600 x 1200, N = 512 19.5 / 20.7; 12000 x 12000, N = 40 103 / 142;
-// but 3000 x 3000, N = 64 23.0 / 22.7; 1000 x 1000, N = 256 20.6 / 19.2; 300 x 5000, N = 96 22.6 / 19.7; 8000 x 200, N = 2000 42 / 40).
+// Two launches instead of one, so the product has to be worth the decode.  The lines are where it is, of the shapes that the
+// general kernel serves (cut-off tiles that line up but stay there among them: cut_off_on_pipe()): 2100 sizes from 300 x 392 to
+// 16000 x 4096, N = 64 to 4096, in eight tilings, bf16.  What moves them: whether the decode has its table form (whole tiles of
+// 128 j columns; half the time and less), whether the general kernel has its faster form (mask words loaded ahead of
+// their slab: whole slabs, up to 64 ranks), and the rounds of the 256 workgroups of the pipelined kernel.  Us, decode and pipelined
+// kernel against the general one:
+//   * Faster form, one round: 1000 x 4096 in 64 x 64 tiles, N = 1000 28 / 45; 2000 x 648, N = 1000 19.5 / 20.8, but N = 400 19 / 17;
+//     300 x 2000, N = 1000 21 / 18; 1024 x 4096, N = 400, 32 tiles 23.5 / 26; 8000 x 2000, N = 96 (a quarter of the column block idle) 24.4 / 23.7; table form: 960 x 512 in 192 x
+//     128, N = 2000 15.6 / 16.9, 4032 x 512, N = 200 15.3 / 14.3.
+//     Two rounds: 8000 x 520, N = 1000 33 / 26, 8000 x 1000 40.4 / 39.3.  More: 8000 x 520, N = 2000 53 / 48, 8000 x 648, N = 4096
+//     99 / 106; table form: 8064 x 512, N = 4096 79 / 86.
+//   * Slower form, up to 64 ranks: 3000 x 3000 in 300 x 300, N = 512 31 / 90; 300 x 392, N = 4096 17 / 21; 2000 x 648, N = 200, 32
+//     tiles 20 / 18; 1000 x 4096, N = 200, 16 tiles 23 / 24; 8000 x 392, N = 1000, two rounds 31 / 29; few columns only on large
+//     matrices: 12000 x 12000, N = 40 103 / 142; 3000 x 3000, N = 64 23.0 / 22.7.
+//   * Ranks above 64: table form 2304 x 2048 in 576 x 512, rank 145, N = 128 20 / 25, 576 x 4096, N = 200 19 / 23; without it 1000
+//     x 648, N = 1000, 64 tiles 30 / 36, 2000 x 2000, N = 200, 32 tiles 32 / 26.
+static bool given_wins(const Geom &g, int64_t N)
+{
+    const int64_t tiles = ((g.m + 127) / 128) * ((N + 127) / 128), pairs = (g.n + 2 * BK - 1) / (2 * BK), work = tiles * pairs;
+    const bool whole = !g.ragged, table = whole && g.c % 128 == 0, ranks = g.k > 64, ahead = g.c % BK == 0 && !ranks;
+    if (g.n < 384) return false;
+    if (ranks && table) return work >= 192;
+    if (N < 96 && (g.m * g.n < ((int64_t)1 << 25) || !(ahead ? table : (!ranks || g.c % 128 == 0)))) return false;
+    if (ahead) {
+        if (tiles > 256) return pairs >= (tiles <= 512 ? (table ? 6 : 8) : (tiles <= 1024 ? 5 : 4) + (table ? 0 : 1));
+        if (table) return pairs >= 4 && work >= (pairs == 4 ? 380 : pairs <= 8 ? 240 : 300) && (tiles >= 48 || N >= 128);
+        if (tiles < 48 || (N < 128 && tiles < 96)) return whole && N >= 128 && tiles >= 24 && work >= 700;
+        return pairs >= (whole ? 4 : 5) && work >= (pairs == 4 ? 900 : pairs == 5 ? (whole ? 480 : 800) : 490);
+    }
+    if (tiles > 256) return tiles > 512 || pairs >= (whole && !ranks ? 4 : 5);
+    if (ranks) return tiles >= 64 && pairs >= (whole ? 4 : 5) && work >= (pairs == 4 ? 380 : 320);
+    return pairs >= 4 && (tiles >= 48 || work >= (!whole ? 512 : tiles >= 32 ? 240 : 280));
+}
+
 bool plan_given(const Geom &g, uint32_t flags, int64_t N, MfmaPlan *out)
 {
     if ((flags & (LRBI_FLAG_TILE_MASK | LRBI_FLAG_SPLITK_MASK)) != 0) return false; // a kernel or a split asked for by flag
     if (N <= 32 || N % 8 != 0 || g.n % 8 != 0) return false;
     if (plan_mfma(g, flags, N, true).tile >= 4) return false; // served without
+    if (!given_wins(g, N)) return false;
     MfmaPlan p;
     p.tile = 14;
     p.bm = p.bn = 128;
     p.mask_given = true;
     const int64_t tiles = ((g.m + 127) / 128) * ((N + 127) / 128), npairs = (g.n + 2 * BK - 1) / (2 * BK);
     int64_t want = tiles < 192 ? 256 / tiles : 1; // one workgroup per compute unit, at least eight slabs each
-    if (g.n < 384 || tiles * npairs < 192 || (N < 96 && g.m * g.n < ((int64_t)1 << 25))) return false;
     if (want > npairs / 4) want = npairs / 4;
     if (want > 64) want = 64;
     if (want < 1) want = 1;

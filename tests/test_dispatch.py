@@ -73,3 +73,27 @@ def test_slices_of_panel_plans(m, n, c, N, pieces, tile, slices):
     p = plan(geom(m, n, 128, c, 16), N, pieces)
     assert (p.tile, p.splitk) == (tile, slices)
     assert p.workspace_bytes == (slices * m * (-(-N // 4) * 4) * 4 if slices > 1 else 0)
+
+
+def given(g, N):
+    p = Plan()
+    fn = internal("_ZN4lrbi10plan_givenERKNS_4GeomEjlPNS_8MfmaPlanE", ctypes.c_bool, vp, ctypes.c_uint32, i64, vp)
+    return p if fn(ctypes.addressof(g), 0, N, ctypes.addressof(p)) else None
+
+
+# sizes at which both ways were timed: the decode first (True) or the general kernel
+@pytest.mark.parametrize("args,N,first", [
+    ((16000, 400, 256, 256, 16), 1000, False), ((8000, 400, 128, 576, 32), 1000, False),  # cut off, lined up, short rows: 44 us against 50
+    ((8000, 520, 64, 64, 8), 1000, False), ((4000, 392, 192, 128, 16), 200, False), ((300, 2000, 300, 256, 33), 400, False),
+    ((292, 3040, 292, 64, 64), 472, False), ((1714, 448, 192, 320, 55), 432, False), ((2000, 2000, 576, 512, 145), 200, False),
+    ((16000, 4096, 64, 64, 8), 64, False), ((2000, 648, 300, 300, 8), 200, False), ((8000, 392, 100, 100, 8), 1000, False),
+    ((16000, 1600, 256, 256, 16), 2000, True), ((1000, 4096, 64, 64, 8), 1000, True), ((960, 640, 192, 128, 16), 2000, True),
+    ((3000, 3000, 300, 300, 8), 512, True), ((12000, 12000, 300, 300, 8), 40, True), ((2304, 2048, 576, 512, 145), 128, True),
+    ((8000, 1000, 100, 100, 8), 1000, True),
+    ((4096, 4096, 256, 256, 16), 1024, False), ((4096, 4096, 128, 192, 16), 1024, False),  # lined up: the mask formed in the kernel
+])
+def test_mask_decoded_first_where_it_pays(args, N, first):
+    p = given(geom(*args), N)
+    assert (p is not None) is first
+    if p is not None:
+        assert p.mask_given and p.tile == PIPE and p.kper % 128 == 0 and p.splitk * p.kper >= args[1] > (p.splitk - 1) * p.kper
