@@ -303,14 +303,24 @@ bool grad256_ok(const Geom &g, const void *dDY, int64_t lddy, const void *dX, in
     return tiles * g.k * g.izw * 4 < (int64_t)1 << 31 && tiles * g.r * g.ipw * 4 < (int64_t)1 << 31;
 }
 // One workgroup per compute unit does its round alone, so the rounds have to be nearly full, or a single one on a long
-// batch (bf16, us, 256 against 128: 4096 x 4096, 256 tiles: batch 128 17.6 / 19.1, 1024 39 / 51; 2304 x 4096, 144 tiles, batch
-// 1024: 31.7 / 34.6; but 4096 x 9216, 576 tiles in three rounds: batch 512 67 / 60, 128 43 / 33; 2048 x 4096, 128 tiles, batch
-// 1024: 31.2 / 29.0).
+// batch, and longer ones the more of them there are: the 128 x 128 form, four workgroups a unit, runs a tile's output under another
+// one's products.  Us, 256 against 128, 256 x 256 tiles of rank 16, f16 and bf16:
+//   * One round: 4096 x 4096, 256 tiles: batch 128 17.3 / 18.6, 1024 39 / 49; 2304 x 4096, 144 tiles, batch 1024 27 / 32, 512 18.3 /
+//     19.9; but 2048 x 4096, 128 tiles, batch 1024 31.2 / 29.0.
+//   * Two: 8192 x 4096, batch 512 50 / 56, 256 37.9 / 37.2, 128 30 / 29; 6912 x 4096, 432 tiles, batch 384 34 / 37.
+//   * More: 8192 x 8192, four, batch 512 97 / 103, 256 71 / 65, 128 57 / 50; 9216 x 9216, 1296 tiles in six (84 % of them full), batch
+//     512 137 / 128, 768 152 / 168, 256 102 / 81; 4096 x 9216, 576 tiles in three (75 %), batch 512 67 / 60.
+//   * Tile widths of 64 (2 j + 1) with more than 32 ranks, whose mask the 128 x 128 form takes longer over: 8192 x 4096 in 128 x 64, rank
+//     40, batch 128 31 / 36, 256 38 / 43; 8192 x 8192, rank 64, batch 128 59 / 68, 256 74 / 82; 12288 x 4096, rank 40, batch 384 67 / 76.
 bool grad256_wins(const Geom &g, int64_t N)
 {
     constexpr int64_t cus = 256;
     const int64_t t256 = ((g.m + 255) / 256) * ((g.n + 255) / 256), rounds = (t256 + cus - 1) / cus;
-    return (N >= 128 && rounds * cus * 5 <= t256 * 6) || (N >= 512 && rounds == 1 && t256 >= 144);
+    const bool full = rounds * cus * 5 <= t256 * 6;
+    if (rounds == 1) return (N >= 128 && full) || (N >= 512 && t256 >= 144);
+    if (rounds <= 4 && g.c % 128 != 0 && g.k > 32) return full && N >= 128;
+    if (rounds == 2) return full && N > 256;
+    return full && (N >= 768 || (N >= 512 && rounds * cus * 9 <= t256 * 10));
 }
 
 int launch_grad256(const Geom &g, lrbi_dtype dt, const void *dDY, int64_t lddy, const void *dX, int64_t ldx, int64_t N,

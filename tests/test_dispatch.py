@@ -97,3 +97,22 @@ def test_mask_decoded_first_where_it_pays(args, N, first):
     assert (p is not None) is first
     if p is not None:
         assert p.mask_given and p.tile == PIPE and p.kper % 128 == 0 and p.splitk * p.kper >= args[1] > (p.splitk - 1) * p.kper
+
+
+# sizes at which both forms of the weight gradient were timed: 256 x 256 tiles (True) or 128 x 128
+@pytest.mark.parametrize("m,n,N,wide", [
+    (4096, 4096, 128, True), (3840, 4096, 1024, True), (2304, 4096, 1024, True), (2048, 4096, 1024, False), (4096, 3328, 256, False),
+    (8192, 4096, 128, False), (8192, 4096, 256, False), (8192, 4096, 512, True), (6912, 4096, 384, True),
+    (8192, 8192, 128, False), (8192, 8192, 256, False), (8192, 8192, 512, True), (12800, 12800, 256, False),
+    (9216, 9216, 128, False), (9216, 9216, 512, False), (9216, 9216, 1024, True), (4096, 9216, 512, False),
+])
+def test_gradient_in_wide_tiles(m, n, N, wide):
+    fn = internal("_ZN4lrbi12grad256_winsERKNS_4GeomEl", ctypes.c_bool, vp, i64)
+    assert fn(ctypes.addressof(geom(m, n, 256, 256, 16)), N) is wide
+    assert fn(ctypes.addressof(geom(m, n, 128, 64, 20)), N) is wide
+
+
+@pytest.mark.parametrize("m,n,N,wide", [(8192, 4096, 128, True), (8192, 8192, 256, True), (12288, 4096, 384, True), (9216, 9216, 256, False)])
+def test_gradient_in_wide_tiles_of_many_ranks(m, n, N, wide):
+    fn = internal("_ZN4lrbi12grad256_winsERKNS_4GeomEl", ctypes.c_bool, vp, i64)
+    assert fn(ctypes.addressof(geom(m, n, 128, 64, 40)), N) is wide
