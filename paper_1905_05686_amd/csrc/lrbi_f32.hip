@@ -116,15 +116,11 @@ __device__ __forceinline__ void add_kept(double &s, unsigned long long bits, int
 }
 
 // mask word of row `row`, word column w
+template <bool AHEAD = false>
 __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
 {
-    const int ti = (int)(row / g.r);
-    return decode_word(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
-}
-__device__ __forceinline__ uint32_t row_word_ahead(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
-{
-    const int ti = (int)(row / g.r);
-    return decode_word_ahead(g, Ip, Iz, ti, (int)(row - (int64_t)ti * g.r), w);
+    const int ti = (int)(row / g.r), il = (int)(row - (int64_t)ti * g.r);
+    return AHEAD ? decode_word_ahead(g, Ip, Iz, ti, il, w) : decode_word(g, Ip, Iz, ti, il, w);
 }
 
 // adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it, without the batch columns in `skip`
@@ -184,7 +180,9 @@ __global__ __launch_bounds__(64 * WAVES) void f32_gemm_t_kernel(Geom g, const T 
             }
         };
         load(0, w[0], y[0]);
-        const uint32_t words = (i0 + lane < g.m) ? row_word_ahead(g, Ip, Iz, i0 + lane, jb) : 0u;
+        // (not with four I_z rows in flight where there are two batch blocks: they took the kernel from 128 to 129 registers and
+        // from two workgroups a compute unit to one, 300 x 8000, 1024 columns 112 -> 172 us)
+        const uint32_t words = (i0 + lane < g.m) ? row_word<NQ == 1 || WAVES == 1>(g, Ip, Iz, i0 + lane, jb) : 0u;
 #pragma unroll
         for (int s = 0; s < kF32Chunk / 2 / U; ++s) {
             if (s + 1 < kF32Chunk / 2 / U) load((s + 1) * U, w[(s + 1) & 1], y[(s + 1) & 1]);
@@ -333,7 +331,8 @@ __global__ __launch_bounds__(64 * WAVES) void f32_gemm_kernel(Geom g, const floa
 
 // dW = (dY X^T) o I_a, fp32.  One wavefront per 32 x (32 NJ) block of dW (no reduction is split: the blocks are many
 // and the batch is short).  Both operands are read four batch columns at a time, in the order described above.
-template <int NJ, bool VEC>
+// AHEAD: the mask words formed with four I_z rows in flight.
+template <int NJ, bool VEC, bool AHEAD>
 __global__ __launch_bounds__(256) void f32_grad_kernel(Geom g, const float *__restrict__ DY, int64_t lddy,
                                                        const float *__restrict__ X, int64_t ldx, int64_t N,
                                                        const uint32_t *__restrict__ Ip, const uint32_t *__restrict__ Iz,
@@ -377,7 +376,7 @@ __global__ __launch_bounds__(256) void f32_grad_kernel(Geom g, const float *__re
     };
     load(0, y[0], x[0]);
     // the block's mask words: lane l < 32 holds row i0 + l of the first word column, the other half the second's
-    const uint32_t words = row_word_ahead(g, Ip, Iz, at_most(i0 + li, g.m - 1), (int)(j0 >> 5) + (NJ == 2 ? half : 0));
+    const uint32_t words = row_word<AHEAD>(g, Ip, Iz, at_most(i0 + li, g.m - 1), (int)(j0 >> 5) + (NJ == 2 ? half : 0));
     for (int64_t q = 0; q < N; q += 16) {
         load(q + 8, y[1], x[1]);
         mma(y[0], x[0], acc[0]);
@@ -476,9 +475,14 @@ int launch_f32_grad(const Geom &g, const float *dDY, int64_t lddy, const float *
     if ((blocks + 3) / 4 > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     const dim3 grid((unsigned)((blocks + 3) / 4));
     const bool vec = (((uintptr_t)dDY | (uintptr_t)dX) & 15) == 0 && lddy % 4 == 0 && ldx % 4 == 0 && N % 4 == 0;
+    // I_z rows ahead unless a word has several tiles, with few rows set in each (us, without and with: 2000 x 2000 in 5 x 5 tiles, rank
+    // 2, 8 columns 13.0 / 16.5, 1000 x 4000 in 100 x 31, rank 40 11.4 / 12.5; a kernel of its own: a test in it took 5 % of the other shapes)
+    const bool ahead = g.c >= 32;
 #define LRBI_LAUNCH_F32(NJ, V)                                                                                     \
-    LRBI_LAUNCH((f32_grad_kernel<NJ, V>), grid, dim3(256), 0, stream, g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, jblocks, \
-                blocks)
+    do {                                                                                                           \
+        auto kern = ahead ? f32_grad_kernel<NJ, V, true> : f32_grad_kernel<NJ, V, false>;                          \
+        LRBI_LAUNCH(kern, grid, dim3(256), 0, stream, g, dDY, lddy, dX, ldx, N, dIp, dIz, dDW, lddw, jblocks, blocks); \
+    } while (0)
     if (nj == 2) {
         if (vec) LRBI_LAUNCH_F32(2, true);
         else LRBI_LAUNCH_F32(2, false);
