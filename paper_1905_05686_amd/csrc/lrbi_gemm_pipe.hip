@@ -501,8 +501,10 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     // first step every wavefront waits until its own pieces of slab s + 1 have landed; the barrier makes the
     // whole slab visible and tells that nobody reads slab s - 1 any more; the second step then runs next to the
     // loads of slab s + NS - 1 into the stage slab s - 1 occupied and to the reads of slab s + 1's operands.
-    // The next panel's mask is formed in any case, behind the last one from stand-ins (and not used): tests there would
-    // cost more than it does.
+    // The next panel's mask is formed in any case, behind the last one from that one's factors (and not used): tests there would
+    // cost more than it does.  Its factors are asked for only where there is one: slab 1 waits for them, and slices of a panel or
+    // two, which have nothing else to wait for, took up to a tenth longer (256 x 4608 convolution, two images of 28 x 28, slices of
+    // one panel 16.8 us against 18.5; 40 images of 10 x 10 on 512 x 2304, slices of 18 slabs 24.1 against 25.4).
     static_assert(PANEL_SLABS == 2 * NS, "two rounds of the ring");
     const bool tail = RAG && k_left < BK; // the last slab is short: multiplied behind the loop
     const int nloop = tail ? nslabs - 1 : nslabs;
@@ -532,7 +534,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                 if constexpr (ps >= 3 && ps <= 5 && !PRE) decode_add();
                 // factor slices of the next panel, requested at the panel's first slab: they have landed, for
                 // every wavefront, behind the next iteration's wait and barrier
-                if constexpr (ps == 0) {
+                if (ps == 0 && s0 + PANEL_SLABS < nslabs) {
                     load_factors();
                     wait_loads<(NS - 3) * 4 + (PRE ? 1 : HALF ? 6 : 2)>(); // slab s + 1 (younger: four, and two or three factor loads, HALF six, PRE one)
                 } else
