@@ -263,10 +263,10 @@ int lrbi_masked_conv3x3(const lrbi_desc *desc, lrbi_dtype dtype, const void *dW,
  * LRBI_STATIC_SCRATCH_BYTES bytes, but the partial sums of a split reduction (and the decoded mask, where it is
  * decoded first and fits behind them) go to a scratch array of that many bytes that is part of the library image on every GPU it runs on (held until
  * the process ends).  The call allocates and frees nothing, on the host side or the device side of HIP.
- *   Not split: shapes whose output alone fills the chip (192 blocks of 128 x 128, or of 128 x 64 or 128 x 32 where rows are
- *   few, on the general kernel).  A workspace lets lrbi_masked_gemm even their last round out; here they run
- *   unsplit, with the bits of lrbi_masked_gemm without a workspace, and leave the array alone; so do shapes
- *   that have no partial sums.
+ *   Without scratch: shapes whose output fills the chip on the general kernel (192 blocks of 128 x 128, or of 128 x 64 or
+ *   128 x 32 where rows are few), and shapes that have no partial sums, run with the bits of lrbi_masked_gemm without a
+ *   workspace and leave the array alone, whichever kernel takes them (lrbi_masked_gemm with a workspace may split their
+ *   reduction or decode their mask first, which gives other roundings).
  *   Limit: other shapes whose partial sums exceed LRBI_STATIC_SCRATCH_BYTES return LRBI_ERR_WORKSPACE before
  *   any launch (all five paper-shaped configurations fit: the largest, 4096 x 9216 at N = 128, needs 16 MiB).
  *   The device of `stream` must be the current device (the scratch array is looked up per current device).

@@ -11,6 +11,7 @@ import paper_1905_05686_amd as lrbi
 import workloads
 from oracle import lrbi_oracle as orc
 from gpu_util import TOL, desc_of, dev, device_factors, to_device, workspace_for
+from test_dispatch import geom, given, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -97,3 +98,54 @@ def test_many_tiles_leave_the_scratch_alone():
     torch.cuda.synchronize()
     assert not torch.equal(split, ref)  # the slices add up in another order
     assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
+def test_many_tiles_whose_slices_would_fit_run_unsplit():
+    """The same on a batch that only the general kernel takes, whose plan with a workspace does have slices."""
+    cfg = workloads.Config("t", 4100, 2056, 256, 256, 16, 0.08, 1004, "f16", 0.03, 3)
+    print("static scratch, slices that would fit", cfg, flush=True)
+    p = plan(geom(4100, 2056, 256, 256, 16), 1004, False)
+    assert p.split_optional and p.splitk > 1 and p.workspace_bytes <= 32 * 1024 * 1024
+    _, d, dIp, dIz, W, X = _case(cfg)
+    ref = lrbi.masked_gemm(d, W, dIp, dIz, X)
+    split = lrbi.masked_gemm(d, W, dIp, dIz, X, workspace=workspace_for(d, lrbi.F16, cfg.N))
+    out = torch.full_like(ref, float("nan"))
+    lrbi.masked_gemm_static(d, W, dIp, dIz, X, out)
+    torch.cuda.synchronize()
+    assert not torch.equal(split, ref)  # the slices add up in another order
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+
+
+def test_decoded_mask_behind_the_planes_of_the_scratch():
+    """Shapes whose mask is decoded first: planes and mask in the static array, two calls in a row, the second smaller."""
+    print("static scratch, mask behind the planes", flush=True)
+    for m, N in ((1200, 512), (900, 264)):
+        p = given(geom(m, 3000, 300, 300, 8), N)
+        assert p.splitk > 1 and p.workspace_bytes + m * 384 <= 32 * 1024 * 1024
+        assert _both(workloads.Config("na-mask", m, 3000, 300, 300, 8, 0.2, N, "bf16", 0.03, 8)) >= p.workspace_bytes + m * 384
+
+
+def test_decoded_mask_that_the_scratch_has_no_room_for():
+    """A mask of 40 MB: the bits of a call with a workspace of the array's size, which rebuilds the mask in the kernel."""
+    m, n, r, c, k, N = 20000, 16000, 500, 500, 8, 40
+    print("static scratch, mask too large", (m, n, r, c, k, N), flush=True)
+    p = given(geom(m, n, r, c, k), N)
+    assert p is not None and m * 2000 > 32 * 1024 * 1024
+    d = lrbi.Desc(m, n, r, c, k)
+    gen = torch.Generator(device=dev()).manual_seed(9)
+
+    def words(shape, valid):  # about one bit in four of the valid ones set
+        draw = lambda: torch.randint(-2 ** 31, 2 ** 31, shape, dtype=torch.int32, device=dev(), generator=gen)  # noqa: E731
+        left = (valid - 32 * torch.arange(shape[1], device=dev())).clamp(0, 32)
+        return draw() & draw() & torch.where(left == 32, -1, (1 << left) - 1).to(torch.int32)
+    ip, iz = words((d.tiles * r, 1), k), words((d.tiles * k, 16), c)
+    W = torch.randn((m, n), device=dev(), generator=gen).half()
+    X = torch.randn((n, N), device=dev(), generator=gen).half()
+    ref = lrbi.masked_gemm(d, W, ip, iz, X, workspace=torch.empty(lrbi.STATIC_SCRATCH_BYTES, dtype=torch.uint8, device=dev()))
+    first = lrbi.masked_gemm(d, W, ip, iz, X, workspace=workspace_for(d, lrbi.F16, N))
+    out = torch.full_like(ref, float("nan"))
+    lrbi.masked_gemm_static(d, W, ip, iz, X, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    assert not torch.equal(first.view(torch.int16), ref.view(torch.int16))
+    assert orc.rel_err(first.double().cpu().numpy(), ref.double().cpu().numpy()) <= 1e-3  # f16 roundings of fp32 sums
