@@ -8,6 +8,7 @@ import workloads
 from oracle import lrbi_oracle as orc
 from gpu_util import (ORACLE_THREADS, TOL, TORCH_DTYPE, desc_of, dev, device_factors, to_device, to_float64,
                       unpack_device_mask, workspace_for)
+from test_dispatch import PIPE, PIPE256, geom, given, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -574,3 +575,52 @@ def test_infinities_in_the_last_row_of_x(m, n, r, c, k, N, tile):
         assert np.array_equal(np.where(np.isinf(Y), Y, 0), np.where(np.isinf(ref), ref, 0))
         ok = np.isfinite(ref)
         assert orc.rel_err(np.where(ok, Y, 0), np.where(ok, ref, 0)) <= TOL["f16"]
+
+
+def _product_and_mask(cfg, data, flags=0):
+    """Y from either entry point against the oracle, the stored mask against it bit for bit."""
+    m, n, N = cfg.m, cfg.n, cfg.N
+    ref, M = _oracle(cfg, data)
+    desc = desc_of(cfg, flags)
+    dIp, dIz = device_factors(desc, data["Ip01"], data["Iz01"])
+    W, X = to_device(data["W"], cfg.dtype), to_device(data["X"], cfg.dtype)
+    for ws in (workspace_for(desc, DT_CODE[cfg.dtype], N), None):
+        _assert_close(lrbi.masked_gemm(desc, W, dIp, dIz, X, workspace=ws), ref, cfg.dtype, "product")
+        mask, Y = lrbi.decode_and_gemm(desc, W, dIp, dIz, X, workspace=ws)
+        torch.cuda.synchronize()
+        _assert_close(Y, ref, cfg.dtype, "mask stored")
+        bits = unpack_device_mask(mask, n)
+        assert np.array_equal(bits[:, :n], M) and not bits[:, n:].any()
+
+
+# sizes of the pipelined kernel's cut-off form that its own rule leaves to another one: the smallest input (one slab of eight
+# columns), two-word half units over several panels, more than 256 tiles with a cut-off last row block
+@pytest.mark.parametrize("m,n,r,c,k,N,dtype", [
+    (127, 8, 128, 64, 5, 40, "bf16"),
+    (300, 1096, 128, 192, 40, 64, "bf16"),
+    (4100, 520, 512, 256, 16, 1032, "bf16"),
+    (130, 1544, 128, 320, 64, 8, "f16"),
+])
+def test_cut_off_tiles_forced_on_the_pipelined_kernel(m, n, r, c, k, N, dtype):
+    print("pipelined kernel asked for, cut-off tiles", m, n, r, c, k, N, dtype, flush=True)
+    g = geom(m, n, r, c, k)
+    assert plan(g, N, True).tile != PIPE and plan(g, N, True, lrbi.flag_tile(PIPE)).tile == PIPE
+    cfg = workloads.Config("rag", m, n, r, c, k, 0.12, N, dtype, 0.05)
+    _product_and_mask(cfg, workloads.make(cfg), lrbi.flag_tile(PIPE))
+
+
+# ... and sizes that reach a form by the rules
+@pytest.mark.parametrize("m,n,r,c,k,N,tile", [
+    (4096, 128, 128, 64, 8, 4096, PIPE256),
+    (3968, 384, 128, 192, 33, 4088, PIPE256),
+    (513, 2312, 256, 576, 16, 128, PIPE),
+    (1152, 2048, 576, 512, 145, 136, None),  # None: the mask decoded first
+    (1153, 2056, 576, 512, 145, 904, None),
+    (520, 3000, 100, 100, 33, 1064, None),
+])
+def test_forms_that_the_rules_choose(m, n, r, c, k, N, tile):
+    print("form chosen by the rules", m, n, r, c, k, N, tile, flush=True)
+    g = geom(m, n, r, c, k)
+    assert (given(g, N) is not None) if tile is None else (given(g, N) is None and plan(g, N, True).tile == tile)
+    cfg = workloads.Config("rule", m, n, r, c, k, 0.12 if k < 64 else 0.03, N, "f16", 0.05)
+    _product_and_mask(cfg, workloads.make(cfg))
