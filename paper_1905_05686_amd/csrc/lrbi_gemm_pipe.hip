@@ -45,6 +45,9 @@ template <int NS, bool HALF = false> struct SmemDma {
 };
 static_assert(SmemDma<4, true>::bytes <= 160 * 1024, "LDS of a compute unit");
 
+// order of a launch's tiles: consecutive ones on one XCD; tile row after tile row instead of groups of four rows
+static constexpr int kOrderXcd = 1, kOrderRows = 2;
+
 
 // CONV: X is not a matrix in memory but a zero-padded activation [B][H + 2][Wd + 2][C] (channels fastest), and column
 // (b, oh, ow) of the product's X holds, at reduction index (kh * 3 + kw) * C + ci, the value act[b][oh + kh][ow + kw][ci]
@@ -71,7 +74,7 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
     Geom g, const uint16_t *__restrict__ W, int64_t ldw, const uint32_t *__restrict__ Ip,
     const uint32_t *__restrict__ Iz, const uint16_t *__restrict__ X, int64_t ldx, int N,
     uint16_t *__restrict__ Y, int64_t ldy, float *__restrict__ P, int64_t ldp, int mblocks, int nblocks,
-    int64_t kper, int xcd_remap, int y_vec_ok, ConvGeom cg, uint4 *__restrict__ mask_out, int64_t mask_pitch16)
+    int64_t kper, int order, int y_vec_ok, ConvGeom cg, uint4 *__restrict__ mask_out, int64_t mask_pitch16)
 {
     static_assert(NS == 4, "LDS stages (an even number: the W operand registers alternate with the slab's parity)");
     static_assert(!SPREAD || NS == 4, "loads spread over the iteration land one iteration later: four stages");
@@ -88,13 +91,18 @@ __global__ __launch_bounds__(PIPE_THREADS) void mfma_gemm_pipe_kernel(
                                                          // (HALF: [128][8][2], per 64-column half unit)
 
     int64_t bid = blockIdx.x;
-    if (xcd_remap) {
+    if (order & kOrderXcd) {
         const int64_t per = gridDim.x / 8;
         bid = (bid % 8) * per + bid / 8;
     }
     const int slice = (int)(bid / ((int64_t)nblocks * mblocks));
+    const int64_t in = bid - (int64_t)slice * nblocks * mblocks;
     int mi, ni;
-    grouped_tile<4>(bid - (int64_t)slice * nblocks * mblocks, mblocks, nblocks, &mi, &ni);
+    if (order & kOrderRows) {
+        mi = (int)(in / nblocks);
+        ni = (int)(in - (int64_t)mi * nblocks);
+    } else
+        grouped_tile<4>(in, mblocks, nblocks, &mi, &ni);
     const int64_t m0 = (int64_t)mi * PIPE_BM;
     const int n0 = ni * PIPE_BN;
     const int kbeg = (int)(slice * kper);
@@ -695,7 +703,14 @@ static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, in
     if (blocks > 0x7FFFFFFF) return LRBI_ERR_SHAPE;
     const bool split = plan.splitk > 1 || plan.planes_only;
     const int y_vec_ok = (((uintptr_t)dY & 7) == 0) && (ldy % 4 == 0);
-    const int xcd_remap = (blocks % 8 == 0) ? 1 : 0;
+    // Groups of four tile rows where the tiles make several rounds or have the chip to themselves.  Slices whose tiles are dealt
+    // to the XCDs in one piece each, and convolutions of two or three tile rows, go row after row (us, groups against rows: 256 x
+    // 4608, two images of 28 x 28, nine slices 18.3 / 16.8, 40 of 10 x 10 on 256 x 2304, four slices 20.7 / 19.8; 384 x 4608, 13 of
+    // 14 x 14 24.9 / 22.9, 96 of 28 x 28 316 / 305; 512 x 4096, N = 2048, four slices 22.6 / 21.2; 4096 x 9216, N = 512 49.6 / 47.7; but
+    // 1500 x 4104, N = 512 20.9 / 21.6; without slices 4096 x 9216, N = 2048 164 / 172, 256 x 4608, 20 of 28 x 28 42.7 / 44.2).
+    const bool xcd = blocks % 8 == 0;
+    const bool rows = plan.splitk > 1 ? (xcd || (CONV && mblocks < 4)) : (CONV && mblocks == 3);
+    const int order = (xcd ? kOrderXcd : 0) | (rows ? kOrderRows : 0);
     const int64_t ldp = (N + 3) / 4 * 4;
     const size_t smem = SmemDma<NS, HALF>::bytes;
     auto kern = split ? mfma_gemm_pipe_kernel<Tag, NS, SPREAD, true, CONV, EMIT, HALF, RAG, PRE>
@@ -703,7 +718,7 @@ static int launch_pipe_t(const Geom &g, const MfmaPlan &plan, const void *dW, in
     LRBI_SET_MAX_LDS(kern, smem);
     LRBI_LAUNCH(kern, dim3((unsigned)blocks), dim3(PIPE_THREADS), smem, stream, g, (const uint16_t *)dW, ldw, dIp, dIz,
                 (const uint16_t *)dX, ldx, (int)N, (uint16_t *)dY, ldy, (float *)dWorkspace, ldp, (int)mblocks,
-                (int)nblocks, plan.kper, xcd_remap, y_vec_ok, cg, (uint4 *)mo.ptr, mo.pitch16);
+                (int)nblocks, plan.kper, order, y_vec_ok, cg, (uint4 *)mo.ptr, mo.pitch16);
     return LRBI_OK;
 }
 
