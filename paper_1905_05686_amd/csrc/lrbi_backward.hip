@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kBwdThreads) void mfma_gemm_t_kernel(
             if (gi < iend) {
                 const int ti = (int)(gi / g.r);
                 const int il = (int)(gi - (int64_t)ti * g.r);
-                word = decode_word_ahead(g, Ip, Iz, ti, il, (j0 >> 5) + (tid & 3));
+                word = decode_word<true>(g, Ip, Iz, ti, il, (j0 >> 5) + (tid & 3));
             }
         }
         Ms[buf * S::ms_words + tid] = word;
@@ -613,7 +613,7 @@ __global__ __launch_bounds__(kBwdThreads) void mfma_grad_kernel(Geom g, const ui
             if (gi < g.m) {
                 const int ti = (int)(gi / g.r);
                 const int il = (int)(gi - (int64_t)ti * g.r);
-                word = decode_word_ahead(g, Ip, Iz, ti, il, (j0 >> 5) + (idx & 3));
+                word = decode_word<true>(g, Ip, Iz, ti, il, (j0 >> 5) + (idx & 3));
             }
         }
         return word;

@@ -120,7 +120,7 @@ template <bool AHEAD = false>
 __device__ __forceinline__ uint32_t row_word(const Geom &g, const uint32_t *Ip, const uint32_t *Iz, int64_t row, int w)
 {
     const int ti = (int)(row / g.r), il = (int)(row - (int64_t)ti * g.r);
-    return AHEAD ? decode_word_ahead(g, Ip, Iz, ti, il, w) : decode_word(g, Ip, Iz, ti, il, w);
+    return decode_word<AHEAD>(g, Ip, Iz, ti, il, w);
 }
 
 // adds the wavefronts' sums of a 32 x (32 NQ) block in wavefront order and stores it, without the batch columns in `skip`

@@ -286,6 +286,11 @@ __device__ __forceinline__ uint32_t bit_range(int lo, int hi)
 // One 32-bit word of the decoded mask: bits j = 32*w .. 32*w+31 of mask row
 // (ti * r + il).  Generic in r, c, k; bits at or beyond column n come out zero.
 // Row i of a tile's mask is the OR of the I_z rows selected by row i of I_p (Eq. 3).
+// AHEAD: up to four selected rows of I_z per round, their reads independent of one another: for kernels that wait for a
+// word with little else to do (transposed products, us, without and with: 4096 x 4096 f32, 64 columns 60 / 56; 2304 x
+// 2048 in 576 x 512 tiles, rank 145, N = 128 30 / 27; 4100 x 9224, N = 128 49 / 46, its gradient 45 / 42).  The stand-alone decode, whose
+// lanes hide the wait among themselves, is slower with it (4100 x 9224: 11.9 / 14.3).
+template <bool AHEAD = false>
 __device__ __forceinline__ uint32_t decode_word(const Geom &g, const uint32_t *__restrict__ Ip,
                                                 const uint32_t *__restrict__ Iz, int ti, int il, int w)
 {
@@ -300,68 +305,48 @@ __device__ __forceinline__ uint32_t decode_word(const Geom &g, const uint32_t *_
         const uint32_t *izt = Iz + t * g.k * (int64_t)g.izw;
         const int off = (int)(j0 - tbeg); // -32 < off < c
         const uint32_t valid = bit_range(off < 0 ? -off : 0, (g.c - off < 32) ? g.c - off : 32);
-        uint32_t v = 0u;
-        for (int iw = 0; iw < g.ipw; ++iw) {
-            uint32_t sel = ip[iw];
-            while (sel) {
-                const int l = __builtin_ctz(sel) + 32 * iw;
-                sel &= sel - 1u;
-                v |= iz_window(izt + (int64_t)l * g.izw, g.izw, off);
-            }
-        }
-        acc |= v & valid;
-    }
-    // a tile cut off at the right edge: whatever its I_z holds beyond column n stays out
-    if (j1 - j0 < 32) acc &= bit_range(0, (int)(j1 - j0));
-    return acc;
-}
-// The same with up to four selected rows of I_z per round, their reads independent of one another: for kernels that wait for a
-// word with little else to do (transposed products, us, against the form above: 4096 x 4096 f32, 64 columns 60 -> 56; 2304 x
-// 2048 in 576 x 512 tiles, rank 145, N = 128 30 -> 27; 4100 x 9224, N = 128 49 -> 46, its gradient 45 -> 42).  The stand-alone decode, whose
-// lanes hide the wait among themselves, is slower with it (4100 x 9224: 11.9 -> 14.3).
-__device__ __forceinline__ uint32_t decode_word_ahead(const Geom &g, const uint32_t *__restrict__ Ip,
-                                                      const uint32_t *__restrict__ Iz, int ti, int il, int w)
-{
-    const int64_t j0 = (int64_t)w * 32;
-    if (j0 >= g.n) return 0u;
-    const int64_t j1 = (j0 + 32 < g.n) ? j0 + 32 : g.n;
-    int tj = (int)(j0 / g.c);
-    uint32_t acc = 0u;
-    for (int64_t tbeg = (int64_t)tj * g.c; tbeg < j1; tbeg += g.c, ++tj) {
-        const int64_t t = (int64_t)ti * g.tile_cols + tj;
-        const uint32_t *ip = Ip + (t * g.r + il) * g.ipw;
-        const uint32_t *izt = Iz + t * g.k * (int64_t)g.izw;
-        const int off = (int)(j0 - tbeg); // -32 < off < c
-        const uint32_t valid = bit_range(off < 0 ? -off : 0, (g.c - off < 32) ? g.c - off : 32);
-        // the 32 bits from `off` on lie in words wa and wb = wa + 1 of an I_z row (a window that starts before the row: in its
-        // first word alone); words that the row does not have read as zero
-        const int s = off & 31, wb = off >= 0 ? (off >> 5) + 1 : 0, wa = wb - 1;
-        const uint32_t ma = (wa >= 0 && wa < g.izw) ? 0xFFFFFFFFu : 0u, mb = wb < g.izw ? 0xFFFFFFFFu : 0u;
-        const uint32_t *za = izt + (ma ? wa : 0), *zb = izt + (mb ? wb : 0);
-        uint32_t a = 0u, b = 0u;
-        for (int iw = 0; iw < g.ipw; ++iw) {
-            uint32_t sel = ip[iw];
-            // where fewer than four are left the last one is read again
-            while (sel) {
-                int64_t row[4];
-                int l = 0;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (sel) l = __builtin_ctz(sel);
+        if constexpr (!AHEAD) {
+            uint32_t v = 0u;
+            for (int iw = 0; iw < g.ipw; ++iw) {
+                uint32_t sel = ip[iw];
+                while (sel) {
+                    const int l = __builtin_ctz(sel) + 32 * iw;
                     sel &= sel - 1u;
-                    row[e] = (int64_t)(l + 32 * iw) * g.izw;
+                    v |= iz_window(izt + (int64_t)l * g.izw, g.izw, off);
                 }
-                uint32_t va[4], vb[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    va[e] = za[row[e]];
-                    vb[e] = zb[row[e]];
-                }
-                a |= (va[0] | va[1]) | (va[2] | va[3]);
-                b |= (vb[0] | vb[1]) | (vb[2] | vb[3]);
             }
+            acc |= v & valid;
+        } else {
+            // the 32 bits from `off` on lie in words wa and wb = wa + 1 of an I_z row (a window that starts before the row: in
+            // its first word alone); words that the row does not have read as zero
+            const int s = off & 31, wb = off >= 0 ? (off >> 5) + 1 : 0, wa = wb - 1;
+            const uint32_t ma = (wa >= 0 && wa < g.izw) ? 0xFFFFFFFFu : 0u, mb = wb < g.izw ? 0xFFFFFFFFu : 0u;
+            const uint32_t *za = izt + (ma ? wa : 0), *zb = izt + (mb ? wb : 0);
+            uint32_t a = 0u, b = 0u;
+            for (int iw = 0; iw < g.ipw; ++iw) {
+                uint32_t sel = ip[iw];
+                // where fewer than four are left the last one is read again
+                while (sel) {
+                    int64_t row[4];
+                    int l = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        if (sel) l = __builtin_ctz(sel);
+                        sel &= sel - 1u;
+                        row[e] = (int64_t)(l + 32 * iw) * g.izw;
+                    }
+                    uint32_t va[4], vb[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        va[e] = za[row[e]];
+                        vb[e] = zb[row[e]];
+                    }
+                    a |= (va[0] | va[1]) | (va[2] | va[3]);
+                    b |= (vb[0] | vb[1]) | (vb[2] | vb[3]);
+                }
+            }
+            acc |= (uint32_t)((((uint64_t)(b & mb) << 32) | (a & ma)) >> s) & valid;
         }
-        acc |= (uint32_t)((((uint64_t)(b & mb) << 32) | (a & ma)) >> s) & valid;
     }
     // a tile cut off at the right edge: whatever its I_z holds beyond column n stays out
     if (j1 - j0 < 32) acc &= bit_range(0, (int)(j1 - j0));
