@@ -1,6 +1,12 @@
 // Fused masked product on the matrix cores, tile kernel with both operands loaded straight into LDS
-// (f16 / bf16, fp32 accumulate): Y = (W o I_a) X with the mask of Eq. 3 rebuilt inside the kernel, for tile shapes
-// that line up with the kernel's blocking (c % 128 == 0, r % 128 == 0, k <= 64, no edge tiles).
+// (f16 / bf16, fp32 accumulate): Y = (W o I_a) X.  Its forms, and what the host asks of each (all: n and N multiples of 8, X in
+// 16-byte pieces, ldw and ldx up to 2^22 elements, for the lanes' 32-bit byte offsets):
+//   * base: the mask of Eq. 3 rebuilt inside the kernel, for tile shapes that line up with its blocking (c % 128 == 0, r % 128 ==
+//     0, k <= 64, whole tiles; I_z in 16-byte pieces, packed factors below 2^31 bytes each); with CONV on a padded activation below
+//     2^32 bytes, with EMIT the mask stored on the way;
+//   * HALF: c an odd multiple of 64;
+//   * RAG: matrices that end inside a tile, or rows that end inside a 128-column unit;
+//   * PRE: any tile shape and rank, on a mask decoded before, its rows up to 2^25 bytes apart.
 //
 // One workgroup of eight wavefronts (two per SIMD) owns a 128 x 128 tile of Y and walks the reduction range in
 // slabs of 64 columns of W.  Wavefront (kg, wq) owns rows 32 wq .. + 31 of the tile for the 16-column steps
@@ -16,7 +22,7 @@
 //     and Inf included, reaches the product).
 //   * The mask itself is rebuilt one panel (512 columns) at a time, one panel ahead, from the panel's slices of
 //     the factors (also loaded straight into LDS): mask row = OR of the I_z rows that the row's I_p word selects
-//     (Eq. 3).
+//     (Eq. 3); PRE copies the panel.
 //   * X stays in its natural [k][n] order in LDS and is read with the transposing LDS read of gfx950.
 //   * One workgroup barrier per slab, without a drain of the loads in flight: what must have landed is waited
 //     for by count.  Two wavefronts per SIMD: measured, one wavefront per SIMD cannot keep enough 8-byte LDS

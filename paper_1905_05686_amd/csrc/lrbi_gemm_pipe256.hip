@@ -4,8 +4,8 @@
 // What bounds the 128 x 128 form on large products is not the matrix pipe but the operand bytes that come through the
 // compute unit's load path and the mask work, both per flop: 32 KB and two masked operand pieces for 512 clocks of matrix
 // work a SIMD (16384 x 16384 bf16, N = 4096: 2454 us; without the loads 1930, without loads, mask and factor work 1443,
-// matrix instructions alone 1178).  A 256 x 256 tile halves both: 1640 us there, at
-// 1300 clocks a slab (1024 of them matrix work) and a clock that the card's power holds at 1.7 GHz.
+// matrix instructions alone 1178).  A 256 x 256 tile halves both: 1644 us there, at 1304 clocks a slab (1024 of them matrix
+// work, 75 the panels) and 1.7 GHz, where matrix instructions alone run at 2.3.
 //
 // One workgroup of eight wavefronts (two per SIMD); wavefront (wm, wn) owns 64 rows x 128 columns of the tile: 128
 // accumulator registers, and per 16-column step two W operands and four X operands for eight matrix instructions.
