@@ -951,8 +951,9 @@ MfmaPlan plan_mfma(const Geom &g, uint32_t flags, int64_t N, bool x_pieces)
 //   * Faster form, one round: 1000 x 4096 in 64 x 64 tiles, N = 1000 28 / 45; 2000 x 648, N = 1000 19.5 / 20.8, but N = 400 19 / 17;
 //     300 x 2000, N = 1000 21 / 18; 1024 x 4096, N = 400, 32 tiles 23.5 / 26; 8000 x 2000, N = 96 (a quarter of the column block idle) 24.4 / 23.7; table form: 960 x 512 in 192 x
 //     128, N = 2000 15.6 / 16.9, 4032 x 512, N = 200 15.3 / 14.3.
-//     Two rounds: 8000 x 520, N = 1000 33 / 26, 8000 x 1000 40.4 / 39.3.  More: 8000 x 520, N = 2000 53 / 48, 8000 x 648, N = 4096
-//     99 / 106; table form: 8064 x 512, N = 4096 79 / 86.
+//     Two rounds: 8000 x 520, N = 1000 33 / 26, 8000 x 1000 40.4 / 39.3.  Three, where the general kernel has two of 512: 8000 x
+//     520 in 256 x 256, N = 1536 42 / 50, 5248 x 512 in 64 x 128, N = 1568 29 / 39.  More: 8000 x 520, N = 2000 53 / 48, 8000 x 648, N =
+//     4096 99 / 106; table form: 8064 x 512, N = 4096 79 / 86.  14034 x 6520, N = 80 60 / 103, but 16000 x 4096, N = 64 44 / 39.
 //   * Slower form, up to 64 ranks: 3000 x 3000 in 300 x 300, N = 512 31 / 90; 300 x 392, N = 4096 17 / 21; 2000 x 648, N = 200, 32
 //     tiles 20 / 18; 1000 x 4096, N = 200, 16 tiles 23 / 24; 8000 x 392, N = 1000, two rounds 31 / 29; few columns only on large
 //     matrices: 12000 x 12000, N = 40 103 / 142; 3000 x 3000, N = 64 23.0 / 22.7.
@@ -964,12 +965,15 @@ static bool given_wins(const Geom &g, int64_t N)
     const bool whole = !g.ragged, table = whole && g.c % 128 == 0, ranks = g.k > 64, ahead = g.c % BK == 0 && !ranks;
     if (g.n < 384) return false;
     if (ranks && table) return work >= 192;
-    if (N < 96 && (g.m * g.n < ((int64_t)1 << 25) || !(ahead ? table : (!ranks || g.c % 128 == 0)))) return false;
+    if (N < 96 && g.m * g.n < ((int64_t)1 << 25)) return false;
+    if (N <= 64 && !(ahead ? table : (!ranks || g.c % 128 == 0))) return false; // (the general kernel's narrower column blocks)
     if (ahead) {
-        if (tiles > 256) return pairs >= (tiles <= 512 ? (table ? 6 : 8) : (tiles <= 1024 ? 5 : 4) + (table ? 0 : 1));
+        const int64_t rounds = (tiles + 255) / 256;
+        if (rounds > 1 && rounds % 2 == 1) return pairs >= 4; // the general kernel's last round, of 512, is half empty
+        if (rounds > 1) return pairs >= (rounds == 2 ? (table ? 6 : 8) : (rounds == 4 ? 5 : 4) + (table ? 0 : 1));
         if (table) return pairs >= 4 && work >= (pairs == 4 ? 380 : pairs <= 8 ? 240 : 300) && (tiles >= 48 || N >= 128);
         if (tiles < 48 || (N < 128 && tiles < 96)) return whole && N >= 128 && tiles >= 24 && work >= 700;
-        return pairs >= (whole ? 4 : 5) && work >= (pairs == 4 ? 900 : pairs == 5 ? (whole ? 480 : 800) : 490);
+        return pairs >= (whole ? 4 : 5) && work >= (pairs == 4 ? 900 : pairs == 5 ? (whole ? 480 : 800) : (whole || g.k <= 48) ? 490 : 700);
     }
     if (tiles > 256) return tiles > 512 || pairs >= (whole && !ranks ? 4 : 5);
     if (ranks) return tiles >= 64 && pairs >= (whole ? 4 : 5) && work >= (pairs == 4 ? 380 : 320);

@@ -89,7 +89,8 @@ def given(g, N):
     ((16000, 4096, 64, 64, 8), 64, False), ((2000, 648, 300, 300, 8), 200, False), ((8000, 392, 100, 100, 8), 1000, False),
     ((16000, 1600, 256, 256, 16), 2000, True), ((1000, 4096, 64, 64, 8), 1000, True), ((960, 640, 192, 128, 16), 2000, True),
     ((3000, 3000, 300, 300, 8), 512, True), ((12000, 12000, 300, 300, 8), 40, True), ((2304, 2048, 576, 512, 145), 128, True),
-    ((8000, 1000, 100, 100, 8), 1000, True),
+    ((8000, 1000, 100, 100, 8), 1000, True), ((14034, 6520, 100, 256, 8), 80, True), ((5248, 512, 64, 128, 16), 1568, True),
+    ((802, 1448, 100, 128, 64), 800, False),
     ((4096, 4096, 256, 256, 16), 1024, False), ((4096, 4096, 128, 192, 16), 1024, False),  # lined up: the mask formed in the kernel
 ])
 def test_mask_decoded_first_where_it_pays(args, N, first):
